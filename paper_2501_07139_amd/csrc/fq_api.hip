@@ -172,6 +172,8 @@ extern "C" int fq_qlinear_mixed(const void *x, int M, const fq_segment *segments
         int e = 0;
         if (M > 16)
             e = fq_launch_gemm_multi(x, M, &w[i], &outs[i], n, st);
+        else if (fq_skinny_pays(M, &w[i], n))
+            e = fq_launch_skinny(x, M, &w[i], &outs[i], n, st);
         else if (stream_all)
             e = fq_launch_gemv_multi(fq_gemv_input{x, nullptr, nullptr, nullptr, 0}, M, &w[i], &outs[i], n, st);
         else
@@ -424,9 +426,12 @@ static int stack_forward_checked(const fq_layer *layers, int L, const uint8_t *b
             return check_hip(e, "decode (persistent kernel)");
     }
 
-    // Decode (M <= 16): four launches per block.  q/k/v and gate/up share a launch each, and every
-    // row-wise step is folded into the input staging of the linear that consumes it.
-    bool decode = M <= 16;
+    // Decode of up to three rows: four launches per block.  q/k/v and gate/up share a launch each, and every
+    // row-wise step is folded into the input staging of the linear that consumes it.  The staging takes the rows one
+    // after another, so from four rows on the linears and the row-wise steps are launches of their own (us per
+    // block, hidden 1024 / ffn 2816: 35 and 34 at three rows, 40 against 29 at four, 106 against 29 at sixteen; rows of
+    // 4096 / 11008 elements do not fit the staging from four rows on: 64 us at four rows against 60 at three).
+    bool decode = M <= 3;
     for (int l = 0; l < L && decode; ++l)
         for (int j = 0; j < 7; ++j)
             decode = decode && fq_gemv_can_stream(M, layers[l].m[j].K, bitvec[7 * l + j], j == 3 ? 3 : 2);
@@ -464,7 +469,7 @@ static int stack_forward_checked(const fq_layer *layers, int L, const uint8_t *b
                 FQ_STEP(check_hip(fq_launch_glue(4, x1, d, nullptr, M, H, x_out, st), "glue rms(add)"));
             continue;
         }
-        // M > 16: the row-wise steps are kernels of their own, two of them per pass where one feeds the other
+        // otherwise the row-wise steps are kernels of their own, two of them per pass where one feeds the other
         // (the residual sum with the norm that reads it; a block's output with the next block's first norm)
         if (l == 0) {
             FQ_STEP(check_hip(fq_launch_glue(0, xcur, nullptr, nullptr, M, H, u, st), "glue rms"));
@@ -666,7 +671,7 @@ extern "C" int fq_prefill_forward(const fq_layer *layers, int L, const uint8_t *
             return rc; \
     } while (0)
         FQ_STEP(check_hip(fq_launch_glue(0, xcur, nullptr, nullptr, M, H, u, st), "glue rms"));
-        if (M > 16) {
+        if (M > 16 || fq_skinny_pays(M, &sel[0], 3)) {
             FQ_STEP(qlinear_multi_checked(u, M, &sel[0], qkv, 3, st));
         } else {
             for (int j = 0; j < 3; ++j)
@@ -677,7 +682,7 @@ extern "C" int fq_prefill_forward(const fq_layer *layers, int L, const uint8_t *
                                                  attn, st), "prefill attention"));
         FQ_STEP(qlinear_checked(a, M, sel[3], o, st));
         FQ_STEP(check_hip(fq_launch_glue2(6, xcur, o, M, H, x1, u, st), "glue add, rms"));
-        if (M > 16) {
+        if (M > 16 || fq_skinny_pays(M, &sel[4], 2)) {
             FQ_STEP(qlinear_multi_checked(u, M, &sel[4], gp, 2, st));
         } else {
             for (int j = 0; j < 2; ++j)

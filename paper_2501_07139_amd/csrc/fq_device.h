@@ -7,6 +7,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
@@ -414,6 +417,94 @@ __device__ __forceinline__ h8 make_h8_bits(uint32_t a, uint32_t b, uint32_t c, u
 {
     const u4v v = {a, b, c, d};
     return __builtin_bit_cast(h8, v);
+}
+
+// biased pair P of a chunk (elements 2v, 2v+1 of k-step P/4, v = P%4) and the class of its bit position;
+// the same fields and constants as unpack_dequant, one pair at a time
+template <int BITS, int P>
+struct PairAt {
+    static constexpr int T = BITS == 2 ? (P & 7) : BITS == 3 ? (P % 5) : BITS == 4 ? (P & 3) : (P & 1);
+    static constexpr int WRAP = BITS == 2 ? 5 : BITS == 3 ? 3 : BITS == 4 ? 2 : 1; // fields per half before the shifted copy
+    static constexpr int DW = BITS == 2 ? (P >> 3) : BITS == 3 ? (P / 5) : BITS == 4 ? (P >> 2) : (P >> 1);
+    static constexpr int SHIFT = T >= WRAP ? (BITS == 2 ? 10 : BITS == 3 ? 9 : 8) : 0;
+    static constexpr int CLS = BITS == 8 ? 0 : (T >= WRAP ? T - WRAP : T);
+    static constexpr uint32_t MASK = BITS == 8 ? 0x00ff00ffu : (((1u << BITS) - 1u) * 0x10001u) << (BITS * CLS);
+};
+
+template <int BITS>
+struct UnpackConsts {
+    static constexpr int NS = UnpackPlan<BITS>::NSHIFT;
+    uint32_t E[NS]; // exponent of 2^(10-p) per class, in vector registers
+    h2 mb[NS];      // -2^(10-p)
+    __device__ __forceinline__ void init()
+    {
+        if constexpr (BITS == 8) {
+            E[0] = exp_for_shift<0>(); mb[0] = minus_bias<0>();
+        } else if constexpr (BITS == 4) {
+            E[0] = exp_for_shift<0>(); E[1] = exp_for_shift<4>();
+            mb[0] = minus_bias<0>(); mb[1] = minus_bias<4>();
+        } else if constexpr (BITS == 3) {
+            E[0] = exp_for_shift<0>(); E[1] = exp_for_shift<3>(); E[2] = exp_for_shift<6>();
+            mb[0] = minus_bias<0>(); mb[1] = minus_bias<3>(); mb[2] = minus_bias<6>();
+        } else {
+            E[0] = exp_for_shift<0>(); E[1] = exp_for_shift<2>(); E[2] = exp_for_shift<4>(); E[3] = exp_for_shift<6>();
+            E[4] = exp_for_shift<8>();
+            mb[0] = minus_bias<0>(); mb[1] = minus_bias<2>(); mb[2] = minus_bias<4>(); mb[3] = minus_bias<6>();
+            mb[4] = minus_bias<8>();
+        }
+    }
+};
+
+template <int BITS, int P>
+__device__ __forceinline__ uint32_t biased_pair(const uint32_t (&C)[BITS], const UnpackConsts<BITS> &uc)
+{
+    if constexpr (BITS == 3 && P == 15) { // the two weights whose bits sit on top of the three dwords
+        uint32_t sp = ((C[0] >> 15) & 0x00010001u) | uc.E[0];
+        sp |= (C[1] >> 14) & 0x00020002u;
+        sp |= (C[2] >> 13) & 0x00040004u;
+        return sp;
+    } else {
+        using A = PairAt<BITS, P>;
+        return ((C[A::DW] >> A::SHIFT) & A::MASK) | uc.E[A::CLS];
+    }
+}
+
+template <int BITS, int P>
+constexpr int pair_class() { return (BITS == 3 && P == 15) ? 0 : PairAt<BITS, P>::CLS; }
+
+template <int... I, class F>
+__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>), in order
+template <int N, class F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    static_for_impl(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
+}
+
+// Operands of k-steps 2*KH and 2*KH+1 of a chunk: code - zero per weight in packed fp16, times the scale if SCALED; the
+// arithmetic of unpack_dequant pair by pair (integer zeros: bias and zero leave in one exact addition).
+template <int BITS, bool INTZ, bool SCALED, int KH>
+__device__ __forceinline__ void unpack_khalf(const uint32_t (&C)[BITS], h2 zero2, h2 scale2, const UnpackConsts<BITS> &uc,
+                                             h8 (&a)[2])
+{
+    static_for<2>([&](auto s_tag) {
+        constexpr int s = decltype(s_tag)::value;
+        h2 q[4];
+        static_for<4>([&](auto v_tag) {
+            constexpr int v = decltype(v_tag)::value, P = 4 * (2 * KH + s) + v, CLS = pair_class<BITS, P>();
+            const h2 b = as_h2(biased_pair<BITS, P>(C, uc));
+            if constexpr (INTZ)
+                q[v] = b + (uc.mb[CLS] - zero2);
+            else
+                q[v] = (b + uc.mb[CLS]) - zero2;
+            if constexpr (SCALED)
+                q[v] *= scale2;
+        });
+        a[s] = make_h8(q[0], q[1], q[2], q[3]);
+    });
 }
 
 __device__ __forceinline__ f4 mfma16x16x32(h8 a, h8 b, f4 c)

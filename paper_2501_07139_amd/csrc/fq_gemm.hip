@@ -381,71 +381,6 @@ __global__ __launch_bounds__(256, 2) void qgemm_multi_kernel(const _Float16 *__r
 // harness): 6-13 % faster than the 128-row kernels at every bit-width.
 constexpr int TBM = 256, TBN = 128, TMB = TBM / 16, TNB = 2;
 
-// biased pair P of a chunk (elements 2v, 2v+1 of k-step P/4, v = P%4) and the class of its bit position;
-// the same fields and constants as unpack_dequant, one pair at a time
-template <int BITS, int P>
-struct PairAt {
-    static constexpr int T = BITS == 2 ? (P & 7) : BITS == 3 ? (P % 5) : BITS == 4 ? (P & 3) : (P & 1);
-    static constexpr int WRAP = BITS == 2 ? 5 : BITS == 3 ? 3 : BITS == 4 ? 2 : 1; // fields per half before the shifted copy
-    static constexpr int DW = BITS == 2 ? (P >> 3) : BITS == 3 ? (P / 5) : BITS == 4 ? (P >> 2) : (P >> 1);
-    static constexpr int SHIFT = T >= WRAP ? (BITS == 2 ? 10 : BITS == 3 ? 9 : 8) : 0;
-    static constexpr int CLS = BITS == 8 ? 0 : (T >= WRAP ? T - WRAP : T);
-    static constexpr uint32_t MASK = BITS == 8 ? 0x00ff00ffu : (((1u << BITS) - 1u) * 0x10001u) << (BITS * CLS);
-};
-
-template <int BITS>
-struct UnpackConsts {
-    static constexpr int NS = UnpackPlan<BITS>::NSHIFT;
-    uint32_t E[NS]; // exponent of 2^(10-p) per class, in vector registers
-    h2 mb[NS];      // -2^(10-p)
-    __device__ __forceinline__ void init()
-    {
-        if constexpr (BITS == 8) {
-            E[0] = exp_for_shift<0>(); mb[0] = minus_bias<0>();
-        } else if constexpr (BITS == 4) {
-            E[0] = exp_for_shift<0>(); E[1] = exp_for_shift<4>();
-            mb[0] = minus_bias<0>(); mb[1] = minus_bias<4>();
-        } else if constexpr (BITS == 3) {
-            E[0] = exp_for_shift<0>(); E[1] = exp_for_shift<3>(); E[2] = exp_for_shift<6>();
-            mb[0] = minus_bias<0>(); mb[1] = minus_bias<3>(); mb[2] = minus_bias<6>();
-        } else {
-            E[0] = exp_for_shift<0>(); E[1] = exp_for_shift<2>(); E[2] = exp_for_shift<4>(); E[3] = exp_for_shift<6>();
-            E[4] = exp_for_shift<8>();
-            mb[0] = minus_bias<0>(); mb[1] = minus_bias<2>(); mb[2] = minus_bias<4>(); mb[3] = minus_bias<6>();
-            mb[4] = minus_bias<8>();
-        }
-    }
-};
-
-template <int BITS, int P>
-__device__ __forceinline__ uint32_t biased_pair(const uint32_t (&C)[BITS], const UnpackConsts<BITS> &uc)
-{
-    if constexpr (BITS == 3 && P == 15) { // the two weights whose bits sit on top of the three dwords
-        uint32_t sp = ((C[0] >> 15) & 0x00010001u) | uc.E[0];
-        sp |= (C[1] >> 14) & 0x00020002u;
-        sp |= (C[2] >> 13) & 0x00040004u;
-        return sp;
-    } else {
-        using A = PairAt<BITS, P>;
-        return ((C[A::DW] >> A::SHIFT) & A::MASK) | uc.E[A::CLS];
-    }
-}
-
-template <int BITS, int P>
-constexpr int pair_class() { return (BITS == 3 && P == 15) ? 0 : PairAt<BITS, P>::CLS; }
-
-template <int... I, class F>
-__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-// f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>), in order
-template <int N, class F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    static_for_impl(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
-}
-
 // The dwords of a chunk that hold k-steps 2*KH and 2*KH+1 (3 bits: all three, the last pair's bits sit on
 // top of every dword), with the row's scale and zero; the other entries of w.c stay unset and unread.
 template <int BITS, int KH>
@@ -471,27 +406,6 @@ __device__ __forceinline__ void load_whalf(WChunk<BITS> &w, const GemmBuffers &b
     const uint32_t meta_off = (uint32_t)(rb * G + g) * 32u, mlo = (uint32_t)(lane & 15) * 2u;
     w.scale = buf_load_u16(buf.scales, mlo, meta_off);
     w.zero = buf_load_u16(buf.zeros, mlo, meta_off);
-}
-
-// Operands of k-steps 2*KH and 2*KH+1 of a chunk: (code - zero) * scale per weight in packed fp16, the
-// arithmetic of unpack_dequant pair by pair (integer zeros: bias and zero leave in one exact addition).
-template <int BITS, bool INTZ, int KH>
-__device__ __forceinline__ void unpack_khalf(const WChunk<BITS> &w, const UnpackConsts<BITS> &uc, h8 (&a)[2])
-{
-    const h2 zero2 = as_h2(w.zero * 0x10001u), scale2 = as_h2(w.scale * 0x10001u);
-    static_for<2>([&](auto s_tag) {
-        constexpr int s = decltype(s_tag)::value;
-        h2 q[4];
-        static_for<4>([&](auto v_tag) {
-            constexpr int v = decltype(v_tag)::value, P = 4 * (2 * KH + s) + v, CLS = pair_class<BITS, P>();
-            const h2 b = as_h2(biased_pair<BITS, P>(w.c, uc));
-            if constexpr (INTZ)
-                q[v] = (b + (uc.mb[CLS] - zero2)) * scale2;
-            else
-                q[v] = ((b + uc.mb[CLS]) - zero2) * scale2;
-        });
-        a[s] = make_h8(q[0], q[1], q[2], q[3]);
-    });
 }
 
 // One 256 x 128 output tile.  Xs0, Xs1: the two activation tiles (256 rows x 128 k each, laid out like the
@@ -568,7 +482,7 @@ __device__ __forceinline__ void qgemm_tall_tile(h8 *Xs0, h8 *Xs1, const _Float16
         auto unpack_all = [&](WChunk<BITS> (&w)[TNB], h8 (&a)[TNB][2]) {
 #pragma unroll
             for (int i = 0; i < TNB; ++i)
-                unpack_khalf<BITS, INTZ, KH>(w[i], uc, a[i]);
+                unpack_khalf<BITS, INTZ, true, KH>(w[i].c, as_h2(w[i].zero * 0x10001u), as_h2(w[i].scale * 0x10001u), uc, a[i]);
         };
         auto load_all = [&](WChunk<BITS> (&w)[TNB], int g) {
 #pragma unroll
@@ -777,8 +691,11 @@ int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_s
     const size_t Np = ((size_t)w.N + 63) / 64 * 64;
     if (!fits_32bit(M, w.K, 2) || Np / 8 * w.K * w.bits >= ((size_t)1 << 32))
         return (int)hipErrorInvalidValue;
-    if (tile_rows == 0)
+    if (tile_rows == 0) {
         tile_rows = choose_tile_rows(M, &w, 1);
+        if (tile_rows == 128 && fq_skinny_pays(M, &w, 1))
+            return fq_launch_skinny(x, M, &w, &out, 1, st);
+    }
     if (tile_rows == 256)
         return launch_tall(x, M, &w, &out, 1, st);
     if (w.ld && w.ld != w.N) // a column range of a wider output: the multi-matrix kernel carries the row pitch
@@ -802,8 +719,11 @@ int fq_launch_gemm_multi(const void *x, int M, const fq_packed_ref *w, void *con
         if (w[i].K != w[0].K || !fits_32bit(M, w[i].K, 2) || Np / 8 * w[i].K * w[i].bits >= ((size_t)1 << 32))
             return (int)hipErrorInvalidValue;
     }
-    if (tile_rows == 0)
+    if (tile_rows == 0) {
         tile_rows = choose_tile_rows(M, w, count);
+        if (tile_rows == 128 && (M <= 16 ? fq_skinny_can(M, w[0].K) : fq_skinny_pays(M, w, count)))
+            return fq_launch_skinny(x, M, w, outs, count, st);
+    }
     if (tile_rows == 256)
         return launch_tall(x, M, w, outs, count, st);
     GemmJobs jobs;

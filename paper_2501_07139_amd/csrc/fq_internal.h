@@ -25,6 +25,10 @@ struct fq_packed_ref {
 
 // Launchers.  Arguments are validated by the callers in fq_api.hip; each returns a hipError_t as int.
 int fq_launch_dequant(const fq_packed_ref &w, void *out, int out_is_fp16, fq_stream st);
+// Few rows (fq_skinny.hip): up to three matrices that share x (same K); whether it is the faster kernel for a launch.
+bool fq_skinny_can(int M, int K);
+bool fq_skinny_pays(int M, const fq_packed_ref *w, int count);
+int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st);
 int fq_launch_gemv(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st);
 // Streaming decode kernel: up to three matrices that share their input and K in one launch (M <= 16).
 // The input is x = f(a, b, c), fp16 [M,K] each, with the block's row-wise glue folded in:

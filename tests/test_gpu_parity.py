@@ -152,6 +152,44 @@ def test_qlinear_tall_tiles_against_oracle(fq, torch, bits, case):
     assert qerr(y, y128.astype(np.float64)) <= 1e-3
 
 
+# Shapes of the few-row kernel: its eleven tile shapes (16/32/48/64 rows x 16/32/64 columns), row tiles that end inside a
+# block of sixteen, column counts that end inside a tile or a block, K of one group, of fewer groups than
+# wavefronts, of one more than a whole turn of them, and of several turns.
+SKINNY_CASES = [(4, 512, 128), (16, 70, 1152), (9, 11008, 384), (17, 4096, 1152), (17, 8200, 1152), (33, 4096, 1152),
+                (48, 11008, 384), (60, 4096, 2176), (64, 11008, 1152), (77, 4096, 1152), (100, 201, 256),
+                (128, 4096, 1152), (200, 4096, 1152), (250, 1030, 1280)]
+
+
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("case", SKINNY_CASES, ids=lambda c: "M%d_N%d_K%d" % c)
+def test_qlinear_few_rows_against_oracle(fq, torch, bits, case):
+    """Integer zeros, then zeros with fractions in some groups (the kernel unpacks those differently).
+
+    Bound: one rounding of the output to fp16 (2^-11 |r|), and where the tile scales its weights in fp16 one more of
+    each weight, at worst 2^-11 sum |x||w|; differences of a code and a fractional zero are exact here, fp32 sums add
+    1e-6 sum |x||w|.  The scales spread over an order of magnitude, so the largest of half a million errors is well over the
+    2e-3 of the row's rms that evenly scaled weights stay below; rounding errors being independent, the rms over
+    all outputs has to stay at sqrt(2) of one rounding (2^-11 / sqrt(3) at most), 4e-4."""
+    M, N, K = case
+    codes = fq_synth.codes(60, N, K, bits)
+    s = (np.abs(fq_synth.activations(61, N, K // 128).astype(np.float32)) * 0.01 + 1e-3).astype(np.float16)
+    X = fq_synth.activations(62, M, K)
+    for frac in (0, 1):
+        z = fq_synth.codes(63, N, K // 128, bits).astype(np.float32)
+        if frac:
+            z[::3, ::2] += 0.25
+        z = z.astype(np.float16)
+        w = fq.PackedMatrix.from_host(codes, s, z, bits)
+        out = Guarded(torch, M * N * 2)
+        fq.fq_qlinear(dev(torch, X), w, out=out.half(M, N))
+        assert out.intact()
+        W = oracle.dequant(codes, s, z)
+        r, size = oracle.qlinear(X, W), oracle.qlinear(np.abs(X), np.abs(W))
+        err = np.abs(host16(out.half(M, N)).astype(np.float64) - r)
+        assert np.all(err <= 2.0 ** -11 * (np.abs(r) + size) + 1e-6 * size)
+        assert np.sqrt(np.mean(err ** 2)) <= 4e-4 * np.sqrt(np.mean(r ** 2))
+
+
 def test_qlinear_tile_rejects_other_tile_heights(fq, torch):
     w, *_ = make_matrix(fq, 1, 64, 128, 4)
     with pytest.raises(fq.FqError) as e:
