@@ -138,18 +138,17 @@ int fq_dequant(const void *packed, const void *scales, const void *zeros,
  *   out[m,n] = sum_k x[m,k] * scale[n,k/128] * (code[n,k] - zero[n,k/128]),
  * fp16 inputs, fp32 accumulation, fp16 output (one rounding).  x fp16 [M,K]
  * row-major and the packed triple: device, read.  out fp16 [M,N] row-major:
- * device, written.  M <= 16 runs the bandwidth-bound streaming kernel (decode),
- * larger M the matrix-core tile kernel (calibration forward).  Any M >= 1,
- * N >= 1.  Scales and zeros may be any finite fp16 (e.g. zero/2^d after
- * truncating d code bits, Section "Elastic Serving").  For M > 16 the
+ * device, written.  Up to three rows run the bandwidth-bound streaming kernel
+ * (decode); from four rows to several hundred (batched decoding, prompts) small
+ * tiles whose wavefronts share K; larger M the matrix-core tile kernels (calibration
+ * forward).  Any M >= 1, N >= 1.  Scales and zeros may be any finite fp16 (e.g.
+ * zero/2^d after truncating d code bits, Section "Elastic Serving").  For M > 16 the
  * activations (M*K*2 bytes) and the packed weights must each stay below
- * 4 GiB, else FQ_ERR_SHAPE.  Two tile kernels exist for M > 16: 128 activation
+ * 4 GiB, else FQ_ERR_SHAPE.  Two large-tile kernels exist: 128 activation
  * rows per workgroup, and 256 rows per workgroup of eight wavefronts with the
  * k-steps of every group split over two wavefront sets (each unpacked weight
- * feeds twice as many matrix instructions); the library takes the 256-row tiles
- * once M > 128 and there is a tile for every compute unit, except from 4096 rows
- * on for 2- and 4-bit matrices wide enough for 128 x 256 tiles (as measured on
- * MI355X).
+ * feeds twice as many matrix instructions); the library takes whichever needs less
+ * time for its rounds of tiles over the chip (as measured on MI355X).
  * fq_qlinear_tile is the same call with the choice
  * made by the caller: tile_rows = 128 or 256 pins a kernel (any M > 16; for tests
  * and tuning; ignored for M <= 16), 0 leaves it to the library; anything else is

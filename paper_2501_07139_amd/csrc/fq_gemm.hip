@@ -627,19 +627,35 @@ int wide_tiles_pay(int M, int N)
 
 int tall_tiles(int M, int N) { return ((N + TBN - 1) / TBN) * ((M + TBM - 1) / TBM); }
 
-// Tile height for a launch of `count` matrices.  A tall tile occupies a whole CU, so tall tiles pay once there is
-// one for every CU and the rows fill more than half of a tile: as measured, 3-14 % faster than the 128-row tiles
-// at 2048 rows at every bit-width.  From 4096 rows on, the 128 x 256 tiles of 2- and 4-bit matrices run several
-// full rounds and are level or 2-6 % ahead, so launches made of such matrices only stay with them.
+// Tile height for a launch of `count` matrices.  Both kernels run in rounds over the 256 CUs, two 128-row tiles or
+// one tall tile a CU, and a round that is not full costs most of a full one.  Measured over 32 groups, 512 to 2048
+// rows, 4096 to 22016 columns (us at 2 / 3 / 4 / 8 bits): a full round of 128-row tiles 63 / 73 / 67 / 73, its last one 47 when
+// at most one tile a CU is left and 4 under a full one otherwise; a full round of tall tiles 61 / 67 / 63 / 66, a last
+// one 50 to 60.  So 640 rows of 11008 columns (430 tiles or 258) take 64 against 110 us, 2048 rows (1376 or 688) 204
+// against 184.  From 4096 rows on, the 128 x 256 tiles of 2- and 4-bit matrices run several full rounds and are level or
+// 2-6 % ahead of the tall ones, so launches made of such matrices only stay with them.
 int choose_tile_rows(int M, const fq_packed_ref *w, int count)
 {
-    long tall = 0;
+    static const double full128[9] = {0, 0, 63, 73, 67, 0, 0, 0, 73}, full256[9] = {0, 0, 61, 67, 63, 0, 0, 0, 66};
+    long tiles = 0, tall = 0;
+    double f128 = 0.0, f256 = 0.0;
     bool all_wide = M >= 4096;
     for (int i = 0; i < count; ++i) {
+        const int t = ((w[i].N + 127) / 128) * ((M + 127) / 128);
+        tiles += t;
         tall += tall_tiles(M, w[i].N);
+        f128 += t * full128[w[i].bits];
+        f256 += t * full256[w[i].bits];
         all_wide = all_wide && (w[i].bits == 2 || w[i].bits == 4) && wide_tiles_pay(M, w[i].N);
     }
-    return (M > 128 && tall >= 256 && !all_wide) ? 256 : 128;
+    if (M <= 128 || tiles <= 256 || all_wide)
+        return 128;
+    f128 /= tiles;
+    f256 /= tiles;
+    const long r128 = tiles % 512, r256 = tall % 256;
+    const double t128 = (tiles / 512) * f128 + (r128 == 0 ? 0.0 : (r128 <= 256 ? 47.0 : f128 - 4.0));
+    const double t256 = (tall / 256) * f256 + (r256 == 0 ? 0.0 : 50.0 + 10.0 * r256 / 256);
+    return t256 < t128 ? 256 : 128;
 }
 
 template <int BITS, int QNB>
