@@ -288,10 +288,10 @@ int fq_glue(int op, const void *a, const void *b, const void *c, int M, int H, v
  * (Algorithm 1) turns into a perplexity and the sensitivity analysis (Section
  * "Efficient Design Space Navigation") compares; the head is not quantized.
  * x [M,K], W [N,K], out [M,N] row-major, device.  K must be a multiple of 128;
- * x and W must each stay below 4 GiB (FQ_ERR_SHAPE otherwise).  Two kernels serve
- * it: 128-row tiles, and 256-row tiles with both operands in LDS once those fill
- * the chip.  fq_dense_f16_tile is the same call with the choice made by the
- * caller: tile_rows = 128 or 256 pins a kernel (any size; for tests and tuning),
+ * x and W must each stay below 4 GiB (FQ_ERR_SHAPE otherwise).  Few rows stream W
+ * through narrow tiles (a decode step's logits); 256-row tiles with both operands
+ * in LDS take over once those fill the chip.  fq_dense_f16_tile is the same call with
+ * the choice made by the caller: tile_rows = 128 or 256 pins a kernel of that height (any size; for tests and tuning),
  * 0 leaves it to the library; anything else is FQ_ERR_SHAPE.
  */
 int fq_dense_f16(const void *x, int M, const void *W, int N, int K, void *out, void *stream);
@@ -318,8 +318,8 @@ int fq_token_nll(const void *logits, const int32_t *labels, int M, int V, float 
  * device, written.  workspace: device scratch of at least
  * fq_head_nll_workspace_bytes(M, V) bytes, 16-byte aligned, owned by the caller,
  * contents undefined afterwards (FQ_ERR_WORKSPACE if NULL or too small).
- * K a multiple of 128; x and W below 4 GiB each (FQ_ERR_SHAPE).  Always runs the
- * 256-row tiles: meant for M * V large enough to fill the chip.
+ * K a multiple of 128; x and W below 4 GiB each (FQ_ERR_SHAPE).  The tiles are those
+ * fq_dense_f16 would choose, or the 256-row ones where it has smaller ones.
  */
 size_t fq_head_nll_workspace_bytes(int M, int V);
 int fq_head_nll(const void *x, int M, const void *W, int V, int K, const int32_t *labels, float *nll_out,

@@ -213,6 +213,8 @@ extern "C" int fq_dense_f16_tile(const void *x, int M, const void *W, int N, int
         return fq_fail(FQ_ERR_SHAPE, "fq_dense_f16: M=%d N=%d K=%d: x and W must each stay below 4 GiB", M, N, K);
     if (tile_rows != 0 && tile_rows != 128 && tile_rows != 256)
         return fq_fail(FQ_ERR_SHAPE, "fq_dense_f16_tile: tile_rows=%d not in {0, 128, 256}", tile_rows);
+    if (tile_rows == 0 && fq_dense_rows_pays(M, N))
+        return check_hip(fq_launch_dense_rows(x, M, W, N, K, out, static_cast<fq_stream>(stream)), "fq_dense_f16 launch");
     const bool tiled = tile_rows ? tile_rows == 256 : fq_dense_tiled_pays(M, N);
     if (tiled)
         return check_hip(fq_launch_dense_tiled(x, M, W, N, K, out, static_cast<fq_stream>(stream)),

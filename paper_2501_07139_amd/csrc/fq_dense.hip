@@ -173,6 +173,217 @@ __global__ __launch_bounds__(512, 2) void dense_kernel(const _Float16 *__restric
     }
 }
 
+// ------------------------------------------------------------------ few rows
+// 16*MB activation rows x 128 weight rows per workgroup of eight wavefronts, for a handful of tokens: the logits of a
+// decode step or of a short prompt.  The weights are read once and that read is the bound (32000 x 4096: 262 MB, 51 us at
+// the rate of a large copy), so the tile is narrow enough for one workgroup on every CU (32000 rows: 250) and LDS is a ring
+// of D stages of 64 k that keeps 70 to 110 KiB a CU under way: the copies of stage kt + D - 1 go out when stage kt is
+// multiplied, and a wavefront waits, by count, for the oldest of its own stages only.  One barrier a stage: behind it
+// every wavefront's copies of the stage have landed and nobody reads the slot that the next copies fill.  Wavefronts are
+// a WM x 8/WM grid over the tile; above 32 rows two by four, which reads fewer operands per product from LDS.
+// Measured: 32000 x 4096 in 54 us at 1 to 32 rows (4.9 TB/s); see fq_dense_rows_pays.
+constexpr int RW = 128; // weight rows of a tile
+
+template <int MB>
+struct RowsTile {
+    static constexpr int WM = MB >= 4 ? 2 : 1;                                   // wavefronts along the activation rows
+    static constexpr int XB = MB / WM, WB = WM;                                  // 16-row blocks of a wavefront: activations, weights
+    static constexpr int STAGE = (RW + 16 * MB) * 8;                             // 16-byte slots: weights, then activations
+    static constexpr int D = MB >= 8 ? 4 : (MB >= 4 ? 6 : 7);                    // 128 to 144 KiB
+    static constexpr int COPIES = 2 + MB / 4;                                    // copies every wavefront issues a stage (the first ones up to one more)
+};
+
+template <int MB, bool FUSED>
+__device__ __forceinline__ void dense_rows_tile(h8 *smem, const _Float16 *__restrict__ x, int M, const _Float16 *__restrict__ W,
+                                                int N, int K, _Float16 *__restrict__ out, const LossParts loss)
+{
+    using T = RowsTile<MB>;
+    constexpr int D = T::D, XB = T::XB, WB = T::WB;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % T::WM, wn = wave / T::WM;
+    // the workgroups of an XCD take a contiguous run of tiles, row-tile fastest: weights shared by row tiles come from its L2
+    const int NT = (N + RW - 1) / RW, MT = (M + 16 * MB - 1) / (16 * MB), total = NT * MT;
+    const int per_xcd = (total + 7) >> 3;
+    const int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (tile >= total)
+        return; // uniform over the workgroup, before any barrier
+    const int m0 = (tile % MT) * 16 * MB, n0 = (tile / MT) * RW;
+    const int KT = K / DK;
+
+    // Copy i of an operand fills rows 8i .. 8i + 7 of its part of a stage, slot (row, pos) with chunk pos ^ (row/2)%8;
+    // the wavefronts take the copies in turn.  Rows past the end of an operand re-read its last row.
+    const fq_rsrc xr = make_rsrc(x, (uint32_t)M * (uint32_t)K * 2u);
+    const fq_rsrc wr = make_rsrc(W, (uint32_t)N * (uint32_t)K * 2u);
+    constexpr int XC = (2 * MB + 7) / 8; // copies of the activations a wavefront issues at most
+    uint32_t woff[2], xoff[XC];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int row = 8 * (wave + 8 * i) + (lane >> 3), ch = (lane & 7) ^ ((row >> 1) & 7);
+        woff[i] = ((uint32_t)min(n0 + row, N - 1) * (uint32_t)K + (uint32_t)ch * 8u) * 2u;
+    }
+#pragma unroll
+    for (int i = 0; i < XC; ++i) {
+        const int row = 8 * (wave + 8 * i) + (lane >> 3), ch = (lane & 7) ^ ((row >> 1) & 7);
+        xoff[i] = ((uint32_t)min(m0 + row, M - 1) * (uint32_t)K + (uint32_t)ch * 8u) * 2u;
+    }
+    auto copy_stage = [&](int kt, int slot) { // past the end: the last stage again, into a slot that is not read any more
+        h8 *const dst = smem + slot * T::STAGE;
+        const uint32_t off = (uint32_t)min(kt, KT - 1) * (DK * 2u);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, dst + 64 * (wave + 8 * i), 16, woff[i], off, 0, 0);
+#pragma unroll
+        for (int i = 0; i < XC; ++i)
+            if (wave + 8 * i < 2 * MB) // uniform over the wavefront
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, dst + RW * 8 + 64 * (wave + 8 * i), 16, xoff[i], off, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    f4 acc[WB][XB];
+#pragma unroll
+    for (int i = 0; i < WB; ++i)
+#pragma unroll
+        for (int j = 0; j < XB; ++j)
+            acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+
+#pragma unroll
+    for (int kt = 0; kt < D - 1; ++kt)
+        copy_stage(kt, kt);
+    for (int kt = 0, slot = 0; kt < KT; ++kt, slot = slot == D - 1 ? 0 : slot + 1) {
+        // at least COPIES * (D - 2) copies are younger than this stage's
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(vmcnt_at_most(T::COPIES * (D - 2)));
+        lds_barrier(); // LDS accesses only: the copies stay in flight
+        __builtin_amdgcn_sched_barrier(0);
+        copy_stage(kt + D - 1, slot == 0 ? D - 1 : slot - 1);
+        const h8 *const stage = smem + slot * T::STAGE;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const int ch = 4 * s + (lane >> 4);
+            h8 a[WB], b[XB];
+#pragma unroll
+            for (int i = 0; i < WB; ++i)
+                a[i] = stage[dense_slot(16 * (WB * wn + i) + (lane & 15), ch)];
+#pragma unroll
+            for (int j = 0; j < XB; ++j)
+                b[j] = stage[RW * 8 + dense_slot(16 * (XB * wm + j) + (lane & 15), ch)];
+#pragma unroll
+            for (int i = 0; i < WB; ++i)
+#pragma unroll
+                for (int j = 0; j < XB; ++j)
+                    acc[i][j] = mfma16x16x32(a[i], b[j], acc[i][j]);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(FQ_WAIT_VMCNT0); // copies past the end have landed ...
+    __syncthreads();                            // ... in every wavefront, and nobody reads a stage any more
+
+    // lane holds m = lane%16 and n = 4*(lane/16) + v of each 16x16 block
+    const int nw = n0 + 16 * WB * wn;
+    if constexpr (FUSED) {
+        float2 *part = reinterpret_cast<float2 *>(smem); // [16 * MB rows][8 / WM column groups]
+        constexpr int CG = 8 / T::WM;
+#pragma unroll
+        for (int j = 0; j < XB; ++j) {
+            const int row = 16 * (XB * wm + j) + (lane & 15), m = m0 + row;
+            const int label = m < M ? loss.labels[m] : -1;
+            float l[4 * WB], mx = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < WB; ++i)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int n = nw + 16 * i + 4 * (lane >> 4) + v;
+                    const float logit = (float)(_Float16)acc[i][j][v]; // what the stored fp16 logit would hold
+                    l[4 * i + v] = n < N ? logit : -INFINITY;
+                    mx = fmaxf(mx, l[4 * i + v]);
+                    if (n == label)
+                        loss.label_logit[m] = logit;
+                }
+            float se = 0.f;
+            if (mx != -INFINITY) {
+#pragma unroll
+                for (int e = 0; e < 4 * WB; ++e)
+                    se += __expf(l[e] - mx);
+            } else { // no number among the lane's few columns: a NaN has to reach the row's sum all the same
+#pragma unroll
+                for (int e = 0; e < 4 * WB; ++e)
+                    if (l[e] != l[e]) {
+                        mx = -3.0e38f;
+                        se = l[e];
+                    }
+            }
+#pragma unroll
+            for (int o = 16; o <= 32; o <<= 1) { // the four lanes that share a row
+                const float m2 = __shfl_xor(mx, o, 64), s2 = __shfl_xor(se, o, 64);
+                lse_merge(mx, se, m2, s2);
+            }
+            if (lane < 16)
+                part[row * CG + wn] = make_float2(mx, se);
+        }
+        __syncthreads();
+        // one pair per row and 64 columns, as the 256-row tiles leave them
+        const int NC = (N + 63) >> 6;
+        for (int e = tid; e < 16 * MB * 2; e += 512) {
+            const int row = e >> 1, half = e & 1, m = m0 + row, c64 = (n0 >> 6) + half;
+            if (m >= M || c64 >= NC)
+                continue;
+            float2 p = part[row * CG + half * (CG / 2)];
+#pragma unroll
+            for (int g = 1; g < CG / 2; ++g) {
+                const float2 q = part[row * CG + half * (CG / 2) + g];
+                lse_merge(p.x, p.y, q.x, q.y);
+            }
+            loss.pairs[(size_t)m * NC + c64] = p;
+        }
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < XB; ++j) {
+        const int m = m0 + 16 * (XB * wm + j) + (lane & 15);
+        if (m >= M)
+            continue;
+#pragma unroll
+        for (int i = 0; i < WB; ++i) {
+            const int n = nw + 16 * i + 4 * (lane >> 4);
+            _Float16 *o = out + (size_t)m * N + n;
+            if (n + 3 < N && (N & 3) == 0) {
+                h4 v = {(_Float16)acc[i][j][0], (_Float16)acc[i][j][1], (_Float16)acc[i][j][2], (_Float16)acc[i][j][3]};
+                *reinterpret_cast<h4 *>(o) = v;
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (n + v < N)
+                        o[v] = (_Float16)acc[i][j][v];
+            }
+        }
+    }
+}
+
+template <int MB, bool FUSED>
+__global__ __launch_bounds__(512, 2) void dense_rows_kernel(const _Float16 *__restrict__ x, int M,
+                                                            const _Float16 *__restrict__ W, int N, int K,
+                                                            _Float16 *__restrict__ out, LossParts loss)
+{
+    __shared__ h8 smem[RowsTile<MB>::D * RowsTile<MB>::STAGE]; // the only LDS object: the compiler adds no waits for the copies in flight
+    dense_rows_tile<MB, FUSED>(smem, x, M, W, N, K, out, loss);
+}
+
+typedef void (*RowsKernel)(const _Float16 *, int, const _Float16 *, int, int, _Float16 *, LossParts);
+
+int launch_rows(bool fused, const void *x, int M, const void *W, int N, int K, void *out, const LossParts &loss, fq_stream st)
+{
+    const int blocks = (M + 15) / 16;
+    static const RowsKernel table[2][4] = {
+        {dense_rows_kernel<1, false>, dense_rows_kernel<2, false>, dense_rows_kernel<4, false>, dense_rows_kernel<8, false>},
+        {dense_rows_kernel<1, true>, dense_rows_kernel<2, true>, dense_rows_kernel<4, true>, dense_rows_kernel<8, true>},
+    };
+    const int log = blocks > 4 ? 3 : (blocks > 2 ? 2 : blocks - 1), mb = 1 << log;
+    const int total = ((N + RW - 1) / RW) * ((M + 16 * mb - 1) / (16 * mb));
+    hipLaunchKernelGGL(table[fused][log], dim3(8 * ((total + 7) / 8)), dim3(512), 0, st, static_cast<const _Float16 *>(x), M,
+                       static_cast<const _Float16 *>(W), N, K, static_cast<_Float16 *>(out), loss);
+    return (int)hipGetLastError();
+}
+
 // One wavefront per row: merge the row's pairs, then nll = log(sum of exp) - label's logit; a label outside
 // [0, V) gives 0, as in the unfused loss.
 __global__ __launch_bounds__(64) void loss_finish_kernel(LossParts loss, int V, float *__restrict__ nll)
@@ -200,8 +411,23 @@ __global__ __launch_bounds__(64) void loss_finish_kernel(LossParts loss, int V, 
 
 } // namespace
 
+// The few-row tiles pay up to two rounds of them over the chip.  Measured (us; 128-row tiles that read the weights lane by
+// lane and, with the loss, 256-row tiles against these): 32000 x 4096 at 1 row 78 against 54, with the loss 105 against
+// 59; 64 rows 74 / 57, 107 / 61; 128 rows 76 / 63, 110 / 67; 256 rows (two rounds) 113 / 98, 117 / 100; 300 rows (three)
+// 129 / 135, 126 / 133.  20000 x 4096 at 384 rows 103 / 89; 4000 x 5120 at 700 rows 76 / 50.
+bool fq_dense_rows_pays(int M, int N)
+{
+    const int blocks = (M + 15) / 16, rows = blocks > 4 ? 128 : (blocks > 2 ? 64 : 16 * blocks);
+    return (long)((M + rows - 1) / rows) * ((N + RW - 1) / RW) <= 512;
+}
+
+int fq_launch_dense_rows(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st)
+{
+    return launch_rows(false, x, M, W, N, K, out, LossParts{}, st);
+}
+
 // Large tiles pay from about half a tile per CU on (measured: 128 tiles of 2048 x 4096 already run 12 % faster
-// than 512 tiles of 128 rows); below that the smaller tiles spread the work over more CUs.
+// than 512 tiles of 128 rows); what is smaller goes to the few-row tiles unless the caller pins the height.
 bool fq_dense_tiled_pays(int M, int N) { return (long)((M + DT - 1) / DT) * ((N + DT - 1) / DT) >= 128; }
 
 // x and W are addressed through 32-bit byte offsets (checked by the caller); K is a multiple of 128.
@@ -228,11 +454,16 @@ int fq_launch_head_nll(const void *x, int M, const void *W, int V, int K, const 
     loss.labels = labels;
     loss.pairs = static_cast<float2 *>(workspace);
     loss.label_logit = reinterpret_cast<float *>(loss.pairs + (size_t)M * ((V + 63) / 64));
-    const int total = ((V + DT - 1) / DT) * ((M + DT - 1) / DT);
-    dim3 grid(8 * ((total + 7) / 8)), block(512);
-    hipLaunchKernelGGL(dense_kernel<true>, grid, block, 0, st, static_cast<const _Float16 *>(x), M,
-                       static_cast<const _Float16 *>(W), V, K, static_cast<_Float16 *>(nullptr), loss);
-    int rc = (int)hipGetLastError();
+    int rc = 0;
+    if (fq_dense_rows_pays(M, V)) {
+        rc = launch_rows(true, x, M, W, V, K, nullptr, loss, st);
+    } else {
+        const int total = ((V + DT - 1) / DT) * ((M + DT - 1) / DT);
+        dim3 grid(8 * ((total + 7) / 8)), block(512);
+        hipLaunchKernelGGL(dense_kernel<true>, grid, block, 0, st, static_cast<const _Float16 *>(x), M,
+                           static_cast<const _Float16 *>(W), V, K, static_cast<_Float16 *>(nullptr), loss);
+        rc = (int)hipGetLastError();
+    }
     if (rc != 0)
         return rc;
     hipLaunchKernelGGL(loss_finish_kernel, dim3(M), dim3(64), 0, st, loss, V, nll);

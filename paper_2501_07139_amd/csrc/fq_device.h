@@ -19,6 +19,19 @@ typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 
 // s_waitcnt immediate that waits for all vector-memory loads only (vmcnt = 0, expcnt and lgkmcnt left at their maxima)
 #define FQ_WAIT_VMCNT0 0x0f70
+// ... for all LDS operations only
+#define FQ_WAIT_LGKMCNT0 0xc07f
+// ... until at most n (n < 64) vector-memory loads are in flight; they complete in the order they were issued
+constexpr int vmcnt_at_most(int n) { return 0x0f70 | (n & 15) | ((n >> 4) << 14); }
+
+// Workgroup barrier that orders LDS accesses only: waits for this wavefront's LDS operations, then for
+// the other wavefronts.  __syncthreads() also fences, and in a kernel that copies into LDS through the
+// vector-memory path the compiler makes that fence wait for every vector load in flight: here that
+// would be the weights.  The memory clobber keeps the compiler from moving accesses across it.
+__device__ __forceinline__ void lds_barrier()
+{
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
 
 __device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
 __device__ __forceinline__ uint32_t as_u32(h2 h) { return __builtin_bit_cast(uint32_t, h); }

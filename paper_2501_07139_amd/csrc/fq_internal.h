@@ -71,6 +71,8 @@ int fq_launch_gemm_multi(const void *x, int M, const fq_packed_ref *w, void *con
                          int tile_rows = 0);
 int fq_launch_dense(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
 // The same product with 256 x 256 tiles, both operands through LDS; pays once its tiles fill the chip.
+bool fq_dense_rows_pays(int M, int N);
+int fq_launch_dense_rows(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
 bool fq_dense_tiled_pays(int M, int N);
 int fq_launch_dense_tiled(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
 // Head GEMM with the token loss in its epilogue; workspace of fq_head_nll_scratch_bytes(M, V) bytes.

@@ -21,9 +21,6 @@ namespace {
 
 constexpr int SNW = 8; // wavefronts per workgroup, each a slice of K
 
-// s_waitcnt immediates: vector-memory operations in flight <= n (n < 64); all LDS operations done
-constexpr int skinny_vmcnt(int n) { return 0x0f70 | (n & 15) | ((n >> 4) << 14); }
-constexpr int SKINNY_LGKM0 = 0xc07f;
 
 struct SkinnyJob {
     const uint32_t *packed;
@@ -189,7 +186,7 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
             for (int half = 0; half < 2; ++half) {
                 // the stage's copies are older than at least the COPIES * (H - 1) copies of the stages behind it
                 __builtin_amdgcn_sched_barrier(0);
-                __builtin_amdgcn_s_waitcnt(skinny_vmcnt(COPIES * (H - 1)));
+                __builtin_amdgcn_s_waitcnt(vmcnt_at_most(COPIES * (H - 1)));
                 __builtin_amdgcn_sched_barrier(0);
                 const h8 *stage = ring + ((2 * t + half) & (H - 1)) * STAGE;
                 h8 xf[2][MB];
@@ -210,7 +207,7 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
                                 acc[u][j] = mfma16x16x32(a[u][2 * half + s], xf[s][j], acc[u][j]);
                         }
                 __builtin_amdgcn_sched_barrier(0);
-                __builtin_amdgcn_s_waitcnt(SKINNY_LGKM0); // the operands have left the slot
+                __builtin_amdgcn_s_waitcnt(FQ_WAIT_LGKMCNT0); // the operands have left the slot
                 copy(2 * t + half + H);
             }
             if constexpr (F32) {

@@ -8,15 +8,6 @@
 
 namespace {
 
-// Workgroup barrier that orders LDS accesses only: waits for this wavefront's LDS operations, then for
-// the other wavefronts.  __syncthreads() also fences, and in a kernel that copies into LDS through the
-// vector-memory path the compiler makes that fence wait for every vector load in flight: here that
-// would be the weights.  The memory clobber keeps the compiler from moving accesses across it.
-__device__ __forceinline__ void lds_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 // Sum over each aligned run of 16 lanes, in all of its lanes: four adds whose second operand comes
 // through the lane-permute path of the ALU (swap within pairs, swap pairs within quads, rotate the row
 // by 4 and by 8).

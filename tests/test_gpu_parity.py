@@ -291,6 +291,48 @@ def test_dense_head_against_oracle(fq, torch, case, tile):
         assert qerr(y, oracle.dense_f16(X, W)) <= TOL
 
 
+# Few rows: the tiles of 16, 32, 64 and 128 rows, rows that end inside a block and in a second row tile, columns that end
+# inside a block, a wavefront's columns and a 64-column group, K of fewer stages than the ring holds and of more.
+ROWS_CASES = [(1, 1000, 128), (16, 70, 384), (17, 1030, 1024), (32, 1, 256), (33, 257, 640), (64, 1001, 1024),
+              (65, 130, 384), (128, 2000, 512), (129, 1003, 256), (300, 66, 1152)]
+
+
+@pytest.mark.parametrize("case", ROWS_CASES, ids=str)
+def test_head_few_rows_against_oracle(fq, torch, case):
+    """Logits at the tolerance of the head, written nowhere else; and the loss of the same call chain, whose logits
+    are the same sums, so that the two calls differ by the order of the fp32 merges only."""
+    M, V, K = case
+    X, W = fq_synth.activations(70, M, K), fq_synth.weights(71, V, K, 0.05).astype(np.float16)
+    out = Guarded(torch, M * V * 2)
+    fq.fq_dense_f16(dev(torch, X), dev(torch, W), out=out.half(M, V))
+    assert out.intact()
+    logits = oracle.dense_f16(X, W)
+    err = np.abs(host16(out.half(M, V)).astype(np.float64) - logits)
+    # one rounding to fp16, and fp32 sums of K products
+    assert np.all(err <= 2.0 ** -11 * np.abs(logits) + 1e-6 * oracle.dense_f16(np.abs(X), np.abs(W)))
+    lab = fq_synth.labels(72, M, V)
+    lab[0] = V - 1
+    lab[M // 2:M // 2 + 1] = -1
+    ws, nll = Guarded(torch, fq.fq_head_nll_workspace_bytes(M, V)), Guarded(torch, M * 4)
+    got = fq.fq_head_nll(dev(torch, X), dev(torch, W), dev(torch, lab), out=nll.f32(M), workspace=ws.bytes())
+    assert ws.intact() and nll.intact()
+    two = fq.fq_token_nll(out.half(M, V).clone(), dev(torch, lab))
+    assert float((got - two).abs().max()) <= 2e-5
+    assert np.max(np.abs(got.cpu().numpy().astype(np.float64) - oracle.token_nll(oracle.round_f16(logits), lab))) <= 2e-3
+
+
+def test_head_nll_few_rows_carries_nan_and_infinity(fq, torch):
+    """A NaN in four columns only (one lane's share) reaches the loss; a 64-column group of -inf adds nothing to it."""
+    M, V, K = 20, 200, 128
+    X, W = np.zeros((M, K), dtype=np.float16), np.zeros((V, K), dtype=np.float16)
+    X[:, 0] = 1.0
+    lab = dev(torch, np.full(M, 150, dtype=np.int32))
+    W[100:104, 0] = np.nan
+    assert np.isnan(fq.fq_head_nll(dev(torch, X), dev(torch, W), lab).cpu().numpy()).all()
+    W[100:104, 0], W[0:64, 0] = 0.0, -np.inf
+    assert np.allclose(fq.fq_head_nll(dev(torch, X), dev(torch, W), lab).cpu().numpy(), math.log(V - 64), atol=1e-4)
+
+
 # ----------------------------------------------------------------------- NLL
 def test_token_nll_closed_forms(fq, torch):
     V = 32000
