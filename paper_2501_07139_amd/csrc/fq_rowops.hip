@@ -157,12 +157,34 @@ __global__ __launch_bounds__(256) void glue2_kernel(const _Float16 *__restrict__
 }
 
 // ------------------------------------------------------------------- NLL
+// Rows of logits: base pointers are 16-byte aligned, rows of V elements are so only if V % 8 == 0.  Elements [0, head) of a row lie before
+// its first aligned chunk of eight, elements [head + 8 * chunks, V) behind its last; both are fewer than eight.
+struct RowSpan {
+    int head, chunks;
+    __device__ __forceinline__ RowSpan(int row, int V)
+    {
+        head = min((int)((8u - (uint32_t)(((uint64_t)row * (uint64_t)V) & 7u)) & 7u), V);
+        chunks = (V - head) >> 3;
+    }
+    // element of thread i's share of the unaligned ends: thread i < head the i-th, then those behind the chunks; -1: none
+    __device__ __forceinline__ int end_element(int i, int V) const
+    {
+        const int e = i < head ? i : i + 8 * chunks;
+        return e < V ? e : -1;
+    }
+};
+
+constexpr int ROW_UNROLL = 4; // chunks a thread loads before it uses the first
+
 // One workgroup per token row; each thread keeps a running (max, sum of
 // exp(l - max)) over its 16-byte chunks, then the pairs are merged across the
-// wavefront and the workgroup.  The label's logit is read directly.
-__global__ __launch_bounds__(256) void nll_kernel(const _Float16 *__restrict__ logits,
-                                                  const int32_t *__restrict__ labels, int V,
-                                                  float *__restrict__ nll)
+// wavefront and the workgroup.  The label's logit is read directly.  Bound by the read; few rows take large
+// workgroups (THREADS), so that the loads of a row are under way together.
+// Measured (us): 2048 x 32000 30; 2048 x 31001, whose rows are not aligned, 29 (element by element 71).
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void nll_kernel(const _Float16 *__restrict__ logits,
+                                                      const int32_t *__restrict__ labels, int V,
+                                                      float *__restrict__ nll)
 {
     const int row = blockIdx.x;
     const int label = labels[row];
@@ -172,32 +194,44 @@ __global__ __launch_bounds__(256) void nll_kernel(const _Float16 *__restrict__ l
         return;
     }
     const _Float16 *l = logits + (size_t)row * V;
+    const RowSpan span(row, V);
+    const h8 *chunk = reinterpret_cast<const h8 *>(l + span.head);
     float mx = -INFINITY, se = 0.f;
-    // rows start 16-byte aligned only if V % 8 == 0; otherwise take the scalar route
-    if ((V & 7) == 0) {
-        const int chunks = V >> 3;
-        for (int ch = threadIdx.x; ch < chunks; ch += 256) {
-            const h8 v = *reinterpret_cast<const h8 *>(l + ch * 8);
-            float cm = (float)v[0];
+    auto add = [&](h8 v) {
+        float cm = (float)v[0];
 #pragma unroll
-            for (int e = 1; e < 8; ++e)
-                cm = fmaxf(cm, (float)v[e]);
-            float cs = 0.f;
+        for (int e = 1; e < 8; ++e)
+            cm = fmaxf(cm, (float)v[e]);
+        float cs = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                cs += __expf((float)v[e] - cm);
-            lse_merge(mx, se, cm, cs);
-        }
-    } else {
-        for (int i = threadIdx.x; i < V; i += 256)
-            lse_merge(mx, se, (float)l[i], 1.0f);
+        for (int e = 0; e < 8; ++e)
+            cs += __expf((float)v[e] - cm);
+        lse_merge(mx, se, cm, cs);
+    };
+    int ch = threadIdx.x;
+    for (; ch + (ROW_UNROLL - 1) * THREADS < span.chunks; ch += ROW_UNROLL * THREADS) {
+        h8 v[ROW_UNROLL];
+#pragma unroll
+        for (int i = 0; i < ROW_UNROLL; ++i)
+            v[i] = chunk[ch + i * THREADS];
+#pragma unroll
+        for (int i = 0; i < ROW_UNROLL; ++i)
+            add(v[i]);
+    }
+    for (; ch < span.chunks; ch += THREADS)
+        add(chunk[ch]);
+    if (threadIdx.x < 16) { // fewer than sixteen elements lie outside the chunks
+        const int e = span.end_element(threadIdx.x, V);
+        if (e >= 0)
+            lse_merge(mx, se, (float)l[e], 1.0f);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const float m2 = __shfl_xor(mx, o, 64), s2 = __shfl_xor(se, o, 64);
         lse_merge(mx, se, m2, s2);
     }
-    __shared__ float pm[4], ps[4];
+    constexpr int WAVES = THREADS / 64;
+    __shared__ float pm[WAVES], ps[WAVES];
     if ((threadIdx.x & 63) == 0) {
         pm[threadIdx.x >> 6] = mx;
         ps[threadIdx.x >> 6] = se;
@@ -205,7 +239,7 @@ __global__ __launch_bounds__(256) void nll_kernel(const _Float16 *__restrict__ l
     __syncthreads();
     if (threadIdx.x == 0) {
         float m = pm[0], s = ps[0];
-        for (int w = 1; w < 4; ++w)
+        for (int w = 1; w < WAVES; ++w)
             lse_merge(m, s, pm[w], ps[w]);
         nll[row] = logf(s) + (m - (float)l[label]); // difference first: exact for fp16 inputs
     }
@@ -276,30 +310,51 @@ int fq_launch_glue2(int op, const void *a, const void *b, int M, int H, void *au
     return (int)hipGetLastError();
 }
 
+// Workgroup size of the two row kernels: up to one row a CU, 1024 threads bring more loads of a long row under way (32000
+// logits, 256 rows: distance 8.5 -> 7.0 us, loss 9.5 -> 7.9; 384 rows: level); short rows only pay for the larger
+// reduction (1000 logits: 3.0 -> 3.8 us).
+static bool wide_rows(int M, int V) { return M <= 256 && V >= 8192; }
+
 // Row-wise Euclidean distance between two logit arrays (sensitivity analysis of the search, Section
 // "Efficient Design Space Navigation").  One workgroup per row, one pass over both rows with 128-bit loads; differences and
-// squares in fp32, four partial sums per thread, then a fixed-order reduction.
-__global__ __launch_bounds__(256) void logit_l2_kernel(const _Float16 *__restrict__ a, const _Float16 *__restrict__ b,
-                                                       int V, float *__restrict__ dist)
+// squares in fp32, four partial sums per thread, then a fixed-order reduction.  The two rows start at the same distance
+// from a 16-byte boundary.  Measured (us): 2048 x 32000 43, 2048 x 31001 41 (element by element 70).
+namespace {
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void logit_l2_kernel(const _Float16 *__restrict__ a, const _Float16 *__restrict__ b,
+                                                           int V, float *__restrict__ dist)
 {
     const int row = blockIdx.x;
     const _Float16 *ra = a + (size_t)row * V, *rb = b + (size_t)row * V;
+    const RowSpan span(row, V);
+    const h8 *ca = reinterpret_cast<const h8 *>(ra + span.head), *cb = reinterpret_cast<const h8 *>(rb + span.head);
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    // rows start 16-byte aligned only if V % 8 == 0; otherwise take the scalar route
-    if ((V & 7) == 0) {
-        const int chunks = V >> 3;
-        for (int ch = threadIdx.x; ch < chunks; ch += 256) {
-            const h8 va = *reinterpret_cast<const h8 *>(ra + ch * 8), vb = *reinterpret_cast<const h8 *>(rb + ch * 8);
-            float d[8];
+    auto add = [&](h8 va, h8 vb) {
+        float d[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                d[e] = (float)va[e] - (float)vb[e];
-            s0 = fmaf(d[0], d[0], s0); s1 = fmaf(d[1], d[1], s1); s2 = fmaf(d[2], d[2], s2); s3 = fmaf(d[3], d[3], s3);
-            s0 = fmaf(d[4], d[4], s0); s1 = fmaf(d[5], d[5], s1); s2 = fmaf(d[6], d[6], s2); s3 = fmaf(d[7], d[7], s3);
+        for (int e = 0; e < 8; ++e)
+            d[e] = (float)va[e] - (float)vb[e];
+        s0 = fmaf(d[0], d[0], s0); s1 = fmaf(d[1], d[1], s1); s2 = fmaf(d[2], d[2], s2); s3 = fmaf(d[3], d[3], s3);
+        s0 = fmaf(d[4], d[4], s0); s1 = fmaf(d[5], d[5], s1); s2 = fmaf(d[6], d[6], s2); s3 = fmaf(d[7], d[7], s3);
+    };
+    int ch = threadIdx.x;
+    for (; ch + (ROW_UNROLL - 1) * THREADS < span.chunks; ch += ROW_UNROLL * THREADS) {
+        h8 va[ROW_UNROLL], vb[ROW_UNROLL];
+#pragma unroll
+        for (int i = 0; i < ROW_UNROLL; ++i) {
+            va[i] = ca[ch + i * THREADS];
+            vb[i] = cb[ch + i * THREADS];
         }
-    } else {
-        for (int i = threadIdx.x; i < V; i += 256) {
-            const float d = (float)ra[i] - (float)rb[i];
+#pragma unroll
+        for (int i = 0; i < ROW_UNROLL; ++i)
+            add(va[i], vb[i]);
+    }
+    for (; ch < span.chunks; ch += THREADS)
+        add(ca[ch], cb[ch]);
+    if (threadIdx.x < 16) {
+        const int e = span.end_element(threadIdx.x, V);
+        if (e >= 0) {
+            const float d = (float)ra[e] - (float)rb[e];
             s0 = fmaf(d, d, s0);
         }
     }
@@ -307,24 +362,37 @@ __global__ __launch_bounds__(256) void logit_l2_kernel(const _Float16 *__restric
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)
         ss += __shfl_xor(ss, o, 64);
-    __shared__ float part[4];
+    constexpr int WAVES = THREADS / 64;
+    __shared__ float part[WAVES];
     if ((threadIdx.x & 63) == 0)
         part[threadIdx.x >> 6] = ss;
     __syncthreads();
-    if (threadIdx.x == 0)
-        dist[row] = sqrtf((part[0] + part[1]) + (part[2] + part[3]));
+    if (threadIdx.x == 0) {
+        float sum = 0.f;
+        for (int w = 0; w < WAVES; ++w)
+            sum += part[w];
+        dist[row] = sqrtf(sum);
+    }
 }
+} // namespace
 
 int fq_launch_logit_l2(const void *a, const void *b, int M, int V, float *dist, fq_stream st)
 {
-    hipLaunchKernelGGL(logit_l2_kernel, dim3(M), dim3(256), 0, st, static_cast<const _Float16 *>(a),
-                       static_cast<const _Float16 *>(b), V, dist);
+    const _Float16 *pa = static_cast<const _Float16 *>(a), *pb = static_cast<const _Float16 *>(b);
+    if (wide_rows(M, V))
+        hipLaunchKernelGGL(logit_l2_kernel<1024>, dim3(M), dim3(1024), 0, st, pa, pb, V, dist);
+    else
+        hipLaunchKernelGGL(logit_l2_kernel<256>, dim3(M), dim3(256), 0, st, pa, pb, V, dist);
     return (int)hipGetLastError();
 }
 
 int fq_launch_nll(const void *logits, const int32_t *labels, int M, int V, float *nll, fq_stream st)
 {
-    hipLaunchKernelGGL(nll_kernel, dim3(M), dim3(256), 0, st, static_cast<const _Float16 *>(logits), labels, V, nll);
+    const _Float16 *l = static_cast<const _Float16 *>(logits);
+    if (wide_rows(M, V))
+        hipLaunchKernelGGL(nll_kernel<1024>, dim3(M), dim3(1024), 0, st, l, labels, V, nll);
+    else
+        hipLaunchKernelGGL(nll_kernel<256>, dim3(M), dim3(256), 0, st, l, labels, V, nll);
     return (int)hipGetLastError();
 }
 

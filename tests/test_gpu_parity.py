@@ -412,6 +412,23 @@ def test_logit_l2_against_oracle(fq, torch, shape):
     assert np.allclose(got, oracle.logit_l2(big, neg), rtol=1e-5)
 
 
+@pytest.mark.parametrize("V", [1, 7, 9, 15, 17, 1003, 8191, 8197, 31001])
+@pytest.mark.parametrize("M", [5, 260])
+def test_row_kernels_on_unaligned_rows(fq, torch, M, V):
+    """Rows that start anywhere between 16-byte boundaries: elements before the first whole chunk, behind the last, and
+    rows without any; both workgroup sizes.  A logit of its own size in every position of the ends makes a missed
+    or doubled one show.  Bounds: those of the aligned rows."""
+    a, b = fq_synth.logits(410, M, V), fq_synth.logits(411, M, V)
+    a[:, :8] += np.arange(1, 1 + min(8, V), dtype=np.float16)[None, :]
+    a[:, -8:] -= np.arange(1, 1 + min(8, V), dtype=np.float16)[None, :]
+    lab = fq_synth.labels(412, M, V)
+    lab[0], lab[-1] = V - 1, 0
+    got = fq.fq_token_nll(dev(torch, a), dev(torch, lab)).cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(got - oracle.token_nll(a, lab))) <= 2e-3
+    got = fq.fq_logit_l2(dev(torch, a), dev(torch, b)).cpu().numpy().astype(np.float64)
+    assert np.allclose(got, oracle.logit_l2(a, b), rtol=1e-5, atol=0)
+
+
 @pytest.mark.parametrize("H", [256, 4096, 11008, 13824])
 def test_glue_steps_against_oracle(fq, torch, H):
     M = 9
