@@ -790,10 +790,19 @@ int fq_launch_gemv_multi(const fq_gemv_input &src, int M, const fq_packed_ref *w
         units[i] = parts[i] > 1 ? (nrb[i] + 7) / 8 * 8 * parts[i] : nrb[i];
         gran[i] = parts[i] > 1 ? 8 * parts[i] : 1;
         unit_cost[i] = row_cost[w[i].bits] / parts[i];
-        nbs[i] = gran[i];
-        used += gran[i];
     }
-    // Hand the remaining workgroups, a granule at a time, to the matrix that would finish last.
+    // Seven eighths of every matrix's share by time at once, then hand the remaining workgroups, a granule at a time, to the
+    // matrix that would finish last.  (All of them a granule at a time took the host 2.5 us for a 4-bit 11008 x 4096 matrix,
+    // longer than the launch itself.)
+    double total_cost = 0.0;
+    for (int i = 0; i < count; ++i)
+        total_cost += units[i] * unit_cost[i];
+    for (int i = 0; i < count; ++i) {
+        const int share = (int)(0.875 * resident * (units[i] * unit_cost[i] / total_cost)) / gran[i] * gran[i];
+        const int most = (units[i] + gran[i] - 1) / gran[i] * gran[i];
+        nbs[i] = share < gran[i] ? gran[i] : (share < most ? share : most);
+        used += nbs[i];
+    }
     for (;;) {
         int worst = -1;
         double worst_t = -1.0;
