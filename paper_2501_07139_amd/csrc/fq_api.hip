@@ -164,7 +164,7 @@ extern "C" int fq_qlinear_mixed(const void *x, int M, const fq_segment *segments
                              segments[i].bits, (int)total};
         outs[i] = static_cast<_Float16 *>(out) + col; // row 0 of the segment's column range; rows are `total` apart
         col += segments[i].N;
-        stream_all = stream_all && fq_gemv_can_stream(M, K, segments[i].bits, 1);
+        stream_all = stream_all && fq_gemv_can_stream(M, K, segments[i].bits, 0);
     }
     // up to three segments share a launch (they share x): the same multi-matrix launches q/k/v and gate/up use
     for (int i = 0; i < count; i += 3) {
@@ -434,9 +434,10 @@ static int stack_forward_checked(const fq_layer *layers, int L, const uint8_t *b
     // block, hidden 1024 / ffn 2816: 35 and 34 at three rows, 40 against 29 at four, 106 against 29 at sixteen; rows of
     // 4096 / 11008 elements do not fit the staging from four rows on: 64 us at four rows against 60 at three).
     bool decode = M <= 3;
+    static const int stack_mode[7] = {5, 5, 5, 2, 3, 3, 4}; // input transform of each linear (mode 1 needs no more than 5)
     for (int l = 0; l < L && decode; ++l)
         for (int j = 0; j < 7; ++j)
-            decode = decode && fq_gemv_can_stream(M, layers[l].m[j].K, bitvec[7 * l + j], j == 3 ? 3 : 2);
+            decode = decode && fq_gemv_can_stream(M, layers[l].m[j].K, bitvec[7 * l + j], stack_mode[j]);
 
     const void *xcur = x_in;
     for (int l = 0; l < L; ++l) {
@@ -542,7 +543,7 @@ extern "C" int fq_decode_step(const fq_layer *layers, int L, const uint8_t *bitv
         return rc;
     for (int l = 0; l < L; ++l)
         for (int j = 0; j < 7; ++j)
-            if (!fq_gemv_can_stream(1, layers[l].m[j].K, bitvec[7 * l + j], 2))
+            if (!fq_gemv_can_stream(1, layers[l].m[j].K, bitvec[7 * l + j], j == 6 ? 6 : (j == 3 ? 0 : 3)))
                 return fq_fail(FQ_ERR_SHAPE, "fq_decode_step: rows of %d elements do not fit the decode kernel",
                                layers[l].m[j].K);
     if (workspace_bytes < fq_decode_workspace_bytes(H, F, Tmax))

@@ -133,15 +133,13 @@ int launch_generic(const void *x, int M, const fq_packed_ref &w, void *out, fq_s
 }
 
 // ---------------------------------------------------------------- streaming
-#ifndef FQ_GNW
-#define FQ_GNW 8
-#endif
-constexpr int GNW = FQ_GNW; // wavefronts per workgroup
+constexpr int GNW = 8; // wavefronts per workgroup (16, one workgroup a CU: slower, 4.3 -> 6.0 us for 4096 x 4096 at 4 bits)
 
-// Groups in flight per wavefront.  HBM throughput here follows the bytes in flight (about 3 us of loaded
-// latency): 16 wavefronts per CU times 4-6 KiB each.
-template <int BITS>
-struct GemvDepth { static constexpr int D = (BITS == 3) ? 2 : (BITS == 8 ? 3 : 4); };
+// Groups in flight per wavefront (D): two.  A wavefront runs its items in whole turns of the ring, so a deeper one makes
+// it run more items past the end of its work (5 groups a wavefront at K = 5120: eight items at four, six at two), and
+// it is more code to fetch; what is in flight is enough at two (16 wavefronts a CU).  Measured, four (three at 8 bits)
+// against two: 13B-shaped block at 2 bits 50.6 -> 44.4 us, 3 / 4 / 8 bits at 4096 x 4096 and above level or up to 15 %
+// better; only long rows of 4 bits (11008 and up: eleven groups a wavefront) are better at four (7.7 against 8.3 us).
 
 struct GemvJob {
     const uint32_t *packed;
@@ -149,7 +147,7 @@ struct GemvJob {
     _Float16 *out;
     int N, bits;
     int blk0, nblk; // the workgroups [blk0, blk0 + nblk) of the launch serve this matrix
-    int split;      // 2- and 3-bit only: work units are the 16-row sub-blocks of a supertile row, not whole rows
+    int split;      // 2- and 3-bit only: 2 or 4 work units per supertile row (2 of 4 sub-blocks, or 1); 0: whole rows
     int ld;         // elements between consecutive rows of out (N, or more when out is a column range of a wider array)
 };
 
@@ -172,6 +170,23 @@ struct GemvInput {
 };
 
 
+// The feed-forward modes (4 and 6) read two long rows: with all of them in LDS there is room for one workgroup a CU
+// (ffn 13824: 95 KiB).  A thread keeps its chunks of the first two trips over the rows in registers instead (62 KiB).
+template <int MODE>
+struct GemvRows {
+    static constexpr int TRIPS = MODE == 4 || MODE == 6 ? 2 : 0;
+    h8 a[TRIPS + 1], b[TRIPS + 1];
+    __device__ __forceinline__ void load(const _Float16 *pa, const _Float16 *pb, int chunks)
+    {
+#pragma unroll
+        for (int t = 0; t < TRIPS; ++t) { // past the end of the row a thread repeats the last chunk
+            const size_t off = (size_t)min((int)threadIdx.x + 64 * GNW * t, chunks - 1) * 8;
+            a[t] = *reinterpret_cast<const h8 *>(pa + off);
+            b[t] = *reinterpret_cast<const h8 *>(pb + off);
+        }
+    }
+};
+
 // Sum over the workgroup, the same value in every thread.  part holds two sets of per-wavefront
 // partials used in turn (which = 0, 1, 0, ...), so one barrier per sum is enough: a wavefront can only
 // be two sums ahead of another after passing the barrier of the sum in between.
@@ -191,8 +206,8 @@ __device__ __forceinline__ float gemv_block_sum(float v, float *part, int which)
 }
 
 // One (work unit, group) item in flight: the packed dwords a lane owns and the scales and zeros.  A unit
-// is S sub-blocks of 16 weight rows: a whole supertile row (whole planes, 128-bit loads), or a single
-// sub-block of a 2- or 3-bit supertile row (just its BITS dwords).
+// is S sub-blocks of 16 weight rows: a whole supertile row (whole planes, 128-bit loads), half of a 3-bit one, or a
+// single sub-block of a 2- or 3-bit supertile row (just its BITS dwords).
 // Scales and zeros: the item needs 2S values per weight row (value 2u the scale, 2u+1 the zero of sub-block
 // u), and every lane of a row's column (lane % 16) would load the same ones.  Instead the four 16-lane
 // groups of the wavefront load four different values with ONE instruction (lane group c of load q fetches
@@ -204,7 +219,7 @@ struct GemvSlot {
     static constexpr bool WHOLE = S == Fmt<BITS>::SUB;
     static constexpr int NMETA = (2 * S + 3) / 4;
     u4v plane[WHOLE ? Fmt<BITS>::PLANES : 1];
-    uint32_t w[WHOLE ? 1 : BITS];
+    uint32_t w[WHOLE ? 1 : S * BITS]; // half of a 3-bit supertile row: four dwords of plane 0 or 2, then two of plane 1
     uint32_t meta[NMETA]; // fp16 bits: in lane group c of meta[q], value 4q + c of weight row lane % 16
 };
 
@@ -217,12 +232,14 @@ struct GemvCursor {
 // S: sub-blocks per work unit (all of a supertile row's, or 1).  With F = SUB/S units per supertile row,
 // unit ub is part (ub/8) % F of supertile row (ub / (8F)) * 8 + ub % 8: the F workgroups that share a
 // supertile row (and read the same cache lines) are 8 apart, i.e. on the same XCD and L2.
-template <int BITS, int MODE, int MV, int S>
+template <int BITS, int MODE, int MV, int S, int D = 2>
 __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvInput in, int M, int K,
-                                          unsigned char *smem, float *part)
+                                          unsigned char *smem, float *part, GemvRows<MODE> &rows)
 {
-    constexpr int SUB = Fmt<BITS>::SUB, ROWS = Fmt<BITS>::ROWS, D = GemvDepth<BITS>::D, TILE = tile_dwords<BITS>();
+    constexpr int SUB = Fmt<BITS>::SUB, ROWS = Fmt<BITS>::ROWS, TILE = tile_dwords<BITS>();
     constexpr int NIN = GemvInputs<MODE>::N, STEP = 64 * GNW;
+    constexpr int RT = GemvRows<MODE>::TRIPS; // trips of the input rows that `rows` holds; the others are in LDS
+    constexpr int SM = MV == 1 ? 1 : 16; // activation rows the group sums are kept for
     constexpr int F = SUB / S;
     constexpr bool WHOLE = F == 1;
     constexpr int NMETA = GemvSlot<BITS, S>::NMETA;
@@ -230,11 +247,11 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
     const int T = (G + GNW - 1) / GNW; // groups per wavefront and supertile row
     const int GP = T * GNW;            // groups rounded up to whole turns of the wavefronts: the rest is zero
     h8 *xl = reinterpret_cast<h8 *>(smem);                                   // [GP*16][M] staged activations
-    float *xsum = reinterpret_cast<float *>(smem + (size_t)GP * 16 * M * 16); // [GP][16] sum of x over the group
-    float *csum = xsum + (size_t)GP * 16;                                    // [GP][16] 2^-E * 1024 * sum of staged x
-    float *esc = csum + (size_t)GP * 16;                                     // [GP][16] 2^-E of the group
-    float *red = esc + (size_t)GP * 16;                                      // [2][GNW][S*MV][64]
-    h8 *raw = reinterpret_cast<h8 *>(red); // [NIN][trips][STEP] raw input row; free again before the first reduction
+    float *xsum = reinterpret_cast<float *>(smem + (size_t)GP * 16 * M * 16); // [GP][SM] sum of x over the group
+    float *csum = xsum + (size_t)GP * SM;                                    // [GP][SM] 2^-E * 1024 * sum of staged x
+    float *esc = csum + (size_t)GP * SM;                                     // [GP][SM] 2^-E of the group
+    float *red = esc + (size_t)GP * SM;                                      // [2][GNW][S*MV][64]
+    h8 *raw = reinterpret_cast<h8 *>(red); // [NIN][trips - RT][STEP] raw input row; free again before the first reduction
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // scalar: keeps tile addressing in SGPRs
@@ -296,6 +313,15 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
             const u2v v = *reinterpret_cast<const u2v *>(tile + plane_off + 2 * pre_part);
             sl.w[0] = v.x;
             sl.w[1] = v.y;
+        } else if constexpr (S == 2) {
+            const u4v v = *reinterpret_cast<const u4v *>(tile + plane_off + 512 * pre_part);
+            const u2v q = *reinterpret_cast<const u2v *>(tile + plane_off + 256 + 2 * pre_part);
+            sl.w[0] = v.x;
+            sl.w[1] = v.y;
+            sl.w[2] = v.z;
+            sl.w[3] = v.w;
+            sl.w[4] = q.x;
+            sl.w[5] = q.y;
         } else {
 #pragma unroll
             for (int i = 0; i < BITS; ++i) {
@@ -324,18 +350,17 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
     // MODE 4 (the expensive transform) is evaluated once: the first pass over the row leaves the eight
     // fp32 products in the two 16-byte slots of its inputs, which only this thread touches.
     using Chunk = GemvChunk<MODE>;
+    const int lds_trips = max(trips - RT, 0);
     auto fetch = [&](int t, Chunk &v, bool first) { // this thread's chunk of trip t, combined
         h8 r[NIN];
 #pragma unroll
         for (int i = 0; i < NIN; ++i)
-            r[i] = raw[(i * trips + t) * STEP + tid];
+            r[i] = raw[(i * lds_trips + t - RT) * STEP + tid];
         if constexpr (MODE == 4) {
             if (first) {
                 gemv_combine<MODE>(r, v);
-                if (t > 0) { // trip 0 stays in registers
-                    raw[t * STEP + tid] = __builtin_bit_cast(h8, f4{v.f[0], v.f[1], v.f[2], v.f[3]});
-                    raw[(trips + t) * STEP + tid] = __builtin_bit_cast(h8, f4{v.f[4], v.f[5], v.f[6], v.f[7]});
-                }
+                raw[(t - RT) * STEP + tid] = __builtin_bit_cast(h8, f4{v.f[0], v.f[1], v.f[2], v.f[3]});
+                raw[(lds_trips + t - RT) * STEP + tid] = __builtin_bit_cast(h8, f4{v.f[4], v.f[5], v.f[6], v.f[7]});
             } else {
                 const f4 lo = __builtin_bit_cast(f4, r[0]), hi = __builtin_bit_cast(f4, r[1]);
 #pragma unroll
@@ -348,14 +373,39 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
             gemv_combine<MODE>(r, v);
         }
     };
-    // The chunk of trip 0 stays in registers between the passes over the row (it is the whole row up
-    // to K = 4096); later trips are fetched from LDS again.
+    // The chunks of the first HELD trips stay in registers between the passes over the row (trip 0 is the whole row up to
+    // K = 4096); later trips are fetched from LDS again.
+    constexpr int HELD = RT > 0 ? RT : 1;
     int sums = 0; // block sums taken so far: selects the partials' buffer
+    // x of the linear (fp16) of chunk kc of row mm: writes it to LDS, and the group sums (the 16 lanes that share a
+    // group are all here: chunks is a multiple of 16)
+    auto store_x = [&](int mm, int kc, h8 xe) {
+        // the group's exponent: its largest |x| (exponent field ex, taken as 1 for zero and subnormal
+        // maxima) is brought to 2^14: E = 29 - ex in [-1, 28]
+        const int ex = min(max((int)(group_max_bits(xe) >> 10), 1), 30), E = 29 - ex;
+        const h8 w = stage_scaled<BITS>(xe, (kc >> 2) & 3, E);
+        xl[(size_t)kc * M + mm] = w;
+        const float sx = row16_sum(gemv_sum(xe)), sc = row16_sum(gemv_sum(w));
+        if ((kc & 15) == 0) {
+            const float einv = __builtin_bit_cast(float, (uint32_t)(127 - E) << 23); // 2^-E
+            xsum[(kc >> 4) * SM + mm] = sx;
+            csum[(kc >> 4) * SM + mm] = einv * (1024.0f * sc); // exact scaling
+            esc[(kc >> 4) * SM + mm] = einv;
+        }
+    };
     auto stage_row = [&](int mm) {
-        Chunk v0;
-        const bool has0 = tid < chunks;
-        if (has0)
-            fetch(0, v0, true);
+        Chunk held[HELD];
+#pragma unroll
+        for (int t = 0; t < HELD; ++t)
+            if (tid + STEP * t < chunks) {
+                if constexpr (RT > 0) {
+                    const h8 r[2] = {rows.a[t], rows.b[t]};
+                    if constexpr (NIN == 2)
+                        gemv_combine<MODE>(r, held[t]);
+                } else {
+                    fetch(t, held[t], true);
+                }
+            }
         float inv1 = 1.0f, inv2 = 1.0f;
         if constexpr (MODE != 0 && MODE != 6) {
             // sum of squares of the row; second: of the fp16 result of the first rms
@@ -372,9 +422,11 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
                             ss = fmaf(v.f[e], v.f[e], ss);
                     }
                 };
-                if (has0)
-                    add(v0);
-                for (int t = 1; t < trips; ++t)
+#pragma unroll
+                for (int t = 0; t < HELD; ++t)
+                    if (tid + STEP * t < chunks)
+                        add(held[t]);
+                for (int t = HELD; t < trips; ++t)
                     if (tid + STEP * t < chunks) {
                         Chunk v;
                         fetch(t, v, !second);
@@ -386,8 +438,6 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
             if constexpr (MODE == 5) // rms twice: the first result is the stored fp16 block output
                 inv2 = 1.0f / sqrtf(gemv_block_sum(squares(true), part, sums++ & 1) / (float)K + 1e-5f);
         }
-        // writes one chunk of x to LDS, and the group sums (the 16 lanes that share a group are all here:
-        // chunks is a multiple of 16)
         auto put = [&](int kc, const Chunk &v) {
             h8 xe; // the linear's input, fp16
             if constexpr (MODE == 0) {
@@ -406,22 +456,13 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
             } else {
                 xe = gemv_scaled(v.f, inv1);
             }
-            // the group's exponent: its largest |x| (exponent field ex, taken as 1 for zero and subnormal
-            // maxima) is brought to 2^14: E = 29 - ex in [-1, 28]
-            const int ex = min(max((int)(group_max_bits(xe) >> 10), 1), 30), E = 29 - ex;
-            const h8 w = stage_scaled<BITS>(xe, (kc >> 2) & 3, E);
-            xl[(size_t)kc * M + mm] = w;
-            const float sx = row16_sum(gemv_sum(xe)), sc = row16_sum(gemv_sum(w));
-            if ((kc & 15) == 0) {
-                const float einv = __builtin_bit_cast(float, (uint32_t)(127 - E) << 23); // 2^-E
-                xsum[(kc >> 4) * 16 + mm] = sx;
-                csum[(kc >> 4) * 16 + mm] = einv * (1024.0f * sc); // exact scaling
-                esc[(kc >> 4) * 16 + mm] = einv;
-            }
+            store_x(mm, kc, xe);
         };
-        if (has0)
-            put(tid, v0);
-        for (int t = 1; t < trips; ++t)
+#pragma unroll
+        for (int t = 0; t < HELD; ++t)
+            if (tid + STEP * t < chunks)
+                put(tid + STEP * t, held[t]);
+        for (int t = HELD; t < trips; ++t)
             if (tid + STEP * t < chunks) {
                 Chunk v;
                 fetch(t, v, false);
@@ -432,8 +473,8 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
     // activation rows past M.
     for (int i = chunks * M + tid; i < GP * 16 * M; i += STEP)
         xl[i] = h8{0, 0, 0, 0, 0, 0, 0, 0};
-    for (int i = tid; i < GP * 16; i += STEP)
-        if ((i & 15) >= M || (i >> 4) >= G) {
+    for (int i = tid; i < GP * SM; i += STEP)
+        if (i % SM >= M || i / SM >= G) {
             xsum[i] = 0.f;
             csum[i] = 0.f;
             esc[i] = 0.f;
@@ -441,11 +482,13 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
     stage_row(0);
     for (int mm = 1; mm < M; ++mm) {
         lds_barrier(); // every thread is done with the previous row
-        for (int t = 0; t < trips; ++t) { // through registers: behind the weights whichever way
+        if constexpr (RT > 0)
+            rows.load(in.a + (size_t)mm * K, in.b + (size_t)mm * K, chunks);
+        for (int t = RT; t < trips; ++t) { // through registers: behind the weights whichever way
             const size_t off = (size_t)mm * K + (size_t)min(tid + STEP * t, chunks - 1) * 8;
 #pragma unroll
             for (int i = 0; i < NIN; ++i)
-                raw[(i * trips + t) * STEP + tid] = *reinterpret_cast<const h8 *>(src[i] + off);
+                raw[(i * lds_trips + t - RT) * STEP + tid] = *reinterpret_cast<const h8 *>(src[i] + off);
         }
         lds_barrier();
         stage_row(mm);
@@ -498,9 +541,9 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
                         eg[v] = e4[v];
                     }
                 } else {
-                    xg[0] = xsum[g * 16];
-                    cg[0] = csum[g * 16];
-                    eg[0] = esc[g * 16];
+                    xg[0] = xsum[g];
+                    cg[0] = csum[g];
+                    eg[0] = esc[g];
                 }
 #pragma unroll
                 for (int u = 0; u < S; ++u) {
@@ -512,6 +555,11 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
                             const u4v pl = ring[d].plane[j >> 2];
                             C[i] = (j & 3) == 0 ? pl.x : ((j & 3) == 1 ? pl.y : ((j & 3) == 2 ? pl.z : pl.w));
                         }
+                    } else if constexpr (S == 2) { // dwords 0..5 of the supertile's twelve, or 6..11
+                        const bool low = unit_part(cur.ub) == 0;
+#pragma unroll
+                        for (int i = 0; i < BITS; ++i)
+                            C[i] = low ? ring[d].w[BITS * u + i] : ring[d].w[(BITS * u + i + 4) % 6];
                     } else {
 #pragma unroll
                         for (int i = 0; i < BITS; ++i)
@@ -583,21 +631,24 @@ __global__ __launch_bounds__(64 * GNW, 4) void gemv_stream_kernel(const _Float16
     // LDS.  The i-th copy of a wavefront fills 64 consecutive 16-byte slots, lane by lane; chunk indices past the
     // end of the row are clamped (their slots are never read).  The destination is the region the bodies call
     // `raw` (behind the staged activations and the three group arrays), the same for every width.
+    GemvRows<MODE> rows;
     {
-        constexpr int NIN = GemvInputs<MODE>::N, STEP = 64 * GNW;
+        constexpr int NIN = GemvInputs<MODE>::N, STEP = 64 * GNW, SM = MV == 1 ? 1 : 16, RT = GemvRows<MODE>::TRIPS;
         const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int GP = (((K >> 7) + GNW - 1) / GNW) * GNW;
-        h8 *raw = reinterpret_cast<h8 *>(smem + (size_t)GP * 16 * M * 16 + 3 * (size_t)GP * 16 * 4);
+        h8 *raw = reinterpret_cast<h8 *>(smem + (size_t)GP * 16 * M * 16 + 3 * (size_t)GP * SM * 4);
         const int chunks = K >> 3, trips = (chunks + STEP - 1) / STEP;
         const _Float16 *const src[3] = {in.a, in.b, in.c};
-        for (int t = 0; t < trips; ++t) {
+        if constexpr (RT > 0)
+            rows.load(in.a, in.b, chunks);
+        for (int t = RT; t < trips; ++t) {
             const size_t off = (size_t)min(tid + STEP * t, chunks - 1) * 8;
 #pragma unroll
             for (int i = 0; i < NIN; ++i)
-                __builtin_amdgcn_global_load_lds(src[i] + off, &raw[(i * trips + t) * STEP + 64 * wave], 16, 0, 0);
+                __builtin_amdgcn_global_load_lds(src[i] + off, &raw[(i * (trips - RT) + t - RT) * STEP + 64 * wave], 16, 0, 0);
         }
-        __builtin_amdgcn_sched_barrier(0); // nothing of the job selection moves ahead of the copies
     }
+    __builtin_amdgcn_sched_barrier(0); // nothing of the job selection moves ahead of the loads
     // the job of this workgroup, selected by value so that its fields stay in scalar registers
     GemvJob job = jobs.j[0];
     if (jobs.count > 1 && (int)blockIdx.x >= jobs.j[1].blk0)
@@ -608,58 +659,64 @@ __global__ __launch_bounds__(64 * GNW, 4) void gemv_stream_kernel(const _Float16
     switch (job.bits) { // uniform across the workgroup
     case 2:
         if (job.split)
-            gemv_body<2, MODE, MV, 1>(job, bj, in, M, K, smem, part);
+            gemv_body<2, MODE, MV, 1>(job, bj, in, M, K, smem, part, rows);
         else
-            gemv_body<2, MODE, MV, 2>(job, bj, in, M, K, smem, part);
+            gemv_body<2, MODE, MV, 2>(job, bj, in, M, K, smem, part, rows);
         break;
     case 3:
-        if (job.split)
-            gemv_body<3, MODE, MV, 1>(job, bj, in, M, K, smem, part);
+        if (job.split == 2)
+            gemv_body<3, MODE, MV, 2>(job, bj, in, M, K, smem, part, rows);
+        else if (job.split)
+            gemv_body<3, MODE, MV, 1>(job, bj, in, M, K, smem, part, rows);
         else
-            gemv_body<3, MODE, MV, 4>(job, bj, in, M, K, smem, part);
+            gemv_body<3, MODE, MV, 4>(job, bj, in, M, K, smem, part, rows);
         break;
-    case 4: gemv_body<4, MODE, MV, 1>(job, bj, in, M, K, smem, part); break;
-    default: gemv_body<8, MODE, MV, 1>(job, bj, in, M, K, smem, part); break;
+    case 4:
+        if (K >= 8192)
+            gemv_body<4, MODE, MV, 1, 4>(job, bj, in, M, K, smem, part, rows);
+        else
+            gemv_body<4, MODE, MV, 1>(job, bj, in, M, K, smem, part, rows);
+        break;
+    default: gemv_body<8, MODE, MV, 1>(job, bj, in, M, K, smem, part, rows); break;
     }
 }
 
 typedef void (*GemvKernel)(const _Float16 *, const _Float16 *, const _Float16 *, _Float16 *, int, int, GemvJobs);
 
 // One kernel per input mode, for a single activation row and for up to sixteen.
-GemvKernel gemv_kernel_for(int mode, int M, int *slot)
-{
-    static const GemvKernel table[7][2] = {
-        {gemv_stream_kernel<0, 1>, gemv_stream_kernel<0, 4>}, {gemv_stream_kernel<1, 1>, gemv_stream_kernel<1, 4>},
-        {gemv_stream_kernel<2, 1>, gemv_stream_kernel<2, 4>}, {gemv_stream_kernel<3, 1>, gemv_stream_kernel<3, 4>},
-        {gemv_stream_kernel<4, 1>, gemv_stream_kernel<4, 4>}, {gemv_stream_kernel<5, 1>, gemv_stream_kernel<5, 4>},
-        {gemv_stream_kernel<6, 1>, gemv_stream_kernel<6, 4>},
-    };
-    const int wide = M == 1 ? 0 : 1;
-    *slot = 2 * mode + wide;
-    return table[mode][wide];
-}
+constexpr int GEMV_VARIANTS = 14, GEMV_MAX_PER_CU = 4;
+const GemvKernel gemv_kernels[GEMV_VARIANTS] = {
+    gemv_stream_kernel<0, 1>, gemv_stream_kernel<0, 4>, gemv_stream_kernel<1, 1>, gemv_stream_kernel<1, 4>,
+    gemv_stream_kernel<2, 1>, gemv_stream_kernel<2, 4>, gemv_stream_kernel<3, 1>, gemv_stream_kernel<3, 4>,
+    gemv_stream_kernel<4, 1>, gemv_stream_kernel<4, 4>, gemv_stream_kernel<5, 1>, gemv_stream_kernel<5, 4>,
+    gemv_stream_kernel<6, 1>, gemv_stream_kernel<6, 4>,
+};
+int gemv_slot(int mode, int M) { return 2 * mode + (M == 1 ? 0 : 1); }
 
 constexpr size_t GEMV_MAX_LDS = 152 * 1024;
 
 // Dynamic LDS of a streaming launch: staged x, the group sums and exponents (groups rounded up to whole turns of
-// the wavefronts), and one region shared by the raw input row (inputs of the mode, whole trips of 512
-// chunks) and the reduction buffers.
-size_t gemv_stream_lds(int M, int K, int bits, int inputs)
+// the wavefronts), and one region shared by the raw input row (inputs of the mode, whole trips of a chunk a
+// thread; none where the rows stay in registers) and the reduction buffers.
+size_t gemv_stream_lds(int M, int K, int bits, int mode)
 {
-    const int sub = bits == 3 ? 4 : (bits == 2 ? 2 : 1), mv = M == 1 ? 1 : 4;
+    const int sub = bits == 3 ? 4 : (bits == 2 ? 2 : 1), mv = M == 1 ? 1 : 4, sm = M == 1 ? 1 : 16;
+    const int inputs = mode == 2 ? 3 : (mode >= 3 ? 2 : 1), threads = 64 * GNW;
     const size_t gp = (size_t)(((K >> 7) + GNW - 1) / GNW) * GNW;
     const size_t red = 2 * (size_t)GNW * sub * mv * 64 * 4;
-    const size_t raw = (size_t)inputs * (((K >> 3) + 64 * GNW - 1) / (64 * GNW)) * (64 * GNW) * 16;
-    return gp * 16 * M * 16 + 3 * gp * 16 * 4 + (red > raw ? red : raw);
+    const int trips = ((K >> 3) + threads - 1) / threads, held = mode == 4 || mode == 6 ? 2 : 0;
+    const size_t raw = (size_t)inputs * (trips > held ? trips - held : 0) * threads * 16;
+    return gp * 16 * M * 16 + 3 * gp * sm * 4 + (red > raw ? red : raw);
 }
+
+constexpr int GEMV_CUS = 256;
 
 int rows_per_supertile(int bits) { return bits == 2 ? 32 : (bits == 3 ? 64 : 16); }
 
 // What a launch needs to know about the device, learnt once per device by fq_gemv_prepare (fq_init, or the
-// first launch on that device): the CU count, and for each of the 14 kernel variants the largest dynamic-LDS
+// first launch on that device): the CU count, and for each kernel variant the largest dynamic-LDS
 // request that still leaves p workgroups resident per CU.  Nothing on the launch path then sets attributes
 // or queries the runtime, so launches can be captured into a graph.
-constexpr int GEMV_VARIANTS = 14, GEMV_MAX_PER_CU = 4;
 struct GemvDevice {
     bool ready = false;
     int cus = 0;
@@ -674,31 +731,29 @@ int gemv_prepare_locked(GemvDevice &d, int dev)
     hipError_t e = hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev);
     if (e != hipSuccess)
         return (int)e;
-    for (int mode = 0; mode < 7; ++mode)
-        for (int wide = 0; wide < 2; ++wide) {
-            int slot = 0;
-            const GemvKernel kernel = gemv_kernel_for(mode, wide ? 16 : 1, &slot);
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)GEMV_MAX_LDS);
-            if (e != hipSuccess)
-                return (int)e;
-            for (int p = 1; p <= GEMV_MAX_PER_CU; ++p) {
-                // occupancy falls as the request grows: bisect for the last request (in KiB) with >= p resident
-                int lo = -1, hi = (int)(GEMV_MAX_LDS >> 10) + 1;
-                while (hi - lo > 1) {
-                    const int mid = (lo + hi) / 2;
-                    int per_cu = 0;
-                    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64 * GNW, (size_t)mid << 10);
-                    if (e != hipSuccess)
-                        return (int)e;
-                    if (per_cu >= p)
-                        lo = mid;
-                    else
-                        hi = mid;
-                }
-                d.max_lds[slot][p] = lo < 0 ? 0 : (size_t)lo << 10;
+    for (int slot = 0; slot < GEMV_VARIANTS; ++slot) {
+        const GemvKernel kernel = gemv_kernels[slot];
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)GEMV_MAX_LDS);
+        if (e != hipSuccess)
+            return (int)e;
+        for (int p = 1; p <= GEMV_MAX_PER_CU; ++p) {
+            // occupancy falls as the request grows: bisect for the last request (in KiB) with >= p resident
+            int lo = -1, hi = (int)(GEMV_MAX_LDS >> 10) + 1;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) / 2;
+                int per_cu = 0;
+                e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 64 * GNW, (size_t)mid << 10);
+                if (e != hipSuccess)
+                    return (int)e;
+                if (per_cu >= p)
+                    lo = mid;
+                else
+                    hi = mid;
             }
+            d.max_lds[slot][p] = lo < 0 ? 0 : (size_t)lo << 10;
         }
+    }
     d.cus = n;
     d.ready = true;
     return 0;
@@ -740,9 +795,9 @@ int fq_gemv_prepare()
     return g_gemv_dev[dev].ready ? 0 : gemv_prepare_locked(g_gemv_dev[dev], dev);
 }
 
-bool fq_gemv_can_stream(int M, int K, int bits, int inputs)
+bool fq_gemv_can_stream(int M, int K, int bits, int mode)
 {
-    return gemv_stream_lds(M, K, bits, inputs) <= GEMV_MAX_LDS;
+    return gemv_stream_lds(M, K, bits, mode) <= GEMV_MAX_LDS;
 }
 
 // Up to three matrices that share the input (same K): one launch.
@@ -751,45 +806,58 @@ int fq_launch_gemv_multi(const fq_gemv_input &src, int M, const fq_packed_ref *w
 {
     if (src.mode < 0 || src.mode > 6)
         return (int)hipErrorInvalidValue;
-    const int inputs = src.mode == 2 ? 3 : (src.mode >= 3 ? 2 : 1);
     GemvJobs jobs;
     jobs.count = count;
-    size_t lds = 0;
     int nrb[3];
-    for (int i = 0; i < count; ++i) {
-        const size_t need = gemv_stream_lds(M, w[i].K, w[i].bits, inputs);
-        lds = lds > need ? lds : need;
+    for (int i = 0; i < count; ++i)
         nrb[i] = ((w[i].N + 63) / 64 * 64) / rows_per_supertile(w[i].bits);
+    const int slot = gemv_slot(src.mode, M);
+    size_t lds = 0;
+    for (int i = 0; i < count; ++i) {
+        const size_t need = gemv_stream_lds(M, w[i].K, w[i].bits, src.mode);
+        lds = lds > need ? lds : need;
     }
-    int slot = 0, resident = 0;
-    const GemvKernel kernel = gemv_kernel_for(src.mode, M, &slot);
+    int resident = 0;
     if (int e = gemv_resident_blocks(slot, lds, &resident))
         return e;
-    // Work units.  Whole supertile rows as a rule; but when even the 16-row sub-blocks of the 2- and 3-bit
-    // matrices (2 or 4 per supertile row) are no more than the resident workgroups, those matrices are
-    // handed out by sub-block, one per workgroup: 4096 x 4096 at 2 bits has only 128 supertile rows, at
-    // 3 bits 64, and half or more of the chip would idle.  (With more sub-blocks than workgroups the split
-    // loses: a sub-block item carries the fixed cost of a whole one.)  The workgroups that share a
-    // supertile row are 8 apart in the grid, i.e. run on one XCD, whose L2 fetches their common lines
-    // once; the job's share of the grid is a multiple of 8 * parts.
-    int split_units = 0;
-    for (int i = 0; i < count; ++i) {
-        const int f = w[i].bits == 2 ? 2 : (w[i].bits == 3 ? 4 : 1);
-        split_units += f > 1 ? (nrb[i] + 7) / 8 * 8 * f : nrb[i];
+    // Work units: whole supertile rows of the 2- and 3-bit matrices (32 and 64 weight rows), halves of the 3-bit ones, or
+    // single sub-blocks of sixteen rows.  Smaller units spread over more CUs but a group of a unit has a fixed cost:
+    // relative to a 4-bit unit, from the instructions of an item, 1.25 / 0.95 for a 2-bit row and its half, 2.5 / 1.6 /
+    // 1.25 for a 3-bit row, its half and its quarter.  A launch takes as long as one unit while every CU has at most one;
+    // two workgroups on a CU take nearly twice as long (the wavefronts are bound by their instructions), so beyond
+    // that it takes its share of all the work, 1.8 units at least.  Measured (us, M = 1, rows / halves / quarters):
+    // 5120 x 5120 at 3 bits 7.9 / 6.5 / 8.6, 4096 x 4096 6.3 / 5.3 / 5.3, 5120 x 13824 14.7 / 11.2 / 15.7, 11008 x 4096
+    // 7.3 / 8.0 / 9.0; 5120 x 5120 at 2 bits 6.4 whole and 7.5 split, 4096 x 11008 8.5 and 7.4.  The workgroups that share a
+    // supertile row are 8 apart in the grid, i.e. run on one XCD, whose L2 fetches their common lines once; the job's
+    // share of the grid is a multiple of 8 * parts.
+    static const double unit_costs[9][3] = {{}, {}, {1.25, 1.25, 0.95}, {2.5, 1.6, 1.25}, {1.0, 1.0, 1.0}, {}, {}, {}, {1.55, 1.55, 1.55}};
+    static const int unit_parts[9][3] = {{}, {}, {1, 1, 2}, {1, 2, 4}, {1, 1, 1}, {}, {}, {}, {1, 1, 1}};
+    int parts[3], units[3], gran[3], nbs[3], order[3], best = 0;
+    double unit_cost[3], best_t = 1e30;
+    for (int option = 0; option < 3; ++option) { // whole rows; halves of the 3-bit ones; quarters of these and halves of the 2-bit ones
+        int n = 0;
+        double work = 0.0, most = 0.0;
+        for (int i = 0; i < count; ++i) {
+            const int f = unit_parts[w[i].bits][option];
+            const int u = f > 1 ? (nrb[i] + 7) / 8 * 8 * f : nrb[i];
+            const double c = unit_costs[w[i].bits][option];
+            n += u;
+            work += u * c;
+            most = most > c ? most : c;
+        }
+        const double t = n <= GEMV_CUS ? most : work / GEMV_CUS > 1.8 * work / n ? work / GEMV_CUS : 1.8 * work / n;
+        if (t < best_t) {
+            best_t = t;
+            best = option;
+        }
     }
-    const bool underfull = split_units <= resident;
-    int parts[3], units[3], gran[3], nbs[3], order[3];
-    double unit_cost[3];
-    // cost of a whole supertile row relative to a 4-bit one (2-bit rows are bound by the unpack, not by
-    // their bytes, so cost grows more slowly than bytes)
-    static const double row_cost[9] = {0, 0, 1.25, 2.5, 1.0, 0, 0, 0, 1.55};
+
     int used = 0;
     for (int i = 0; i < count; ++i) {
-        const int f = w[i].bits == 2 ? 2 : (w[i].bits == 3 ? 4 : 1);
-        parts[i] = (underfull && f > 1) ? f : 1;
+        parts[i] = unit_parts[w[i].bits][best];
         units[i] = parts[i] > 1 ? (nrb[i] + 7) / 8 * 8 * parts[i] : nrb[i];
         gran[i] = parts[i] > 1 ? 8 * parts[i] : 1;
-        unit_cost[i] = row_cost[w[i].bits] / parts[i];
+        unit_cost[i] = unit_costs[w[i].bits][best];
     }
     // Seven eighths of every matrix's share by time at once, then hand the remaining workgroups, a granule at a time, to the
     // matrix that would finish last.  (All of them a granule at a time took the host 2.5 us for a 4-bit 11008 x 4096 matrix,
@@ -831,14 +899,14 @@ int fq_launch_gemv_multi(const fq_gemv_input &src, int M, const fq_packed_ref *w
         const int i = order[k];
         jobs.j[k] = GemvJob{static_cast<const uint32_t *>(w[i].packed), static_cast<const _Float16 *>(w[i].scales),
                             static_cast<const _Float16 *>(w[i].zeros), static_cast<_Float16 *>(outs[i]), w[i].N,
-                            w[i].bits, blk0, nbs[i], parts[i] > 1 ? 1 : 0, w[i].ld ? w[i].ld : w[i].N};
+                            w[i].bits, blk0, nbs[i], parts[i] > 1 ? parts[i] : 0, w[i].ld ? w[i].ld : w[i].N};
         blk0 += nbs[i];
     }
     for (int i = count; i < 3; ++i)
         jobs.j[i] = GemvJob{nullptr, nullptr, nullptr, nullptr, 0, 0, blk0, 0, 0, 0};
     const GemvInput in = {static_cast<const _Float16 *>(src.a), static_cast<const _Float16 *>(src.b),
                           static_cast<const _Float16 *>(src.c), static_cast<_Float16 *>(src.aux), src.mode};
-    hipLaunchKernelGGL(kernel, dim3(blk0), dim3(64 * GNW), lds, st, in.a, in.b, in.c, in.aux, M, w[0].K, jobs);
+    hipLaunchKernelGGL(gemv_kernels[slot], dim3(blk0), dim3(64 * GNW), lds, st, in.a, in.b, in.c, in.aux, M, w[0].K, jobs);
     return (int)hipGetLastError();
 }
 
@@ -846,7 +914,7 @@ int fq_launch_gemv(const void *x, int M, const fq_packed_ref &w, void *out, fq_s
 {
     if (fq_skinny_pays(M, &w, 1))
         return fq_launch_skinny(x, M, &w, &out, 1, st);
-    if (fq_gemv_can_stream(M, w.K, w.bits, 1)) {
+    if (fq_gemv_can_stream(M, w.K, w.bits, 0)) {
         const fq_gemv_input src = {x, nullptr, nullptr, nullptr, 0};
         return fq_launch_gemv_multi(src, M, &w, &out, 1, st);
     }

@@ -343,19 +343,20 @@ double tile_kernel_us(int M, const fq_packed_ref *w, int count)
 // Whether the kernel's 32-bit byte offsets reach all of a launch's activations and of a tile's weights.
 bool fq_skinny_can(int M, int K) { return K <= (1 << 22) && (size_t)M * K * 2 < ((size_t)1 << 32); }
 
-// Whether a launch goes to the skinny kernel.  Few rows (M <= 16): from four rows on, where the streaming kernel stages
-// one row after another (4096 x 4096, 4 bits: 7.5 against 5.8 us at 4 rows, 17 against 6.0 at 16; at one row 4.4
-// against 6.1), and where that kernel has no room for the rows.  More rows: where the model above puts it ahead of the
-// tile kernel (4096 x 11008, 3 bits: 23 against 109 us at 77 rows, 34 against 116 at 256, 64 against 117 at 512).
+// Whether a launch goes to the skinny kernel.  Few rows (M <= 16): from four rows on, three of long rows, where the
+// streaming kernel stages one row after another (4096 x 4096, 4 bits: 7.5 against 5.8 us at 4 rows, 17 against 6.0 at 16; at
+// one row 4.2 against 6.1; 4096 x 11008 at 3 rows 11.3 against 10), and where that kernel has no room for the rows.
+// More rows: where the model above puts it ahead of the tile kernel (4096 x 11008, 3 bits: 23 against 109 us at 77 rows,
+// 34 against 116 at 256, 64 against 117 at 512).
 bool fq_skinny_pays(int M, const fq_packed_ref *w, int count)
 {
     if (!fq_skinny_can(M, w[0].K))
         return false;
     if (M > 16)
         return skinny_plan(M, w, count).us < tile_kernel_us(M, w, count);
-    bool stream = M < 4;
+    bool stream = M < 3 || (M == 3 && w[0].K < 8192);
     for (int i = 0; i < count; ++i)
-        stream = stream && fq_gemv_can_stream(M, w[i].K, w[i].bits, 1);
+        stream = stream && fq_gemv_can_stream(M, w[i].K, w[i].bits, 0);
     return !stream;
 }
 

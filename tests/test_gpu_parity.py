@@ -152,6 +152,25 @@ def test_qlinear_tall_tiles_against_oracle(fq, torch, bits, case):
     assert qerr(y, y128.astype(np.float64)) <= 1e-3
 
 
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("case", [(1, 5000, 128), (2, 5000, 1152), (1, 5120, 640), (3, 4100, 384), (1, 200, 8320)],
+                         ids=lambda c: "M%d_N%d_K%d" % c)
+def test_qlinear_decode_units_against_oracle(fq, torch, bits, case):
+    """Between 4096 and 8192 rows the decode kernel hands 3-bit supertile rows out by halves; rows that end inside a
+    half, K of fewer groups than wavefronts and of whole and broken turns of their ring, long rows of 4 bits."""
+    M, N, K = case
+    w, codes, s, z = make_matrix(fq, 80, N, K, bits)
+    X = fq_synth.activations(81, M, K)
+    out = Guarded(torch, M * N * 2)
+    fq.fq_qlinear(dev(torch, X), w, out=out.half(M, N))
+    assert out.intact()
+    # One rounding to fp16 (2^-11), and the kernel's codes carry a bias of 1024 that leaves each group's sum by
+    # subtraction: its roundings in fp32 are 2^-24 of 1024 sum |x|, against 2-bit codes and K = 128 up to 5e-4 of the
+    # row's rms each, a few of them per group.
+    r = oracle.qlinear(X, oracle.dequant(codes, s, z))
+    assert qerr(host16(out.half(M, N)), r) <= TOL
+
+
 # Shapes of the few-row kernel: its eleven tile shapes (16/32/48/64 rows x 16/32/64 columns), row tiles that end inside a
 # block of sixteen, column counts that end inside a tile or a block, K of one group, of fewer groups than
 # wavefronts, of one more than a whole turn of them, and of several turns.
