@@ -233,9 +233,10 @@ struct GemvCursor {
 // unit ub is part (ub/8) % F of supertile row (ub / (8F)) * 8 + ub % 8: the F workgroups that share a
 // supertile row (and read the same cache lines) are 8 apart, i.e. on the same XCD and L2.
 template <int BITS, int MODE, int MV, int S, int D = 2>
-__device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvInput in, int M, int K,
+__device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvInput in, int rows_given, int K,
                                           unsigned char *smem, float *part, GemvRows<MODE> &rows)
 {
+    const int M = MV == 1 ? 1 : rows_given; // a constant for one row: operand addresses are then immediates
     constexpr int SUB = Fmt<BITS>::SUB, ROWS = Fmt<BITS>::ROWS, TILE = tile_dwords<BITS>();
     constexpr int NIN = GemvInputs<MODE>::N, STEP = 64 * GNW;
     constexpr int RT = GemvRows<MODE>::TRIPS; // trips of the input rows that `rows` holds; the others are in LDS
@@ -250,7 +251,8 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
     float *xsum = reinterpret_cast<float *>(smem + (size_t)GP * 16 * M * 16); // [GP][SM] sum of x over the group
     float *csum = xsum + (size_t)GP * SM;                                    // [GP][SM] 2^-E * 1024 * sum of staged x
     float *esc = csum + (size_t)GP * SM;                                     // [GP][SM] 2^-E of the group
-    float *red = esc + (size_t)GP * SM;                                      // [2][GNW][S*MV][64]
+    f4 *sums1 = reinterpret_cast<f4 *>(xsum);                                // one row: the three of a group together, [GP]
+    float *red = xsum + (size_t)GP * (MV == 1 ? 4 : 3 * SM);                 // [2][GNW][S*MV][64]
     h8 *raw = reinterpret_cast<h8 *>(red); // [NIN][trips - RT][STEP] raw input row; free again before the first reduction
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -388,9 +390,14 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
         const float sx = row16_sum(gemv_sum(xe)), sc = row16_sum(gemv_sum(w));
         if ((kc & 15) == 0) {
             const float einv = __builtin_bit_cast(float, (uint32_t)(127 - E) << 23); // 2^-E
-            xsum[(kc >> 4) * SM + mm] = sx;
-            csum[(kc >> 4) * SM + mm] = einv * (1024.0f * sc); // exact scaling
-            esc[(kc >> 4) * SM + mm] = einv;
+            const float sb = einv * (1024.0f * sc); // exact scaling
+            if constexpr (MV == 1) {
+                sums1[kc >> 4] = f4{sx, sb, einv, 0.f};
+            } else {
+                xsum[(kc >> 4) * SM + mm] = sx;
+                csum[(kc >> 4) * SM + mm] = sb;
+                esc[(kc >> 4) * SM + mm] = einv;
+            }
         }
     };
     auto stage_row = [&](int mm) {
@@ -475,9 +482,13 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
         xl[i] = h8{0, 0, 0, 0, 0, 0, 0, 0};
     for (int i = tid; i < GP * SM; i += STEP)
         if (i % SM >= M || i / SM >= G) {
-            xsum[i] = 0.f;
-            csum[i] = 0.f;
-            esc[i] = 0.f;
+            if constexpr (MV == 1) {
+                sums1[i] = f4{0.f, 0.f, 0.f, 0.f};
+            } else {
+                xsum[i] = 0.f;
+                csum[i] = 0.f;
+                esc[i] = 0.f;
+            }
         }
     stage_row(0);
     for (int mm = 1; mm < M; ++mm) {
@@ -541,9 +552,10 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
                         eg[v] = e4[v];
                     }
                 } else {
-                    xg[0] = xsum[g];
-                    cg[0] = csum[g];
-                    eg[0] = esc[g];
+                    const f4 sg = sums1[g];
+                    xg[0] = sg[0];
+                    cg[0] = sg[1];
+                    eg[0] = sg[2];
                 }
 #pragma unroll
                 for (int u = 0; u < S; ++u) {
@@ -636,7 +648,7 @@ __global__ __launch_bounds__(64 * GNW, 4) void gemv_stream_kernel(const _Float16
         constexpr int NIN = GemvInputs<MODE>::N, STEP = 64 * GNW, SM = MV == 1 ? 1 : 16, RT = GemvRows<MODE>::TRIPS;
         const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int GP = (((K >> 7) + GNW - 1) / GNW) * GNW;
-        h8 *raw = reinterpret_cast<h8 *>(smem + (size_t)GP * 16 * M * 16 + 3 * (size_t)GP * SM * 4);
+        h8 *raw = reinterpret_cast<h8 *>(smem + (size_t)GP * 16 * (MV == 1 ? 1 : M) * 16 + (size_t)GP * (MV == 1 ? 4 : 3 * SM) * 4);
         const int chunks = K >> 3, trips = (chunks + STEP - 1) / STEP;
         const _Float16 *const src[3] = {in.a, in.b, in.c};
         if constexpr (RT > 0)
@@ -700,13 +712,13 @@ constexpr size_t GEMV_MAX_LDS = 152 * 1024;
 // thread; none where the rows stay in registers) and the reduction buffers.
 size_t gemv_stream_lds(int M, int K, int bits, int mode)
 {
-    const int sub = bits == 3 ? 4 : (bits == 2 ? 2 : 1), mv = M == 1 ? 1 : 4, sm = M == 1 ? 1 : 16;
+    const int sub = bits == 3 ? 4 : (bits == 2 ? 2 : 1), mv = M == 1 ? 1 : 4;
     const int inputs = mode == 2 ? 3 : (mode >= 3 ? 2 : 1), threads = 64 * GNW;
     const size_t gp = (size_t)(((K >> 7) + GNW - 1) / GNW) * GNW;
     const size_t red = 2 * (size_t)GNW * sub * mv * 64 * 4;
     const int trips = ((K >> 3) + threads - 1) / threads, held = mode == 4 || mode == 6 ? 2 : 0;
     const size_t raw = (size_t)inputs * (trips > held ? trips - held : 0) * threads * 16;
-    return gp * 16 * M * 16 + 3 * gp * sm * 4 + (red > raw ? red : raw);
+    return gp * 16 * M * 16 + gp * (M == 1 ? 4 : 48) * 4 + (red > raw ? red : raw);
 }
 
 constexpr int GEMV_CUS = 256;
