@@ -174,13 +174,17 @@ struct RowSpan {
     }
 };
 
-constexpr int ROW_UNROLL = 4; // chunks a thread loads before it uses the first
+// Chunks a thread loads before it uses the first.  The last trip takes the loads it has no chunk for from the row's
+// last one: with a loop of whole trips and another for the rest, the lanes of one wavefront part and it runs both, the
+// rest load by load (loss of 2048 x 8000 logits 11.4 -> 9.9 us, 300 x 32000 9.7 -> 8.9; two chunks 10.4 and 9.3).  A row
+// of one chunk a thread loads just that (distance of 2048 x 1000: 4.0 us with the repeated loads, 3.8 without).
+constexpr int ROW_UNROLL = 4;
 
 // One workgroup per token row; each thread keeps a running (max, sum of
 // exp(l - max)) over its 16-byte chunks, then the pairs are merged across the
 // wavefront and the workgroup.  The label's logit is read directly.  Bound by the read; few rows take large
 // workgroups (THREADS), so that the loads of a row are under way together.
-// Measured (us): 2048 x 32000 30; 2048 x 31001, whose rows are not aligned, 29 (element by element 71).
+// Measured (us): 2048 x 32000 27; 2048 x 31001, whose rows are not aligned, 27 (element by element 71).
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void nll_kernel(const _Float16 *__restrict__ logits,
                                                       const int32_t *__restrict__ labels, int V,
@@ -208,18 +212,21 @@ __global__ __launch_bounds__(THREADS) void nll_kernel(const _Float16 *__restrict
             cs += __expf((float)v[e] - cm);
         lse_merge(mx, se, cm, cs);
     };
-    int ch = threadIdx.x;
-    for (; ch + (ROW_UNROLL - 1) * THREADS < span.chunks; ch += ROW_UNROLL * THREADS) {
-        h8 v[ROW_UNROLL];
+    if (span.chunks <= THREADS) {
+        if ((int)threadIdx.x < span.chunks)
+            add(chunk[threadIdx.x]);
+    } else {
+        for (int ch = threadIdx.x; ch < span.chunks; ch += ROW_UNROLL * THREADS) {
+            h8 v[ROW_UNROLL];
 #pragma unroll
-        for (int i = 0; i < ROW_UNROLL; ++i)
-            v[i] = chunk[ch + i * THREADS];
+            for (int i = 0; i < ROW_UNROLL; ++i)
+                v[i] = chunk[min(ch + i * THREADS, span.chunks - 1)];
 #pragma unroll
-        for (int i = 0; i < ROW_UNROLL; ++i)
-            add(v[i]);
+            for (int i = 0; i < ROW_UNROLL; ++i)
+                if (ch + i * THREADS < span.chunks)
+                    add(v[i]);
+        }
     }
-    for (; ch < span.chunks; ch += THREADS)
-        add(chunk[ch]);
     if (threadIdx.x < 16) { // fewer than sixteen elements lie outside the chunks
         const int e = span.end_element(threadIdx.x, V);
         if (e >= 0)
@@ -311,7 +318,7 @@ int fq_launch_glue2(int op, const void *a, const void *b, int M, int H, void *au
 }
 
 // Workgroup size of the two row kernels: up to one row a CU, 1024 threads bring more loads of a long row under way (32000
-// logits, 256 rows: distance 8.5 -> 7.0 us, loss 9.5 -> 7.9; 384 rows: level); short rows only pay for the larger
+// logits, 256 rows: distance 8.5 -> 7.0 us, loss 9.5 -> 7.9; 384 rows: level, all with the earlier loop); short rows only pay for the larger
 // reduction (1000 logits: 3.0 -> 3.8 us).
 static bool wide_rows(int M, int V) { return M <= 256 && V >= 8192; }
 
@@ -337,20 +344,24 @@ __global__ __launch_bounds__(THREADS) void logit_l2_kernel(const _Float16 *__res
         s0 = fmaf(d[0], d[0], s0); s1 = fmaf(d[1], d[1], s1); s2 = fmaf(d[2], d[2], s2); s3 = fmaf(d[3], d[3], s3);
         s0 = fmaf(d[4], d[4], s0); s1 = fmaf(d[5], d[5], s1); s2 = fmaf(d[6], d[6], s2); s3 = fmaf(d[7], d[7], s3);
     };
-    int ch = threadIdx.x;
-    for (; ch + (ROW_UNROLL - 1) * THREADS < span.chunks; ch += ROW_UNROLL * THREADS) {
-        h8 va[ROW_UNROLL], vb[ROW_UNROLL];
+    if (span.chunks <= THREADS) {
+        if ((int)threadIdx.x < span.chunks)
+            add(ca[threadIdx.x], cb[threadIdx.x]);
+    } else {
+        for (int ch = threadIdx.x; ch < span.chunks; ch += ROW_UNROLL * THREADS) {
+            h8 va[ROW_UNROLL], vb[ROW_UNROLL];
 #pragma unroll
-        for (int i = 0; i < ROW_UNROLL; ++i) {
-            va[i] = ca[ch + i * THREADS];
-            vb[i] = cb[ch + i * THREADS];
+            for (int i = 0; i < ROW_UNROLL; ++i) {
+                const int at = min(ch + i * THREADS, span.chunks - 1);
+                va[i] = ca[at];
+                vb[i] = cb[at];
+            }
+#pragma unroll
+            for (int i = 0; i < ROW_UNROLL; ++i)
+                if (ch + i * THREADS < span.chunks)
+                    add(va[i], vb[i]);
         }
-#pragma unroll
-        for (int i = 0; i < ROW_UNROLL; ++i)
-            add(va[i], vb[i]);
     }
-    for (; ch < span.chunks; ch += THREADS)
-        add(ca[ch], cb[ch]);
     if (threadIdx.x < 16) {
         const int e = span.end_element(threadIdx.x, V);
         if (e >= 0) {

@@ -448,6 +448,21 @@ def test_row_kernels_on_unaligned_rows(fq, torch, M, V):
     assert np.allclose(got, oracle.logit_l2(a, b), rtol=1e-5, atol=0)
 
 
+@pytest.mark.parametrize("V", [2040, 2048, 2056, 4104, 8184, 8192, 8200, 32768, 32776])
+@pytest.mark.parametrize("M", [5, 260])
+def test_row_kernels_around_whole_trips(fq, torch, M, V):
+    """Rows of one chunk a thread, one more, and around whole trips of four chunks a thread, for both workgroup sizes.
+    The last chunk stands out, so that one dropped, or added again by a thread past the row's end, shows.  Bounds:
+    those of the other sizes."""
+    a, b = fq_synth.logits(413, M, V), fq_synth.logits(414, M, V)
+    a[:, -8:] += np.float16(6)
+    lab = fq_synth.labels(415, M, V)
+    got = fq.fq_token_nll(dev(torch, a), dev(torch, lab)).cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(got - oracle.token_nll(a, lab))) <= 2e-3
+    got = fq.fq_logit_l2(dev(torch, a), dev(torch, b)).cpu().numpy().astype(np.float64)
+    assert np.allclose(got, oracle.logit_l2(a, b), rtol=1e-5, atol=0)
+
+
 @pytest.mark.parametrize("H", [256, 4096, 11008, 13824])
 def test_glue_steps_against_oracle(fq, torch, H):
     M = 9
