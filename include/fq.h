@@ -239,8 +239,8 @@ int fq_stack_forward_noalloc(const fq_layer *layers, int L, const uint8_t *bitve
  * packed weights through LDS rings that keep loading across the block's four
  * dependent phases, and meeting at a grid-wide barrier after each phase.
  *   fq_set_decode_mode(1) selects that kernel for M == 1 where it applies; mode 0,
- *     the default, runs the per-phase launches that also serve 2 <= M <= 16 (four
- *     launches per block).  The previous mode is returned.  Process-wide.  As
+ *     the default, runs the per-phase launches that also serve two and three rows
+ *     (four launches per block).  The previous mode is returned.  Process-wide.  As
  *     measured on MI355X the per-phase launches are the faster of the two.
  * Every wait of the persistent kernel's barrier is bounded by a timer; a workgroup
  * that waits longer gives up, the launch still ends, its results are invalid, and

@@ -1,4 +1,5 @@
-// Decode path: dequant-GEMV for 1 <= M <= 16 rows of activations.
+// Decode path: dequant-GEMV, for one to three rows of activations as the library dispatches it
+// (four rows on are faster in the few-row kernel: see fq_skinny_pays); the bodies take up to sixteen.
 //
 // The served hybrid model generates one token at a time on a memory-constrained
 // device (FlexQuant, arXiv 2501.07139, Section "Introduction"), so these kernels
@@ -31,7 +32,7 @@
 //  - Wavefronts reduce through LDS in a fixed order: results are deterministic.
 //
 // Generic kernel: same arithmetic as the GEMM (exact code - zero in fp16), x read
-// from global memory; used when M*K is too large for LDS.
+// from global memory; used when M*K is too large for LDS and for the few-row kernel's offsets.
 #include "fq_device.h"
 #include "fq_internal.h"
 #include "fq_stage.h"
@@ -236,7 +237,10 @@ template <int BITS, int MODE, int MV, int S, int D = 2>
 __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvInput in, int rows_given, int K,
                                           unsigned char *smem, float *part, GemvRows<MODE> &rows)
 {
-    const int M = MV == 1 ? 1 : rows_given; // a constant for one row: operand addresses are then immediates
+    // A constant for one row: operand addresses are then immediates.  The loop is bound by instruction issue; with
+    // the three sums of a group in one 16-byte LDS read this took a 7B-shaped block from 37.6 to 36.1 us (bits
+    // 2/4/8/2/4/4/2) and a 13B-shaped one from 49.0 to 47.8.
+    const int M = MV == 1 ? 1 : rows_given;
     constexpr int SUB = Fmt<BITS>::SUB, ROWS = Fmt<BITS>::ROWS, TILE = tile_dwords<BITS>();
     constexpr int NIN = GemvInputs<MODE>::N, STEP = 64 * GNW;
     constexpr int RT = GemvRows<MODE>::TRIPS; // trips of the input rows that `rows` holds; the others are in LDS
