@@ -202,14 +202,11 @@ __global__ __launch_bounds__(THREADS) void nll_kernel(const _Float16 *__restrict
     const h8 *chunk = reinterpret_cast<const h8 *>(l + span.head);
     float mx = -INFINITY, se = 0.f;
     auto add = [&](h8 v) {
-        float cm = (float)v[0];
-#pragma unroll
-        for (int e = 1; e < 8; ++e)
-            cm = fmaxf(cm, (float)v[e]);
-        float cs = 0.f;
+        float e8[8], cm, cs;
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-            cs += __expf((float)v[e] - cm);
+            e8[e] = (float)v[e];
+        lse_pair(e8, cm, cs);
         lse_merge(mx, se, cm, cs);
     };
     if (span.chunks <= THREADS) {
@@ -229,8 +226,12 @@ __global__ __launch_bounds__(THREADS) void nll_kernel(const _Float16 *__restrict
     }
     if (threadIdx.x < 16) { // fewer than sixteen elements lie outside the chunks
         const int e = span.end_element(threadIdx.x, V);
-        if (e >= 0)
-            lse_merge(mx, se, (float)l[e], 1.0f);
+        if (e >= 0) {
+            const float e1[1] = {(float)l[e]};
+            float em, es;
+            lse_pair(e1, em, es);
+            lse_merge(mx, se, em, es);
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {

@@ -448,6 +448,30 @@ def test_row_kernels_on_unaligned_rows(fq, torch, M, V):
     assert np.allclose(got, oracle.logit_l2(a, b), rtol=1e-5, atol=0)
 
 
+@pytest.mark.parametrize("V", [31, 100, 2040, 8000, 8001, 32000, 32001])
+@pytest.mark.parametrize("M", [5, 260])
+def test_token_nll_of_masked_rows(fq, torch, M, V):
+    """Logits of -inf add nothing wherever they stand: whole chunks of them behind, before and between a thread's other
+    ones, all but the label, and next to one NaN, which reaches the loss; both workgroup sizes, rows aligned and not.
+    Bounds: those of finite rows."""
+    x = fq_synth.logits(416, M, V)
+    lab = (fq_synth.labels(417, M, V) % (V // 4) + V // 2).astype(np.int32)
+    x[0, V - V // 4:] = -np.inf
+    x[1, :V // 2] = -np.inf
+    x[2, np.arange(V) // 16 % 2 == 1] = -np.inf
+    x[3] = -np.inf
+    x[np.arange(M), lab] = np.float16(1.5)
+    got = fq.fq_token_nll(dev(torch, x), dev(torch, lab)).cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(got - oracle.token_nll(x, lab))) <= 2e-3
+    assert got[3] == 0.0
+    for at, width in ((0, 1), (V // 2 - 1, 1), (V // 2 - 1, 15), (V - 1, 1), (V - 1, 9)):  # labels lie between V / 2 and 3 V / 4
+        y = x.copy()
+        y[:, max(0, at - 24):at + 24] = -np.inf
+        y[:, max(0, at - width + 1):at + 1] = np.nan
+        y[np.arange(M), lab] = np.float16(1.5)
+        assert np.isnan(fq.fq_token_nll(dev(torch, y), dev(torch, lab)).cpu().numpy()).all(), (at, width)
+
+
 @pytest.mark.parametrize("V", [2040, 2048, 2056, 4104, 8184, 8192, 8200, 32768, 32776])
 @pytest.mark.parametrize("M", [5, 260])
 def test_row_kernels_around_whole_trips(fq, torch, M, V):
