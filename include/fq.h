@@ -142,7 +142,10 @@ int fq_dequant(const void *packed, const void *scales, const void *zeros,
  * (decode); from four rows to several hundred (batched decoding, prompts) small
  * tiles whose wavefronts share K; larger M the matrix-core tile kernels (calibration
  * forward).  Any M >= 1, N >= 1.  Scales and zeros may be any finite fp16 (e.g.
- * zero/2^d after truncating d code bits, Section "Elastic Serving").  For M > 16 the
+ * zero/2^d after truncating d code bits, Section "Elastic Serving").  Up to 16 rows
+ * codes and zeros enter exactly, in fp32 sums; for M > 16 the weights are formed in
+ * fp16, code - zero and its product with the scale rounded to eleven bits each
+ * (exact differences: integer zeros up to 1024, and zero/2^d of the width).  For M > 16 the
  * activations (M*K*2 bytes) and the packed weights must each stay below
  * 4 GiB, else FQ_ERR_SHAPE.  Two large-tile kernels exist: 128 activation
  * rows per workgroup, and 256 rows per workgroup of eight wavefronts with the

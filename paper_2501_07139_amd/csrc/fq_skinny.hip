@@ -10,9 +10,10 @@
 // both straight from global memory into registers, one group ahead.  The activations of a k-step are loaded into
 // the registers that the k-step has just been multiplied from.
 //
-// Arithmetic: code - zero in fp16 (exact for integer zeros), fp32 sums per group, and the group's scale applied to the
-// sum in fp32; tiles too large for a second set of accumulators scale the weights in fp16 instead, like the large
-// tiles of the calibration forward.  Sums over the wavefronts in a fixed order.
+// Arithmetic: code - zero in fp16, fp32 sums per group, and the group's scale applied to the sum in fp32; tiles too large
+// for a second set of accumulators scale the weights in fp16 instead, like the large tiles of the calibration
+// forward.  Tiles of sixteen rows, which decoding uses, multiply the codes and take the zero from the group's sum in fp32
+// (see ZERO_APART).  Sums over the wavefronts in a fixed order.
 #include "fq_device.h"
 #include "fq_internal.h"
 
@@ -79,6 +80,16 @@ __device__ __forceinline__ void skinny_unpack(const uint32_t (&C)[BITS], h2 zero
     a[3] = hi[1];
 }
 
+// The four halves that lane FROM of each run of sixteen lanes holds, in all of its lanes.
+template <int FROM>
+__device__ __forceinline__ h4 row16_bcast(u2v v)
+{
+    constexpr int CTRL = 0x150 + FROM; // row_newbcast
+    const u2v all = {(uint32_t)__builtin_amdgcn_update_dpp(0, (int)v.x, CTRL, 0xf, 0xf, true),
+                     (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v.y, CTRL, 0xf, 0xf, true)};
+    return __builtin_bit_cast(h4, all);
+}
+
 // Activation stages of half a group (two k-steps, 128 bytes a row) that a wavefront keeps in LDS.
 template <int MB>
 struct SkinnyRing { static constexpr int H = MB <= 2 ? 4 : 2, STAGE = 16 * MB * 8; }; // STAGE: 16-byte slots
@@ -97,6 +108,11 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
                                             int tile, int row_tiles)
 {
     constexpr bool F32 = S < 4 || MB == 1; // scale applied to the group's sums in fp32
+    // Zeros leave through the group's sums, sum code x - zero sum x, so that any fp16 zero is exact, as in the decode kernel
+    // (2048 x 2048, 16 rows at 2 bits, error over the rms of the result: 2.06e-4, the output's own rounding; with code - zero
+    // in fp16 2.3e-4 for fractional zeros and 4.0e-4 for odd ones beyond 1024).  sum x is one more matrix product, of rows
+    // of ones: level in time, and there is no branch on the zeros.
+    constexpr bool ZERO_APART = MB == 1;
     constexpr int H = SkinnyRing<MB>::H, STAGE = SkinnyRing<MB>::STAGE, COPIES = 2 * MB;
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -138,20 +154,38 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, dst + 64 * i, 16, xoff[i], off, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         };
-        uint32_t w[S][BITS], zr[S];
-        h4 sc[S];       // F32: scales of the rows 4c..4c+3, whose sums the lane holds
-        uint32_t ss[S]; // else: scale of the row r, whose weights the lane unpacks
+        uint32_t w[S][BITS];
+        h4 sc[S];              // F32: scales of the rows 4c..4c+3, whose sums the lane holds
+        uint32_t ss[S], zr[S]; // scale (not F32) and zero of the row r, whose weights the lane unpacks
+        // ZERO_APART: scales and zeros of the rows 4c..4c+3 of two sub-blocks in one load: all lanes of one c need the same
+        // eight bytes of each, so lanes r / 4 = 0, 1, 2, 3 take scales and zeros of the first, then of the second, and
+        // the others get them by broadcasts within the sixteen lanes (21085 x 1024 at 2 bits, 6 rows: 9.3 us with a load for
+        // each, 8.1 with this one).
+        constexpr int NM = (S + 1) / 2;
+        const char *meta_lane[NM];
+        u2v meta[NM];
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+            const _Float16 *from = (r & 4) ? job.zeros : job.scales;
+            meta_lane[q] = reinterpret_cast<const char *>(from + ((size_t)(sb0 + min(2 * q + (r >> 3), S - 1)) * G * 16 + 4 * c));
+        }
         auto load_w = [&](int t) { // past the end: the last group again (nobody uses it)
             const int g = min(wave + SNW * t, G - 1);
             skinny_load<BITS, S>(packed, sb0 % SUB, G, g, lane, w);
+            if constexpr (ZERO_APART) {
+#pragma unroll
+                for (int q = 0; q < NM; ++q)
+                    meta[q] = *reinterpret_cast<const u2v *>(meta_lane[q] + (size_t)g * 32);
+                return;
+            }
 #pragma unroll
             for (int u = 0; u < S; ++u) {
-                const uint32_t meta = (uint32_t)(u * G + g) * 32u;
-                zr[u] = buf_load_u16(zeros, 2u * (uint32_t)r, meta);
+                const uint32_t at = (uint32_t)(u * G + g) * 32u;
+                zr[u] = buf_load_u16(zeros, 2u * (uint32_t)r, at);
                 if constexpr (F32)
-                    sc[u] = __builtin_bit_cast(h4, buf_load_b64(scales, 8u * (uint32_t)c, meta));
+                    sc[u] = __builtin_bit_cast(h4, buf_load_b64(scales, 8u * (uint32_t)c, at));
                 else
-                    ss[u] = buf_load_u16(scales, 2u * (uint32_t)r, meta);
+                    ss[u] = buf_load_u16(scales, 2u * (uint32_t)r, at);
             }
         };
         load_w(0);
@@ -164,24 +198,34 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
             rd[s] = r * 8 + ((4 * s + c) ^ (r >> 1));
         for (int t = 0; t < turns; ++t) {
             h8 a[S][4];
-            float scf[S][4];
+            float scf[S][4], zf[S][4];
+            static_for<S>([&](auto u_tag) {
+                constexpr int u = decltype(u_tag)::value;
+                if constexpr (ZERO_APART) {
+                    skinny_unpack<BITS, true, !F32>(w[u], h2{0, 0}, h2{}, a[u]); // the codes themselves
+                    const h4 s4 = row16_bcast<8 * (u & 1)>(meta[u / 2]), z4 = row16_bcast<8 * (u & 1) + 4>(meta[u / 2]);
 #pragma unroll
-            for (int u = 0; u < S; ++u) {
-                const h2 z2 = as_h2(zr[u] * 0x10001u), s2 = F32 ? h2{} : as_h2(ss[u] * 0x10001u);
-                const _Float16 z = z2[0];
-                // integer zeros (what the quantizer produces): bias and zero leave in one addition
-                if (__builtin_amdgcn_ballot_w64(z != __builtin_truncf16(z)) == 0)
-                    skinny_unpack<BITS, true, !F32>(w[u], z2, s2, a[u]);
-                else
-                    skinny_unpack<BITS, false, !F32>(w[u], z2, s2, a[u]);
-                if constexpr (F32) {
+                    for (int v = 0; v < 4; ++v) {
+                        scf[u][v] = (float)s4[v];
+                        zf[u][v] = (float)z4[v];
+                    }
+                } else {
+                    const h2 z2 = as_h2(zr[u] * 0x10001u), s2 = F32 ? h2{} : as_h2(ss[u] * 0x10001u);
+                    const _Float16 z = z2[0];
+                    // integer zeros (what the quantizer produces): bias and zero leave in one addition
+                    if (__builtin_amdgcn_ballot_w64(z != __builtin_truncf16(z)) == 0)
+                        skinny_unpack<BITS, true, !F32>(w[u], z2, s2, a[u]);
+                    else
+                        skinny_unpack<BITS, false, !F32>(w[u], z2, s2, a[u]);
+                    if constexpr (F32) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        scf[u][v] = (float)sc[u][v];
+                        for (int v = 0; v < 4; ++v)
+                            scf[u][v] = (float)sc[u][v];
+                    }
                 }
-            }
+            });
             load_w(t + 1);
-            f4 p[S][MB];
+            f4 p[S][MB], xs = {0.f, 0.f, 0.f, 0.f}; // xs: sum over the group of the lane's activation row
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 // the stage's copies are older than at least the COPIES * (H - 1) copies of the stages behind it
@@ -206,6 +250,12 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
                             else
                                 acc[u][j] = mfma16x16x32(a[u][2 * half + s], xf[s][j], acc[u][j]);
                         }
+                if constexpr (ZERO_APART) {
+                    const _Float16 one = 1;
+#pragma unroll
+                    for (int s = 0; s < 2; ++s)
+                        xs = mfma16x16x32(h8{one, one, one, one, one, one, one, one}, xf[s][0], xs);
+                }
                 __builtin_amdgcn_sched_barrier(0);
                 __builtin_amdgcn_s_waitcnt(FQ_WAIT_LGKMCNT0); // the operands have left the slot
                 copy(2 * t + half + H);
@@ -217,7 +267,7 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
                     for (int j = 0; j < MB; ++j)
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
-                            acc[u][j][v] = fmaf(scf[u][v], p[u][j][v], acc[u][j][v]);
+                            acc[u][j][v] = fmaf(scf[u][v], ZERO_APART ? fmaf(-zf[u][v], xs[v], p[u][j][v]) : p[u][j][v], acc[u][j][v]);
             }
         }
     }

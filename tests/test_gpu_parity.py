@@ -209,6 +209,38 @@ def test_qlinear_few_rows_against_oracle(fq, torch, bits, case):
         assert np.sqrt(np.mean(err ** 2)) <= 4e-4 * np.sqrt(np.mean(r ** 2))
 
 
+@pytest.mark.parametrize("zeros", ["fractions", "odd_large", "largest", "negative"])
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("case", [(1, 300, 1024), (2, 300, 1024), (3, 300, 8320), (4, 70, 128), (4, 300, 2048), (16, 5200, 1152),
+                                  (16, 11008, 1280)], ids=lambda c: "M%d_N%d_K%d" % c)
+def test_qlinear_of_a_few_rows_takes_any_zero_exactly(fq, torch, bits, case, zeros):
+    """Up to sixteen rows no weight is rounded, whatever its zero: beside the output's rounding (2^-11 |r|) there are only
+    those of fp32 sums, a few 2^-24 of sum |x| scale (code + |zero|), and up to three rows of the bias of 1024 that
+    the streamed codes carry.  A code - zero rounded to fp16 would be 2^-12 of it off per weight.  Some of the groups
+    keep integer zeros, and zeros in steps that are exact beside every code."""
+    M, N, K = case
+    G = K // 128
+    rng = np.random.default_rng(1000 * bits + N + K)
+    codes = fq_synth.codes(64, N, K, bits)
+    s = (np.abs(fq_synth.activations(65, N, G).astype(np.float32)) * 1e-4 + 1e-4).astype(np.float16)
+    X = fq_synth.activations(66, M, K)
+    z = {"fractions": rng.uniform(0, 2 ** bits, (N, G)), "odd_large": 2 * rng.integers(512, 1024, (N, G)) + 1,
+         "largest": rng.choice([65504.0, 64512.0, 40000.0, 2049.0, 1e-6], (N, G)),
+         "negative": -rng.uniform(0, 300, (N, G))}[zeros].astype(np.float16)
+    z[:, 1::3] = fq_synth.codes(67, N, G, bits)[:, 1::3]
+    z[:, 2::6] += np.float16(2.0 ** (bits - 11)) * (np.abs(z[:, 2::6]) < 2 ** bits)
+    w = fq.PackedMatrix.from_host(codes, s, z, bits)
+    out = Guarded(torch, M * N * 2)
+    fq.fq_qlinear(dev(torch, X), w, out=out.half(M, N))
+    assert out.intact()
+    r = oracle.qlinear(X, oracle.dequant(codes, s, z))
+    per_code = codes.astype(np.float32) + np.repeat(np.abs(z.astype(np.float32)), 128, axis=1) + (1024.0 if M <= 3 else 0.0)
+    size = oracle.qlinear(np.abs(X), per_code * np.repeat(s.astype(np.float32), 128, axis=1))
+    err = np.abs(host16(out.half(M, N)).astype(np.float64) - r)
+    bound = 2.0 ** -11 * np.abs(r) + 1e-6 * size + 2.0 ** -25
+    assert np.count_nonzero(err > bound) == 0
+
+
 def test_qlinear_tile_rejects_other_tile_heights(fq, torch):
     w, *_ = make_matrix(fq, 1, 64, 128, 4)
     with pytest.raises(fq.FqError) as e:
