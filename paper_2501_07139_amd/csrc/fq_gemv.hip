@@ -172,10 +172,12 @@ struct GemvInput {
 
 
 // The feed-forward modes (4 and 6) read two long rows: with all of them in LDS there is room for one workgroup a CU
-// (ffn 13824: 95 KiB).  A thread keeps its chunks of the first two trips over the rows in registers instead (62 KiB).
-template <int MODE>
+// (ffn 13824: 95 KiB).  With one activation row a thread keeps its chunks of the first two trips over them in registers
+// instead (62 KiB).  With more rows the registers are taken: sixteen would spill (two 13B-shaped blocks of 8 bits at two
+// rows 189 us against 172 with the rows in LDS, 7B-shaped 129 against 122).
+template <int MODE, int MV>
 struct GemvRows {
-    static constexpr int TRIPS = MODE == 4 || MODE == 6 ? 2 : 0;
+    static constexpr int TRIPS = MV == 1 && (MODE == 4 || MODE == 6) ? 2 : 0;
     h8 a[TRIPS + 1], b[TRIPS + 1];
     __device__ __forceinline__ void load(const _Float16 *pa, const _Float16 *pb, int chunks)
     {
@@ -235,7 +237,7 @@ struct GemvCursor {
 // supertile row (and read the same cache lines) are 8 apart, i.e. on the same XCD and L2.
 template <int BITS, int MODE, int MV, int S, int D = 2>
 __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvInput in, int rows_given, int K,
-                                          unsigned char *smem, float *part, GemvRows<MODE> &rows)
+                                          unsigned char *smem, float *part, GemvRows<MODE, MV> &rows)
 {
     // A constant for one row: operand addresses are then immediates.  The loop is bound by instruction issue; with
     // the three sums of a group in one 16-byte LDS read this took a 7B-shaped block from 37.6 to 36.1 us (bits
@@ -243,7 +245,7 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
     const int M = MV == 1 ? 1 : rows_given;
     constexpr int SUB = Fmt<BITS>::SUB, ROWS = Fmt<BITS>::ROWS, TILE = tile_dwords<BITS>();
     constexpr int NIN = GemvInputs<MODE>::N, STEP = 64 * GNW;
-    constexpr int RT = GemvRows<MODE>::TRIPS; // trips of the input rows that `rows` holds; the others are in LDS
+    constexpr int RT = GemvRows<MODE, MV>::TRIPS; // trips of the input rows that `rows` holds; the others are in LDS
     constexpr int SM = MV == 1 ? 1 : 16; // activation rows the group sums are kept for
     constexpr int F = SUB / S;
     constexpr bool WHOLE = F == 1;
@@ -647,9 +649,9 @@ __global__ __launch_bounds__(64 * GNW, 4) void gemv_stream_kernel(const _Float16
     // LDS.  The i-th copy of a wavefront fills 64 consecutive 16-byte slots, lane by lane; chunk indices past the
     // end of the row are clamped (their slots are never read).  The destination is the region the bodies call
     // `raw` (behind the staged activations and the three group arrays), the same for every width.
-    GemvRows<MODE> rows;
+    GemvRows<MODE, MV> rows;
     {
-        constexpr int NIN = GemvInputs<MODE>::N, STEP = 64 * GNW, SM = MV == 1 ? 1 : 16, RT = GemvRows<MODE>::TRIPS;
+        constexpr int NIN = GemvInputs<MODE>::N, STEP = 64 * GNW, SM = MV == 1 ? 1 : 16, RT = GemvRows<MODE, MV>::TRIPS;
         const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         const int GP = (((K >> 7) + GNW - 1) / GNW) * GNW;
         h8 *raw = reinterpret_cast<h8 *>(smem + (size_t)GP * 16 * (MV == 1 ? 1 : M) * 16 + (size_t)GP * (MV == 1 ? 4 : 3 * SM) * 4);
@@ -680,12 +682,12 @@ __global__ __launch_bounds__(64 * GNW, 4) void gemv_stream_kernel(const _Float16
             gemv_body<2, MODE, MV, 2>(job, bj, in, M, K, smem, part, rows);
         break;
     case 3:
-        if (job.split == 2)
-            gemv_body<3, MODE, MV, 2>(job, bj, in, M, K, smem, part, rows);
-        else if (job.split)
+        if (job.split == 4)
             gemv_body<3, MODE, MV, 1>(job, bj, in, M, K, smem, part, rows);
-        else
+        else if (job.split == 0)
             gemv_body<3, MODE, MV, 4>(job, bj, in, M, K, smem, part, rows);
+        else
+            gemv_body<3, MODE, MV, 2>(job, bj, in, M, K, smem, part, rows);
         break;
     case 4:
         if (K >= 8192)
@@ -720,7 +722,7 @@ size_t gemv_stream_lds(int M, int K, int bits, int mode)
     const int inputs = mode == 2 ? 3 : (mode >= 3 ? 2 : 1), threads = 64 * GNW;
     const size_t gp = (size_t)(((K >> 7) + GNW - 1) / GNW) * GNW;
     const size_t red = 2 * (size_t)GNW * sub * mv * 64 * 4;
-    const int trips = ((K >> 3) + threads - 1) / threads, held = mode == 4 || mode == 6 ? 2 : 0;
+    const int trips = ((K >> 3) + threads - 1) / threads, held = M == 1 && (mode == 4 || mode == 6) ? 2 : 0;
     const size_t raw = (size_t)inputs * (trips > held ? trips - held : 0) * threads * 16;
     return gp * 16 * M * 16 + gp * (M == 1 ? 4 : 48) * 4 + (red > raw ? red : raw);
 }
