@@ -161,6 +161,13 @@ int fq_qlinear(const void *x, int M, const void *packed, const void *scales, con
                int N, int K, int bits, int group, void *out, void *stream);
 int fq_qlinear_tile(const void *x, int M, const void *packed, const void *scales, const void *zeros,
                     int N, int K, int bits, int group, void *out, int tile_rows, void *stream);
+/*
+ * The kernel that fq_qlinear takes, or a launch of up to three matrices that share x (host only; for tests and tools).
+ * N, bits: host, count entries.  route_out (host, 3 ints): one of FQ_ROUTE_*, then rows and columns of its tiles
+ * (0, 0 for the first two).
+ */
+enum { FQ_ROUTE_STREAM, FQ_ROUTE_GENERIC, FQ_ROUTE_FEW_ROWS, FQ_ROUTE_TILES_128, FQ_ROUTE_TILES_256 };
+int fq_qlinear_route(int M, const int *N, const int *bits, int count, int K, int *route_out);
 
 /*
  * Mixed precision WITHIN a matrix (Section "Large Language Model Quantization":

@@ -59,6 +59,7 @@ def _load() -> ctypes.CDLL:
         "fq_dequant": (ci, [vp, vp, vp, ci, ci, ci, ci, vp, ci, vp]),
         "fq_qlinear": (ci, [vp, ci, vp, vp, vp, ci, ci, ci, ci, vp, vp]),
         "fq_qlinear_tile": (ci, [vp, ci, vp, vp, vp, ci, ci, ci, ci, vp, ci, vp]),
+        "fq_qlinear_route": (ci, [ci, vp, vp, ci, ci, vp]),
         "fq_stream_read": (ci, [vp, ctypes.c_size_t, vp, vp]),
         "fq_qlinear_mixed": (ci, [vp, ci, vp, ci, ci, ci, vp, vp]),
         "fq_stack_workspace_bytes": (sz, [ci, ci, ci]),
@@ -104,7 +105,7 @@ EXPORTS = ("fq_last_error", "fq_version", "fq_quantize_rtn", "fq_packed_bytes", 
            "fq_attn_prefill_workspace_bytes", "fq_prefill_workspace_bytes", "fq_attn_prefill", "fq_prefill_forward",
            "fq_init", "fq_dense_f16_tile", "fq_rope_table", "fq_stack_forward_noalloc", "fq_set_decode_mode",
            "fq_decode_give_up_ticks", "fq_async_error", "fq_clear_async_error", "fq_decode_partition", "fq_decode_persistent",
-           "fq_decode_persistent_launches")
+           "fq_decode_persistent_launches", "fq_qlinear_route")
 
 
 def _check(rc: int) -> None:
@@ -237,6 +238,17 @@ def fq_qlinear(x, w: PackedMatrix, out=None, stream=None, group: int = GROUP, ti
     _check(_lib.fq_qlinear_tile(_dp(x), M, _dp(w.packed), _dp(w.scales), _dp(w.zeros), w.N, w.K, w.bits, group,
                                 _dp(out), tile_rows, _stream(stream)))
     return out
+
+
+ROUTES = ("stream", "generic", "few_rows", "tiles_128", "tiles_256")
+
+
+def fq_qlinear_route(M: int, N, bits, K: int):
+    """(name, tile rows, tile columns) of the kernel for one matrix, or for up to three (sequences N, bits) that share x."""
+    N, bits = (_np(np.atleast_1d(np.asarray(v, dtype=np.int32)), np.int32) for v in (N, bits))
+    out = np.zeros(3, dtype=np.int32)
+    _check(_lib.fq_qlinear_route(M, _hp(N), _hp(bits), len(N), K, _hp(out)))
+    return ROUTES[out[0]], int(out[1]), int(out[2])
 
 
 MAX_SEGMENTS = 8

@@ -131,6 +131,34 @@ extern "C" int fq_qlinear_tile(const void *x, int M, const void *packed, const v
     return qlinear_checked(x, M, w, out, static_cast<fq_stream>(stream), tile_rows);
 }
 
+extern "C" int fq_qlinear_route(int M, const int *N, const int *bits, int count, int K, int *route_out)
+{
+    if (!N || !bits || !route_out)
+        return fq_fail(FQ_ERR_NULL, "fq_qlinear_route: NULL argument");
+    if (M <= 0 || count < 1 || count > 3 || K <= 0 || K % 128 != 0)
+        return fq_fail(FQ_ERR_SHAPE, "fq_qlinear_route: M=%d count=%d K=%d", M, count, K);
+    fq_packed_ref w[3];
+    bool stream = true;
+    for (int i = 0; i < count; ++i) {
+        if (N[i] <= 0 || fq_bits_index(bits[i]) < 0)
+            return fq_fail(N[i] <= 0 ? FQ_ERR_SHAPE : FQ_ERR_BITS, "fq_qlinear_route: N=%d bits=%d", N[i], bits[i]);
+        w[i] = fq_packed_ref{nullptr, nullptr, nullptr, N[i], K, bits[i]};
+        stream = stream && fq_gemv_can_stream(M, K, bits[i], 0);
+    }
+    route_out[1] = route_out[2] = 0;
+    if (M <= 16 ? fq_skinny_pays(M, w, count) : fq_gemm_tile_rows(M, w, count) == 0) {
+        route_out[0] = FQ_ROUTE_FEW_ROWS;
+        fq_skinny_tile(M, w, count, &route_out[1], &route_out[2]);
+    } else if (M <= 16) {
+        route_out[0] = stream ? FQ_ROUTE_STREAM : FQ_ROUTE_GENERIC;
+    } else {
+        route_out[1] = fq_gemm_tile_rows(M, w, count);
+        route_out[2] = 128;
+        route_out[0] = route_out[1] == 256 ? FQ_ROUTE_TILES_256 : FQ_ROUTE_TILES_128;
+    }
+    return FQ_OK;
+}
+
 extern "C" int fq_qlinear_mixed(const void *x, int M, const fq_segment *segments, int count, int K, int group,
                                 void *out, void *stream)
 {

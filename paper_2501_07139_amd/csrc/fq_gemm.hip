@@ -702,16 +702,25 @@ static int launch_tall(const void *x, int M, const fq_packed_ref *w, void *const
     return (int)hipGetLastError();
 }
 
+// Up to sixteen rows (the linears of a stack forward, which has no use for the streaming kernel then) the few-row kernel
+// serves every launch whose offsets it can hold.
+int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count)
+{
+    const int rows = choose_tile_rows(M, w, count);
+    if (rows == 128 && (M <= 16 ? fq_skinny_can(M, w[0].K) : fq_skinny_pays(M, w, count)))
+        return 0;
+    return rows;
+}
+
 int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st, int tile_rows)
 {
     const size_t Np = ((size_t)w.N + 63) / 64 * 64;
     if (!fits_32bit(M, w.K, 2) || Np / 8 * w.K * w.bits >= ((size_t)1 << 32))
         return (int)hipErrorInvalidValue;
-    if (tile_rows == 0) {
-        tile_rows = choose_tile_rows(M, &w, 1);
-        if (tile_rows == 128 && fq_skinny_pays(M, &w, 1))
-            return fq_launch_skinny(x, M, &w, &out, 1, st);
-    }
+    if (tile_rows == 0)
+        tile_rows = fq_gemm_tile_rows(M, &w, 1);
+    if (tile_rows == 0)
+        return fq_launch_skinny(x, M, &w, &out, 1, st);
     if (tile_rows == 256)
         return launch_tall(x, M, &w, &out, 1, st);
     if (w.ld && w.ld != w.N) // a column range of a wider output: the multi-matrix kernel carries the row pitch
@@ -735,11 +744,10 @@ int fq_launch_gemm_multi(const void *x, int M, const fq_packed_ref *w, void *con
         if (w[i].K != w[0].K || !fits_32bit(M, w[i].K, 2) || Np / 8 * w[i].K * w[i].bits >= ((size_t)1 << 32))
             return (int)hipErrorInvalidValue;
     }
-    if (tile_rows == 0) {
-        tile_rows = choose_tile_rows(M, w, count);
-        if (tile_rows == 128 && (M <= 16 ? fq_skinny_can(M, w[0].K) : fq_skinny_pays(M, w, count)))
-            return fq_launch_skinny(x, M, w, outs, count, st);
-    }
+    if (tile_rows == 0)
+        tile_rows = fq_gemm_tile_rows(M, w, count);
+    if (tile_rows == 0)
+        return fq_launch_skinny(x, M, w, outs, count, st);
     if (tile_rows == 256)
         return launch_tall(x, M, w, outs, count, st);
     GemmJobs jobs;

@@ -28,6 +28,7 @@ int fq_launch_dequant(const fq_packed_ref &w, void *out, int out_is_fp16, fq_str
 // Few rows (fq_skinny.hip): up to three matrices that share x (same K); whether it is the faster kernel for a launch.
 bool fq_skinny_can(int M, int K);
 bool fq_skinny_pays(int M, const fq_packed_ref *w, int count);
+void fq_skinny_tile(int M, const fq_packed_ref *w, int count, int *rows, int *columns);
 int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st);
 int fq_launch_gemv(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st);
 // Streaming decode kernel: up to three matrices that share their input and K in one launch (M <= 16).
@@ -63,7 +64,9 @@ int fq_decode_set_mode(int mode);    // 0: per-phase launches (default), 1: pers
 unsigned long long fq_decode_launches(); // persistent launches queued by this process so far
 int fq_decode_available(int H, int F); // pages per ring if the persistent kernel would run, else 0
 void fq_decode_partition_of(unsigned bits4, int ph, int N, int wg, int grid, int *out6);
-// M > 16.  tile_rows: 0 lets the library choose between the 128-row and the 256-row tile kernels, 128 or 256 pins one.
+// M > 16.  Height of the large tiles of a launch (128 or 256), 0: the few-row kernel.
+int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count);
+// tile_rows: 0 lets the library choose, 128 or 256 pins one of the large-tile kernels.
 int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st, int tile_rows = 0);
 // Up to three matrices with the same input (same K) in one launch, M > 16.
 int fq_launch_gemm_multi(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st,

@@ -338,13 +338,20 @@ struct SkinnyPlan {
     double us;
 };
 
-// Tile shape for a launch.  The time of a shape, as fitted to measurements at 4096 x 4096, 11008 x 4096 and 4096 x
-// 11008, all widths, 1 to 512 rows (within 10 %): a launch costs 2 us, a round of tiles over the chip 1.6 us (3.2 us
-// for the largest sums to add up) beside its turns of eight groups, and a turn 0.1 + 0.29 S + 0.34 MB us -- unpacking S
+// Tile shape for a launch of more than sixteen rows.  The time of a shape, as fitted to measurements at 4096 x 4096, 11008
+// x 4096 and 4096 x 11008, all widths, 1 to 512 rows: a launch costs 2 us, a round of tiles over the chip 1.6 us (3.2
+// us for the largest sums to add up) beside its turns of eight groups, and a turn 0.1 + 0.29 S + 0.34 MB us -- unpacking S
 // sub-blocks and moving MB row blocks of activations add up, the matrix instructions hide behind them.  8-bit chunks
 // are twice the bytes, 3-bit ones that are less than a supertile come in single dwords (0.39 and 0.45 S us).  The
 // smallest shapes leave room for a second workgroup on a CU, so their rounds are not whole ones.  4 x 1 is never ahead
-// of 2 x 2.
+// of 2 x 2.  The turns take no less than the activations need to reach an XCD's L2 at 0.8 TB/s: with thirty and more row
+// tiles the tiles that an XCD works on share hardly any (2048 rows of 1024 x 2816: 37 us where the turns alone would be 24).
+// Over 2300 sizes of 17 to 3000 rows half the launches are within 9 % of this, a twentieth more than 25 % off.
+//
+// Up to sixteen rows every shape has one row block and the number of sub-blocks is all there is to choose (it does not change
+// a sum).  Fitted to 2500 sizes of 64 to 24000 columns with each S: 3.4 us and a turn of 0.13 + 0.28 S us (8 bits 0.37 S;
+// 3-bit S < 4: 0.2 + 0.5 S) while every CU has one tile; a second one on some CUs costs nearly a second turn, and from two a
+// CU on the time grows with the tiles.  64 columns a tile just beyond one round (20739 x 1664, 4 bits) 11.3 us, 32 columns 9.8.
 SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
 {
     SkinnyPlan best = {1, 0, 1, 1e30};
@@ -352,19 +359,41 @@ SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
     for (int sl = 0; sl < 3; ++sl) {
         const int S = 1 << sl;
         long col_tiles = 0;
-        double sub = 0.29; // us per sub-block
+        double sub = 0.0, one_block = 0.0; // us of a turn: a sub-block's; all of a tile of one row block
         for (int i = 0; i < count; ++i) {
             col_tiles += (w[i].N + 16 * S - 1) / (16 * S);
-            const double u = w[i].bits == 8 ? 0.39 : (w[i].bits == 3 && S < 4 ? 0.45 : 0.29);
+            const bool dwords = w[i].bits == 3 && S < 4;
+            const double u = w[i].bits == 8 ? 0.39 : (dwords ? 0.45 : 0.29);
             sub = sub > u ? sub : u;
+            const double t = dwords ? 0.2 + 0.5 * S : 0.13 + (w[i].bits == 8 ? 0.37 : 0.28) * S;
+            one_block = one_block > t ? one_block : t;
+        }
+        if (blocks == 1) {
+            const double waves = (double)col_tiles / SKINNY_CUS;
+            double fixed = 3.4, factor = 1.0;
+            if (waves > 1.0 && S == 4) {
+                factor = (double)(long)(waves + 0.999);
+                fixed = 2.4 + factor;
+            } else if (waves > 1.0) {
+                factor = S == 1 ? (waves <= 2.0 ? 2.2 : 1.5 * waves) : (waves <= 2.0 ? 1.9 : 1.25 * waves);
+                fixed = 3.1 + 0.3 * waves;
+            }
+            const double us = fixed + factor * turns * one_block;
+            if (us < best.us)
+                best = {1, sl, 1, us};
+            continue;
         }
         for (int mb = 1; mb <= (S == 1 ? 3 : 4); ++mb) {
             const int row_tiles = (blocks + mb - 1) / mb;
             if ((blocks + row_tiles - 1) / row_tiles != mb)
                 continue; // as many row tiles of fewer blocks do
-            const double waves = (double)(row_tiles * col_tiles) / SKINNY_CUS;
+            const double tiles = (double)row_tiles * (double)col_tiles, waves = tiles / SKINNY_CUS;
             const double rounds = waves <= 1.0 ? 1.0 : ((mb == 1 && S <= 2) ? 1.15 * waves : (double)(long)(waves + 0.999));
-            const double us = 2.0 + rounds * ((S == 4 && mb > 1 ? 3.2 : 1.6) + turns * (0.1 + sub * S + 0.34 * mb));
+            const double in_xcd = tiles > 8.0 ? tiles / 8.0 : 1.0; // 32 of them at a time, row-tile fastest
+            const double rows = 16.0 * mb * (row_tiles < 32 ? (row_tiles < in_xcd ? row_tiles : in_xcd) : (in_xcd < 32.0 ? in_xcd : 32.0));
+            const double l2 = (in_xcd > 32.0 ? in_xcd / 32.0 : 1.0) * rows * w[0].K * 2.0 / 0.8e6; // us
+            const double work = rounds * turns * (0.1 + sub * S + 0.34 * mb);
+            const double us = 2.0 + rounds * (S == 4 && mb > 1 ? 3.2 : 1.6) + (work > l2 ? work : l2);
             if (us < best.us)
                 best = {mb, sl, row_tiles, us};
         }
@@ -372,8 +401,10 @@ SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
     return best;
 }
 
-// Time of the 128-row tile kernel on the same launch, fitted to the same measurements: a group of 128 k takes 1.2 us
-// while half the CUs have a tile, 1.4 us up to one tile a CU, and from 1.5 us (3 bits: 1.8) on with two on some.
+// Time of the 128-row tile kernel on the same launch: 5.4 us and 1.31 us a group of 128 k up to one tile a CU, from 1.5
+// us (3 bits: 1.8) a group on with two on some.  Over 2300 sizes the time is 0.8 to 1.15 of this from K = 1024 on, where at
+// most one tile a CU is there, and 1 to 1.5 below; with more tiles 0.86 to 1.1 from K = 4096 on and up to twice this on short
+// rows, which go to the few-row kernel.
 double tile_kernel_us(int M, const fq_packed_ref *w, int count)
 {
     long tiles = 0;
@@ -384,8 +415,8 @@ double tile_kernel_us(int M, const fq_packed_ref *w, int count)
     }
     if (tiles > 2 * SKINNY_CUS)
         return 0.0; // several rounds of tiles fill the chip: the large tiles are the better ones
-    const double group = tiles <= SKINNY_CUS / 2 ? 1.2 : (tiles <= SKINNY_CUS ? 1.4 : 1.5 + three + 0.7 * (tiles - SKINNY_CUS) / SKINNY_CUS);
-    return 2.0 + (w[0].K >> 7) * group;
+    const double group = tiles <= SKINNY_CUS ? 1.31 : 1.5 + three + 0.7 * (tiles - SKINNY_CUS) / SKINNY_CUS;
+    return 5.4 + (w[0].K >> 7) * group;
 }
 
 } // namespace
@@ -395,19 +426,33 @@ bool fq_skinny_can(int M, int K) { return K <= (1 << 22) && (size_t)M * K * 2 < 
 
 // Whether a launch goes to the skinny kernel.  Few rows (M <= 16): from four rows on, three of long rows, where the
 // streaming kernel stages one row after another (4096 x 4096, 4 bits: 7.5 against 5.8 us at 4 rows, 17 against 6.0 at 16; at
-// one row 4.2 against 6.1; 4096 x 11008 at 3 rows 11.3 against 10), and where that kernel has no room for the rows.
-// More rows: where the model above puts it ahead of the tile kernel (4096 x 11008, 3 bits: 23 against 109 us at 77 rows,
-// 34 against 116 at 256, 64 against 117 at 512).
+// one row 4.2 against 6.1; 4096 x 11008 at 3 rows 11.3 against 10), and where that kernel has no room for the rows.  Four
+// rows of more columns than one round of the widest tiles covers stay with the streaming kernel unless they are
+// short or long ones (19741 x 1792 at 2 bits 9.2 against 11.0 us, and level on average from 1024 to 8192; below, 0.75 of
+// its time, above 0.9), three also if they are long (21160 x 8192 at 3 bits 22.6 against 25.2).  More rows: where the models above put it ahead of the tile kernel (4096 x 11008, 3 bits: 23 against
+// 109 us at 77 rows, 34 against 116 at 256, 64 against 117 at 512; 1024 x 2816, 2 bits, at 2048 rows 37 against 30).
 bool fq_skinny_pays(int M, const fq_packed_ref *w, int count)
 {
     if (!fq_skinny_can(M, w[0].K))
         return false;
     if (M > 16)
         return skinny_plan(M, w, count).us < tile_kernel_us(M, w, count);
-    bool stream = M < 3 || (M == 3 && w[0].K < 8192);
+    const int K = w[0].K;
+    long columns = 0;
     for (int i = 0; i < count; ++i)
-        stream = stream && fq_gemv_can_stream(M, w[i].K, w[i].bits, 0);
+        columns += w[i].N;
+    const bool wide = columns > 64 * SKINNY_CUS;
+    bool stream = M < 3 || (M == 3 && (K < 8192 || wide)) || (M == 4 && K >= 1024 && K < 8192 && wide);
+    for (int i = 0; i < count; ++i)
+        stream = stream && fq_gemv_can_stream(M, K, w[i].bits, 0);
     return !stream;
+}
+
+void fq_skinny_tile(int M, const fq_packed_ref *w, int count, int *rows, int *columns)
+{
+    const SkinnyPlan plan = skinny_plan(M, w, count);
+    *rows = 16 * plan.mb;
+    *columns = 16 << plan.s_log2;
 }
 
 // Up to three matrices that share the input (same K), in one launch.

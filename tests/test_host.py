@@ -212,3 +212,44 @@ def test_new_entry_points_validate_their_arguments_on_the_host():
     assert lib.fq_stream_read(16, 40, 16, None) == -2 and lib.fq_stream_read(16, 0, 16, None) == -2
     assert lib.fq_stream_read(24, 64, 16, None) == -5
     assert fq.fq_set_decode_mode(0) in (0, 1)
+
+
+# ------------------------------------------------------------ dispatch by time
+def route(M, N, bits, K):
+    return fq.fq_qlinear_route(M, N, bits, K)[0]
+
+
+@pytest.mark.parametrize("bits", BITS)
+def test_few_row_kernel_leaves_the_sizes_that_others_run_faster(bits):
+    """Sizes at which the few-row kernel was measured slower than the kernel of the general path: many rows whose
+    activations no L2 holds (2048 x 1024 x 2816: 37 against 30 us), three and four rows of wide matrices (four of
+    19741 x 1792: 11.0 against 9.2); and neighbours at which it is the faster one."""
+    for M, N, K in ((2048, 1024, 2816), (1890, 1420, 6400), (2480, 1066, 15616)):
+        assert route(M, N, bits, K) == "tiles_128"
+    for M, N, K in ((1024, 1024, 2816), (512, 4096, 4096), (77, 4096, 11008), (300, 70, 256)):
+        assert route(M, N, bits, K) == "few_rows"
+    for M, N, K in ((3, 21160, 8192), (4, 19741, 1792), (4, 18581, 1024), (3, 4096, 4096), (2, 4096, 4096), (1, 11008, 4096)):
+        assert route(M, N, bits, K) == "stream"
+    for M, N, K in ((3, 4096, 11008), (4, 4096, 4096), (4, 16384, 4096), (4, 20000, 512), (4, 20000, 11008), (5, 20000, 2048), (16, 512, 512)):
+        assert route(M, N, bits, K) == "few_rows"
+    # 64 columns a tile just beyond one round of tiles over the chip pay for a second one (20739 x 1664: 11.3 against 9.8 us)
+    assert fq.fq_qlinear_route(5, 20739, bits, 1664)[1:] == (16, 64 if bits == 3 else 32)
+    assert fq.fq_qlinear_route(5, 16384, bits, 1664)[1:] == (16, 64)
+
+
+def test_route_takes_every_size_that_the_linear_takes():
+    for M in (1, 2, 3, 4, 16, 17, 128, 129, 2048, 4096, 70000):
+        for N in (1, 64, 70, 4096, 30000):
+            for K in (128, 1152, 4096, 16384):
+                name, rows, cols = fq.fq_qlinear_route(M, [N, N], [3, 8], K)
+                assert name in fq.ROUTES and (rows > 0) == (cols > 0) == (name not in ("stream", "generic"))
+                assert name in (("stream", "few_rows") if M <= 16 else ("few_rows", "tiles_128", "tiles_256"))
+    assert route(3, 64, 4, (1 << 22) + 128) == "generic" and route(16, 64, 4, 1 << 22) == "few_rows"
+    out = np.zeros(3, dtype=np.int32)
+    one = np.array([4], dtype=np.int32)
+    p = [a.ctypes.data_as(ctypes.c_void_p) for a in (one, one, out)]
+    assert fq._lib.fq_qlinear_route(1, None, p[1], 1, 128, p[2]) == -1
+    for M, count, K in ((0, 1, 128), (1, 0, 128), (1, 4, 128), (1, 1, 100), (1, 1, 0)):
+        assert fq._lib.fq_qlinear_route(M, p[0], p[1], count, K, p[2]) == -2
+    with pytest.raises(fq.FqError):
+        fq.fq_qlinear_route(1, 64, 5, 128)
