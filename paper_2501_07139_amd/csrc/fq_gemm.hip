@@ -632,7 +632,11 @@ int tall_tiles(int M, int N) { return ((N + TBN - 1) / TBN) * ((M + TBM - 1) / T
 // rows, 4096 to 22016 columns (us at 2 / 3 / 4 / 8 bits): a full round of 128-row tiles 63 / 73 / 67 / 73, its last one 47 when
 // at most one tile a CU is left and 4 under a full one otherwise; a full round of tall tiles 61 / 67 / 63 / 66, a last
 // one 50 to 60.  So 640 rows of 11008 columns (430 tiles or 258) take 64 against 110 us, 2048 rows (1376 or 688) 204
-// against 184.  From 4096 rows on, the 128 x 256 tiles of 2- and 4-bit matrices run several full rounds and are level or
+// against 184.  All of it follows the number of groups, but on shorter rows a round of tall tiles keeps up to 1.5 us more (the
+// two halves of its K meet through LDS): without them such rows went to tall tiles that took up to a third longer (229
+// rows of 20424 x 128 11.9 against 9.0 us, 1932 of 3144 x 384 15.8 against 13.9).  Of 960 sizes 12 are more than 2 % slower
+// than in tall tiles wherever there are 256 of them, the rule without rounds (56 were), and on average they are 8 %
+// faster.  From 4096 rows on, the 128 x 256 tiles of 2- and 4-bit matrices run several full rounds and are level or
 // 2-6 % ahead of the tall ones, so launches made of such matrices only stay with them.
 int choose_tile_rows(int M, const fq_packed_ref *w, int count)
 {
@@ -655,7 +659,9 @@ int choose_tile_rows(int M, const fq_packed_ref *w, int count)
     const long r128 = tiles % 512, r256 = tall % 256;
     const double t128 = (tiles / 512) * f128 + (r128 == 0 ? 0.0 : (r128 <= 256 ? 47.0 : f128 - 4.0));
     const double t256 = (tall / 256) * f256 + (r256 == 0 ? 0.0 : 50.0 + 10.0 * r256 / 256);
-    return t256 < t128 ? 256 : 128;
+    const double length = w[0].K / 4096.0; // of the rows, in those that the figures above were taken with
+    const double fixed256 = length < 1.0 ? 1.5 * (1.0 - length) * (tall / 256 + (r256 != 0)) : 0.0;
+    return t256 * length + fixed256 < t128 * length ? 256 : 128;
 }
 
 template <int BITS, int QNB>
