@@ -157,27 +157,41 @@ __global__ __launch_bounds__(256) void glue2_kernel(const _Float16 *__restrict__
 }
 
 // ------------------------------------------------------------------- NLL
-// Rows of logits: base pointers are 16-byte aligned, rows of V elements are so only if V % 8 == 0.  Elements [0, head) of a row lie before
-// its first aligned chunk of eight, elements [head + 8 * chunks, V) behind its last; both are fewer than eight.
+// How a row of V logits is read (base pointers are 16-byte aligned, so a row is only if V % 8 == 0): in chunks of eight; in
+// chunks from its first aligned element on, with up to seven elements before and behind them; or element by element.
+enum RowMode { ROW_ALIGNED, ROW_ANY, ROW_ELEMENTS };
+
+// Up to 512 elements are two loads a thread: the ends of a row that is not aligned would take as long (500 logits, 2048 rows:
+// distance 3.1 us, 3.3 with chunks; 1001 logits 3.4 and 3.3).
+RowMode row_mode(int V) { return (V & 7) == 0 ? ROW_ALIGNED : (V <= 512 ? ROW_ELEMENTS : ROW_ANY); }
+
+template <RowMode MODE>
 struct RowSpan {
-    int head, chunks;
+    int head, chunks; // elements before the first chunk; chunks
     __device__ __forceinline__ RowSpan(int row, int V)
     {
-        head = min((int)((8u - (uint32_t)(((uint64_t)row * (uint64_t)V) & 7u)) & 7u), V);
-        chunks = (V - head) >> 3;
+        head = MODE == ROW_ANY ? min((int)((8u - (uint32_t)(((uint64_t)row * (uint64_t)V) & 7u)) & 7u), V) : 0;
+        chunks = MODE == ROW_ELEMENTS ? 0 : (V - head) >> 3;
     }
-    // element of thread i's share of the unaligned ends: thread i < head the i-th, then those behind the chunks; -1: none
-    __device__ __forceinline__ int end_element(int i, int V) const
+    // use(i) for the elements outside the chunks: fewer than sixteen, one a thread, or all of the row
+    template <int THREADS, class F>
+    __device__ __forceinline__ void ends(int V, F &&use) const
     {
-        const int e = i < head ? i : i + 8 * chunks;
-        return e < V ? e : -1;
+        if constexpr (MODE == ROW_ELEMENTS) {
+            for (int i = threadIdx.x; i < V; i += THREADS)
+                use(i);
+        } else if constexpr (MODE == ROW_ANY) {
+            const int i = threadIdx.x, e = i < head ? i : i + 8 * chunks;
+            if (i < 16 && e < V)
+                use(e);
+        }
     }
 };
 
-// Chunks a thread loads before it uses the first.  The last trip takes the loads it has no chunk for from the row's
-// last one: with a loop of whole trips and another for the rest, the lanes of one wavefront part and it runs both, the
-// rest load by load (loss of 2048 x 8000 logits 11.4 -> 9.9 us, 300 x 32000 9.7 -> 8.9; two chunks 10.4 and 9.3).  A row
-// of one chunk a thread loads just that (distance of 2048 x 1000: 4.0 us with the repeated loads, 3.8 without).
+// Chunks a thread loads before it uses the first, where a row has more than two a thread.  The last trip takes the loads it has
+// no chunk for from the row's last one: with a loop of whole trips and another for the rest, the lanes of one wavefront
+// part and it runs both, the rest load by load (loss of 2048 x 8000 logits 11.4 -> 9.9 us, 300 x 32000 9.7 -> 8.9; two chunks
+// 10.4 and 9.3).  Shorter rows gain nothing by it (loss of 512 x 4096 logits 3.6 us against 3.45).
 constexpr int ROW_UNROLL = 4;
 
 // One workgroup per token row; each thread keeps a running (max, sum of
@@ -185,7 +199,7 @@ constexpr int ROW_UNROLL = 4;
 // wavefront and the workgroup.  The label's logit is read directly.  Bound by the read; few rows take large
 // workgroups (THREADS), so that the loads of a row are under way together.
 // Measured (us): 2048 x 32000 27; 2048 x 31001, whose rows are not aligned, 27 (element by element 71).
-template <int THREADS>
+template <int THREADS, RowMode MODE>
 __global__ __launch_bounds__(THREADS) void nll_kernel(const _Float16 *__restrict__ logits,
                                                       const int32_t *__restrict__ labels, int V,
                                                       float *__restrict__ nll)
@@ -198,7 +212,7 @@ __global__ __launch_bounds__(THREADS) void nll_kernel(const _Float16 *__restrict
         return;
     }
     const _Float16 *l = logits + (size_t)row * V;
-    const RowSpan span(row, V);
+    const RowSpan<MODE> span(row, V);
     const h8 *chunk = reinterpret_cast<const h8 *>(l + span.head);
     float mx = -INFINITY, se = 0.f;
     auto add = [&](h8 v) {
@@ -209,9 +223,9 @@ __global__ __launch_bounds__(THREADS) void nll_kernel(const _Float16 *__restrict
         lse_pair(e8, cm, cs);
         lse_merge(mx, se, cm, cs);
     };
-    if (span.chunks <= THREADS) {
-        if ((int)threadIdx.x < span.chunks)
-            add(chunk[threadIdx.x]);
+    if (span.chunks <= 2 * THREADS) {
+        for (int ch = threadIdx.x; ch < span.chunks; ch += THREADS)
+            add(chunk[ch]);
     } else {
         for (int ch = threadIdx.x; ch < span.chunks; ch += ROW_UNROLL * THREADS) {
             h8 v[ROW_UNROLL];
@@ -224,15 +238,10 @@ __global__ __launch_bounds__(THREADS) void nll_kernel(const _Float16 *__restrict
                     add(v[i]);
         }
     }
-    if (threadIdx.x < 16) { // fewer than sixteen elements lie outside the chunks
-        const int e = span.end_element(threadIdx.x, V);
-        if (e >= 0) {
-            const float e1[1] = {(float)l[e]};
-            float em, es;
-            lse_pair(e1, em, es);
-            lse_merge(mx, se, em, es);
-        }
-    }
+    span.template ends<THREADS>(V, [&](int i) {
+        const float e = (float)l[i]; // lse_pair of one logit: 1, or 0 for -inf, or NaN
+        lse_merge(mx, se, fmaxf(e, LSE_FLOOR), e == -INFINITY ? 0.f : (e - e) + 1.f);
+    });
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         const float m2 = __shfl_xor(mx, o, 64), s2 = __shfl_xor(se, o, 64);
@@ -319,22 +328,22 @@ int fq_launch_glue2(int op, const void *a, const void *b, int M, int H, void *au
 }
 
 // Workgroup size of the two row kernels: up to one row a CU, 1024 threads bring more loads of a long row under way (32000
-// logits, 256 rows: distance 8.5 -> 7.0 us, loss 9.5 -> 7.9; 384 rows: level, all with the earlier loop); short rows only pay for the larger
-// reduction (1000 logits: 3.0 -> 3.8 us).
-static bool wide_rows(int M, int V) { return M <= 256 && V >= 8192; }
+// logits, 256 rows: distance 8.3 -> 6.4 us, loss 9.4 -> 6.7; 384 rows: level); shorter rows only pay for the larger
+// reduction (loss of 8192 logits 3.8 -> 4.3 us, of 16384 level; the distance reads two rows: 8192 logits 3.2 -> 3.05).
+static bool wide_rows(int M, int V, int longer) { return M <= 256 && V >= longer; }
 
 // Row-wise Euclidean distance between two logit arrays (sensitivity analysis of the search, Section
 // "Efficient Design Space Navigation").  One workgroup per row, one pass over both rows with 128-bit loads; differences and
 // squares in fp32, four partial sums per thread, then a fixed-order reduction.  The two rows start at the same distance
 // from a 16-byte boundary.  Measured (us): 2048 x 32000 43, 2048 x 31001 41 (element by element 70).
 namespace {
-template <int THREADS>
+template <int THREADS, RowMode MODE>
 __global__ __launch_bounds__(THREADS) void logit_l2_kernel(const _Float16 *__restrict__ a, const _Float16 *__restrict__ b,
                                                            int V, float *__restrict__ dist)
 {
     const int row = blockIdx.x;
     const _Float16 *ra = a + (size_t)row * V, *rb = b + (size_t)row * V;
-    const RowSpan span(row, V);
+    const RowSpan<MODE> span(row, V);
     const h8 *ca = reinterpret_cast<const h8 *>(ra + span.head), *cb = reinterpret_cast<const h8 *>(rb + span.head);
     float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
     auto add = [&](h8 va, h8 vb) {
@@ -345,9 +354,11 @@ __global__ __launch_bounds__(THREADS) void logit_l2_kernel(const _Float16 *__res
         s0 = fmaf(d[0], d[0], s0); s1 = fmaf(d[1], d[1], s1); s2 = fmaf(d[2], d[2], s2); s3 = fmaf(d[3], d[3], s3);
         s0 = fmaf(d[4], d[4], s0); s1 = fmaf(d[5], d[5], s1); s2 = fmaf(d[6], d[6], s2); s3 = fmaf(d[7], d[7], s3);
     };
-    if (span.chunks <= THREADS) {
-        if ((int)threadIdx.x < span.chunks)
-            add(ca[threadIdx.x], cb[threadIdx.x]);
+    // two loads a chunk: with small workgroups, several on a CU, more in flight gain nothing up to 16384 logits (1024 x 8192
+    // 5.6 us, 6.1 with four trips' loads at once; 300 x 32000 8.9 and 7.9)
+    if (span.chunks <= (THREADS == 256 && MODE == ROW_ALIGNED ? 8 : 2) * THREADS) {
+        for (int ch = threadIdx.x; ch < span.chunks; ch += THREADS)
+            add(ca[ch], cb[ch]);
     } else {
         for (int ch = threadIdx.x; ch < span.chunks; ch += ROW_UNROLL * THREADS) {
             h8 va[ROW_UNROLL], vb[ROW_UNROLL];
@@ -363,13 +374,10 @@ __global__ __launch_bounds__(THREADS) void logit_l2_kernel(const _Float16 *__res
                     add(va[i], vb[i]);
         }
     }
-    if (threadIdx.x < 16) {
-        const int e = span.end_element(threadIdx.x, V);
-        if (e >= 0) {
-            const float d = (float)ra[e] - (float)rb[e];
-            s0 = fmaf(d, d, s0);
-        }
-    }
+    span.template ends<THREADS>(V, [&](int i) {
+        const float d = (float)ra[i] - (float)rb[i];
+        s0 = fmaf(d, d, s0);
+    });
     float ss = (s0 + s1) + (s2 + s3);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)
@@ -388,23 +396,33 @@ __global__ __launch_bounds__(THREADS) void logit_l2_kernel(const _Float16 *__res
 }
 } // namespace
 
+// [256 or 1024 threads][RowMode]; rows read element by element are never long enough for the larger workgroups
+typedef void (*L2Kernel)(const _Float16 *, const _Float16 *, int, float *);
+typedef void (*NllKernel)(const _Float16 *, const int32_t *, int, float *);
+static const L2Kernel l2_kernels[2][3] = {
+    {logit_l2_kernel<256, ROW_ALIGNED>, logit_l2_kernel<256, ROW_ANY>, logit_l2_kernel<256, ROW_ELEMENTS>},
+    {logit_l2_kernel<1024, ROW_ALIGNED>, logit_l2_kernel<1024, ROW_ANY>, nullptr}};
+static const NllKernel nll_kernels[2][3] = {
+    {nll_kernel<256, ROW_ALIGNED>, nll_kernel<256, ROW_ANY>, nll_kernel<256, ROW_ELEMENTS>},
+    {nll_kernel<1024, ROW_ALIGNED>, nll_kernel<1024, ROW_ANY>, nullptr}};
+
+template <class Kernel, class... Args>
+static void launch_rows(const Kernel (&kernels)[2][3], int M, int V, bool wide, fq_stream st, Args... args)
+{
+    hipLaunchKernelGGL(kernels[wide][row_mode(V)], dim3(M), dim3(wide ? 1024 : 256), 0, st, args...);
+}
+
 int fq_launch_logit_l2(const void *a, const void *b, int M, int V, float *dist, fq_stream st)
 {
     const _Float16 *pa = static_cast<const _Float16 *>(a), *pb = static_cast<const _Float16 *>(b);
-    if (wide_rows(M, V))
-        hipLaunchKernelGGL(logit_l2_kernel<1024>, dim3(M), dim3(1024), 0, st, pa, pb, V, dist);
-    else
-        hipLaunchKernelGGL(logit_l2_kernel<256>, dim3(M), dim3(256), 0, st, pa, pb, V, dist);
+    launch_rows(l2_kernels, M, V, wide_rows(M, V, 8192), st, pa, pb, V, dist);
     return (int)hipGetLastError();
 }
 
 int fq_launch_nll(const void *logits, const int32_t *labels, int M, int V, float *nll, fq_stream st)
 {
     const _Float16 *l = static_cast<const _Float16 *>(logits);
-    if (wide_rows(M, V))
-        hipLaunchKernelGGL(nll_kernel<1024>, dim3(M), dim3(1024), 0, st, l, labels, V, nll);
-    else
-        hipLaunchKernelGGL(nll_kernel<256>, dim3(M), dim3(256), 0, st, l, labels, V, nll);
+    launch_rows(nll_kernels, M, V, wide_rows(M, V, 16384), st, l, labels, V, nll);
     return (int)hipGetLastError();
 }
 

@@ -463,7 +463,7 @@ def test_logit_l2_against_oracle(fq, torch, shape):
     assert np.allclose(got, oracle.logit_l2(big, neg), rtol=1e-5)
 
 
-@pytest.mark.parametrize("V", [1, 7, 9, 15, 17, 1003, 8191, 8197, 31001])
+@pytest.mark.parametrize("V", [1, 7, 9, 15, 17, 255, 257, 511, 513, 1003, 8191, 8197, 16387, 31001])
 @pytest.mark.parametrize("M", [5, 260])
 def test_row_kernels_on_unaligned_rows(fq, torch, M, V):
     """Rows that start anywhere between 16-byte boundaries: elements before the first whole chunk, behind the last, and
@@ -504,7 +504,7 @@ def test_token_nll_of_masked_rows(fq, torch, M, V):
         assert np.isnan(fq.fq_token_nll(dev(torch, y), dev(torch, lab)).cpu().numpy()).all(), (at, width)
 
 
-@pytest.mark.parametrize("V", [2040, 2048, 2056, 4104, 8184, 8192, 8200, 32768, 32776])
+@pytest.mark.parametrize("V", [2040, 2048, 2056, 4096, 4104, 8184, 8192, 8200, 16384, 16392, 32768, 32776])
 @pytest.mark.parametrize("M", [5, 260])
 def test_row_kernels_around_whole_trips(fq, torch, M, V):
     """Rows of one chunk a thread, one more, and around whole trips of four chunks a thread, for both workgroup sizes.
