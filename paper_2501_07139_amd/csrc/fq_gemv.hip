@@ -852,7 +852,9 @@ int fq_launch_gemv_multi(const fq_gemv_input &src, int M, const fq_packed_ref *w
     // 5120 x 5120 at 3 bits 7.9 / 6.5 / 8.6, 4096 x 4096 6.3 / 5.3 / 5.3, 5120 x 13824 14.7 / 11.2 / 15.7, 11008 x 4096
     // 7.3 / 8.0 / 9.0; 5120 x 5120 at 2 bits 6.4 whole and 7.5 split, 4096 x 11008 8.5 and 7.4.  The workgroups that share a
     // supertile row are 8 apart in the grid, i.e. run on one XCD, whose L2 fetches their common lines once; the job's
-    // share of the grid is a multiple of 8 * parts.
+    // share of the grid is a multiple of 8 * parts.  With more than one row a unit's cost grows with its sub-blocks (each
+    // finishes four rows), so of two options that a third matrix makes equal the smaller units are the better ones (819 rows
+    // each of 11008 at 8 and 2 bits, two rows: 10.6 -> 9.3 us).
     static const double unit_costs[9][3] = {{}, {}, {1.25, 1.25, 0.95}, {2.5, 1.6, 1.25}, {1.0, 1.0, 1.0}, {}, {}, {}, {1.55, 1.55, 1.55}};
     static const int unit_parts[9][3] = {{}, {}, {1, 1, 2}, {1, 2, 4}, {1, 1, 1}, {}, {}, {}, {1, 1, 1}};
     int parts[3], units[3], gran[3], nbs[3], order[3], best = 0;
@@ -869,7 +871,7 @@ int fq_launch_gemv_multi(const fq_gemv_input &src, int M, const fq_packed_ref *w
             most = most > c ? most : c;
         }
         const double t = n <= GEMV_CUS ? most : work / GEMV_CUS > 1.8 * work / n ? work / GEMV_CUS : 1.8 * work / n;
-        if (t < best_t) {
+        if (t < best_t || (M > 1 && t == best_t)) {
             best_t = t;
             best = option;
         }
