@@ -171,12 +171,14 @@ def test_qlinear_decode_units_against_oracle(fq, torch, bits, case):
     assert qerr(host16(out.half(M, N)), r) <= TOL
 
 
-# Shapes of the few-row kernel: its eleven tile shapes (16/32/48/64 rows x 16/32/64 columns), row tiles that end inside a
-# block of sixteen, column counts that end inside a tile or a block, K of one group, of fewer groups than
-# wavefronts, of one more than a whole turn of them, and of several turns.
+# Shapes of the few-row kernel: its eleven tile shapes (16/32/48/64 rows x 16/32/64 columns) at every width, as the library
+# chooses them (tests/test_host.py holds this list against the rule), row tiles that end inside a block of sixteen, column
+# counts that end inside a tile or a block, K of one group, of fewer groups than wavefronts, of one more than a whole
+# turn of them, and of several turns.
 SKINNY_CASES = [(4, 512, 128), (16, 70, 1152), (9, 11008, 384), (17, 4096, 1152), (17, 8200, 1152), (33, 4096, 1152),
                 (48, 11008, 384), (60, 4096, 2176), (64, 11008, 1152), (77, 4096, 1152), (100, 201, 256),
-                (128, 4096, 1152), (200, 4096, 1152), (250, 1030, 1280)]
+                (128, 4096, 1152), (200, 4096, 1152), (250, 1030, 1280), (5, 4150, 384), (1036, 98, 128), (620, 230, 896),
+                (1045, 193, 128)]
 
 
 @pytest.mark.parametrize("bits", BITS)
@@ -200,6 +202,7 @@ def test_qlinear_few_rows_against_oracle(fq, torch, bits, case):
         z = z.astype(np.float16)
         w = fq.PackedMatrix.from_host(codes, s, z, bits)
         out = Guarded(torch, M * N * 2)
+        assert fq.fq_qlinear_route(M, N, bits, K)[0] == "few_rows"
         fq.fq_qlinear(dev(torch, X), w, out=out.half(M, N))
         assert out.intact()
         W = oracle.dequant(codes, s, z)
@@ -239,6 +242,21 @@ def test_qlinear_of_a_few_rows_takes_any_zero_exactly(fq, torch, bits, case, zer
     err = np.abs(host16(out.half(M, N)).astype(np.float64) - r)
     bound = 2.0 ** -11 * np.abs(r) + 1e-6 * size + 2.0 ** -25
     assert np.count_nonzero(err > bound) == 0
+
+
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("M", [1, 5])
+def test_qlinear_of_very_long_rows_against_oracle(fq, torch, bits, M):
+    """Rows that neither the decode kernel's LDS nor the few-row kernel's offsets hold: the generic kernel.  Its wavefronts sum
+    8200 groups each in fp32, roundings of 2^-24 of the sum so far that add up to less than 1e-4 of the row's rms."""
+    N, K = 5, (1 << 22) + 128
+    assert fq.fq_qlinear_route(M, N, bits, K)[0] == "generic"
+    w, codes, s, z = make_matrix(fq, 90, N, K, bits)
+    X = fq_synth.activations(91, M, K)
+    out = Guarded(torch, M * N * 2)
+    fq.fq_qlinear(dev(torch, X), w, out=out.half(M, N))
+    assert out.intact()
+    assert qerr(host16(out.half(M, N)), oracle.qlinear(X, oracle.dequant(codes, s, z))) <= TOL
 
 
 def test_qlinear_tile_rejects_other_tile_heights(fq, torch):
@@ -646,10 +664,8 @@ def build_selected_stack(fq, hidden, ffn, layers, bitvec, seed):
                          ids=["7b_M2048", "13b_M4096", "7b_M1", "13b_M1", "7b_M16"])
 def test_llama_shaped_stack_sampled_rows(fq, torch, model, M, probs):
     """Two blocks at Llama-2 7B / 13B shapes in the launch configuration the benchmark times; rows of the
-    stack are independent, so the oracle runs a sample of them through both blocks.  Sixteen rows of 4096
-    or 11008 elements do not fit the decode kernel's LDS staging: that case takes the row-wise steps as
-    launches of their own, the shared-input linears through the matrix-core kernel and o/down through the
-    generic small-M kernel."""
+    stack are independent, so the oracle runs a sample of them through both blocks.  Sixteen rows take the
+    row-wise steps as launches of their own and all linears through the few-row kernel."""
     sh = fq_synth.MODEL_SHAPES[model]
     L = 2
     bitvec = fq_synth.bit_vector(11, 7 * L, probs=probs)
@@ -824,14 +840,17 @@ def test_gemm_unpack_is_bit_exact_through_an_identity(fq, torch, bits, shape, fr
 
 @pytest.mark.parametrize("fractional", [False, True], ids=["int_zero", "frac_zero"])
 @pytest.mark.parametrize("bits", BITS)
-@pytest.mark.parametrize("M", [1, 16])
-@pytest.mark.parametrize("shape", [(4096, 4096), (11008, 4096), (96, 512), (4096, 11008)], ids=lambda s: "N%d_K%d" % s)
+@pytest.mark.parametrize("M,shape", [(M, s) for M in (1, 16) for s in ((4096, 4096), (11008, 4096), (96, 512), (4096, 11008))] +
+                         [(M, s) for M in (2, 3) for s in ((4096, 512), (5120, 512), (11008, 512), (96, 8064))] + [(2, (96, 8320))],
+                         ids=lambda v: "N%d_K%d" % v if isinstance(v, tuple) else "M%d" % v)
 def test_gemv_unpack_is_bit_exact_on_one_hot_rows(fq, torch, bits, M, shape, fractional):
-    """One-hot activations: the decode kernel must return single dequantized weights rounded once to fp16
-    (bias, group exponent and zero all leave exactly).  4096 x 4096 at 2 and 3 bits runs the sub-block work
-    units, the other shapes whole supertile rows; the positions walk through all 128 places of a group and
-    through different groups."""
+    """One-hot activations: up to three rows the decode kernel, at sixteen the few-row kernel must return single
+    dequantized weights rounded once to fp16 (bias, group exponent and zero all leave exactly).  4096 rows of weights at
+    2 and 3 bits run the smallest work units of the decode kernel, 5120 at 3 bits halves, 11008 whole supertile rows, each
+    with its body for one activation row and for several; long rows of 4 bits have a body of their own.  The positions
+    walk through all 128 places of a group and through different groups."""
     N, K = shape
+    assert fq.fq_qlinear_route(M, N, bits, K)[0] == ("stream" if M <= 3 else "few_rows")
     w, W32 = _random_packing(fq, 950 + bits, N, K, bits, fractional)
     want16 = oracle.round_f16(W32.astype(np.float64))
     G = K // 128
@@ -845,12 +864,12 @@ def test_gemv_unpack_is_bit_exact_on_one_hot_rows(fq, torch, bits, M, shape, fra
 
 
 @pytest.mark.parametrize("bits", BITS)
-@pytest.mark.parametrize("M", [1, 16])
+@pytest.mark.parametrize("M", [1, 2, 3, 16])
 @pytest.mark.parametrize("scale", [1e-2, 1e-3, 1e-4, 30.0])
 def test_gemv_keeps_its_accuracy_for_small_and_large_activations(fq, torch, bits, M, scale):
-    """The decode kernel stages x times a power of two per bit field; a per-group exponent keeps the staged
-    values normal fp16 numbers, so the 2e-3 bar holds whatever the scale of the activations (fq_qlinear takes
-    any fp16 x), as it does for the matrix-core kernel at M = 17."""
+    """The decode kernel (up to three rows) stages x times a power of two per bit field; a per-group exponent keeps the
+    staged values normal fp16 numbers, so the 2e-3 bar holds whatever the scale of the activations (fq_qlinear
+    takes any fp16 x), as it does for the few-row kernel, which takes x as it is, at M = 16 and 17."""
     N, K = 512, 4096
     w, codes, s, z = make_matrix(fq, 120 + bits, N, K, bits)
     W32 = oracle.dequant(codes, s, z)
@@ -986,11 +1005,12 @@ def test_qlinear_mixed_widths_within_a_matrix(fq, torch, M, case):
 
 
 def test_qlinear_mixed_full_size_sampled(fq, torch):
-    """The benchmark's mixed matrix (4096 rows as 60/30/10 % at 2/3/4 bits, K = 4096) at M = 2048: the launch has
-    a 256-row tile for every compute unit, so the runs go through the 256-row tiles with a row pitch wider
-    than their own N (odd run widths included).  Sampled rows and columns against the oracle; guard bytes."""
-    K, M = 4096, 2048
+    """The benchmark's mixed matrix (4096 rows as 60/30/10 % at 2/3/4 bits, K = 4096) at 1536 rows, where its one launch
+    takes the 256-row tiles, with a row pitch wider than the runs' own N (odd run widths included).  Sampled rows and
+    columns against the oracle; guard bytes."""
+    K, M = 4096, 1536
     runs = [(2433, 2), (1231, 3), (432, 4)]
+    assert fq.fq_qlinear_route(M, [N for N, _ in runs], [b for _, b in runs], K)[0] == "tiles_256"
     rng = np.random.default_rng(17)
     segs, sampled, cols_all, col0 = [], [], [], 0
     for i, (N, bits) in enumerate(runs):

@@ -262,3 +262,16 @@ def test_route_takes_every_size_that_the_linear_takes():
         assert fq._lib.fq_qlinear_route(M, p[0], p[1], count, K, p[2]) == -2
     with pytest.raises(fq.FqError):
         fq.fq_qlinear_route(1, 64, 5, 128)
+
+
+@pytest.mark.parametrize("bits", BITS)
+def test_parity_cases_reach_every_tile_of_the_few_row_kernel(bits):
+    """The tile shapes that the rule chooses over 20000 sizes against those of the GPU test's list of cases."""
+    from test_gpu_parity import SKINNY_CASES
+
+    rng = np.random.default_rng(7)
+    size = lambda lo, hi: int(np.exp(rng.uniform(np.log(lo), np.log(hi))))
+    draws = [(size(3, 3000), size(1, 30000), 128 * size(1, 130)) for _ in range(20000)]
+    reached = {fq.fq_qlinear_route(M, N, bits, K) for M, N, K in draws}
+    assert {r for r in reached if r[0] == "few_rows"} == {fq.fq_qlinear_route(M, N, bits, K) for M, N, K in SKINNY_CASES}
+    assert len({r for r in reached if r[0] == "few_rows"}) == 11
