@@ -139,14 +139,14 @@ int fq_dequant(const void *packed, const void *scales, const void *zeros,
  * fp16 inputs, fp32 accumulation, fp16 output (one rounding).  x fp16 [M,K]
  * row-major and the packed triple: device, read.  out fp16 [M,N] row-major:
  * device, written.  Up to three rows run the bandwidth-bound streaming kernel
- * (decode); from four rows to several hundred (batched decoding, prompts) small
+ * (decode); from there to several hundred (batched decoding, prompts) small
  * tiles whose wavefronts share K; larger M the matrix-core tile kernels (calibration
  * forward).  Any M >= 1, N >= 1.  Scales and zeros may be any finite fp16 (e.g.
  * zero/2^d after truncating d code bits, Section "Elastic Serving").  Up to 16 rows
- * codes and zeros enter exactly, in fp32 sums; for M > 16 the weights are formed in
- * fp16, code - zero and its product with the scale rounded to eleven bits each
- * (exact differences: integer zeros up to 1024, and zero/2^d of the width).  For M > 16 the
- * activations (M*K*2 bytes) and the packed weights must each stay below
+ * (and K up to 2^22) codes and zeros enter exactly, in fp32 sums; beyond, code - zero
+ * is formed in fp16 and may round, and so may its product with the scale (exact
+ * differences: integer zeros up to 1024, and zero/2^d of the width).  For M > 16
+ * the activations (M*K*2 bytes) and the packed weights must each stay below
  * 4 GiB, else FQ_ERR_SHAPE.  Two large-tile kernels exist: 128 activation
  * rows per workgroup, and 256 rows per workgroup of eight wavefronts with the
  * k-steps of every group split over two wavefront sets (each unpacked weight

@@ -44,7 +44,7 @@ int check_matrix(const char *fn, const void *packed, const void *scales, const v
     return FQ_OK;
 }
 
-// The M > 16 kernels address each array through 32-bit byte offsets.
+// The tile kernels (M > 16) address each array through 32-bit byte offsets.
 bool below_4gib(size_t a, size_t b, size_t elem_bytes) { return a * b * elem_bytes < ((size_t)1 << 32); }
 
 int qlinear_checked(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st, int tile_rows = 0)
@@ -56,7 +56,7 @@ int qlinear_checked(const void *x, int M, const fq_packed_ref &w, void *out, fq_
     return check_hip(e, "fq_qlinear launch");
 }
 
-// M > 16: the linears that share an input (q/k/v, gate/up) in one launch.
+// The linears that share an input (q/k/v, gate/up) in one launch of the few-row or a tile kernel.
 int qlinear_multi_checked(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st)
 {
     for (int i = 0; i < count; ++i)
@@ -243,8 +243,7 @@ extern "C" int fq_dense_f16_tile(const void *x, int M, const void *W, int N, int
         return fq_fail(FQ_ERR_SHAPE, "fq_dense_f16_tile: tile_rows=%d not in {0, 128, 256}", tile_rows);
     if (tile_rows == 0 && fq_dense_rows_pays(M, N))
         return check_hip(fq_launch_dense_rows(x, M, W, N, K, out, static_cast<fq_stream>(stream)), "fq_dense_f16 launch");
-    const bool tiled = tile_rows ? tile_rows == 256 : fq_dense_tiled_pays(M, N);
-    if (tiled)
+    if (tile_rows != 128) // what the few-row tiles leave is at least half a large tile a CU
         return check_hip(fq_launch_dense_tiled(x, M, W, N, K, out, static_cast<fq_stream>(stream)),
                          "fq_dense_f16 launch");
     return check_hip(fq_launch_dense(x, M, W, N, K, out, static_cast<fq_stream>(stream)), "fq_dense_f16 launch");

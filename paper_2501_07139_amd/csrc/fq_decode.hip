@@ -149,7 +149,7 @@ template <int LO, int HI>
 __device__ __forceinline__ void wait_vm_le(int n)
 {
     if constexpr (LO == HI) {
-        __builtin_amdgcn_s_waitcnt(gemv_wait_vmcnt(LO));
+        __builtin_amdgcn_s_waitcnt(vmcnt_at_most(LO));
     } else {
         constexpr int MID = (LO + HI) / 2;
         if (n <= MID)

@@ -414,7 +414,9 @@ __global__ __launch_bounds__(64) void loss_finish_kernel(LossParts loss, int V, 
 // The few-row tiles pay up to two rounds of them over the chip.  Measured (us; 128-row tiles that read the weights lane by
 // lane and, with the loss, 256-row tiles against these): 32000 x 4096 at 1 row 78 against 54, with the loss 105 against
 // 59; 64 rows 74 / 57, 107 / 61; 128 rows 76 / 63, 110 / 67; 256 rows (two rounds) 113 / 98, 117 / 100; 300 rows (three)
-// 129 / 135, 126 / 133.  20000 x 4096 at 384 rows 103 / 89; 4000 x 5120 at 700 rows 76 / 50.
+// 129 / 135, 126 / 133.  20000 x 4096 at 384 rows 103 / 89; 4000 x 5120 at 700 rows 76 / 50.  The line was drawn where row
+// tiles read the weights again; a single row tile does not, but beyond 65536 columns it goes to the 256-row tiles all the
+// same (70000 x 4096 at one row: 203 us).
 bool fq_dense_rows_pays(int M, int N)
 {
     const int blocks = (M + 15) / 16, rows = blocks > 4 ? 128 : (blocks > 2 ? 64 : 16 * blocks);
@@ -425,10 +427,6 @@ int fq_launch_dense_rows(const void *x, int M, const void *W, int N, int K, void
 {
     return launch_rows(false, x, M, W, N, K, out, LossParts{}, st);
 }
-
-// Large tiles pay from about half a tile per CU on (measured: 128 tiles of 2048 x 4096 already run 12 % faster
-// than 512 tiles of 128 rows); what is smaller goes to the few-row tiles unless the caller pins the height.
-bool fq_dense_tiled_pays(int M, int N) { return (long)((M + DT - 1) / DT) * ((N + DT - 1) / DT) >= 128; }
 
 // x and W are addressed through 32-bit byte offsets (checked by the caller); K is a multiple of 128.
 int fq_launch_dense_tiled(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st)

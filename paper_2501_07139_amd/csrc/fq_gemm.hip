@@ -1,4 +1,4 @@
-// Calibration-forward path: dequant-GEMM for M > 16 rows of activations, and the
+// Calibration-forward path: dequant-GEMM for many rows of activations, and the
 // unquantized fp16 head GEMM.
 //
 // Scoring one candidate hybrid model means a full forward of the calibration

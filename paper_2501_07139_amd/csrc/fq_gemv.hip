@@ -1,5 +1,5 @@
-// Decode path: dequant-GEMV, for one to three rows of activations as the library dispatches it
-// (four rows on are faster in the few-row kernel: see fq_skinny_pays); the bodies take up to sixteen.
+// Decode path: dequant-GEMV for one to four rows of activations (more, and most of three and four, are faster in the
+// few-row kernel: see fq_skinny_pays).  The bodies for several rows fill the operand's sixteen with repeats of the last.
 //
 // The served hybrid model generates one token at a time on a memory-constrained
 // device (FlexQuant, arXiv 2501.07139, Section "Introduction"), so these kernels
@@ -706,13 +706,13 @@ __global__ __launch_bounds__(64 * GNW, 4) void gemv_stream_kernel(const _Float16
 
 typedef void (*GemvKernel)(const _Float16 *, const _Float16 *, const _Float16 *, _Float16 *, int, int, GemvJobs);
 
-// One kernel per input mode, for a single activation row and for up to sixteen.
+// One kernel per input mode, for a single activation row and for several (mode 6, the decode step's, has one only).
 constexpr int GEMV_VARIANTS = 14, GEMV_MAX_PER_CU = 4;
 const GemvKernel gemv_kernels[GEMV_VARIANTS] = {
     gemv_stream_kernel<0, 1>, gemv_stream_kernel<0, 4>, gemv_stream_kernel<1, 1>, gemv_stream_kernel<1, 4>,
     gemv_stream_kernel<2, 1>, gemv_stream_kernel<2, 4>, gemv_stream_kernel<3, 1>, gemv_stream_kernel<3, 4>,
     gemv_stream_kernel<4, 1>, gemv_stream_kernel<4, 4>, gemv_stream_kernel<5, 1>, gemv_stream_kernel<5, 4>,
-    gemv_stream_kernel<6, 1>, gemv_stream_kernel<6, 4>,
+    gemv_stream_kernel<6, 1>, nullptr,
 };
 int gemv_slot(int mode, int M) { return 2 * mode + (M == 1 ? 0 : 1); }
 
@@ -756,6 +756,8 @@ int gemv_prepare_locked(GemvDevice &d, int dev)
         return (int)e;
     for (int slot = 0; slot < GEMV_VARIANTS; ++slot) {
         const GemvKernel kernel = gemv_kernels[slot];
+        if (!kernel)
+            continue;
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)GEMV_MAX_LDS);
         if (e != hipSuccess)
@@ -827,7 +829,7 @@ bool fq_gemv_can_stream(int M, int K, int bits, int mode)
 int fq_launch_gemv_multi(const fq_gemv_input &src, int M, const fq_packed_ref *w, void *const *outs, int count,
                          fq_stream st)
 {
-    if (src.mode < 0 || src.mode > 6)
+    if (src.mode < 0 || src.mode > 6 || !gemv_kernels[gemv_slot(src.mode, M)])
         return (int)hipErrorInvalidValue;
     GemvJobs jobs;
     jobs.count = count;

@@ -31,7 +31,7 @@ bool fq_skinny_pays(int M, const fq_packed_ref *w, int count);
 void fq_skinny_tile(int M, const fq_packed_ref *w, int count, int *rows, int *columns);
 int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st);
 int fq_launch_gemv(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st);
-// Streaming decode kernel: up to three matrices that share their input and K in one launch (M <= 16).
+// Streaming decode kernel: up to three matrices that share their input and K in one launch (M <= 4).
 // The input is x = f(a, b, c), fp16 [M,K] each, with the block's row-wise glue folded in:
 //   mode 0: a   1: rms(a)   2: rms(a+b+c)   3: aux = a+b, rms(aux)   4: rms(silu(a)*b)   5: aux = rms(a+b), rms(aux)
 //   mode 6: silu(a)*b
@@ -68,14 +68,14 @@ void fq_decode_partition_of(unsigned bits4, int ph, int N, int wg, int grid, int
 int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count);
 // tile_rows: 0 lets the library choose, 128 or 256 pins one of the large-tile kernels.
 int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st, int tile_rows = 0);
-// Up to three matrices with the same input (same K) in one launch, M > 16.
+// Up to three matrices with the same input (same K) in one launch; M > 16, or any M for the few-row kernel.
 int fq_launch_gemm_multi(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st,
                          int tile_rows = 0);
-int fq_launch_dense(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
-// The same product with 256 x 256 tiles, both operands through LDS; pays once its tiles fill the chip.
+// Dense fp16 product: tiles of 16 to 128 rows that stream W, and whether they are the library's choice; 256 x 256 tiles, both
+// operands through LDS, for what they leave; 128-row tiles, only where a caller asks for that height.
 bool fq_dense_rows_pays(int M, int N);
 int fq_launch_dense_rows(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
-bool fq_dense_tiled_pays(int M, int N);
+int fq_launch_dense(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
 int fq_launch_dense_tiled(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
 // Head GEMM with the token loss in its epilogue; workspace of fq_head_nll_scratch_bytes(M, V) bytes.
 size_t fq_head_nll_scratch_bytes(int M, int V);

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256) void glue_kernel(const _Float16 *__restrict__ 
     }
 }
 
-// Two consecutive row-wise steps of the block in one pass (M > 16), each rounded to fp16 where the separate
+// Two consecutive row-wise steps of the block in one pass (where they are launches of their own), each rounded to fp16 where the separate
 // kernels would store it, so the values are those of the two calls:
 //   OP 6: aux = a + b,       out = rms(aux)     the residual after the output projection and the FFN's input
 //   OP 7: aux = rms(a + b),  out = rms(aux)     a block's output and the next block's first normalisation

@@ -5,10 +5,10 @@
 // of 128 x 128 would leave most CUs idle (4096 columns are 32 such tiles) and walk all of K one group after another.
 // Here a workgroup owns 16*MB rows x 16*S columns of the output and its eight wavefronts share K: wavefront w takes
 // groups w, w + 8, ...  The wavefronts have nothing to exchange before their partial sums meet in LDS at the end, so
-// there is no barrier in the loop and no operand goes through LDS: weights come as packed chunks (a lane's 32 weights
-// of a group are its operands of four k-steps), activations as operands (sixteen rows by 64 contiguous bytes a load),
-// both straight from global memory into registers, one group ahead.  The activations of a k-step are loaded into
-// the registers that the k-step has just been multiplied from.
+// there is no barrier in the loop.  Weights come as packed chunks (a lane's 32 weights of a group are its operands of
+// four k-steps) straight from global memory into registers, requested when the group before them has been unpacked;
+// activations through a ring of half groups in LDS that is the wavefront's own, filled by direct copies (as operands straight
+// from global memory, consecutive lanes in different rows, they took twice as long).
 //
 // Arithmetic: code - zero in fp16, fp32 sums per group, and the group's scale applied to the sum in fp32; tiles too large
 // for a second set of accumulators scale the weights in fp16 instead, like the large tiles of the calibration
@@ -19,9 +19,7 @@
 
 namespace {
 
-
 constexpr int SNW = 8; // wavefronts per workgroup, each a slice of K
-
 
 struct SkinnyJob {
     const uint32_t *packed;
@@ -228,7 +226,9 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
             f4 p[S][MB], xs = {0.f, 0.f, 0.f, 0.f}; // xs: sum over the group of the lane's activation row
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
-                // the stage's copies are older than at least the COPIES * (H - 1) copies of the stages behind it
+                // The stage's copies are older than the COPIES * (H - 1) copies of the stages behind it.  The loads of
+                // load_w lie between them too but are not counted, so the wait reaches into the next group's weights,
+                // asked for half a turn ago or less.
                 __builtin_amdgcn_sched_barrier(0);
                 __builtin_amdgcn_s_waitcnt(vmcnt_at_most(COPIES * (H - 1)));
                 __builtin_amdgcn_sched_barrier(0);

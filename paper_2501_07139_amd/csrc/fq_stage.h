@@ -148,9 +148,6 @@ __device__ __forceinline__ uint32_t group_max_bits(h8 x)
     return m;
 }
 
-// s_waitcnt immediate: vector-memory loads in flight <= n (n < 64), the other counters left alone
-constexpr int gemv_wait_vmcnt(int n) { return 0x0f70 | (n & 15) | ((n >> 4) << 14); }
-
 } // namespace
 
 #endif
