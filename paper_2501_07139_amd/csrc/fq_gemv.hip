@@ -681,19 +681,25 @@ __global__ __launch_bounds__(64 * GNW, 4) void gemv_stream_kernel(const _Float16
         else
             gemv_body<2, MODE, MV, 2>(job, bj, in, M, K, smem, part, rows);
         break;
-    case 3: {
-        // sub-blocks per unit, in the order of the code: with several rows the halves behind the others (5.2 -> 5.15 us at two
-        // rows and small sizes), with one row in front (7B-shaped decode blocks of 3 bits 2 % slower the other way round)
-        constexpr int S0 = MV == 1 ? 2 : 1, S1 = MV == 1 ? 1 : 4, S2 = MV == 1 ? 4 : 2;
-        const int s = job.split == 0 ? 4 : (job.split == 2 ? 2 : 1);
-        if (s == S0)
-            gemv_body<3, MODE, MV, S0>(job, bj, in, M, K, smem, part, rows);
-        else if (s == S1)
-            gemv_body<3, MODE, MV, S1>(job, bj, in, M, K, smem, part, rows);
-        else
-            gemv_body<3, MODE, MV, S2>(job, bj, in, M, K, smem, part, rows);
+    case 3:
+        // Several rows: the halves behind the others (5.2 -> 5.15 us at two rows and small sizes); one row: in front (7B-shaped
+        // decode blocks of 3 bits are 2 % slower the other way round).
+        if constexpr (MV == 1) {
+            if (job.split == 2)
+                gemv_body<3, MODE, MV, 2>(job, bj, in, M, K, smem, part, rows);
+            else if (job.split)
+                gemv_body<3, MODE, MV, 1>(job, bj, in, M, K, smem, part, rows);
+            else
+                gemv_body<3, MODE, MV, 4>(job, bj, in, M, K, smem, part, rows);
+        } else {
+            if (job.split == 4)
+                gemv_body<3, MODE, MV, 1>(job, bj, in, M, K, smem, part, rows);
+            else if (job.split == 0)
+                gemv_body<3, MODE, MV, 4>(job, bj, in, M, K, smem, part, rows);
+            else
+                gemv_body<3, MODE, MV, 2>(job, bj, in, M, K, smem, part, rows);
+        }
         break;
-    }
     case 4:
         if (K >= 8192)
             gemv_body<4, MODE, MV, 1, 4>(job, bj, in, M, K, smem, part, rows);
