@@ -145,7 +145,8 @@ int fq_dequant(const void *packed, const void *scales, const void *zeros,
  * zero/2^d after truncating d code bits, Section "Elastic Serving").  Up to 16 rows
  * (and K up to 2^22) codes and zeros enter exactly, in fp32 sums; beyond, code - zero
  * is formed in fp16 and may round, and so may its product with the scale (exact
- * differences: integer zeros up to 1024, and zero/2^d of the width).  For M > 16
+ * differences: integer zeros up to 1024, and zero/2^d of the width; integers above
+ * 64000 overflow there).  For M > 16
  * the activations (M*K*2 bytes) and the packed weights must each stay below
  * 4 GiB, else FQ_ERR_SHAPE.  Two large-tile kernels exist: 128 activation
  * rows per workgroup, and 256 rows per workgroup of eight wavefronts with the
