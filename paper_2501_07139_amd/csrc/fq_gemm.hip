@@ -638,7 +638,11 @@ int tall_tiles(int M, int N) { return ((N + TBN - 1) / TBN) * ((M + TBM - 1) / T
 // than in tall tiles wherever there are 256 of them, the rule without rounds (56 were), and on average they are 8 %
 // faster.  From 4096 rows on, the 128 x 256 tiles of 2- and 4-bit matrices run several full rounds and are level or
 // 2-6 % ahead of the tall ones, so launches made of such matrices only stay with them.
-int choose_tile_rows(int M, const fq_packed_ref *w, int count)
+//
+// us: the time that the choice is expected to take.  Up to 256 tiles, one a CU: 5.4 us and 1.31 us a group of 128 k; up to 512,
+// 1.5 us (3 bits 1.8) a group and more the more CUs have two; beyond, the rounds above and 6 us (tall tiles 3), on rows
+// shorter than 4096 up to 6 more.  Over 900 sizes (see skinny_plan) the time is 0.9 to 1.25 of this from K = 1500 on.
+int choose_tile_rows(int M, const fq_packed_ref *w, int count, double *us)
 {
     static const double full128[9] = {0, 0, 63, 73, 67, 0, 0, 0, 73}, full256[9] = {0, 0, 61, 67, 63, 0, 0, 0, 66};
     long tiles = 0, tall = 0;
@@ -652,7 +656,12 @@ int choose_tile_rows(int M, const fq_packed_ref *w, int count)
         f256 += t * full256[w[i].bits];
         all_wide = all_wide && (w[i].bits == 2 || w[i].bits == 4) && wide_tiles_pay(M, w[i].N);
     }
-    if (M <= 128 || tiles <= 256 || all_wide)
+    const int G = w[0].K >> 7;
+    double three = 0.0;
+    for (int i = 0; i < count; ++i)
+        three = w[i].bits == 3 ? 0.3 : three;
+    *us = 5.4 + G * (tiles <= 256 ? 1.31 : 1.5 + three + 0.7 * (tiles - 256) / 256.0);
+    if (tiles <= 256)
         return 128;
     f128 /= tiles;
     f256 /= tiles;
@@ -661,7 +670,13 @@ int choose_tile_rows(int M, const fq_packed_ref *w, int count)
     const double t256 = (tall / 256) * f256 + (r256 == 0 ? 0.0 : 50.0 + 10.0 * r256 / 256);
     const double length = w[0].K / 4096.0; // of the rows, in those that the figures above were taken with
     const double fixed256 = length < 1.0 ? 1.5 * (1.0 - length) * (tall / 256 + (r256 != 0)) : 0.0;
-    return t256 * length + fixed256 < t128 * length ? 256 : 128;
+    const double brief = length < 1.0 ? 6.0 * (1.0 - length) : 0.0;
+    if (M > 128 && !all_wide && t256 * length + fixed256 < t128 * length) {
+        *us = 3.0 + t256 * length + fixed256 + brief;
+        return 256;
+    }
+    *us = tiles <= 512 ? *us + brief : 6.0 + t128 * length + brief;
+    return 128;
 }
 
 template <int BITS, int QNB>
@@ -709,11 +724,14 @@ static int launch_tall(const void *x, int M, const fq_packed_ref *w, void *const
 }
 
 // Up to sixteen rows (the linears of a stack forward, which has no use for the streaming kernel then) the few-row kernel
-// serves every launch whose offsets it can hold.
+// serves every launch whose offsets it can hold; beyond, the launches for which it is expected to be the faster one
+// (measured in us: 77 rows of 4096 x 11008 at 3 bits 18 against 109, 300 35 against 116, 611 69 against 117; 300 of 11008 x 4096 45 against 50, 611 83
+// against 57).
 int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count)
 {
-    const int rows = choose_tile_rows(M, w, count);
-    if (rows == 128 && (M <= 16 ? fq_skinny_can(M, w[0].K) : fq_skinny_pays(M, w, count)))
+    double us = 0.0;
+    const int rows = choose_tile_rows(M, w, count, &us);
+    if (fq_skinny_can(M, w[0].K) && (M <= 16 || fq_skinny_us(M, w, count) < 0.97 * us))
         return 0;
     return rows;
 }

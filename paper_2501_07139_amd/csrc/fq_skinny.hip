@@ -10,10 +10,12 @@
 // activations through a ring of half groups in LDS that is the wavefront's own, filled by direct copies (as operands straight
 // from global memory, consecutive lanes in different rows, they took twice as long).
 //
-// Arithmetic: code - zero in fp16, fp32 sums per group, and the group's scale applied to the sum in fp32; tiles too large
-// for a second set of accumulators scale the weights in fp16 instead, like the large tiles of the calibration
-// forward.  Tiles of sixteen rows, which decoding uses, multiply the codes and take the zero from the group's sum in fp32
-// (see ZERO_APART).  Sums over the wavefronts in a fixed order.
+// Two bodies: tiles of 16 or 32 columns, or of sixteen rows (skinny_tile), and tiles of 64 columns and two to eight blocks of sixteen rows
+// (skinny_wide_tile), which unpack a weight once for all of them.
+//
+// Arithmetic: code - zero in fp16, fp32 sums per group, and the group's scale applied to the sum in fp32.  Tiles of sixteen
+// rows, which decoding uses, multiply the codes and take the zero from the group's sum in fp32 (see ZERO_APART).  Sums over
+// the wavefronts in a fixed order.
 #include "fq_device.h"
 #include "fq_internal.h"
 
@@ -32,46 +34,60 @@ struct SkinnyJobs {
     int count, total;
 };
 
-// The packed dwords of S consecutive sixteen-row sub-blocks of group g.  S divides 4 and the rows of a matrix are padded
-// to 64, so every sub-block exists.  packed: descriptor of the supertile rows from the one that holds the first sub-block;
-// part: the first sub-block's place in it.
+// The packed dwords of S consecutive sixteen-row sub-blocks of group g, in the order that skinny_chunk expects.  S divides 4
+// and the rows of a matrix are padded to 64, so every sub-block exists.  packed: descriptor of the supertile rows from the
+// one that holds the first sub-block; part: the first sub-block's place in it.
 template <int BITS, int S>
-__device__ __forceinline__ void skinny_load(fq_rsrc packed, int part, int G, int g, int lane, uint32_t (&C)[S][BITS])
+__device__ __forceinline__ void skinny_load(fq_rsrc packed, int part, int G, int g, int lane, uint32_t (&w)[S * BITS])
 {
-    constexpr int SUB = Fmt<BITS>::SUB, TILE = tile_dwords<BITS>() * 4;
-    constexpr int PER = S < SUB ? S : SUB; // sub-blocks taken from one supertile
+    constexpr int SUB = Fmt<BITS>::SUB, TILE = tile_dwords<BITS>() * 4, PLANES = Fmt<BITS>::PLANES;
+    const uint32_t lo = (uint32_t)lane * 16u;
+    if constexpr (S >= SUB) { // whole planes: a lane's dwords of a supertile are consecutive over them
 #pragma unroll
-    for (int t = 0; t < S / PER; ++t) {
-        const uint32_t off = (uint32_t)(t * G + g) * (uint32_t)TILE;
-        if constexpr (SUB == 1) {
-            buf_load_chunk<BITS>(packed, off, 0, lane, C[t]);
-        } else if constexpr (PER == SUB) { // whole planes: the sub-blocks' dwords are consecutive in a lane's run over them
-            u4v pl[Fmt<BITS>::PLANES];
+        for (int t = 0; t < S / SUB; ++t)
 #pragma unroll
-            for (int p = 0; p < Fmt<BITS>::PLANES; ++p)
-                pl[p] = buf_load_b128(packed, (uint32_t)lane * 16u + 1024u * p, off);
-#pragma unroll
-            for (int j = 0; j < SUB * BITS; ++j) {
-                const u4v v = pl[j >> 2];
-                C[t * PER + j / BITS][j % BITS] = (j & 3) == 0 ? v.x : ((j & 3) == 1 ? v.y : ((j & 3) == 2 ? v.z : v.w));
+            for (int p = 0; p < PLANES; ++p) {
+                const u4v v = buf_load_b128(packed, lo + 1024u * p, (uint32_t)(t * G + g) * (uint32_t)TILE);
+                w[4 * (PLANES * t + p)] = v.x;
+                w[4 * (PLANES * t + p) + 1] = v.y;
+                w[4 * (PLANES * t + p) + 2] = v.z;
+                w[4 * (PLANES * t + p) + 3] = v.w;
             }
-        } else {
-#pragma unroll
-            for (int u = 0; u < PER; ++u)
-                buf_load_chunk<BITS>(packed, off, part + u, lane, C[u]);
-        }
+    } else if constexpr (BITS == 3 && S == 2) { // dwords 0..5 or 6..11: a whole plane and half of the middle one
+        const u4v v = buf_load_b128(packed, lo + (part == 0 ? 0u : 2048u), (uint32_t)g * (uint32_t)TILE);
+        const u2v q = buf_load_b64(packed, lo + (part == 0 ? 1024u : 1032u), (uint32_t)g * (uint32_t)TILE);
+        w[0] = v.x;
+        w[1] = v.y;
+        w[2] = v.z;
+        w[3] = v.w;
+        w[4] = q.x;
+        w[5] = q.y;
+    } else {
+        buf_load_chunk<BITS>(packed, (uint32_t)g * (uint32_t)TILE, part, lane, w);
     }
 }
 
-// The four k-steps' operands of a chunk: code - zero in fp16, times the scale if SCALED (see unpack_khalf).
-template <int BITS, bool INTZ, bool SCALED>
-__device__ __forceinline__ void skinny_unpack(const uint32_t (&C)[BITS], h2 zero2, h2 scale2, h8 (&a)[4])
+// Sub-block u's dwords.
+template <int BITS, int S>
+__device__ __forceinline__ void skinny_chunk(const uint32_t (&w)[S * BITS], int part, int u, uint32_t (&C)[BITS])
 {
-    UnpackConsts<BITS> uc; // afresh: what the two forms share would be taken out of them, ahead of the branch
-    uc.init();
+#pragma unroll
+    for (int i = 0; i < BITS; ++i) {
+        const int at = u * BITS + i;
+        if constexpr (BITS == 3 && S == 2)
+            C[i] = part == 0 ? w[at] : w[(at + 4) % 6];
+        else
+            C[i] = w[at];
+    }
+}
+
+// The four k-steps' operands of a chunk: code - zero in fp16 (see unpack_khalf).
+template <int BITS, bool INTZ>
+__device__ __forceinline__ void skinny_unpack(const uint32_t (&C)[BITS], h2 zero2, const UnpackConsts<BITS> &uc, h8 (&a)[4])
+{
     h8 lo[2], hi[2];
-    unpack_khalf<BITS, INTZ, SCALED, 0>(C, zero2, scale2, uc, lo);
-    unpack_khalf<BITS, INTZ, SCALED, 1>(C, zero2, scale2, uc, hi);
+    unpack_khalf<BITS, INTZ, false, 0>(C, zero2, h2{}, uc, lo);
+    unpack_khalf<BITS, INTZ, false, 1>(C, zero2, h2{}, uc, hi);
     a[0] = lo[0];
     a[1] = lo[1];
     a[2] = hi[0];
@@ -88,24 +104,62 @@ __device__ __forceinline__ h4 row16_bcast(u2v v)
     return __builtin_bit_cast(h4, all);
 }
 
+// Partial sums of RED blocks of 16 x 16 at a time go through LDS.
+template <int MB, int S>
+struct SkinnyRed { static constexpr int N = MB * S <= 16 ? MB * S : (MB * S % 16 == 0 ? 16 : (MB * S % 14 == 0 ? 14 : (MB * S % 12 == 0 ? 12 : 10))); };
+
+// The sums of the wavefronts, in a fixed order, and the store.
+template <int MB, int S>
+__device__ __forceinline__ void skinny_store(h8 *smem, const f4 (&acc)[S][MB], int M, int G, const SkinnyJob &job, int m0, int sb0)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, c = lane >> 4;
+    // The partial sums take the rings' memory: every wavefront's copies have to land first.
+    __builtin_amdgcn_s_waitcnt(FQ_WAIT_VMCNT0);
+    // block (u, j): lane holds m = 16j + lane%16 and n = 16u + 4*(lane/16) + v; four values at once where every row of
+    // the output (a column range of a wider array when ld > N) starts 8-byte aligned
+    const bool vec_ok = (job.ld & 3) == 0 && (reinterpret_cast<uintptr_t>(job.out) & 7) == 0;
+    const int waves = min(SNW, G);
+    constexpr int RED = SkinnyRed<MB, S>::N;
+    f4 *red = reinterpret_cast<f4 *>(smem);
+    static_assert(MB * S % RED == 0);
+    static_for<MB * S / RED>([&](auto pass_tag) {
+        constexpr int first = decltype(pass_tag)::value * RED; // block b = u * MB + j
+        __syncthreads();
+        static_for<RED>([&](auto b_tag) {
+            constexpr int b = decltype(b_tag)::value, u = (first + b) / MB, j = (first + b) % MB;
+            red[(wave * RED + b) * 64 + lane] = acc[u][j];
+        });
+        __syncthreads();
+        for (int b = wave; b < RED; b += SNW) {
+            f4 sum = red[b * 64 + lane];
+            for (int v = 1; v < waves; ++v)
+                sum += red[(v * RED + b) * 64 + lane];
+            const int m = m0 + 16 * ((first + b) % MB) + r, n = 16 * (sb0 + (first + b) / MB) + 4 * c;
+            if (m >= M)
+                continue;
+            _Float16 *o = job.out + (size_t)m * job.ld + n;
+            if (n + 3 < job.N && vec_ok) {
+                *reinterpret_cast<h4 *>(o) = h4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (n + v < job.N)
+                        o[v] = (_Float16)sum[v];
+            }
+        }
+    });
+}
+
 // Activation stages of half a group (two k-steps, 128 bytes a row) that a wavefront keeps in LDS.
 template <int MB>
 struct SkinnyRing { static constexpr int H = MB <= 2 ? 4 : 2, STAGE = 16 * MB * 8; }; // STAGE: 16-byte slots
 
-// LDS in 16-byte slots: the wavefronts' rings, and later the partial sums.
-template <int MB, int S>
-constexpr int skinny_slots()
-{
-    constexpr int ring = SNW * SkinnyRing<MB>::H * SkinnyRing<MB>::STAGE, red = SNW * MB * S * 64;
-    return ring > red ? ring : red;
-}
-
-// One tile of 16*MB rows x 16*S columns.
+// A tile of 16*MB rows x 16*S columns: S <= 2, or sixteen rows.
 template <int BITS, int MB, int S>
 __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict__ x, int M, int K, const SkinnyJob job,
                                             int tile, int row_tiles)
 {
-    constexpr bool F32 = S < 4 || MB == 1; // scale applied to the group's sums in fp32
     // Zeros leave through the group's sums, sum code x - zero sum x, so that any fp16 zero is exact, as in the decode kernel
     // (2048 x 2048, 16 rows at 2 bits, error over the rms of the result: 2.06e-4, the output's own rounding; with code - zero
     // in fp16 2.3e-4 for fractional zeros and 4.0e-4 for odd ones beyond 1024).  sum x is one more matrix product, of rows
@@ -152,9 +206,9 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, dst + 64 * i, 16, xoff[i], off, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         };
-        uint32_t w[S][BITS];
-        h4 sc[S];              // F32: scales of the rows 4c..4c+3, whose sums the lane holds
-        uint32_t ss[S], zr[S]; // scale (not F32) and zero of the row r, whose weights the lane unpacks
+        uint32_t w[S * BITS];
+        h4 sc[S];       // scales of the rows 4c..4c+3, whose sums the lane holds
+        uint32_t zr[S]; // zero of the row r, whose weights the lane unpacks
         // ZERO_APART: scales and zeros of the rows 4c..4c+3 of two sub-blocks in one load: all lanes of one c need the same
         // eight bytes of each, so lanes r / 4 = 0, 1, 2, 3 take scales and zeros of the first, then of the second, and
         // the others get them by broadcasts within the sixteen lanes (21085 x 1024 at 2 bits, 6 rows: 9.3 us with a load for
@@ -180,10 +234,7 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
             for (int u = 0; u < S; ++u) {
                 const uint32_t at = (uint32_t)(u * G + g) * 32u;
                 zr[u] = buf_load_u16(zeros, 2u * (uint32_t)r, at);
-                if constexpr (F32)
-                    sc[u] = __builtin_bit_cast(h4, buf_load_b64(scales, 8u * (uint32_t)c, at));
-                else
-                    ss[u] = buf_load_u16(scales, 2u * (uint32_t)r, at);
+                sc[u] = __builtin_bit_cast(h4, buf_load_b64(scales, 8u * (uint32_t)c, at));
             }
         };
         load_w(0);
@@ -199,8 +250,12 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
             float scf[S][4], zf[S][4];
             static_for<S>([&](auto u_tag) {
                 constexpr int u = decltype(u_tag)::value;
+                uint32_t C[BITS];
+                skinny_chunk<BITS, S>(w, sb0 % SUB, u, C);
+                UnpackConsts<BITS> uc; // afresh: what the two forms share would be taken out of them, ahead of the branch
+                uc.init();
                 if constexpr (ZERO_APART) {
-                    skinny_unpack<BITS, true, !F32>(w[u], h2{0, 0}, h2{}, a[u]); // the codes themselves
+                    skinny_unpack<BITS, true>(C, h2{0, 0}, uc, a[u]); // the codes themselves
                     const h4 s4 = row16_bcast<8 * (u & 1)>(meta[u / 2]), z4 = row16_bcast<8 * (u & 1) + 4>(meta[u / 2]);
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
@@ -208,18 +263,16 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
                         zf[u][v] = (float)z4[v];
                     }
                 } else {
-                    const h2 z2 = as_h2(zr[u] * 0x10001u), s2 = F32 ? h2{} : as_h2(ss[u] * 0x10001u);
+                    const h2 z2 = as_h2(zr[u] * 0x10001u);
                     const _Float16 z = z2[0];
                     // integer zeros (what the quantizer produces): bias and zero leave in one addition
                     if (__builtin_amdgcn_ballot_w64(z != __builtin_truncf16(z)) == 0)
-                        skinny_unpack<BITS, true, !F32>(w[u], z2, s2, a[u]);
+                        skinny_unpack<BITS, true>(C, z2, uc, a[u]);
                     else
-                        skinny_unpack<BITS, false, !F32>(w[u], z2, s2, a[u]);
-                    if constexpr (F32) {
+                        skinny_unpack<BITS, false>(C, z2, uc, a[u]);
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            scf[u][v] = (float)sc[u][v];
-                    }
+                    for (int v = 0; v < 4; ++v)
+                        scf[u][v] = (float)sc[u][v];
                 }
             });
             load_w(t + 1);
@@ -244,12 +297,8 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
 #pragma unroll
                     for (int u = 0; u < S; ++u)
 #pragma unroll
-                        for (int j = 0; j < MB; ++j) {
-                            if constexpr (F32)
-                                p[u][j] = mfma16x16x32(a[u][2 * half + s], xf[s][j], (half | s) == 0 ? f4{0.f, 0.f, 0.f, 0.f} : p[u][j]);
-                            else
-                                acc[u][j] = mfma16x16x32(a[u][2 * half + s], xf[s][j], acc[u][j]);
-                        }
+                        for (int j = 0; j < MB; ++j)
+                            p[u][j] = mfma16x16x32(a[u][2 * half + s], xf[s][j], (half | s) == 0 ? f4{0.f, 0.f, 0.f, 0.f} : p[u][j]);
                 if constexpr (ZERO_APART) {
                     const _Float16 one = 1;
 #pragma unroll
@@ -260,50 +309,205 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
                 __builtin_amdgcn_s_waitcnt(FQ_WAIT_LGKMCNT0); // the operands have left the slot
                 copy(2 * t + half + H);
             }
-            if constexpr (F32) {
 #pragma unroll
-                for (int u = 0; u < S; ++u)
+            for (int u = 0; u < S; ++u)
 #pragma unroll
-                    for (int j = 0; j < MB; ++j)
+                for (int j = 0; j < MB; ++j)
 #pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            acc[u][j][v] = fmaf(scf[u][v], ZERO_APART ? fmaf(-zf[u][v], xs[v], p[u][j][v]) : p[u][j][v], acc[u][j][v]);
-            }
+                    for (int v = 0; v < 4; ++v)
+                        acc[u][j][v] = fmaf(scf[u][v], ZERO_APART ? fmaf(-zf[u][v], xs[v], p[u][j][v]) : p[u][j][v], acc[u][j][v]);
         }
     }
 
-    // The partial sums take the rings' memory: every wavefront's copies have to land first.
-    __builtin_amdgcn_s_waitcnt(FQ_WAIT_VMCNT0);
-    __syncthreads();
-    f4 *red = reinterpret_cast<f4 *>(smem);
+    skinny_store<MB, S>(smem, acc, M, G, job, m0, sb0);
+}
+
+// A tile of 16*MB rows x 64 columns, MB = 2 .. 8.  An unpacked operand feeds MB products and an activation four, and the largest
+// tiles make one round over the chip of what takes two or three of the smaller ones (4096 columns: up to 512 rows; 11008: up
+// to 128).  Bound by what the wavefronts issue: 300 x 4096 x 11008 at 2 bits 37 us in tiles of 80 rows, 21 of them without the
+// copies, the weight loads, the unpack and the scales (48 rows: 51).  A stage of the ring is sixteen rows of one group, so that it takes the same memory for
+// every MB, and the scale is applied to the group's sums in fp32, block by block.
+constexpr int WIDE_H = 4, WIDE_STAGE = 256, WIDE_COPIES = 4; // stages, 16-byte slots of one, copies that fill one
+constexpr int META_TURNS = 4, META_SLOTS = 16;               // scales and zeros of a turn: 256 bytes
+
+template <int BITS, int MB>
+__device__ __forceinline__ void skinny_wide_tile(h8 *smem, const _Float16 *__restrict__ x, int M, int K, const SkinnyJob job,
+                                            int tile, int row_tiles)
+{
+    constexpr int S = 4, H = WIDE_H, STAGE = WIDE_STAGE, COPIES = WIDE_COPIES;
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, c = lane >> 4;
+    const int G = K >> 7;
+    const int m0 = (tile % row_tiles) * (16 * MB), sb0 = (tile / row_tiles) * S;
+    // descriptors of what the tile reads of the matrix: S sub-blocks of every group
+    constexpr int SUB = Fmt<BITS>::SUB, TILE = tile_dwords<BITS>();
+    const fq_rsrc packed = make_rsrc(job.packed + (size_t)(sb0 / SUB) * G * TILE, (uint32_t)((S + SUB - 1) / SUB * G) * (TILE * 4u));
+
+    f4 acc[S][MB];
 #pragma unroll
     for (int u = 0; u < S; ++u)
 #pragma unroll
         for (int j = 0; j < MB; ++j)
-            red[((wave * S + u) * MB + j) * 64 + lane] = acc[u][j];
-    __syncthreads();
-    // block (u, j): lane holds m = 16j + lane%16 and n = 16u + 4*(lane/16) + v; four values at once where every row of
-    // the output (a column range of a wider array when ld > N) starts 8-byte aligned
-    const bool vec_ok = (job.ld & 3) == 0 && (reinterpret_cast<uintptr_t>(job.out) & 7) == 0;
-    const int waves = min(SNW, G);
-    for (int b = wave; b < S * MB; b += SNW) {
-        f4 sum = red[b * 64 + lane];
-        for (int w = 1; w < waves; ++w)
-            sum += red[(w * S * MB + b) * 64 + lane];
-        const int m = m0 + 16 * (b % MB) + r, n = 16 * (sb0 + b / MB) + 4 * c;
-        if (m >= M)
-            continue;
-        _Float16 *o = job.out + (size_t)m * job.ld + n;
-        if (n + 3 < job.N && vec_ok) {
-            *reinterpret_cast<h4 *>(o) = h4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
-        } else {
+            acc[u][j] = f4{0.f, 0.f, 0.f, 0.f};
+
+    if (wave < G) { // uniform over the wavefront
+        // Copies, global memory straight into the ring: copy i of a stage fills rows 4i .. 4i + 3, slot (row, pos) with
+        // chunk pos ^ row of the row's sixteen, so that the operand reads below touch every bank once.  The row is
+        // part of the lane offset, which the descriptor's range check covers: rows past M read as zero and are not stored.
+        h8 *const ring = smem + wave * (H * STAGE);
+        const fq_rsrc xr = make_rsrc(x, (uint32_t)M * (uint32_t)K * 2u);
+        uint32_t xoff[COPIES];
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (n + v < job.N)
-                    o[v] = (_Float16)sum[v];
+        for (int i = 0; i < COPIES; ++i) {
+            const int row = 4 * i + c;
+            xoff[i] = ((uint32_t)(m0 + row) * (uint32_t)K + 8u * (uint32_t)(r ^ row)) * 2u;
+        }
+        const int turns = (G - wave + SNW - 1) / SNW; // groups of this wavefront
+        int nt = 0, nj = 0, ns = 0;                   // group, row block and slot of the next copy
+        auto copy = [&]() { // past the end: the last group's rows again, into a stage that is not read any more
+            const uint32_t off = (uint32_t)(wave + SNW * min(nt, turns - 1)) * 256u;
+            uint32_t down = (uint32_t)nj * (32u * (uint32_t)K);
+            asm volatile("" : "+s"(down)); // added here: the sums of all row blocks would be kept in registers
+            h8 *dst = ring + ns * STAGE;
+#pragma unroll
+            for (int i = 0; i < COPIES; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, dst + 64 * i, 16, xoff[i] + down, off, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            ns = (ns + 1) & (H - 1);
+            if (++nj == MB) {
+                nj = 0;
+                ++nt;
+            }
+        };
+        uint32_t w[S * BITS];
+        // Scales and zeros of the S sub-blocks, one copy of a dword a lane: sub-block u's sixteen scales and sixteen zeros
+        // at bytes 64u and 64u + 32 of the turn's slots.
+        char *const metas = reinterpret_cast<char *>(smem + SNW * H * STAGE + wave * (META_TURNS * META_SLOTS));
+        const char *const meta_lane = reinterpret_cast<const char *>((lane & 8) ? job.zeros : job.scales) +
+                                      ((size_t)(sb0 + min(lane >> 4, S - 1)) * G * 32 + 4 * (lane & 7));
+        auto load_w = [&](int t) { // past the end: the last group again (nobody uses it)
+            const int g = min(wave + SNW * t, G - 1);
+            skinny_load<BITS, S>(packed, sb0 % SUB, G, g, lane, w);
+            __builtin_amdgcn_global_load_lds(meta_lane + (size_t)g * 32, metas + (t % META_TURNS) * (META_SLOTS * 16), 4, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        load_w(0);
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+            copy();
+        int rd[4]; // slot of operand (row r, k-step s) in a stage
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            rd[s] = r * 16 + ((4 * s + c) ^ r);
+        int slot = 0; // of the stage whose operands are read next
+        constexpr bool ROOM = MB <= 5; // registers for operands one stage ahead and for the scales
+        h8 xf[ROOM ? 2 : 1][4];
+        auto read = [&](h8 (&to)[4]) {
+            // Loads complete in the order they were issued, and the copies of H - 1 stages are younger than this one's.  The
+            // loads of load_w may be among them but are not counted (how many they are is the compiler's affair): the
+            // wait then reaches a little further than it has to.
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(vmcnt_at_most(COPIES * (H - 1)));
+            __builtin_amdgcn_sched_barrier(0);
+            const h8 *stage = ring + slot * STAGE;
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                to[s] = stage[rd[s]];
+            slot = (slot + 1) & (H - 1);
+        };
+        for (int t = 0; t < turns; ++t) {
+            read(xf[0]);
+            // the turn's scales and zeros, issued a turn ago: a turn's copies are younger (at the start, H stages')
+            __builtin_amdgcn_s_waitcnt(vmcnt_at_most(COPIES * (MB < H ? MB : H)));
+            __builtin_amdgcn_sched_barrier(0);
+            const char *const meta = metas + (t % META_TURNS) * (META_SLOTS * 16);
+            h8 a[S][4];
+            h4 scales[S]; // of the rows 4c..4c+3, whose sums the lane holds
+            uint32_t C[S][BITS];
+            h2 z2[S];
+            bool frac = false;
+#pragma unroll
+            for (int u = 0; u < S; ++u) {
+                skinny_chunk<BITS, S>(w, sb0 % SUB, u, C[u]);
+                if constexpr (ROOM)
+                    scales[u] = *reinterpret_cast<const h4 *>(meta + 64 * u + 8 * c);
+                const _Float16 z = *reinterpret_cast<const _Float16 *>(meta + 64 * u + 32 + 2 * r); // of the row r, whose weights the lane unpacks
+                z2[u] = h2{z, z};
+                frac |= z != __builtin_truncf16(z);
+            }
+            // integer zeros (what the quantizer produces): bias and zero leave in one addition
+            if (__builtin_amdgcn_ballot_w64(frac) == 0) {
+                UnpackConsts<BITS> uc; // afresh: what the two forms share would be taken out of them, ahead of the branch
+                uc.init();
+#pragma unroll
+                for (int u = 0; u < S; ++u)
+                    skinny_unpack<BITS, true>(C[u], z2[u], uc, a[u]);
+            } else {
+                UnpackConsts<BITS> uc;
+                uc.init();
+#pragma unroll
+                for (int u = 0; u < S; ++u)
+                    skinny_unpack<BITS, false>(C[u], z2[u], uc, a[u]);
+            }
+            load_w(t + 1);
+            static_for<MB>([&](auto j_tag) {
+                constexpr int j = decltype(j_tag)::value;
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_waitcnt(FQ_WAIT_LGKMCNT0); // the operands have left their stage
+                copy();
+                if constexpr (ROOM && j + 1 < MB)
+                    read(xf[(j + 1) & 1]); // on their way during the products below
+                if constexpr (!ROOM) {
+                    int off = 8 * c;
+                    asm volatile("" : "+v"(off)); // read again: kept over the blocks they would spill
+#pragma unroll
+                    for (int u = 0; u < S; ++u)
+                        scales[u] = *reinterpret_cast<const h4 *>(meta + 64 * u + off);
+                }
+                f4 p[S];
+                __builtin_amdgcn_s_setprio(1); // products ahead of the other wavefront's unpacking
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int u = 0; u < S; ++u)
+                        p[u] = mfma16x16x32(a[u][s], xf[ROOM ? j & 1 : 0][s], s == 0 ? f4{0.f, 0.f, 0.f, 0.f} : p[u]);
+#pragma unroll
+                for (int u = 0; u < S; ++u)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        acc[u][j][v] = fmaf((float)scales[u][v], p[u][v], acc[u][j][v]);
+                __builtin_amdgcn_s_setprio(0);
+                if constexpr (!ROOM && j + 1 < MB)
+                    read(xf[0]);
+            });
         }
     }
+
+    skinny_store<MB, S>(smem, acc, M, G, job, m0, sb0);
 }
+
+// LDS in 16-byte slots: the wavefronts' rings, and later the partial sums.
+template <int MB, int S>
+constexpr int skinny_slots()
+{
+    constexpr int ring = SNW * (MB > 1 && S == 4 ? WIDE_H * WIDE_STAGE + META_TURNS * META_SLOTS : SkinnyRing<MB>::H * SkinnyRing<MB>::STAGE);
+    constexpr int red = SNW * SkinnyRed<MB, S>::N * 64;
+    return ring > red ? ring : red;
+}
+
+template <int BITS, int MB, int S>
+__device__ __forceinline__ void skinny_any(h8 *smem, const _Float16 *__restrict__ x, int M, int K, const SkinnyJob &job, int tile,
+                                           int row_tiles)
+{
+    if constexpr (MB > 1 && S == 4)
+        skinny_wide_tile<BITS, MB>(smem, x, M, K, job, tile, row_tiles);
+    else
+        skinny_tile<BITS, MB, S>(smem, x, M, K, job, tile, row_tiles);
+}
+
+// 8-bit chunks and more than five row blocks are more registers than there are; skinny_plan does not put them together.
+constexpr int WIDEST_8BIT = 5;
 
 template <int MB, int S>
 __global__ __launch_bounds__(64 * SNW, (MB == 1 && S <= 2) ? 4 : 2) void skinny_kernel(const _Float16 *__restrict__ x, int M, int K,
@@ -322,10 +526,13 @@ __global__ __launch_bounds__(64 * SNW, (MB == 1 && S <= 2) ? 4 : 2) void skinny_
         job = jobs.j[2];
     tile -= job.tile0;
     switch (job.bits) {
-    case 2: skinny_tile<2, MB, S>(smem, x, M, K, job, tile, row_tiles); break;
-    case 3: skinny_tile<3, MB, S>(smem, x, M, K, job, tile, row_tiles); break;
-    case 4: skinny_tile<4, MB, S>(smem, x, M, K, job, tile, row_tiles); break;
-    default: skinny_tile<8, MB, S>(smem, x, M, K, job, tile, row_tiles); break;
+    case 2: skinny_any<2, MB, S>(smem, x, M, K, job, tile, row_tiles); break;
+    case 3: skinny_any<3, MB, S>(smem, x, M, K, job, tile, row_tiles); break;
+    case 4: skinny_any<4, MB, S>(smem, x, M, K, job, tile, row_tiles); break;
+    default:
+        if constexpr (MB <= WIDEST_8BIT)
+            skinny_any<8, MB, S>(smem, x, M, K, job, tile, row_tiles);
+        break;
     }
 }
 
@@ -338,85 +545,81 @@ struct SkinnyPlan {
     double us;
 };
 
-// Tile shape for a launch of more than sixteen rows.  The time of a shape, as fitted to measurements at 4096 x 4096, 11008
-// x 4096 and 4096 x 11008, all widths, 1 to 512 rows: a launch costs 2 us, a round of tiles over the chip 1.6 us (3.2
-// us for the largest sums to add up) beside its turns of eight groups, and a turn 0.1 + 0.29 S + 0.34 MB us -- unpacking S
-// sub-blocks and moving MB row blocks of activations add up, the matrix instructions hide behind them.  8-bit chunks
-// are twice the bytes, 3-bit ones that are less than a supertile come in single dwords (0.39 and 0.45 S us).  The
-// smallest shapes leave room for a second workgroup on a CU, so their rounds are not whole ones.  4 x 1 is never ahead
-// of 2 x 2.  The turns take no less than the activations need to reach an XCD's L2 at 0.8 TB/s: with thirty and more row
-// tiles the tiles that an XCD works on share hardly any (2048 rows of 1024 x 2816: 37 us where the turns alone would be 24).
-// Over 2300 sizes of 17 to 3000 rows half the launches are within 9 % of this, a twentieth more than 25 % off.
+// Tile shape for a launch, by estimated time.  More than sixteen rows, fitted to 900 sizes of 17 to 1400 rows, 200 to 27648
+// columns and K = 256 to 13824, every shape that can serve each (half of all times within 7 %; the shape chosen is 0.7 % slower
+// than the best one on average, 15 % at worst):
+//  - 64 columns, 32 rows and more: 2.2 us, 1.9 + 0.48 MB us a round over the chip (larger sums to add up), 0.6 + 0.4 MB us a
+//    turn of eight groups -- unpacking, then the products and the copies of MB blocks (8 bits 0.36 more, 3 bits 0.08).
+//  - 16 and 32 columns: 2.7 us, 1.8 us a round, 0.03 + 0.11 S + 0.29 MB + 0.03 S MB us a turn (8 bits 0.21 S, single dwords
+//    of 3 bits 0.32 S): moving the activations is what a turn takes.
+//  - sixteen rows: as below, 4.4 us and 0.88 of the turns; the smallest leave room for a second workgroup on a CU.
+// The turns take no less than the activations need to reach an XCD's L2 at 0.8 TB/s: with thirty and more row tiles the tiles
+// that an XCD works on share hardly any.  80 rows and more a tile are the choice wherever a round of them takes what would be two of smaller
+// ones: 300 x 4096 x 4096 at 4 bits 23.5 -> 17.5 us, 300 x 4096 x 11008 at 2 bits 48 -> 35, 77 x 11008 x 4096 23.6 -> 17.2, 512
+// x 4096 x 11008 at 2 bits 60 -> 53; up to 1536 rows, from where on the large tiles serve what is left.
 //
 // Up to sixteen rows every shape has one row block and the number of sub-blocks is all there is to choose (it does not change
 // a sum).  Fitted to 2500 sizes of 64 to 24000 columns with each S: 3.4 us and a turn of 0.13 + 0.28 S us (8 bits 0.37 S;
-// 3-bit S < 4: 0.2 + 0.5 S) while every CU has one tile; a second one on some CUs costs nearly a second turn, and from two a
+// 3 bits S = 1 0.7, S = 2 1.2) while every CU has one tile; a second one on some CUs costs nearly a second turn, and from two a
 // CU on the time grows with the tiles.  64 columns a tile just beyond one round (20739 x 1664, 4 bits) 11.3 us, 32 columns 9.8.
 SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
 {
     SkinnyPlan best = {1, 0, 1, 1e30};
     const int blocks = (M + 15) / 16, turns = ((w[0].K >> 7) + SNW - 1) / SNW;
+    bool eight = false;
+    for (int i = 0; i < count; ++i)
+        eight = eight || w[i].bits == 8;
     for (int sl = 0; sl < 3; ++sl) {
         const int S = 1 << sl;
         long col_tiles = 0;
-        double sub = 0.0, one_block = 0.0; // us of a turn: a sub-block's; all of a tile of one row block
+        double one_block = 0.0; // us of a turn of a tile of one row block
         for (int i = 0; i < count; ++i) {
             col_tiles += (w[i].N + 16 * S - 1) / (16 * S);
-            const bool dwords = w[i].bits == 3 && S < 4;
-            const double u = w[i].bits == 8 ? 0.39 : (dwords ? 0.45 : 0.29);
-            sub = sub > u ? sub : u;
-            const double t = dwords ? 0.2 + 0.5 * S : 0.13 + (w[i].bits == 8 ? 0.37 : 0.28) * S;
+            const double t = w[i].bits == 3 && (S == 1 || (S == 2 && blocks == 1)) ? 0.2 + 0.5 * S : 0.13 + (w[i].bits == 8 ? 0.37 : 0.28) * S;
             one_block = one_block > t ? one_block : t;
         }
-        if (blocks == 1) {
-            const double waves = (double)col_tiles / SKINNY_CUS;
-            double fixed = 3.4, factor = 1.0;
-            if (waves > 1.0 && S == 4) {
-                factor = (double)(long)(waves + 0.999);
-                fixed = 2.4 + factor;
-            } else if (waves > 1.0) {
-                factor = S == 1 ? (waves <= 2.0 ? 2.2 : 1.5 * waves) : (waves <= 2.0 ? 1.9 : 1.25 * waves);
-                fixed = 3.1 + 0.3 * waves;
-            }
-            const double us = fixed + factor * turns * one_block;
-            if (us < best.us)
-                best = {1, sl, 1, us};
-            continue;
-        }
-        for (int mb = 1; mb <= (S == 1 ? 3 : 4); ++mb) {
+        const int largest = S == 1 ? 3 : (S == 2 ? 4 : (M > 1536 ? 4 : (eight ? WIDEST_8BIT : 8)));
+        for (int mb = 1; mb <= largest; ++mb) {
             const int row_tiles = (blocks + mb - 1) / mb;
             if ((blocks + row_tiles - 1) / row_tiles != mb)
                 continue; // as many row tiles of fewer blocks do
             const double tiles = (double)row_tiles * (double)col_tiles, waves = tiles / SKINNY_CUS;
-            const double rounds = waves <= 1.0 ? 1.0 : ((mb == 1 && S <= 2) ? 1.15 * waves : (double)(long)(waves + 0.999));
-            const double in_xcd = tiles > 8.0 ? tiles / 8.0 : 1.0; // 32 of them at a time, row-tile fastest
-            const double rows = 16.0 * mb * (row_tiles < 32 ? (row_tiles < in_xcd ? row_tiles : in_xcd) : (in_xcd < 32.0 ? in_xcd : 32.0));
-            const double l2 = (in_xcd > 32.0 ? in_xcd / 32.0 : 1.0) * rows * w[0].K * 2.0 / 0.8e6; // us
-            const double work = rounds * turns * (0.1 + sub * S + 0.34 * mb);
-            const double us = 2.0 + rounds * (S == 4 && mb > 1 ? 3.2 : 1.6) + (work > l2 ? work : l2);
-            if (us < best.us)
-                best = {mb, sl, row_tiles, us};
+            const double whole = waves <= 1.0 ? 1.0 : (double)(long)(waves + 0.999);
+            double fixed, work;
+            if (mb == 1) {
+                double factor = 1.0;
+                fixed = blocks == 1 ? 3.4 : (S == 4 ? 4.6 : 4.4);
+                if (waves > 1.0 && S == 4) {
+                    factor = whole;
+                    fixed += factor - 1.0;
+                } else if (waves > 1.0) {
+                    factor = S == 1 ? (waves <= 2.0 ? 2.2 : 1.5 * waves) : (waves <= 2.0 ? 1.9 : (blocks == 1 ? 1.25 : 1.4) * waves);
+                    fixed += 0.3 * waves - 0.3;
+                }
+                work = factor * turns * one_block * (blocks == 1 ? 1.0 : 0.88);
+            } else {
+                double mean = 0.0, most = 0.0; // us of a turn, over the tiles of the launch
+                for (int i = 0; i < count; ++i) {
+                    const int bits = w[i].bits;
+                    const double t = S == 4 ? 0.6 + 0.4 * mb + (bits == 8 ? 0.36 : (bits == 3 ? 0.08 : 0.0))
+                                            : 0.03 + (bits == 8 ? 0.21 : (bits == 3 && S == 1 ? 0.32 : 0.11)) * S + 0.29 * mb + 0.03 * S * mb;
+                    mean += t * ((w[i].N + 16 * S - 1) / (16 * S)) / (double)col_tiles;
+                    most = most > t ? most : t;
+                }
+                fixed = S == 4 ? 2.2 + whole * (1.9 + 0.48 * mb) : (S == 1 ? 2.4 : 2.7) + 1.8 * whole;
+                work = whole * turns * (whole == 1.0 ? most : mean);
+            }
+            if (blocks > 1) {
+                const double in_xcd = tiles > 8.0 ? tiles / 8.0 : 1.0; // 32 of them at a time, row-tile fastest
+                const double rows = 16.0 * mb * (row_tiles < 32 ? (row_tiles < in_xcd ? row_tiles : in_xcd) : (in_xcd < 32.0 ? in_xcd : 32.0));
+                const double l2 = (in_xcd > 32.0 ? in_xcd / 32.0 : 1.0) * rows * w[0].K * 2.0 / 0.8e6; // us
+                work = work > l2 ? work : l2;
+            }
+            if (fixed + work < best.us)
+                best = {mb, sl, row_tiles, fixed + work};
         }
     }
     return best;
-}
-
-// Time of the 128-row tile kernel on the same launch: 5.4 us and 1.31 us a group of 128 k up to one tile a CU, from 1.5
-// us (3 bits: 1.8) a group on with two on some.  Over 2300 sizes the time is 0.8 to 1.15 of this from K = 1024 on, where at
-// most one tile a CU is there, and 1 to 1.5 below; with more tiles 0.86 to 1.1 from K = 4096 on and up to twice this on short
-// rows, which go to the few-row kernel.
-double tile_kernel_us(int M, const fq_packed_ref *w, int count)
-{
-    long tiles = 0;
-    double three = 0.0;
-    for (int i = 0; i < count; ++i) {
-        tiles += (long)((w[i].N + 127) / 128) * ((M + 127) / 128);
-        three = w[i].bits == 3 ? 0.3 : three;
-    }
-    if (tiles > 2 * SKINNY_CUS)
-        return 0.0; // several rounds of tiles fill the chip: the large tiles are the better ones
-    const double group = tiles <= SKINNY_CUS ? 1.31 : 1.5 + three + 0.7 * (tiles - SKINNY_CUS) / SKINNY_CUS;
-    return 5.4 + (w[0].K >> 7) * group;
 }
 
 } // namespace
@@ -424,19 +627,17 @@ double tile_kernel_us(int M, const fq_packed_ref *w, int count)
 // Whether the kernel's 32-bit byte offsets reach all of a launch's activations and of a tile's weights.
 bool fq_skinny_can(int M, int K) { return K <= (1 << 22) && (size_t)M * K * 2 < ((size_t)1 << 32); }
 
-// Whether a launch goes to the skinny kernel.  Few rows (M <= 16): from four rows on, three of long rows, where the
+// Whether a launch of up to sixteen rows goes to the skinny kernel (more rows: see fq_gemm_tile_rows): from four rows on,
+// three of long rows, where the
 // streaming kernel stages one row after another (4096 x 4096, 4 bits: 7.5 against 5.8 us at 4 rows, 17 against 6.0 at 16; at
 // one row 4.2 against 6.1; 4096 x 11008 at 3 rows 11.3 against 10), and where that kernel has no room for the rows.  Four
 // rows of more columns than one round of the widest tiles covers stay with the streaming kernel unless they are
 // short or long ones (19741 x 1792 at 2 bits 9.2 against 11.0 us, and level on average from 1024 to 8192; below, 0.75 of
-// its time, above 0.9), three also if they are long (21160 x 8192 at 3 bits 22.6 against 25.2).  More rows: where the models above put it ahead of the tile kernel (4096 x 11008, 3 bits: 23 against
-// 109 us at 77 rows, 34 against 116 at 256, 64 against 117 at 512; 1024 x 2816, 2 bits, at 2048 rows 37 against 30).
+// its time, above 0.9), three also if they are long (21160 x 8192 at 3 bits 22.6 against 25.2).
 bool fq_skinny_pays(int M, const fq_packed_ref *w, int count)
 {
     if (!fq_skinny_can(M, w[0].K))
         return false;
-    if (M > 16)
-        return skinny_plan(M, w, count).us < tile_kernel_us(M, w, count);
     const int K = w[0].K;
     long columns = 0;
     for (int i = 0; i < count; ++i)
@@ -448,21 +649,29 @@ bool fq_skinny_pays(int M, const fq_packed_ref *w, int count)
     return !stream;
 }
 
+double fq_skinny_us(int M, const fq_packed_ref *w, int count) { return skinny_plan(M, w, count).us; }
+
 void fq_skinny_tile(int M, const fq_packed_ref *w, int count, int *rows, int *columns)
 {
     const SkinnyPlan plan = skinny_plan(M, w, count);
-    *rows = 16 * plan.mb;
+    *rows = 16 * (plan.mb <= 4 ? plan.mb : (plan.mb + 1) / 2); // more: two tiles, one above the other (see fq.h)
     *columns = 16 << plan.s_log2;
 }
+
+int fq_skinny_blocks(int M, const fq_packed_ref *w, int count) { return skinny_plan(M, w, count).mb; }
 
 // Up to three matrices that share the input (same K), in one launch.
 int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st)
 {
-    static const SkinnyKernel table[4][3] = {
+    static const SkinnyKernel table[8][3] = {
         {skinny_kernel<1, 1>, skinny_kernel<1, 2>, skinny_kernel<1, 4>},
         {skinny_kernel<2, 1>, skinny_kernel<2, 2>, skinny_kernel<2, 4>},
         {skinny_kernel<3, 1>, skinny_kernel<3, 2>, skinny_kernel<3, 4>},
         {nullptr, skinny_kernel<4, 2>, skinny_kernel<4, 4>},
+        {nullptr, nullptr, skinny_kernel<5, 4>},
+        {nullptr, nullptr, skinny_kernel<6, 4>},
+        {nullptr, nullptr, skinny_kernel<7, 4>},
+        {nullptr, nullptr, skinny_kernel<8, 4>},
     };
     const SkinnyPlan plan = skinny_plan(M, w, count);
     SkinnyJobs jobs;

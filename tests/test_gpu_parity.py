@@ -212,6 +212,39 @@ def test_qlinear_few_rows_against_oracle(fq, torch, bits, case):
         assert np.sqrt(np.mean(err ** 2)) <= 4e-4 * np.sqrt(np.mean(r ** 2))
 
 
+# Tiles of 64 columns that take two to eight row blocks at once: (M, N, K) and the blocks; the last row block full, with one row,
+# and with most; columns at and beside a multiple of 64; fewer groups than wavefronts, one turn, a second one for
+# some, several.
+WIDE_CASES = [((30, 11000, 1152), 2), ((48, 11008, 384), 3), ((200, 4096, 1152), 4), ((65, 8200, 1152), 5), ((80, 8250, 1024), 5),
+              ((81, 10001, 1152), 6), ((96, 11008, 1152), 6), ((110, 9100, 1152), 7), ((112, 8300, 2176), 7), ((128, 11008, 1152), 8),
+              ((113, 8200, 3200), 8)]
+
+
+# 8-bit matrices take at most five row blocks
+@pytest.mark.parametrize("bits, case, blocks", [(b, c, n) for c, n in WIDE_CASES for b in BITS if b < 8 or n <= 5],
+                         ids=lambda c: "M%d_N%d_K%d" % c if isinstance(c, tuple) else str(c))
+def test_qlinear_wide_few_row_tiles_against_oracle(fq, torch, bits, case, blocks):
+    """Integer zeros, then fractions in some groups.  Bound: one rounding of the output (2^-11 |r|) and fp32 sums, 1e-6 sum
+    |x||w|; code - zero is exact here and the scale is applied in fp32.  2^-24: subnormal results."""
+    M, N, K = case
+    codes = fq_synth.codes(70, N, K, bits)
+    s = (np.abs(fq_synth.activations(71, N, K // 128).astype(np.float32)) * 0.01 + 1e-3).astype(np.float16)
+    X = fq_synth.activations(72, M, K)
+    assert fq.fq_few_row_blocks(M, N, bits, K) == blocks and fq.fq_qlinear_route(M, N, bits, K)[2] == 64
+    for frac in (0, 1):
+        z = fq_synth.codes(73, N, K // 128, bits).astype(np.float32)
+        if frac:
+            z[::3, ::2] += 0.25
+        z = z.astype(np.float16)
+        out = Guarded(torch, M * N * 2)
+        fq.fq_qlinear(dev(torch, X), fq.PackedMatrix.from_host(codes, s, z, bits), out=out.half(M, N))
+        assert out.intact()
+        W = oracle.dequant(codes, s, z)
+        r, size = oracle.qlinear(X, W), oracle.qlinear(np.abs(X), np.abs(W))
+        err = np.abs(host16(out.half(M, N)).astype(np.float64) - r)
+        assert np.all(err <= 2.0 ** -11 * np.abs(r) + 1e-6 * size + 2.0 ** -24)
+
+
 @pytest.mark.parametrize("zeros", ["fractions", "odd_large", "largest", "negative"])
 @pytest.mark.parametrize("bits", BITS)
 @pytest.mark.parametrize("case", [(1, 300, 1024), (2, 300, 1024), (3, 300, 8320), (4, 70, 128), (4, 300, 2048), (16, 5200, 1152),
