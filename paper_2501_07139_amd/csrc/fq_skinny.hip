@@ -556,7 +556,7 @@ struct SkinnyPlan {
 // The turns take no less than the activations need to reach an XCD's L2 at 0.8 TB/s: with thirty and more row tiles the tiles
 // that an XCD works on share hardly any.  80 rows and more a tile are the choice wherever a round of them takes what would be two of smaller
 // ones: 300 x 4096 x 4096 at 4 bits 23.5 -> 17.5 us, 300 x 4096 x 11008 at 2 bits 48 -> 35, 77 x 11008 x 4096 23.6 -> 17.2, 512
-// x 4096 x 11008 at 2 bits 60 -> 53; up to 1536 rows, from where on the large tiles serve what is left.
+// x 4096 x 11008 at 2 bits 60 -> 53; up to 1280 rows; beyond, an XCD's L2 holds none of the activations that its tiles share (1500 x 4096 x 11008 at 2 bits: 184 against 155).
 //
 // Up to sixteen rows every shape has one row block and the number of sub-blocks is all there is to choose (it does not change
 // a sum).  Fitted to 2500 sizes of 64 to 24000 columns with each S: 3.4 us and a turn of 0.13 + 0.28 S us (8 bits 0.37 S;
@@ -578,7 +578,7 @@ SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
             const double t = w[i].bits == 3 && (S == 1 || (S == 2 && blocks == 1)) ? 0.2 + 0.5 * S : 0.13 + (w[i].bits == 8 ? 0.37 : 0.28) * S;
             one_block = one_block > t ? one_block : t;
         }
-        const int largest = S == 1 ? 3 : (S == 2 ? 4 : (M > 1536 ? 4 : (eight ? WIDEST_8BIT : 8)));
+        const int largest = S == 1 ? 3 : (S == 2 ? 4 : (M > 1280 ? 4 : (eight ? WIDEST_8BIT : 8)));
         for (int mb = 1; mb <= largest; ++mb) {
             const int row_tiles = (blocks + mb - 1) / mb;
             if ((blocks + row_tiles - 1) / row_tiles != mb)
