@@ -303,13 +303,20 @@ int fq_glue(int op, const void *a, const void *b, const void *c, int M, int H, v
  * "Efficient Design Space Navigation") compares; the head is not quantized.
  * x [M,K], W [N,K], out [M,N] row-major, device.  K must be a multiple of 128;
  * x and W must each stay below 4 GiB (FQ_ERR_SHAPE otherwise).  Few rows stream W
- * through narrow tiles (a decode step's logits); 256-row tiles with both operands
+ * through narrow tiles (a decode step's logits), products that would leave CUs idle
+ * go through smaller ones whose wavefronts share K; 256-row tiles with both operands
  * in LDS take over once those fill the chip.  fq_dense_f16_tile is the same call with
  * the choice made by the caller: tile_rows = 128 or 256 pins a kernel of that height (any size; for tests and tuning),
  * 0 leaves it to the library; anything else is FQ_ERR_SHAPE.
  */
 int fq_dense_f16(const void *x, int M, const void *W, int N, int K, void *out, void *stream);
 int fq_dense_f16_tile(const void *x, int M, const void *W, int N, int K, void *out, int tile_rows, void *stream);
+/*
+ * The kernel that fq_dense_f16 takes, or fq_head_nll (loss != 0) with V = N (host only; for tests and tools).
+ * route_out (host, 3 ints): one of FQ_DENSE_*, then rows and columns of its tiles.
+ */
+enum { FQ_DENSE_TILES_256, FQ_DENSE_STREAM, FQ_DENSE_SHARED_K };
+int fq_dense_route(int M, int N, int K, int loss, int *route_out);
 
 /*
  * Fused log-softmax cross-entropy per token (the quantity whose mean,

@@ -61,6 +61,7 @@ def _load() -> ctypes.CDLL:
         "fq_qlinear_tile": (ci, [vp, ci, vp, vp, vp, ci, ci, ci, ci, vp, ci, vp]),
         "fq_qlinear_route": (ci, [ci, vp, vp, ci, ci, vp]),
         "fq_few_row_blocks": (ci, [ci, vp, vp, ci, ci]),
+        "fq_dense_route": (ci, [ci, ci, ci, ci, vp]),
         "fq_stream_read": (ci, [vp, ctypes.c_size_t, vp, vp]),
         "fq_qlinear_mixed": (ci, [vp, ci, vp, ci, ci, ci, vp, vp]),
         "fq_stack_workspace_bytes": (sz, [ci, ci, ci]),
@@ -106,7 +107,7 @@ EXPORTS = ("fq_last_error", "fq_version", "fq_quantize_rtn", "fq_packed_bytes", 
            "fq_attn_prefill_workspace_bytes", "fq_prefill_workspace_bytes", "fq_attn_prefill", "fq_prefill_forward",
            "fq_init", "fq_dense_f16_tile", "fq_rope_table", "fq_stack_forward_noalloc", "fq_set_decode_mode",
            "fq_decode_give_up_ticks", "fq_async_error", "fq_clear_async_error", "fq_decode_partition", "fq_decode_persistent",
-           "fq_decode_persistent_launches", "fq_qlinear_route", "fq_few_row_blocks")
+           "fq_decode_persistent_launches", "fq_qlinear_route", "fq_few_row_blocks", "fq_dense_route")
 
 
 def _check(rc: int) -> None:
@@ -389,6 +390,16 @@ def fq_glue(op: int, a, b=None, c=None, out=None, stream=None):
         out = torch.empty_like(a)
     _check(_lib.fq_glue(op, _dp(a), _dp(b), _dp(c), M, H, _dp(out), _stream(stream)))
     return out
+
+
+DENSE_ROUTES = ("tiles_256", "stream", "shared_k")
+
+
+def fq_dense_route(M: int, N: int, K: int, loss: bool = False):
+    """(name, tile rows, tile columns) of the kernel that fq_dense_f16 takes, or fq_head_nll (loss)."""
+    out = np.zeros(3, dtype=np.int32)
+    _check(_lib.fq_dense_route(M, N, K, int(loss), _hp(out)))
+    return DENSE_ROUTES[out[0]], int(out[1]), int(out[2])
 
 
 def fq_dense_f16(x, W, out=None, stream=None, tile_rows: int = 0):

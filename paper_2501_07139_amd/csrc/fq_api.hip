@@ -255,12 +255,22 @@ extern "C" int fq_dense_f16_tile(const void *x, int M, const void *W, int N, int
         return fq_fail(FQ_ERR_SHAPE, "fq_dense_f16: M=%d N=%d K=%d: x and W must each stay below 4 GiB", M, N, K);
     if (tile_rows != 0 && tile_rows != 128 && tile_rows != 256)
         return fq_fail(FQ_ERR_SHAPE, "fq_dense_f16_tile: tile_rows=%d not in {0, 128, 256}", tile_rows);
-    if (tile_rows == 0 && fq_dense_rows_pays(M, N))
-        return check_hip(fq_launch_dense_rows(x, M, W, N, K, out, static_cast<fq_stream>(stream)), "fq_dense_f16 launch");
+    if (tile_rows == 0 && fq_dense_few_pays(M, N, K))
+        return check_hip(fq_launch_dense_few(x, M, W, N, K, out, static_cast<fq_stream>(stream)), "fq_dense_f16 launch");
     if (tile_rows != 128) // what the few-row tiles leave is at least half a large tile a CU
         return check_hip(fq_launch_dense_tiled(x, M, W, N, K, out, static_cast<fq_stream>(stream)),
                          "fq_dense_f16 launch");
     return check_hip(fq_launch_dense(x, M, W, N, K, out, static_cast<fq_stream>(stream)), "fq_dense_f16 launch");
+}
+
+extern "C" int fq_dense_route(int M, int N, int K, int loss, int *route_out)
+{
+    if (!route_out)
+        return fq_fail(FQ_ERR_NULL, "fq_dense_route: NULL argument");
+    if (M <= 0 || N <= 0 || K <= 0 || K % 128 != 0)
+        return fq_fail(FQ_ERR_SHAPE, "fq_dense_route: M=%d N=%d K=%d (K must be a positive multiple of 128)", M, N, K);
+    fq_dense_plan(M, N, K, loss != 0, &route_out[0], &route_out[1], &route_out[2]);
+    return FQ_OK;
 }
 
 extern "C" int fq_glue(int op, const void *a, const void *b, const void *c, int M, int H, void *out, void *stream)

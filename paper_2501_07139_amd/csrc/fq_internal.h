@@ -73,10 +73,11 @@ int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_s
 // Up to three matrices with the same input (same K) in one launch; M > 16, or any M for the few-row kernel.
 int fq_launch_gemm_multi(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st,
                          int tile_rows = 0);
-// Dense fp16 product: tiles of 16 to 128 rows that stream W, and whether they are the library's choice; 256 x 256 tiles, both
-// operands through LDS, for what they leave; 128-row tiles, only where a caller asks for that height.
-bool fq_dense_rows_pays(int M, int N);
-int fq_launch_dense_rows(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
+// Dense fp16 product: tiles of 16 to 128 rows that stream W or share K, and whether they are the library's choice; 256 x 256 tiles,
+// both operands through LDS, for what they leave; 128-row tiles, only where a caller asks for that height.
+void fq_dense_plan(int M, int N, int K, bool fused, int *kind, int *rows, int *columns); // kind: see FQ_DENSE_*
+bool fq_dense_few_pays(int M, int N, int K);
+int fq_launch_dense_few(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
 int fq_launch_dense(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
 int fq_launch_dense_tiled(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
 // Head GEMM with the token loss in its epilogue; workspace of fq_head_nll_scratch_bytes(M, V) bytes.

@@ -423,6 +423,56 @@ def test_head_few_rows_against_oracle(fq, torch, case):
     assert np.max(np.abs(got.cpu().numpy().astype(np.float64) - oracle.token_nll(oracle.round_f16(logits), lab))) <= 2e-3
 
 
+# (M, V, K), the kernel and tile of the logits, the rows of the loss's tile: every tile of the kernel whose wavefronts share K,
+# with rows and columns that end inside a block or tile, one group, fewer groups than wavefronts, one turn and several; and the
+# streaming one of 96 rows.
+SHARED_K_CASES = [((1, 20, 640), ("shared_k", 16, 16), 16), ((33, 20, 256), ("shared_k", 16, 16), 16),
+                  ((1, 4117, 1024), ("shared_k", 16, 32), 16), ((16, 6272, 4096), ("shared_k", 16, 64), 16),
+                  ((17, 2093, 1024), ("shared_k", 32, 16), 16), ((101, 1377, 384), ("shared_k", 32, 32), 16),
+                  ((819, 259, 1024), ("shared_k", 32, 32), 32), ((72, 4129, 640), ("shared_k", 32, 64), 32),
+                  ((33, 2874, 1152), ("shared_k", 48, 16), 16), ((104, 2308, 384), ("shared_k", 48, 32), 32),
+                  ((102, 4104, 640), ("shared_k", 48, 64), 48), ((101, 2727, 512), ("shared_k", 64, 32), 32),
+                  ((100, 6249, 768), ("shared_k", 64, 64), 64), ((67, 5559, 640), ("shared_k", 80, 32), 48),
+                  ((67, 8403, 1024), ("shared_k", 80, 64), 80), ((82, 8409, 1792), ("shared_k", 96, 64), 96),
+                  ((105, 8227, 1664), ("shared_k", 112, 64), 112), ((116, 8725, 1792), ("shared_k", 128, 64), 128),
+                  ((82, 8264, 1152), ("stream", 96, 128), 96), ((180, 1300, 128), ("stream", 96, 128), 96)]
+
+
+@pytest.mark.parametrize("case, route, loss_rows", SHARED_K_CASES, ids=lambda c: "-".join(map(str, c)) if isinstance(c, tuple) else "")
+def test_head_of_few_rows_and_columns_against_oracle(fq, torch, case, route, loss_rows):
+    """Logits to one rounding and fp32 sums, written nowhere else; the loss of the same sums, to the order of its merges."""
+    M, V, K = case
+    assert fq.fq_dense_route(M, V, K) == route
+    assert fq.fq_dense_route(M, V, K, loss=True)[:2] == (route[0], loss_rows)
+    X, W = fq_synth.activations(80, M, K), fq_synth.weights(81, V, K, 0.05).astype(np.float16)
+    lab = fq_synth.labels(82, M, V)
+    lab[0] = V - 1
+    lab[M // 2:M // 2 + 1] = -1
+    out = Guarded(torch, M * V * 2)
+    ws, nll = Guarded(torch, fq.fq_head_nll_workspace_bytes(M, V)), Guarded(torch, M * 4)
+    fq.fq_dense_f16(dev(torch, X), dev(torch, W), out=out.half(M, V))
+    got = fq.fq_head_nll(dev(torch, X), dev(torch, W), dev(torch, lab), out=nll.f32(M), workspace=ws.bytes())
+    assert out.intact() and ws.intact() and nll.intact()
+    assert float((got - fq.fq_token_nll(out.half(M, V).clone(), dev(torch, lab))).abs().max()) <= 2e-5
+    rows = np.unique(np.concatenate([np.arange(min(M, 6)), np.arange(max(0, M - 20), M)]))
+    logits = oracle.dense_f16(X[rows], W)
+    err = np.abs(host16(out.half(M, V))[rows].astype(np.float64) - logits)
+    assert np.all(err <= 2.0 ** -11 * np.abs(logits) + 1e-6 * oracle.dense_f16(np.abs(X[rows]), np.abs(W)))
+
+
+def test_head_nll_of_shared_k_carries_nan_and_infinity(fq, torch):
+    """As below, in the kernel whose wavefronts share K: a NaN in four columns reaches the loss, 64 columns of -inf add nothing."""
+    M, V, K = 20, 200, 1024
+    assert fq.fq_dense_route(M, V, K, loss=True)[0] == "shared_k"
+    X, W = np.zeros((M, K), dtype=np.float16), np.zeros((V, K), dtype=np.float16)
+    X[:, 0] = 1.0
+    lab = dev(torch, np.full(M, 150, dtype=np.int32))
+    W[100:104, 0] = np.nan
+    assert np.isnan(fq.fq_head_nll(dev(torch, X), dev(torch, W), lab).cpu().numpy()).all()
+    W[100:104, 0], W[0:64, 0] = 0.0, -np.inf
+    assert np.allclose(fq.fq_head_nll(dev(torch, X), dev(torch, W), lab).cpu().numpy(), math.log(V - 64), atol=1e-4)
+
+
 def test_head_nll_few_rows_carries_nan_and_infinity(fq, torch):
     """A NaN in four columns only (one lane's share) reaches the loss; a 64-column group of -inf adds nothing to it."""
     M, V, K = 20, 200, 128

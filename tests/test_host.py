@@ -275,3 +275,18 @@ def test_parity_cases_reach_every_tile_of_the_few_row_kernel(bits):
     reached = {fq.fq_qlinear_route(M, N, bits, K) for M, N, K in draws}
     assert {r for r in reached if r[0] == "few_rows"} == {fq.fq_qlinear_route(M, N, bits, K) for M, N, K in SKINNY_CASES}
     assert len({r for r in reached if r[0] == "few_rows"}) == 11
+
+
+def test_logits_and_loss_share_k_together():
+    """Sharing K changes the order of a logit's sum, so the head and the loss have to agree on it; and every size has a tile."""
+    rng = np.random.default_rng(11)
+    size = lambda lo, hi: int(np.exp(rng.uniform(np.log(lo), np.log(hi))))
+    for _ in range(5000):
+        M, V, K = size(1, 5000), size(1, 200000), 128 * size(1, 200)
+        logits, loss = fq.fq_dense_route(M, V, K), fq.fq_dense_route(M, V, K, loss=True)
+        assert (logits[0] == "shared_k") == (loss[0] == "shared_k") and logits[0] in fq.DENSE_ROUTES
+        assert loss[0] != "shared_k" or loss[2] == 64
+    out = np.zeros(3, dtype=np.int32)
+    assert fq._lib.fq_dense_route(1, 1, 128, 0, None) == -1
+    for M, V, K in ((0, 1, 128), (1, 0, 128), (1, 1, 100), (1, 1, 0)):
+        assert fq._lib.fq_dense_route(M, V, K, 0, out.ctypes.data_as(ctypes.c_void_p)) == -2
