@@ -100,6 +100,20 @@ def _load() -> ctypes.CDLL:
 
 
 _lib = _load()
+
+
+def _load_bind():
+    """The extension module that the small calls go through (csrc/fq_bind.cpp), bound to the library just loaded."""
+    try:
+        from . import _bind
+    except ImportError as e:
+        raise ImportError(f"{_PKG}/_bind is not built ({e}); run `python paper_2501_07139_amd/build.py`") from e
+    names = ("fq_qlinear_tile", "fq_qlinear_mixed", "fq_dense_f16", "fq_head_nll", "fq_token_nll", "fq_logit_l2")
+    _bind.bind(*(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in names))
+    return _bind
+
+
+_bind = _load_bind()
 EXPORTS = ("fq_last_error", "fq_version", "fq_quantize_rtn", "fq_packed_bytes", "fq_meta_count", "fq_pack_groups",
            "fq_dequant", "fq_qlinear", "fq_qlinear_tile", "fq_qlinear_mixed", "fq_stream_read", "fq_stack_workspace_bytes", "fq_stack_forward", "fq_glue", "fq_dense_f16",
            "fq_token_nll", "fq_logit_l2", "fq_head_nll_workspace_bytes", "fq_head_nll",
@@ -110,6 +124,8 @@ EXPORTS = ("fq_last_error", "fq_version", "fq_quantize_rtn", "fq_packed_bytes", 
            "fq_decode_persistent_launches", "fq_qlinear_route", "fq_few_row_blocks", "fq_dense_route")
 
 
+# The calls below that small ones are made of go through _bind where nothing is to be allocated; it answers None to whatever it does
+# not take, and the rest of the function allocates, or raises.
 def _check(rc: int) -> None:
     if rc != FQ_OK:
         raise FqError(rc, _lib.fq_last_error().decode())
@@ -230,6 +246,11 @@ def fq_dequant(w: PackedMatrix, fp16: bool = False, stream=None):
 
 
 def fq_qlinear(x, w: PackedMatrix, out=None, stream=None, group: int = GROUP, tile_rows: int = 0):
+    if out is not None:
+        rc = _bind.qlinear(x, w, out, stream, group, tile_rows)
+        if rc is not None:
+            _check(rc)
+            return out
     x = _dev(x, torch.float16, "x")
     M, K = x.shape
     if K != w.K:
@@ -269,6 +290,11 @@ class _Segment(ctypes.Structure):
 
 def fq_qlinear_mixed(x, segments, out=None, stream=None, group: int = GROUP):
     """One matrix stored as runs of output rows, each a PackedMatrix of its own bit-width over the same K."""
+    if out is not None:
+        rc = _bind.mixed(x, segments, out, stream, group)
+        if rc is not None:
+            _check(rc)
+            return out
     x = _dev(x, torch.float16, "x")
     M, K = x.shape
     if not 1 <= len(segments) <= MAX_SEGMENTS:
@@ -404,6 +430,11 @@ def fq_dense_route(M: int, N: int, K: int, loss: bool = False):
 
 def fq_dense_f16(x, W, out=None, stream=None, tile_rows: int = 0):
     """tile_rows = 128 or 256 pins one of the two kernels (fq_dense_f16_tile); 0 lets the library choose."""
+    if out is not None and not tile_rows:
+        rc = _bind.dense_f16(x, W, out, stream)
+        if rc is not None:
+            _check(rc)
+            return out
     x = _dev(x, torch.float16, "x")
     W = _dev(W, torch.float16, "W")
     M, K = x.shape
@@ -420,6 +451,11 @@ def fq_dense_f16(x, W, out=None, stream=None, tile_rows: int = 0):
 
 
 def fq_logit_l2(a, b, out=None, stream=None):
+    if out is not None:
+        rc = _bind.logit_l2(a, b, out, stream)
+        if rc is not None:
+            _check(rc)
+            return out
     a = _dev(a, torch.float16, "a")
     b = _dev(b, torch.float16, "b")
     if a.shape != b.shape or a.dim() != 2:
@@ -436,6 +472,11 @@ def fq_head_nll_workspace_bytes(M: int, V: int) -> int:
 
 
 def fq_head_nll(x, W, labels, out=None, workspace=None, stream=None):
+    if out is not None and workspace is not None:
+        rc = _bind.head_nll(x, W, labels, out, workspace, stream)
+        if rc is not None:
+            _check(rc)
+            return out
     x = _dev(x, torch.float16, "x")
     W = _dev(W, torch.float16, "W")
     labels = _dev(labels, torch.int32, "labels")
@@ -453,6 +494,11 @@ def fq_head_nll(x, W, labels, out=None, workspace=None, stream=None):
 
 
 def fq_token_nll(logits, labels, out=None, stream=None):
+    if out is not None:
+        rc = _bind.token_nll(logits, labels, out, stream)
+        if rc is not None:
+            _check(rc)
+            return out
     logits = _dev(logits, torch.float16, "logits")
     labels = _dev(labels, torch.int32, "labels")
     M, V = logits.shape

@@ -1,4 +1,4 @@
-"""Build libfq.so (HIP kernels + C-ABI) for gfx950, in-tree.
+"""Build libfq.so (HIP kernels + C-ABI) for gfx950 and the extension module of the binding, in-tree.
 
     python paper_2501_07139_amd/build.py
 """
@@ -7,6 +7,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -14,6 +15,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libfq.so")
+BIND = os.path.join(PKG, "_bind" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 SOURCES = ["fq_host.cpp", "fq_api.hip", "fq_gemv.hip", "fq_decode.hip", "fq_skinny.hip", "fq_gemm.hip", "fq_dense.hip", "fq_attn.hip", "fq_rowops.hip"]
 
@@ -51,10 +53,28 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_bind() -> None:
+    """The extension module that takes Python calls to libfq's entry points; it loads with torch, whose libraries it names."""
+    import torch
+
+    root = os.path.dirname(torch.__file__)
+    include = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+               sysconfig.get_paths()["include"], "/opt/rocm/include", os.path.join(ROOT, "include")]
+    cmd = ["g++", "-O2", "-fPIC", "-shared", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-I{d}" for d in include),
+           os.path.join(CSRC, "fq_bind.cpp"), "-o", BIND, "-L" + os.path.join(root, "lib"), "-ltorch_python", "-ltorch_cpu",
+           "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed on fq_bind.cpp:\n" + res.stderr)
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        bind = ex.submit(_build_bind)
         objs = list(ex.map(_compile, SOURCES))
+        bind.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:

@@ -1155,3 +1155,47 @@ def test_qlinear_on_seeded_random_shapes(fq, torch, case):
         torch.cuda.synchronize()
         assert out.intact(), tile_rows
         assert qerr(host16(out.half(M, N)), want) <= TOL, tile_rows
+
+
+def test_calls_with_an_output_agree_with_those_that_allocate(fq, torch):
+    """With every buffer given a call goes through the extension module: the same results bit for bit, on the current stream, on one
+    given by object or by handle, and the same refusals."""
+    M, N, K, V = 5, 96, 256, 300
+    x, W = dev(torch, fq_synth.activations(90, M, K)), dev(torch, fq_synth.weights(91, V, K, 0.05).astype(np.float16))
+    lab = dev(torch, fq_synth.labels(92, M, V))
+    w = fq.PackedMatrix.from_host(*oracle.quantize_rtn(fq_synth.weights(93, N, K), 4), 4)
+    w3 = fq.PackedMatrix.from_host(*oracle.quantize_rtn(fq_synth.weights(94, 70, K), 3), 3)
+    h, f = dict(dtype=torch.float16, device="cuda"), dict(dtype=torch.float32, device="cuda")
+    logits = fq.fq_dense_f16(x, W)
+    ws = torch.empty(fq.fq_head_nll_workspace_bytes(M, V), dtype=torch.uint8, device="cuda")
+    calls = [(lambda **k: fq.fq_qlinear(x, w, **k), lambda: torch.empty(M, N, **h)),
+             (lambda **k: fq.fq_qlinear(x.repeat(8, 1), w, tile_rows=128, **k), lambda: torch.empty(8 * M, N, **h)),
+             (lambda **k: fq.fq_qlinear_mixed(x, [w, w3], **k), lambda: torch.empty(M, N + 70, **h)),
+             (lambda **k: fq.fq_dense_f16(x, W, **k), lambda: torch.empty(M, V, **h)),
+             (lambda **k: fq.fq_head_nll(x, W, lab, **(dict(k, workspace=ws) if k else k)), lambda: torch.empty(M, **f)),
+             (lambda **k: fq.fq_token_nll(logits, lab, **k), lambda: torch.empty(M, **f)),
+             (lambda **k: fq.fq_logit_l2(logits, logits.flip(0), **k), lambda: torch.empty(M, **f))]
+    side = torch.cuda.Stream()
+    for call, buffer in calls:
+        want = call()
+        torch.cuda.synchronize()
+        for stream in (None, side, side.cuda_stream):
+            out = buffer().fill_(7)
+            torch.cuda.synchronize()
+            assert call(out=out, **({} if stream is None else {"stream": stream})) is out
+            torch.cuda.synchronize()
+            assert torch.equal(out, want)
+        with torch.cuda.stream(side):
+            out = call(out=buffer().fill_(7))
+        side.synchronize()
+        assert torch.equal(out, want)
+    with pytest.raises(fq.FqError):
+        fq.fq_qlinear(x[:, :128].contiguous(), w, out=calls[0][1]())
+    with pytest.raises(TypeError):
+        fq.fq_qlinear(x.t(), w, out=calls[0][1]())
+    with pytest.raises(TypeError):
+        fq.fq_qlinear(x, w, out=calls[0][1]().float())
+    with pytest.raises(fq.FqError):
+        fq.fq_qlinear(x, w, out=calls[0][1](), group=64)
+    with pytest.raises(fq.FqError):
+        fq.fq_qlinear(x, w, out=calls[0][1](), tile_rows=64)

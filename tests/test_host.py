@@ -290,3 +290,19 @@ def test_logits_and_loss_share_k_together():
     assert fq._lib.fq_dense_route(1, 1, 128, 0, None) == -1
     for M, V, K in ((0, 1, 128), (1, 0, 128), (1, 1, 100), (1, 1, 0)):
         assert fq._lib.fq_dense_route(M, V, K, 0, out.ctypes.data_as(ctypes.c_void_p)) == -2
+
+
+def test_extension_module_leaves_what_it_does_not_take():
+    """Anything but plain contiguous device tensors of the right type goes the long way, which raises."""
+    import torch
+
+    x, w = torch.zeros(2, 128, dtype=torch.float16), fq.PackedMatrix(*[torch.zeros(64)] * 3, 64, 128, 4)
+    for call in (lambda: fq._bind.qlinear(x, w, x, None, 128, 0), lambda: fq._bind.qlinear(None, None, None, None, 128, 0),
+                 lambda: fq._bind.qlinear(x, w, x), lambda: fq._bind.mixed(x, [w], x, None, 128), lambda: fq._bind.mixed(x, 5, x, None, 128),
+                 lambda: fq._bind.dense_f16(x, x, x, None), lambda: fq._bind.head_nll(x, x, x, x, x, None),
+                 lambda: fq._bind.token_nll(x, x, x, None), lambda: fq._bind.logit_l2(x, x, x, None)):
+        assert call() is None
+    for call in (lambda: fq.fq_qlinear(x, w, out=x), lambda: fq.fq_dense_f16(x, x, out=x), lambda: fq.fq_logit_l2(x, x, out=x),
+                 lambda: fq.fq_token_nll(x, x, out=x), lambda: fq.fq_qlinear_mixed(x, [w], out=x), lambda: fq.fq_head_nll(x, x, x, out=x, workspace=x)):
+        with pytest.raises(TypeError, match="device tensor"):
+            call()
