@@ -33,6 +33,14 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// An argument of the running kernel where it stands in the argument buffer, `at` bytes from its start: fields picked by an index that is
+// known at run time only are loaded from there, where a by-value argument would be copied to scratch memory first.
+template <class T>
+__device__ __forceinline__ const T *kernel_argument(int at)
+{
+    return reinterpret_cast<const T *>((const char *)__builtin_amdgcn_kernarg_segment_ptr() + at);
+}
+
 __device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
 __device__ __forceinline__ uint32_t as_u32(h2 h) { return __builtin_bit_cast(uint32_t, h); }
 

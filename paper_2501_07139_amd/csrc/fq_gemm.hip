@@ -27,6 +27,7 @@
 #include "fq_device.h"
 #include "fq_internal.h"
 
+#include <climits>
 #include <type_traits>
 #include <utility>
 
@@ -330,27 +331,33 @@ struct GemmJob {
     const uint32_t *packed;
     const _Float16 *scales, *zeros;
     _Float16 *out;
-    int N, bits, qnb, tile0; // tile0: index of the matrix's first tile in the launch's list
-    int ld;                  // elements between consecutive rows of out
+    int N, bits;
+    int ld;  // elements between consecutive rows of out
+    int qnb; // 128-row tiles: width, see qgemm_tile
 };
 struct GemmJobs {
     GemmJob j[3];
-    int count, total;
 };
 
-__global__ __launch_bounds__(256, 2) void qgemm_multi_kernel(const _Float16 *__restrict__ x, int M, int K, GemmJobs jobs)
+// The scalars of both kernels below are preloaded into registers at wavefront start; the matrix that they select is then one round of
+// loads from the argument buffer.  first1, first2: first tile of the second and third matrix, beyond the last tile where there is none.
+constexpr int GEMM_JOBS_AT = 32; // bytes of the arguments ahead of the jobs: a pointer and five numbers
+
+__device__ __forceinline__ GemmJob gemm_job(int &tile, int first1, int first2)
+{
+    const int index = (tile >= first1) + (tile >= first2);
+    tile -= index == 0 ? 0 : (index == 1 ? first1 : first2);
+    return kernel_argument<GemmJobs>(GEMM_JOBS_AT)->j[index];
+}
+
+__global__ __launch_bounds__(256, 2) void qgemm_multi_kernel(const _Float16 *__restrict__ x, int M, int K, int total, int first1, int first2,
+                                                             GemmJobs)
 {
     __shared__ h8 Xs[2][QBM * 16];
-    int tile = xcd_tile(jobs.total);
+    int tile = xcd_tile(total);
     if (tile < 0)
         return;
-    int ji = 0;
-    if (jobs.count > 1 && tile >= jobs.j[1].tile0)
-        ji = 1;
-    if (jobs.count > 2 && tile >= jobs.j[2].tile0)
-        ji = 2;
-    const GemmJob job = ji == 0 ? jobs.j[0] : (ji == 1 ? jobs.j[1] : jobs.j[2]); // selected by value
-    tile -= job.tile0;
+    const GemmJob job = gemm_job(tile, first1, first2);
     switch (job.bits * 8 + job.qnb) {
     case 2 * 8 + 4: qgemm_tile<2, 4>(Xs, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile); break;
     case 4 * 8 + 4: qgemm_tile<4, 4>(Xs, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile); break;
@@ -583,32 +590,16 @@ __device__ __forceinline__ void qgemm_tall_tile(h8 *Xs0, h8 *Xs1, const _Float16
     }
 }
 
-struct TallJob {
-    const uint32_t *packed;
-    const _Float16 *scales, *zeros;
-    _Float16 *out;
-    int N, bits, tile0, ld;
-};
-struct TallJobs {
-    TallJob j[3];
-    int count, total;
-};
-
 // Eight wavefronts of 256 registers each: one workgroup per CU, two wavefronts per SIMD.
-__global__ __launch_bounds__(512, 1) void qgemm_tall_kernel(const _Float16 *__restrict__ x, int M, int K, TallJobs jobs)
+__global__ __launch_bounds__(512, 1) void qgemm_tall_kernel(const _Float16 *__restrict__ x, int M, int K, int total, int first1, int first2,
+                                                            GemmJobs)
 {
     __shared__ h8 Xs0[TBM * 16];
     __shared__ h8 Xs1[TBM * 16];
-    int tile = xcd_tile(jobs.total);
+    int tile = xcd_tile(total);
     if (tile < 0)
         return;
-    int ji = 0;
-    if (jobs.count > 1 && tile >= jobs.j[1].tile0)
-        ji = 1;
-    if (jobs.count > 2 && tile >= jobs.j[2].tile0)
-        ji = 2;
-    const TallJob job = ji == 0 ? jobs.j[0] : (ji == 1 ? jobs.j[1] : jobs.j[2]);
-    tile -= job.tile0;
+    const GemmJob job = gemm_job(tile, first1, first2);
     switch (job.bits) {
     case 2: qgemm_tall_tile<2>(Xs0, Xs1, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile); break;
     case 3: qgemm_tall_tile<3>(Xs0, Xs1, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile); break;
@@ -706,20 +697,32 @@ int launch_q(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream 
 // The kernels address x, the packed weights and the scales/zeros through 32-bit byte offsets.
 static bool fits_32bit(size_t a, size_t b, size_t elem_bytes) { return a * b * elem_bytes < ((size_t)1 << 32); }
 
+namespace {
+
+// The jobs of a launch; tiles(i): tiles of matrix i; qnb(i): its tile width.
+struct GemmLaunch {
+    GemmJobs jobs = {};
+    int first[4] = {0, INT_MAX, INT_MAX, INT_MAX}, total = 0;
+    template <class T, class Q>
+    GemmLaunch(const fq_packed_ref *w, void *const *outs, int count, T &&tiles, Q &&qnb)
+    {
+        for (int i = 0; i < count; ++i) {
+            jobs.j[i] = GemmJob{static_cast<const uint32_t *>(w[i].packed), static_cast<const _Float16 *>(w[i].scales),
+                                static_cast<const _Float16 *>(w[i].zeros), static_cast<_Float16 *>(outs[i]), w[i].N,
+                                w[i].bits, w[i].ld ? w[i].ld : w[i].N, qnb(i)};
+            first[i] = total;
+            total += tiles(i);
+        }
+    }
+};
+
+} // namespace
+
 static int launch_tall(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st)
 {
-    TallJobs jobs;
-    jobs.count = count;
-    int total = 0;
-    for (int i = 0; i < count; ++i) {
-        jobs.j[i] = TallJob{static_cast<const uint32_t *>(w[i].packed), static_cast<const _Float16 *>(w[i].scales),
-                            static_cast<const _Float16 *>(w[i].zeros), static_cast<_Float16 *>(outs[i]), w[i].N,
-                            w[i].bits, total, w[i].ld ? w[i].ld : w[i].N};
-        total += tall_tiles(M, w[i].N);
-    }
-    jobs.total = total;
-    hipLaunchKernelGGL(qgemm_tall_kernel, dim3(8 * ((total + 7) / 8)), dim3(512), 0, st,
-                       static_cast<const _Float16 *>(x), M, w[0].K, jobs);
+    const GemmLaunch l(w, outs, count, [&](int i) { return tall_tiles(M, w[i].N); }, [](int) { return 0; });
+    hipLaunchKernelGGL(qgemm_tall_kernel, dim3(8 * ((l.total + 7) / 8)), dim3(512), 0, st,
+                       static_cast<const _Float16 *>(x), M, w[0].K, l.total, l.first[1], l.first[2], l.jobs);
     return (int)hipGetLastError();
 }
 
@@ -774,19 +777,10 @@ int fq_launch_gemm_multi(const void *x, int M, const fq_packed_ref *w, void *con
         return fq_launch_skinny(x, M, w, outs, count, st);
     if (tile_rows == 256)
         return launch_tall(x, M, w, outs, count, st);
-    GemmJobs jobs;
-    jobs.count = count;
-    int total = 0;
-    for (int i = 0; i < count; ++i) {
-        const int qnb = ((w[i].bits == 2 || w[i].bits == 4) && wide_tiles_pay(M, w[i].N)) ? 4 : 2;
-        jobs.j[i] = GemmJob{static_cast<const uint32_t *>(w[i].packed), static_cast<const _Float16 *>(w[i].scales),
-                            static_cast<const _Float16 *>(w[i].zeros), static_cast<_Float16 *>(outs[i]), w[i].N,
-                            w[i].bits, qnb, total, w[i].ld ? w[i].ld : w[i].N};
-        total += ((w[i].N + 64 * qnb - 1) / (64 * qnb)) * ((M + QBM - 1) / QBM);
-    }
-    jobs.total = total;
-    hipLaunchKernelGGL(qgemm_multi_kernel, dim3(8 * ((total + 7) / 8)), dim3(256), 0, st,
-                       static_cast<const _Float16 *>(x), M, w[0].K, jobs);
+    auto qnb = [&](int i) { return (w[i].bits == 2 || w[i].bits == 4) && wide_tiles_pay(M, w[i].N) ? 4 : 2; };
+    const GemmLaunch l(w, outs, count, [&](int i) { return ((w[i].N + 64 * qnb(i) - 1) / (64 * qnb(i))) * ((M + QBM - 1) / QBM); }, qnb);
+    hipLaunchKernelGGL(qgemm_multi_kernel, dim3(8 * ((l.total + 7) / 8)), dim3(256), 0, st,
+                       static_cast<const _Float16 *>(x), M, w[0].K, l.total, l.first[1], l.first[2], l.jobs);
     return (int)hipGetLastError();
 }
 

@@ -37,6 +37,7 @@
 #include "fq_internal.h"
 #include "fq_stage.h"
 
+#include <climits>
 #include <mutex>
 
 namespace {
@@ -154,8 +155,8 @@ struct GemvJob {
 
 struct GemvJobs {
     GemvJob j[3];
-    int count;
 };
+constexpr int GEMV_JOBS_AT = 48; // bytes of the kernel's arguments ahead of the jobs: four pointers and four numbers
 
 // Where the linear's input x comes from.  The row-wise steps between the linears of the block are
 // folded into the staging of x (rms(t) = t / sqrt(mean(t^2) + 1e-5), results rounded to fp16 where
@@ -634,12 +635,12 @@ __device__ __forceinline__ void gemv_body(const GemvJob job, int bj, const GemvI
     }
 }
 
-// Four wavefronts per SIMD, i.e. two workgroups per CU.  The inputs, M and K come first and as plain pointers
-// and integers: the build asks the compiler to have these ten dwords preloaded into scalar registers at wavefront
-// start, so the copies of the input row go out without waiting for a load of the kernel arguments.
+// Four wavefronts per SIMD, i.e. two workgroups per CU.  The inputs and the numbers come first, ahead of the jobs: the build has
+// leading scalar arguments preloaded into registers at wavefront start, so the copies of the input row go out without waiting for a
+// load of the kernel arguments.  blk1, blk2: first workgroup of the second and third job, INT_MAX where there is none.
 template <int MODE, int MV>
 __global__ __launch_bounds__(64 * GNW, 4) void gemv_stream_kernel(const _Float16 *in_a, const _Float16 *in_b, const _Float16 *in_c,
-                                                                  _Float16 *in_aux, int M, int K, GemvJobs jobs)
+                                                                  _Float16 *in_aux, int M, int K, int blk1, int blk2, GemvJobs)
 {
     const GemvInput in = {in_a, in_b, in_c, in_aux, MODE};
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -667,12 +668,8 @@ __global__ __launch_bounds__(64 * GNW, 4) void gemv_stream_kernel(const _Float16
         }
     }
     __builtin_amdgcn_sched_barrier(0); // nothing of the job selection moves ahead of the loads
-    // the job of this workgroup, selected by value so that its fields stay in scalar registers
-    GemvJob job = jobs.j[0];
-    if (jobs.count > 1 && (int)blockIdx.x >= jobs.j[1].blk0)
-        job = jobs.j[1];
-    if (jobs.count > 2 && (int)blockIdx.x >= jobs.j[2].blk0)
-        job = jobs.j[2];
+    // the job of this workgroup: one round of loads from the argument buffer, at an index known without any
+    const GemvJob job = kernel_argument<GemvJobs>(GEMV_JOBS_AT)->j[((int)blockIdx.x >= blk1) + ((int)blockIdx.x >= blk2)];
     const int bj = blockIdx.x - job.blk0;
     switch (job.bits) { // uniform across the workgroup
     case 2:
@@ -710,7 +707,7 @@ __global__ __launch_bounds__(64 * GNW, 4) void gemv_stream_kernel(const _Float16
     }
 }
 
-typedef void (*GemvKernel)(const _Float16 *, const _Float16 *, const _Float16 *, _Float16 *, int, int, GemvJobs);
+typedef void (*GemvKernel)(const _Float16 *, const _Float16 *, const _Float16 *, _Float16 *, int, int, int, int, GemvJobs);
 
 // One kernel per input mode, for a single activation row and for several (mode 6, the decode step's, has one only).
 constexpr int GEMV_VARIANTS = 14, GEMV_MAX_PER_CU = 4;
@@ -837,8 +834,7 @@ int fq_launch_gemv_multi(const fq_gemv_input &src, int M, const fq_packed_ref *w
 {
     if (src.mode < 0 || src.mode > 6 || !gemv_kernels[gemv_slot(src.mode, M)])
         return (int)hipErrorInvalidValue;
-    GemvJobs jobs;
-    jobs.count = count;
+    GemvJobs jobs = {};
     int nrb[3];
     for (int i = 0; i < count; ++i)
         nrb[i] = ((w[i].N + 63) / 64 * 64) / rows_per_supertile(w[i].bits);
@@ -935,11 +931,10 @@ int fq_launch_gemv_multi(const fq_gemv_input &src, int M, const fq_packed_ref *w
                             w[i].bits, blk0, nbs[i], parts[i] > 1 ? parts[i] : 0, w[i].ld ? w[i].ld : w[i].N};
         blk0 += nbs[i];
     }
-    for (int i = count; i < 3; ++i)
-        jobs.j[i] = GemvJob{nullptr, nullptr, nullptr, nullptr, 0, 0, blk0, 0, 0, 0};
     const GemvInput in = {static_cast<const _Float16 *>(src.a), static_cast<const _Float16 *>(src.b),
                           static_cast<const _Float16 *>(src.c), static_cast<_Float16 *>(src.aux), src.mode};
-    hipLaunchKernelGGL(gemv_kernels[slot], dim3(blk0), dim3(64 * GNW), lds, st, in.a, in.b, in.c, in.aux, M, w[0].K, jobs);
+    hipLaunchKernelGGL(gemv_kernels[slot], dim3(blk0), dim3(64 * GNW), lds, st, in.a, in.b, in.c, in.aux, M, w[0].K,
+                       count > 1 ? jobs.j[1].blk0 : INT_MAX, count > 2 ? jobs.j[2].blk0 : INT_MAX, jobs);
     return (int)hipGetLastError();
 }
 

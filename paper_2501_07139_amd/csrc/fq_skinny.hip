@@ -19,6 +19,8 @@
 #include "fq_device.h"
 #include "fq_internal.h"
 
+#include <climits>
+
 namespace {
 
 constexpr int SNW = 8; // wavefronts per workgroup, each a slice of K
@@ -27,12 +29,12 @@ struct SkinnyJob {
     const uint32_t *packed;
     const _Float16 *scales, *zeros;
     _Float16 *out;
-    int N, bits, tile0, ld; // tile0: index of the matrix's first tile in the launch's list
+    int N, bits, ld, pad;
 };
 struct SkinnyJobs {
     SkinnyJob j[3];
-    int count, total;
 };
+constexpr int SKINNY_JOBS_AT = 32; // bytes of the kernel's arguments ahead of the jobs: a pointer and six numbers
 
 // The packed dwords of S consecutive sixteen-row sub-blocks of group g, in the order that skinny_chunk expects.  S divides 4
 // and the rows of a matrix are padded to 64, so every sub-block exists.  packed: descriptor of the supertile rows from the
@@ -509,22 +511,23 @@ __device__ __forceinline__ void skinny_any(h8 *smem, const _Float16 *__restrict_
 // 8-bit chunks and more than five row blocks are more registers than there are; skinny_plan does not put them together.
 constexpr int WIDEST_8BIT = 5;
 
+// The scalars come first: the build has them preloaded into registers at wavefront start, so that which tile, of which matrix, is known
+// without a round trip to the argument buffer and one round fetches that matrix's fields.  (Selected by value from all three, with
+// nothing preloaded, they took four rounds one after another: 4096 x 4096 at 4 rows and 2 bits 6.0 us against 5.4.)  first1, first2: first tile of the second and
+// third matrix, beyond the last tile where there is none.
 template <int MB, int S>
-__global__ __launch_bounds__(64 * SNW, (MB == 1 && S <= 2) ? 4 : 2) void skinny_kernel(const _Float16 *__restrict__ x, int M, int K,
-                                                                                 int row_tiles, SkinnyJobs jobs)
+__global__ __launch_bounds__(64 * SNW, (MB == 1 && S <= 2) ? 4 : 2) void skinny_kernel(const _Float16 *__restrict__ x, int M, int K, int row_tiles,
+                                                                                 int total, int first1, int first2, SkinnyJobs jobs)
 {
     __shared__ h8 smem[skinny_slots<MB, S>()]; // the kernel's only LDS object: see the waits in skinny_tile
     // the workgroups of an XCD take a contiguous run of tiles (row-tile fastest): tiles that share weights share an L2
-    const int per_xcd = (jobs.total + 7) >> 3;
+    const int per_xcd = (total + 7) >> 3;
     int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (tile >= jobs.total)
+    if (tile >= total)
         return; // uniform over the workgroup, before any barrier
-    SkinnyJob job = jobs.j[0];
-    if (jobs.count > 1 && tile >= jobs.j[1].tile0)
-        job = jobs.j[1];
-    if (jobs.count > 2 && tile >= jobs.j[2].tile0)
-        job = jobs.j[2];
-    tile -= job.tile0;
+    const int index = (tile >= first1) + (tile >= first2);
+    const SkinnyJob job = kernel_argument<SkinnyJobs>(SKINNY_JOBS_AT)->j[index];
+    tile -= index == 0 ? 0 : (index == 1 ? first1 : first2);
     switch (job.bits) {
     case 2: skinny_any<2, MB, S>(smem, x, M, K, job, tile, row_tiles); break;
     case 3: skinny_any<3, MB, S>(smem, x, M, K, job, tile, row_tiles); break;
@@ -536,7 +539,7 @@ __global__ __launch_bounds__(64 * SNW, (MB == 1 && S <= 2) ? 4 : 2) void skinny_
     }
 }
 
-typedef void (*SkinnyKernel)(const _Float16 *, int, int, int, SkinnyJobs);
+typedef void (*SkinnyKernel)(const _Float16 *, int, int, int, int, int, int, SkinnyJobs);
 
 constexpr int SKINNY_CUS = 256;
 
@@ -674,19 +677,16 @@ int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *
         {nullptr, nullptr, skinny_kernel<8, 4>},
     };
     const SkinnyPlan plan = skinny_plan(M, w, count);
-    SkinnyJobs jobs;
-    jobs.count = count;
-    int total = 0;
+    SkinnyJobs jobs = {};
+    int first[4] = {0, INT_MAX, INT_MAX, INT_MAX}, total = 0;
     for (int i = 0; i < count; ++i) {
         jobs.j[i] = SkinnyJob{static_cast<const uint32_t *>(w[i].packed), static_cast<const _Float16 *>(w[i].scales),
                               static_cast<const _Float16 *>(w[i].zeros), static_cast<_Float16 *>(outs[i]), w[i].N, w[i].bits,
-                              total, w[i].ld ? w[i].ld : w[i].N};
+                              w[i].ld ? w[i].ld : w[i].N, 0};
+        first[i] = total;
         total += plan.row_tiles * ((w[i].N + (16 << plan.s_log2) - 1) >> (4 + plan.s_log2));
     }
-    for (int i = count; i < 3; ++i)
-        jobs.j[i] = jobs.j[0];
-    jobs.total = total;
     hipLaunchKernelGGL(table[plan.mb - 1][plan.s_log2], dim3(8 * ((total + 7) / 8)), dim3(64 * SNW), 0, st,
-                       static_cast<const _Float16 *>(x), M, w[0].K, plan.row_tiles, jobs);
+                       static_cast<const _Float16 *>(x), M, w[0].K, plan.row_tiles, total, first[1], first[2], jobs);
     return (int)hipGetLastError();
 }
