@@ -91,6 +91,26 @@ def test_attn_decode_against_oracle(fq, torch, case):
         assert d.max() <= 1 and np.mean(d == 0) > 0.98, pos
 
 
+@pytest.mark.parametrize("splits", [2, 4, 5, 16, 17, 63, 64, 65])
+def test_attn_decode_merges_every_split(fq, torch, splits):
+    """First and last position of the last split, on both sides of the merge kernels' limits of 16 and 64 splits."""
+    Tmax, H = 128 * splits, 256
+    rng = np.random.default_rng(splits)
+    K = rng.normal(size=(Tmax, H)).astype(np.float16)
+    V = rng.normal(size=(Tmax, H)).astype(np.float16)
+    rope = fq.rope_table(Tmax)
+    for pos in (Tmax - 128, Tmax - 1):
+        q = (rng.normal(size=H) * 1.5).astype(np.float16)
+        k, v = K[pos], V[pos]
+        got = host16(fq.fq_attn_decode(dev(torch, q), dev(torch, k), dev(torch, v), dev(torch, to_heads(K, 2)),
+                                       dev(torch, to_heads(V, 2)), pos, rope))
+        Kw = K.copy()
+        Kw[pos] = oracle.round_f16(ref.rope(k, pos, 2))
+        want = ref.attention(oracle.round_f16(ref.rope(q, pos, 2)), Kw[:pos + 1], V[:pos + 1], 2)
+        # bound of the test above: fp16 result and one fp16 rounding of q' and k', which moves a score by up to 2^-11 of |q||k|
+        assert rel_err(got, want) <= 2e-3, pos
+
+
 def test_attn_decode_closed_forms(fq, torch):
     n_heads, Tmax = 2, 260
     H = 256
