@@ -283,8 +283,8 @@ int fq_launch_attn_decode(const void *q, const void *k, const void *v, void *k_c
 // the head-major key cache), copies v into the value cache and also writes it transposed, [head][128][Tp],
 // through an LDS tile, so that the second product below finds the positions of one dimension contiguous.
 //
-// attn_prefill_kernel, per (128 query rows, head), 4 wavefronts x 2 blocks of 16 query rows, over the
-// key/value tiles of 64 positions up to the diagonal, in double-buffered LDS tiles:
+// attn_prefill_kernel, per (128 query rows, head), 4 wavefronts x 2 blocks of 16 query rows (fewer rows on smaller
+// grids, see fq_launch_attn_prefill), over the key/value tiles of 64 positions up to the diagonal, in double-buffered LDS tiles:
 //   S^T = K . Q'^T     16x16x32 MFMA, A = key rows from LDS, B = the wavefront's query rows (registers)
 //   a lane then holds scores of ONE query row (column l%16): running max and sum need only in-lane work and
 //   two cross-lane steps; P = exp(S - max) rounded to fp16 is, as it stands in the lane, the B operand of
@@ -306,30 +306,46 @@ struct PrefillArgs {
     int T, Tp, Tmax, H, NQ, heads;
 };
 
-__global__ __launch_bounds__(256) void attn_prep_kernel(PrefillArgs p)
+constexpr int PREP = 512; // threads of attn_prep_kernel
+
+__global__ __launch_bounds__(PREP) void attn_prep_kernel(PrefillArgs p)
 {
     __shared__ _Float16 vs[PT][AD + 2]; // +2 halves: the column reads below spread over the banks
-    const int t0 = blockIdx.x * PT, head = blockIdx.y, tid = threadIdx.x;
-    for (int c = tid; c < PT * 16; c += 256) {
-        const int row = c >> 4, r = c & 15, t = t0 + row;
-        h8 vv = {};
-        if (t < p.T) {
-            const size_t src = (size_t)t * p.H + (size_t)head * AD + 8 * r;
-            const f4 lo = *reinterpret_cast<const f4 *>(p.rope + (size_t)t * AD + 8 * r);
-            const f4 hi = *reinterpret_cast<const f4 *>(p.rope + (size_t)t * AD + 8 * r + 4);
-            const float cs[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            *reinterpret_cast<h8 *>(p.qr + src) = rope8(*reinterpret_cast<const h8 *>(p.q + src), cs);
+    const int t0 = blockIdx.x * PT, head = blockIdx.y, tid = threadIdx.x, r = tid & 15;
+    // All loads of a thread's rows go out before the first is used, rows past T as the last one (not stored): row after row,
+    // each waiting for its own, the call took 1.2 us more (32 heads, 128 to 300 positions).  Two rows a thread: with four the registers cost
+    // the largest grids what that gains (2048 positions).
+    constexpr int NR = PT * 16 / PREP;
+    h8 qi[NR], ki[NR], vi[NR];
+    f4 lo[NR], hi[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int t = min(t0 + (tid >> 4) + PREP / 16 * i, p.T - 1);
+        const size_t src = (size_t)t * p.H + (size_t)head * AD + 8 * r;
+        lo[i] = *reinterpret_cast<const f4 *>(p.rope + (size_t)t * AD + 8 * r);
+        hi[i] = *reinterpret_cast<const f4 *>(p.rope + (size_t)t * AD + 8 * r + 4);
+        qi[i] = *reinterpret_cast<const h8 *>(p.q + src);
+        ki[i] = *reinterpret_cast<const h8 *>(p.k + src);
+        vi[i] = *reinterpret_cast<const h8 *>(p.v + src);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+        const int row = (tid >> 4) + PREP / 16 * i, t = t0 + row;
+        const bool real = t < p.T;
+        if (real) {
+            const float cs[8] = {lo[i][0], lo[i][1], lo[i][2], lo[i][3], hi[i][0], hi[i][1], hi[i][2], hi[i][3]};
+            *reinterpret_cast<h8 *>(p.qr + (size_t)t * p.H + (size_t)head * AD + 8 * r) = rope8(qi[i], cs);
             const size_t dst = ((size_t)head * p.Tmax + t) * AD + 8 * r;
-            *reinterpret_cast<h8 *>(p.kc + dst) = rope8(*reinterpret_cast<const h8 *>(p.k + src), cs);
-            vv = *reinterpret_cast<const h8 *>(p.v + src);
-            *reinterpret_cast<h8 *>(p.vc + dst) = vv;
+            *reinterpret_cast<h8 *>(p.kc + dst) = rope8(ki[i], cs);
+            *reinterpret_cast<h8 *>(p.vc + dst) = vi[i];
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-            vs[row][8 * r + e] = vv[e]; // zeros past T: they meet zero weights, and 0 * 0 stays 0
+            vs[row][8 * r + e] = real ? vi[i][e] : (_Float16)0.f; // zeros past T: they meet zero weights, and 0 * 0 stays 0
     }
     __syncthreads();
-    for (int c = tid; c < AD * (PT / 8); c += 256) {
+    for (int c = tid; c < AD * (PT / 8); c += PREP) {
         const int d = c >> 3, j = c & 7;
         h8 o;
 #pragma unroll
@@ -339,8 +355,8 @@ __global__ __launch_bounds__(256) void attn_prep_kernel(PrefillArgs p)
     }
 }
 
-constexpr int QB = 2;            // blocks of 16 query rows per wavefront
-constexpr int QT = 4 * 16 * QB;  // query rows per workgroup
+// query rows per workgroup: four wavefronts, KS of them share QB blocks of sixteen rows and halve (KS = 2) every key tile
+constexpr int prefill_rows(int QB, int KS) { return 4 * 16 * QB / KS; }
 
 // row of the key tile that feeds row r of score block b: chosen so that the eight positions a lane ends up
 // holding for one k-step of the second product, (4g..4g+3 of blocks 2ks and 2ks+1), are the contiguous
@@ -350,8 +366,10 @@ __device__ __forceinline__ int key_row(int b, int r) { return 32 * (b >> 1) + 8 
 // bits 0-1 and 3-4 of the row number
 __device__ __forceinline__ int key_slot(int row, int ch) { return row * 16 + (ch ^ ((row & 3) | ((row >> 1) & 12))); }
 
+template <int QB, int KS>
 __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs p)
 {
+    constexpr int QT = prefill_rows(QB, KS), KB = 4 / KS; // KB: score blocks (sixteen positions) a wavefront has of a tile
     // Key tiles [64 positions][16 chunks] (see key_slot); value tiles: 16-byte slot sl (eight positions) of
     // dimension row d at d*8 + (sl ^ ((d >> 1) & 7)).  Two of each, as separate arrays named statically in
     // a loop unrolled by two: the compiler then knows that the key tile being read is not the one the
@@ -369,7 +387,8 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs p)
     const int qt = p.NQ - 1 - job / p.heads, head = job % p.heads;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, g = lane >> 4;
-    const int q0 = qt * QT + 16 * QB * wave; // first query row of this wavefront
+    const int kpart = wave % KS, qpart = wave / KS;
+    const int q0 = qt * QT + 16 * QB * qpart; // first query row of this wavefront
     const int last_tile = min((qt * QT + QT - 1) / PT, p.Tp / PT - 1);
 
     // the wavefront's query rows as B operands of the four k-steps over the head dimension
@@ -443,44 +462,45 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs p)
         if (jt < last_tile)
             load_tiles(PAR ? Ks0 : Ks1, jt + 1);
 
-        // a wavefront whose every query row lies before the tile has nothing to add (uniform per wavefront)
-        if (jt * PT <= q0 + 16 * QB - 1) {
-            // scores of 64 positions against the wavefront's query rows, transposed: S^T = K . Q'^T
-            f4 st[QB][4];
+        // a wavefront whose every query row lies before its part of the tile has nothing to add (uniform per wavefront)
+        const int first = jt * PT + PT / KS * kpart;
+        if (first <= q0 + 16 * QB - 1) {
+            // scores of its positions against the wavefront's query rows, transposed: S^T = K . Q'^T
+            f4 st[QB][KB];
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
+            for (int b = 0; b < KB; ++b) {
 #pragma unroll
                 for (int qi = 0; qi < QB; ++qi)
                     st[qi][b] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int s = 0; s < 4; ++s) {
-                    const h8 ka = Kcur[key_slot(key_row(b, col), 4 * s + g)];
+                    const h8 ka = Kcur[key_slot(key_row(KB * kpart + b, col), 4 * s + g)];
 #pragma unroll
                     for (int qi = 0; qi < QB; ++qi)
                         st[qi][b] = mfma16x16x32(ka, qb[qi][s], st[qi][b]);
                 }
             }
-            // lane: query row q0 + 16qi + col; st[qi][b][v] belongs to position jt*64 + key_row(b, 4g + v).
+            // lane: query row q0 + 16qi + col; st[qi][b][v] belongs to position jt*64 + key_row(KB * kpart + b, 4g + v).
             // Scores are kept in units of log2(e) / sqrt(128), so that the exponentials are bare exp2; only
             // tiles that reach the diagonal need the mask (it also hides the positions past T).
             constexpr float kScale = 0.08838834764831845f * 1.4426950408889634f;
-            const bool diagonal = jt * PT + PT - 1 > q0; // uniform per wavefront
-            h8 pb[QB][2];
+            const bool diagonal = first + PT / KS - 1 > q0; // uniform per wavefront
+            h8 pb[QB][KB / 2];
 #pragma unroll
             for (int qi = 0; qi < QB; ++qi) {
                 float tmax = -INFINITY;
                 if (diagonal) {
 #pragma unroll
-                    for (int b = 0; b < 4; ++b)
+                    for (int b = 0; b < KB; ++b)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
-                            const int kv = jt * PT + key_row(b, 4 * g + v);
+                            const int kv = jt * PT + key_row(KB * kpart + b, 4 * g + v);
                             st[qi][b][v] = kv <= q0 + 16 * qi + col ? st[qi][b][v] * kScale : -INFINITY;
                             tmax = fmaxf(tmax, st[qi][b][v]);
                         }
                 } else {
 #pragma unroll
-                    for (int b = 0; b < 4; ++b)
+                    for (int b = 0; b < KB; ++b)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             st[qi][b][v] *= kScale;
@@ -494,7 +514,7 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs p)
                 const float mref = mnew == -INFINITY ? 0.f : mnew;
                 float psum = 0.f;
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
+                for (int b = 0; b < KB; ++b)
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const float e = __builtin_amdgcn_exp2f(st[qi][b][v] - mref);
@@ -511,13 +531,13 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs p)
                 }
                 l[qi] += psum;
             }
-            // O^T += V^T . P^T; k-slot e of k-step ks is position 32ks + 8g + e: one slot of a value row
+            // O^T += V^T . P^T; k-slot e of the tile's k-step ks is position 32ks + 8g + e: one slot of a value row
 #pragma unroll
             for (int db = 0; db < 8; ++db) {
                 const int d = 16 * db + col, sw = (d >> 1) & 7;
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) {
-                    const h8 va = Vcur[d * 8 + ((4 * ks + g) ^ sw)];
+                for (int ks = 0; ks < KB / 2; ++ks) {
+                    const h8 va = Vcur[d * 8 + ((4 * (KB / 2 * kpart + ks) + g) ^ sw)];
 #pragma unroll
                     for (int qi = 0; qi < QB; ++qi)
                         acc[qi][db] = mfma16x16x32(va, pb[qi][ks], acc[qi][db]);
@@ -537,6 +557,34 @@ __global__ __launch_bounds__(256, 2) void attn_prefill_kernel(PrefillArgs p)
     if (jt <= last_tile)
         tile_step(jt, std::integral_constant<int, 0>{});
 
+    if constexpr (KS == 2) { // both halves' sums meet in LDS (every read of the tiles lies before the last barrier), in the wavefront of the first
+        h8 *const acc_at = qpart == 0 ? Ks0 : Ks1;
+        float *const row_at = reinterpret_cast<float *>(Vs0) + 128 * QB * qpart;
+        static_assert(sizeof(acc) * 64 <= sizeof(Ks0) && 2 * 128 * QB * sizeof(float) <= sizeof(Vs0), "room for a wavefront's sums");
+        if (kpart == 1) {
+#pragma unroll
+            for (int qi = 0; qi < QB; ++qi) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    acc_at[64 * (8 * qi + i) + lane] = __builtin_bit_cast(h8, acc[qi][i]);
+                row_at[128 * qi + lane] = mx[qi];
+                row_at[128 * qi + 64 + lane] = l[qi];
+            }
+        }
+        __syncthreads();
+        if (kpart == 1)
+            return;
+#pragma unroll
+        for (int qi = 0; qi < QB; ++qi) {
+            const float m2 = row_at[128 * qi + lane], l2 = row_at[128 * qi + 64 + lane];
+            const float mnew = fmaxf(mx[qi], m2), mref = mnew == -INFINITY ? 0.f : mnew; // -inf: a half without a position for these rows
+            const float s1 = __builtin_amdgcn_exp2f(mx[qi] - mref), s2 = __builtin_amdgcn_exp2f(m2 - mref);
+            l[qi] = l[qi] * s1 + l2 * s2;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                acc[qi][i] = acc[qi][i] * s1 + __builtin_bit_cast(f4, acc_at[64 * (8 * qi + i) + lane]) * s2;
+        }
+    }
 #pragma unroll
     for (int qi = 0; qi < QB; ++qi) {
         float lsum = l[qi];
@@ -564,6 +612,22 @@ size_t fq_attn_prefill_scratch_bytes(int T, int n_heads)
     return (size_t)T * n_heads * AD * 2 + (size_t)n_heads * AD * prefill_tp(T) * 2;
 }
 
+template <int QB, int KS>
+static void launch_prefill(PrefillArgs a, fq_stream st)
+{
+    a.NQ = (a.T + prefill_rows(QB, KS) - 1) / prefill_rows(QB, KS);
+    hipLaunchKernelGGL((attn_prefill_kernel<QB, KS>), dim3(a.NQ * a.heads), dim3(256), 0, st, a);
+}
+
+// Query rows per workgroup.  A CU holds two workgroups, and a workgroup's time is its key tiles, one after another, each mostly
+// latency and the reads of its operands from LDS.  128 rows read the least LDS per product and serve the largest grids; while
+// smaller tiles are still resident together, more of them at a time are worth the repeated reads: 64 rows up to three
+// workgroups a CU, and 32 rows, every key tile halved between two wavefronts, up to two and a half.  Measured with the preparing kernel (us,
+// 128 / 64 / 32 rows): 8 heads, 611 positions 24.9 / 18.4 / 16.6, 2048 63 / 45 / 39, 4096 113 / 79 / 97; 32 heads, 128 positions
+// 12.6 / 10.7 / 10.7, 300 18.9 / 15.7 / 16.1, 611 31 / 25.5 / 24.8, 800 35 / 28.6 / 31.8, 1200 50 / 38.6 / 49, 1500 59 / 53.7 / 66, 2048
+// 76 / 81 / 102.  (64 rows as two wavefronts of 32 rows by two halves read half the LDS of 64 rows and are slower: 611 positions
+// 27.6, 1200 43.)
+//
 // Shapes validated by the caller: 0 < T <= Tmax, head dimension 128, 16-byte aligned pointers, the byte
 // sizes of one head's cache and of one head's transposed values below 4 GiB.
 int fq_launch_attn_prefill(const void *q, const void *k, const void *v, int T, void *k_cache, void *v_cache,
@@ -583,12 +647,17 @@ int fq_launch_attn_prefill(const void *q, const void *k, const void *v, int T, v
     a.Tp = prefill_tp(T);
     a.Tmax = Tmax;
     a.H = n_heads * AD;
-    hipLaunchKernelGGL(attn_prep_kernel, dim3(a.Tp / PT, n_heads), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(attn_prep_kernel, dim3(a.Tp / PT, n_heads), dim3(PREP), 0, st, a);
     int rc = (int)hipGetLastError();
     if (rc != 0)
         return rc;
-    a.NQ = (T + QT - 1) / QT;
     a.heads = n_heads;
-    hipLaunchKernelGGL(attn_prefill_kernel, dim3(a.NQ * n_heads), dim3(256), 0, st, a);
+    const auto tiles = [&](int rows) { return (T + rows - 1) / rows * n_heads; };
+    if (tiles(prefill_rows(1, 2)) <= 640)
+        launch_prefill<1, 2>(a, st);
+    else if (tiles(prefill_rows(1, 1)) <= 768)
+        launch_prefill<1, 1>(a, st);
+    else
+        launch_prefill<2, 1>(a, st);
     return (int)hipGetLastError();
 }

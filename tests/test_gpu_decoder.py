@@ -253,6 +253,32 @@ def test_attn_prefill_against_oracle(fq, torch, case):
             assert rel_err(got[t], want) <= 2e-3, t
 
 
+@pytest.mark.parametrize("case", [(2, 31), (2, 32), (2, 33), (2, 96), (2, 97), (3, 129), (32, 640), (32, 641), (32, 1536), (32, 1537)],
+                         ids=str)
+def test_attn_prefill_at_the_edges_of_its_tiles(fq, torch, case):
+    """Rows at the edges of the 32-, 64- and 128-row query tiles and halves of key tiles, at lengths on both sides of where
+    the tile changes (32 heads); caches with NaN past T."""
+    n_heads, T = case
+    H = 128 * n_heads
+    rng = np.random.default_rng(T)
+    q = (rng.normal(size=(T, H)) * 1.5).astype(np.float16)
+    k = rng.normal(size=(T, H)).astype(np.float16)
+    v = rng.normal(size=(T, H)).astype(np.float16)
+    rope = fq.rope_table(T + 5)
+    kc = torch.full((n_heads, T + 5, 128), float("nan"), dtype=torch.float16, device="cuda")
+    vc = torch.full_like(kc, float("nan"))
+    got = host16(fq.fq_attn_prefill(dev(torch, q), dev(torch, k), dev(torch, v), kc, vc, rope))
+    gK, gV = from_heads(host16(kc)), from_heads(host16(vc))
+    assert np.array_equal(gV[:T].view(np.uint16), v.view(np.uint16))
+    assert np.isnan(gK[T:].astype(np.float32)).all() and np.isnan(gV[T:].astype(np.float32)).all()
+    kr = oracle.round_f16(np.stack([ref.rope(k[t], t, n_heads) for t in range(T)]))
+    last = (T - 1) // 64 * 64
+    for t in sorted({t for t in (0, 15, 16, 31, 32, 33, 63, 64, 95, 96, 127, 128, last - 1, last, last + 31, last + 32, T - 2, T - 1)
+                     if 0 <= t < T}):
+        want = ref.attention(oracle.round_f16(ref.rope(q[t], t, n_heads)), kr[:t + 1], v[:t + 1], n_heads)
+        assert rel_err(got[t], want) <= 2e-3, t  # the bound of the test above
+
+
 def test_prefill_forward_against_oracle_and_decode_continues_from_it(fq, torch):
     stack, host, sh = build_real_stack(fq, 830)
     L, H, nh, Tmax, T = sh["layers"], sh["hidden"], sh["hidden"] // 128, 160, 150
