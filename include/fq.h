@@ -165,13 +165,10 @@ int fq_qlinear_tile(const void *x, int M, const void *packed, const void *scales
 /*
  * The kernel that fq_qlinear takes, or a launch of up to three matrices that share x (host only; for tests and tools).
  * N, bits: host, count entries.  route_out (host, 3 ints): one of FQ_ROUTE_*, then rows and columns of its tiles
- * (0, 0 for the first two).  A workgroup of the few-row kernel takes one tile, or two of 64 columns and up to 64 rows, one
- * above the other, for which it unpacks the weights once: fq_few_row_blocks says how many blocks of sixteen rows it
- * takes together (1 to 8; 0: another kernel, or an argument that fq_qlinear_route refuses).
+ * (0, 0 for the first two).
  */
 enum { FQ_ROUTE_STREAM, FQ_ROUTE_GENERIC, FQ_ROUTE_FEW_ROWS, FQ_ROUTE_TILES_128, FQ_ROUTE_TILES_256 };
 int fq_qlinear_route(int M, const int *N, const int *bits, int count, int K, int *route_out);
-int fq_few_row_blocks(int M, const int *N, const int *bits, int count, int K);
 
 /*
  * Mixed precision WITHIN a matrix (Section "Large Language Model Quantization":

@@ -131,8 +131,7 @@ extern "C" int fq_qlinear_tile(const void *x, int M, const void *packed, const v
     return qlinear_checked(x, M, w, out, static_cast<fq_stream>(stream), tile_rows);
 }
 
-// The route of a launch; blocks: row blocks of sixteen that a workgroup of the few-row kernel takes, else 0.
-static int linear_route(int M, const int *N, const int *bits, int count, int K, int *route_out, int *blocks)
+extern "C" int fq_qlinear_route(int M, const int *N, const int *bits, int count, int K, int *route_out)
 {
     if (!N || !bits || !route_out)
         return fq_fail(FQ_ERR_NULL, "fq_qlinear_route: NULL argument");
@@ -146,11 +145,10 @@ static int linear_route(int M, const int *N, const int *bits, int count, int K, 
         w[i] = fq_packed_ref{nullptr, nullptr, nullptr, N[i], K, bits[i]};
         stream = stream && fq_gemv_can_stream(M, K, bits[i], 0);
     }
-    route_out[1] = route_out[2] = *blocks = 0;
+    route_out[1] = route_out[2] = 0;
     if (M <= 16 ? fq_skinny_pays(M, w, count) : fq_gemm_tile_rows(M, w, count) == 0) {
         route_out[0] = FQ_ROUTE_FEW_ROWS;
         fq_skinny_tile(M, w, count, &route_out[1], &route_out[2]);
-        *blocks = fq_skinny_blocks(M, w, count);
     } else if (M <= 16) {
         route_out[0] = stream ? FQ_ROUTE_STREAM : FQ_ROUTE_GENERIC;
     } else {
@@ -159,18 +157,6 @@ static int linear_route(int M, const int *N, const int *bits, int count, int K, 
         route_out[0] = route_out[1] == 256 ? FQ_ROUTE_TILES_256 : FQ_ROUTE_TILES_128;
     }
     return FQ_OK;
-}
-
-extern "C" int fq_qlinear_route(int M, const int *N, const int *bits, int count, int K, int *route_out)
-{
-    int blocks = 0;
-    return linear_route(M, N, bits, count, K, route_out, &blocks);
-}
-
-extern "C" int fq_few_row_blocks(int M, const int *N, const int *bits, int count, int K)
-{
-    int route[3], blocks = 0;
-    return linear_route(M, N, bits, count, K, route, &blocks) == FQ_OK ? blocks : 0;
 }
 
 extern "C" int fq_qlinear_mixed(const void *x, int M, const fq_segment *segments, int count, int K, int group,

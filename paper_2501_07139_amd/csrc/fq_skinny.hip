@@ -657,11 +657,9 @@ double fq_skinny_us(int M, const fq_packed_ref *w, int count) { return skinny_pl
 void fq_skinny_tile(int M, const fq_packed_ref *w, int count, int *rows, int *columns)
 {
     const SkinnyPlan plan = skinny_plan(M, w, count);
-    *rows = 16 * (plan.mb <= 4 ? plan.mb : (plan.mb + 1) / 2); // more: two tiles, one above the other (see fq.h)
+    *rows = 16 * plan.mb;
     *columns = 16 << plan.s_log2;
 }
-
-int fq_skinny_blocks(int M, const fq_packed_ref *w, int count) { return skinny_plan(M, w, count).mb; }
 
 // Up to three matrices that share the input (same K), in one launch.
 int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st)

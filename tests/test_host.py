@@ -266,15 +266,17 @@ def test_route_takes_every_size_that_the_linear_takes():
 
 @pytest.mark.parametrize("bits", BITS)
 def test_parity_cases_reach_every_tile_of_the_few_row_kernel(bits):
-    """The tile shapes that the rule chooses over 20000 sizes against those of the GPU test's list of cases."""
-    from test_gpu_parity import SKINNY_CASES
+    """The tile shapes that the rule chooses over 20000 sizes against those of the GPU tests' lists of cases, and their number: up
+    to 64 rows eleven, and of 64 columns 80 rows, with less than 8 bits 96, 112 and 128 too."""
+    from test_gpu_parity import SKINNY_CASES, WIDE_CASES
 
     rng = np.random.default_rng(7)
     size = lambda lo, hi: int(np.exp(rng.uniform(np.log(lo), np.log(hi))))
     draws = [(size(3, 3000), size(1, 30000), 128 * size(1, 130)) for _ in range(20000)]
     reached = {fq.fq_qlinear_route(M, N, bits, K) for M, N, K in draws}
-    assert {r for r in reached if r[0] == "few_rows"} == {fq.fq_qlinear_route(M, N, bits, K) for M, N, K in SKINNY_CASES}
-    assert len({r for r in reached if r[0] == "few_rows"}) == 11
+    cases = SKINNY_CASES + [c for c, blocks in WIDE_CASES if bits < 8 or blocks <= 5]
+    assert {r for r in reached if r[0] == "few_rows"} == {fq.fq_qlinear_route(M, N, bits, K) for M, N, K in cases}
+    assert len({r for r in reached if r[0] == "few_rows"}) == (12 if bits == 8 else 15)
 
 
 def test_logits_and_loss_share_k_together():
