@@ -245,6 +245,77 @@ def test_qlinear_wide_few_row_tiles_against_oracle(fq, torch, bits, case, blocks
         assert np.all(err <= 2.0 ** -11 * np.abs(r) + 1e-6 * size + 2.0 ** -24)
 
 
+def sampled_columns(rng, N, count):
+    """Columns of a matrix of N rows: some at random, and those on either side of the blocks of 16 and 64 at its ends."""
+    edges = [n for n in (0, 15, 16, 63, 64, (N - 1) // 64 * 64 - 1, (N - 1) // 64 * 64, (N - 1) // 16 * 16, N - 1) if 0 <= n < N]
+    return np.unique(np.concatenate([rng.integers(0, N, size=count), edges]))
+
+
+# The same tiles over rows of more than 32 groups, where a wavefront's slots for scales and zeros are filled again: (M, N, K) and the
+# blocks, on both sides of every difference between the bodies.
+LONG_WIDE_CASES = [((600, 830, 5248), 2), ((620, 830, 5248), 3), ((640, 1180, 5248), 4), ((600, 1635, 5248), 5), ((600, 2055, 5248), 6),
+                   ((600, 2335, 4224), 7), ((600, 2720, 5248), 8), ((600, 620, 11008), 2), ((600, 1635, 11008), 5)]
+
+
+@pytest.mark.parametrize("bits, case, blocks", [(b, c, n) for c, n in LONG_WIDE_CASES for b in BITS if b < 8 or n <= 5],
+                         ids=lambda c: "M%d_N%d_K%d" % c if isinstance(c, tuple) else str(c))
+def test_qlinear_wide_few_row_tiles_over_long_rows(fq, torch, bits, case, blocks):
+    """Scales and zeros differ from group to group; sampled columns, and the bound of the test above."""
+    M, N, K = case
+    assert fq.fq_qlinear_route(M, N, bits, K) == ("few_rows", 16 * blocks, 64)
+    codes = fq_synth.codes(74, N, K, bits)
+    s = (np.abs(fq_synth.activations(75, N, K // 128).astype(np.float32)) * 0.01 + 1e-3).astype(np.float16)
+    X = fq_synth.activations(76, M, K)
+    cols = sampled_columns(np.random.default_rng(3), N, 60)
+    for frac in (0, 1):
+        z = fq_synth.codes(77, N, K // 128, bits).astype(np.float32)
+        if frac:
+            z[::3, ::2] += 0.25
+        z = z.astype(np.float16)
+        out = Guarded(torch, M * N * 2)
+        fq.fq_qlinear(dev(torch, X), fq.PackedMatrix.from_host(codes, s, z, bits), out=out.half(M, N))
+        assert out.intact()
+        W = oracle.dequant(codes[cols], s[cols], z[cols])
+        r, size = oracle.qlinear(X, W), oracle.qlinear(np.abs(X), np.abs(W))
+        err = np.abs(host16(out.half(M, N))[:, cols].astype(np.float64) - r)
+        assert np.all(err <= 2.0 ** -11 * np.abs(r) + 1e-6 * size + 2.0 ** -24)
+
+
+# Launches of several matrices: odd column offsets, a row pitch that is not a matrix's own N, matrices of few and many tiles in
+# every place, and one of 8 bits, which keeps all of the launch to five blocks.
+@pytest.mark.parametrize("M, rows, runs", [(77, 32, [(2433, 2), (1231, 3), (432, 4)]), (100, 48, [(2433, 2), (1231, 3), (432, 4)]),
+                                           (200, 80, [(2433, 2), (1231, 3), (432, 4)]), (300, 112, [(2433, 2), (1231, 3), (432, 4)]),
+                                           (300, 48, [(1231, 8), (2433, 2), (400, 4)]), (200, 80, [(2433, 2), (400, 4), (1231, 8)]),
+                                           (512, 80, [(2433, 2), (1231, 8), (400, 3)]), (128, 128, [(5000, 2), (3001, 4), (2999, 3)]),
+                                           (77, 80, [(5000, 3), (3001, 4), (2999, 2)]), (400, 64, [(2433, 4), (1663, 3)])])
+def test_qlinear_wide_few_row_tiles_in_launches_of_several_matrices(fq, torch, M, rows, runs):
+    """Sampled columns of every matrix against the oracle, with the bound of the test above; guard bytes, and no element left out."""
+    K, total = 4224, sum(N for N, _ in runs)
+    assert fq.fq_qlinear_route(M, [N for N, _ in runs], [b for _, b in runs], K) == ("few_rows", rows, 64)
+    rng = np.random.default_rng(21)
+    segs, sampled, cols_all, col0 = [], [], [], 0
+    for i, (N, bits) in enumerate(runs):
+        codes = fq_synth.codes(91 + i, N, K, bits)
+        s = (np.abs(fq_synth.activations(94 + i, N, K // 128).astype(np.float32)) * 0.01 + 1e-3).astype(np.float16)
+        z = (fq_synth.codes(97 + i, N, K // 128, bits).astype(np.float32) + 0.25 * (i == 1)).astype(np.float16)
+        segs.append(fq.PackedMatrix.from_host(codes, s, z, bits))
+        cols = sampled_columns(rng, N, 50)
+        sampled.append(oracle.dequant(codes[cols], s[cols], z[cols]))
+        cols_all.append(col0 + cols)
+        col0 += N
+    X = fq_synth.activations(90, M, K)
+    out = Guarded(torch, M * total * 2)
+    out.half(M, total).fill_(float("nan"))
+    fq.fq_qlinear_mixed(dev(torch, X), segs, out=out.half(M, total))
+    assert out.intact()
+    y = host16(out.half(M, total)).astype(np.float64)
+    assert np.all(np.isfinite(y))
+    W = np.concatenate(sampled, axis=0)
+    r, size = oracle.qlinear(X, W), oracle.qlinear(np.abs(X), np.abs(W))
+    err = np.abs(y[:, np.concatenate(cols_all)] - r)
+    assert np.all(err <= 2.0 ** -11 * np.abs(r) + 1e-6 * size + 2.0 ** -24)
+
+
 @pytest.mark.parametrize("zeros", ["fractions", "odd_large", "largest", "negative"])
 @pytest.mark.parametrize("bits", BITS)
 @pytest.mark.parametrize("case", [(1, 300, 1024), (2, 300, 1024), (3, 300, 8320), (4, 70, 128), (4, 300, 2048), (16, 5200, 1152),
