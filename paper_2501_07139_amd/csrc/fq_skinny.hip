@@ -13,9 +13,9 @@
 // Two bodies: tiles of 16 or 32 columns, or of sixteen rows (skinny_tile), and tiles of 64 columns and two to eight blocks of sixteen rows
 // (skinny_wide_tile), which unpack a weight once for all of them.
 //
-// Arithmetic: code - zero in fp16, fp32 sums per group, and the group's scale applied to the sum in fp32.  Tiles of sixteen
-// rows, which decoding uses, multiply the codes and take the zero from the group's sum in fp32 (see ZERO_APART).  Sums over
-// the wavefronts in a fixed order.
+// Arithmetic: code - zero in fp16, fp32 sums per group, and the group's scale applied to the sum in fp32.  Tiles of sixteen rows,
+// which decoding uses, of sixteen columns and of 32 by 32 multiply the codes and take the zero from the group's sum in fp32
+// (see ZERO_APART).  Sums over the wavefronts in a fixed order.
 #include "fq_device.h"
 #include "fq_internal.h"
 
@@ -165,8 +165,9 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
     // Zeros leave through the group's sums, sum code x - zero sum x, so that any fp16 zero is exact, as in the decode kernel
     // (2048 x 2048, 16 rows at 2 bits, error over the rms of the result: 2.06e-4, the output's own rounding; with code - zero
     // in fp16 2.3e-4 for fractional zeros and 4.0e-4 for odd ones beyond 1024).  sum x is one more matrix product, of rows
-    // of ones: level in time, and there is no branch on the zeros.
-    constexpr bool ZERO_APART = MB == 1;
+    // of ones, and there is no branch on the zeros.  Sixteen rows: level in time; 32 x 32 and 32 x 16, which serve what sixteen rows
+    // otherwise would: 0.5 and 0.9 % more over 230 sizes; 48 x 16 2.5 %, and so would the others be.
+    constexpr bool ZERO_APART = S == 1 || MB <= 2;
     constexpr int H = SkinnyRing<MB>::H, STAGE = SkinnyRing<MB>::STAGE, COPIES = 2 * MB;
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -278,7 +279,7 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
                 }
             });
             load_w(t + 1);
-            f4 p[S][MB], xs = {0.f, 0.f, 0.f, 0.f}; // xs: sum over the group of the lane's activation row
+            f4 p[S][MB], xs[MB] = {}; // xs: sums over the group of the lane's activation rows
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 // The stage's copies are older than the COPIES * (H - 1) copies of the stages behind it.  The loads of
@@ -305,7 +306,9 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
                     const _Float16 one = 1;
 #pragma unroll
                     for (int s = 0; s < 2; ++s)
-                        xs = mfma16x16x32(h8{one, one, one, one, one, one, one, one}, xf[s][0], xs);
+#pragma unroll
+                        for (int j = 0; j < MB; ++j)
+                            xs[j] = mfma16x16x32(h8{one, one, one, one, one, one, one, one}, xf[s][j], xs[j]);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 __builtin_amdgcn_s_waitcnt(FQ_WAIT_LGKMCNT0); // the operands have left the slot
@@ -317,7 +320,7 @@ __device__ __forceinline__ void skinny_tile(h8 *smem, const _Float16 *__restrict
                 for (int j = 0; j < MB; ++j)
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
-                        acc[u][j][v] = fmaf(scf[u][v], ZERO_APART ? fmaf(-zf[u][v], xs[v], p[u][j][v]) : p[u][j][v], acc[u][j][v]);
+                        acc[u][j][v] = fmaf(scf[u][v], ZERO_APART ? fmaf(-zf[u][v], xs[j][v], p[u][j][v]) : p[u][j][v], acc[u][j][v]);
         }
     }
 
@@ -561,13 +564,17 @@ struct SkinnyPlan {
 // ones: 300 x 4096 x 4096 at 4 bits 23.5 -> 17.5 us, 300 x 4096 x 11008 at 2 bits 48 -> 35, 77 x 11008 x 4096 23.6 -> 17.2, 512
 // x 4096 x 11008 at 2 bits 60 -> 53; up to 1280 rows; beyond, an XCD's L2 holds none of the activations that its tiles share (1500 x 4096 x 11008 at 2 bits: 184 against 155).
 //
+// Five blocks of short rows (65 to 80 rows, K up to 1024, from 8193 columns on) stay in tiles of sixteen rows, which take any zero
+// exactly, where those are expected to be close (15 %; 2 % to taller tiles that make no single round of it): one round of all five
+// blocks is faster (78 x 9284 x 1024 at 2 bits 8.9 against 10.7 us) but rounds code - zero.
+//
 // Up to sixteen rows every shape has one row block and the number of sub-blocks is all there is to choose (it does not change
 // a sum).  Fitted to 2500 sizes of 64 to 24000 columns with each S: 3.4 us and a turn of 0.13 + 0.28 S us (8 bits 0.37 S;
 // 3 bits S = 1 0.7, S = 2 1.2) while every CU has one tile; a second one on some CUs costs nearly a second turn, and from two a
 // CU on the time grows with the tiles.  64 columns a tile just beyond one round (20739 x 1664, 4 bits) 11.3 us, 32 columns 9.8.
 SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
 {
-    SkinnyPlan best = {1, 0, 1, 1e30};
+    SkinnyPlan best = {1, 0, 1, 1e30}, sixteen = best; // sixteen: of the tiles of sixteen rows
     const int blocks = (M + 15) / 16, turns = ((w[0].K >> 7) + SNW - 1) / SNW;
     bool eight = false;
     for (int i = 0; i < count; ++i)
@@ -620,8 +627,12 @@ SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
             }
             if (fixed + work < best.us)
                 best = {mb, sl, row_tiles, fixed + work};
+            if (mb == 1 && fixed + work < sixteen.us)
+                sixteen = {mb, sl, row_tiles, fixed + work};
         }
     }
+    if (blocks == 5 && turns == 1 && best.s_log2 == 2 && sixteen.us < best.us * (best.mb == 5 ? 1.15 : 1.02))
+        return sixteen;
     return best;
 }
 

@@ -215,7 +215,7 @@ def test_qlinear_few_rows_against_oracle(fq, torch, bits, case):
 # Tiles of 64 columns that take two to eight row blocks at once: (M, N, K) and the blocks; the last row block full, with one row,
 # and with most; columns at and beside a multiple of 64; fewer groups than wavefronts, one turn, a second one for
 # some, several.
-WIDE_CASES = [((30, 11000, 1152), 2), ((48, 11008, 384), 3), ((200, 4096, 1152), 4), ((65, 8200, 1152), 5), ((80, 8250, 1024), 5),
+WIDE_CASES = [((30, 11000, 1152), 2), ((48, 11008, 384), 3), ((200, 4096, 1152), 4), ((65, 8200, 1152), 5), ((80, 8250, 1152), 5),
               ((81, 10001, 1152), 6), ((96, 11008, 1152), 6), ((110, 9100, 1152), 7), ((112, 8300, 2176), 7), ((128, 11008, 1152), 8),
               ((113, 8200, 3200), 8)]
 
@@ -346,6 +346,39 @@ def test_qlinear_of_a_few_rows_takes_any_zero_exactly(fq, torch, bits, case, zer
     err = np.abs(host16(out.half(M, N)).astype(np.float64) - r)
     bound = 2.0 ** -11 * np.abs(r) + 1e-6 * size + 2.0 ** -25
     assert np.count_nonzero(err > bound) == 0
+
+
+@pytest.mark.parametrize("zeros", ["fractions", "odd_large", "largest", "negative"])
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("case", [(210, 290, 256), (433, 421, 256), (429, 196, 1024), (825, 135, 1536), (33, 4096, 1152), (60, 4096, 2176),
+                                  (1036, 98, 128), (71, 8207, 640), (80, 8250, 1024)],
+                         ids=lambda c: "M%d_N%d_K%d" % c)
+def test_qlinear_few_row_tiles_take_any_zero_exactly(fq, torch, bits, case, zeros):
+    """Nor do the taller tiles of sixteen columns and of 32 by 32 round any weight, which serve sizes that tiles of sixteen rows would
+    serve otherwise: the bound of the test above, on sampled columns; and for sizes that tiles of 64 columns and 80 rows would
+    serve faster.  A third of the groups keep integer zeros."""
+    M, N, K = case
+    G = K // 128
+    rng = np.random.default_rng(1000 * bits + N + K)
+    codes = fq_synth.codes(84, N, K, bits)
+    s = (np.abs(fq_synth.activations(85, N, G).astype(np.float32)) * 1e-4 + 1e-4).astype(np.float16)
+    X = fq_synth.activations(86, M, K)
+    z = {"fractions": rng.uniform(0, 2 ** bits, (N, G)), "odd_large": 2 * rng.integers(512, 1024, (N, G)) + 1,
+         "largest": rng.choice([65504.0, 64512.0, 40000.0, 2049.0, 1e-6], (N, G)),
+         "negative": -rng.uniform(0, 300, (N, G))}[zeros].astype(np.float16)
+    z[:, 1::3] = fq_synth.codes(87, N, G, bits)[:, 1::3]
+    name, rows, columns = fq.fq_qlinear_route(M, N, bits, K)
+    assert name == "few_rows" and (rows == 16 or columns == 16 or (rows, columns) == (32, 32))
+    out = Guarded(torch, M * N * 2)
+    fq.fq_qlinear(dev(torch, X), fq.PackedMatrix.from_host(codes, s, z, bits), out=out.half(M, N))
+    assert out.intact()
+    cols = sampled_columns(rng, N, 90)
+    codes, s, z = codes[cols], s[cols], z[cols]
+    r = oracle.qlinear(X, oracle.dequant(codes, s, z))
+    per_code = codes.astype(np.float32) + np.repeat(np.abs(z.astype(np.float32)), 128, axis=1)
+    size = oracle.qlinear(np.abs(X), per_code * np.repeat(s.astype(np.float32), 128, axis=1))
+    err = np.abs(host16(out.half(M, N))[:, cols].astype(np.float64) - r)
+    assert np.count_nonzero(err > 2.0 ** -11 * np.abs(r) + 1e-6 * size + 2.0 ** -25) == 0
 
 
 @pytest.mark.parametrize("bits", BITS)

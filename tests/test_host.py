@@ -237,6 +237,15 @@ def test_few_row_kernel_leaves_the_sizes_that_others_run_faster(bits):
     assert fq.fq_qlinear_route(5, 16384, bits, 1664)[1:] == (16, 64)
 
 
+def test_short_rows_of_five_blocks_keep_their_zeros_exact():
+    """65 to 80 rows of up to 1024: not the tiles of 64 columns and several row blocks, which round code - zero to fp16, where three
+    rounds of sixteen rows take little more time."""
+    for M, N, bits, K in ((71, 8207, 2, 640), (80, 8250, 4, 1024), (73, 9473, 2, 1024), (69, 9624, 8, 640), (65, [1, 9368], [2, 4], 640),
+                          (79, [3227, 12, 5099], [3, 8, 2], 896), (68, [48, 3, 9480], [3, 8, 4], 1024)):
+        name, rows, columns = fq.fq_qlinear_route(M, N, bits, K)
+        assert name == "few_rows" and (rows == 16 or columns == 16 or (rows, columns) == (32, 32))
+
+
 def test_tall_tiles_leave_short_rows_to_the_others():
     """A round of 256-row tiles has a fixed part that the 128-row ones lack: measured 11.9 against 9.0 us at the first of
     these, 13.0 / 10.0, 15.8 / 13.9, 13.4 / 11.9 (and 110 / 64 for two rounds, the second one almost empty); and sizes at which the tall ones are faster."""
