@@ -340,6 +340,10 @@ __device__ __forceinline__ void skinny_wide_tile(h8 *smem, const _Float16 *__res
                                             int tile, int row_tiles)
 {
     constexpr int S = 4, H = WIDE_H, STAGE = WIDE_STAGE, COPIES = WIDE_COPIES;
+    // Bodies that have registers for the sums and operands but for little else: what follows from the lane is formed where it is used.  Kept
+    // over the turns it would spill, and a reload waits for every copy in flight (3 bits, 128 rows: 9 % more time); bodies with room take 3 to 5 %
+    // more time this way.
+    constexpr bool TIGHT = (BITS == 3 && MB == 8) || (BITS == 4 && MB >= 7);
 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, c = lane >> 4;
@@ -362,22 +366,20 @@ __device__ __forceinline__ void skinny_wide_tile(h8 *smem, const _Float16 *__res
         // part of the lane offset, which the descriptor's range check covers: rows past M read as zero and are not stored.
         h8 *const ring = smem + wave * (H * STAGE);
         const fq_rsrc xr = make_rsrc(x, (uint32_t)M * (uint32_t)K * 2u);
-        uint32_t xoff[COPIES];
-#pragma unroll
-        for (int i = 0; i < COPIES; ++i) {
-            const int row = 4 * i + c;
-            xoff[i] = ((uint32_t)(m0 + row) * (uint32_t)K + 8u * (uint32_t)(r ^ row)) * 2u;
-        }
+        // of copy 0; copy i's is 4 i rows further, and 64 i (bits that K * 2, a multiple of 256, leaves clear) exchanged in it
+        uint32_t xoff = ((uint32_t)(m0 + c) * (uint32_t)K + 8u * (uint32_t)(r ^ c)) * 2u;
         const int turns = (G - wave + SNW - 1) / SNW; // groups of this wavefront
         int nt = 0, nj = 0, ns = 0;                   // group, row block and slot of the next copy
         auto copy = [&]() { // past the end: the last group's rows again, into a stage that is not read any more
             const uint32_t off = (uint32_t)(wave + SNW * min(nt, turns - 1)) * 256u;
             uint32_t down = (uint32_t)nj * (32u * (uint32_t)K);
             asm volatile("" : "+s"(down)); // added here: the sums of all row blocks would be kept in registers
+            if constexpr (TIGHT)
+                asm volatile("" : "+v"(xoff));
             h8 *dst = ring + ns * STAGE;
 #pragma unroll
             for (int i = 0; i < COPIES; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, dst + 64 * i, 16, xoff[i] + down, off, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, dst + 64 * i, 16, (xoff ^ (64u * i)) + (down + 8u * i * (uint32_t)K), off, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             ns = (ns + 1) & (H - 1);
             if (++nj == MB) {
@@ -385,15 +387,22 @@ __device__ __forceinline__ void skinny_wide_tile(h8 *smem, const _Float16 *__res
                 ++nt;
             }
         };
+        auto lane_here = [&]() {
+            int l = lane;
+            if constexpr (TIGHT)
+                asm volatile("" : "+v"(l));
+            return l;
+        };
         uint32_t w[S * BITS];
         // Scales and zeros of the S sub-blocks, one copy of a dword a lane: sub-block u's sixteen scales and sixteen zeros
         // at bytes 64u and 64u + 32 of the turn's slots.
         char *const metas = reinterpret_cast<char *>(smem + SNW * H * STAGE + wave * (META_TURNS * META_SLOTS));
-        const char *const meta_lane = reinterpret_cast<const char *>((lane & 8) ? job.zeros : job.scales) +
-                                      ((size_t)(sb0 + min(lane >> 4, S - 1)) * G * 32 + 4 * (lane & 7));
         auto load_w = [&](int t) { // past the end: the last group again (nobody uses it)
             const int g = min(wave + SNW * t, G - 1);
-            skinny_load<BITS, S>(packed, sb0 % SUB, G, g, lane, w);
+            const int l = lane_here();
+            skinny_load<BITS, S>(packed, sb0 % SUB, G, g, l, w);
+            const char *const meta_lane = reinterpret_cast<const char *>((l & 8) ? job.zeros : job.scales) +
+                                          ((size_t)(sb0 + (l >> 4)) * G * 32 + 4 * (l & 7));
             __builtin_amdgcn_global_load_lds(meta_lane + (size_t)g * 32, metas + (t % META_TURNS) * (META_SLOTS * 16), 4, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -401,10 +410,6 @@ __device__ __forceinline__ void skinny_wide_tile(h8 *smem, const _Float16 *__res
 #pragma unroll
         for (int h = 0; h < H; ++h)
             copy();
-        int rd[4]; // slot of operand (row r, k-step s) in a stage
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-            rd[s] = r * 16 + ((4 * s + c) ^ r);
         int slot = 0; // of the stage whose operands are read next
         constexpr bool ROOM = MB <= 5; // registers for operands one stage ahead and for the scales
         h8 xf[ROOM ? 2 : 1][4];
@@ -416,9 +421,10 @@ __device__ __forceinline__ void skinny_wide_tile(h8 *smem, const _Float16 *__res
             __builtin_amdgcn_s_waitcnt(vmcnt_at_most(COPIES * (H - 1)));
             __builtin_amdgcn_sched_barrier(0);
             const h8 *stage = ring + slot * STAGE;
+            const int l = lane_here(), rd = (l & 15) * 16 + ((l >> 4) ^ (l & 15)); // slot of operand (row r, k-step 0)
 #pragma unroll
             for (int s = 0; s < 4; ++s)
-                to[s] = stage[rd[s]];
+                to[s] = stage[rd ^ (4 * s)];
             slot = (slot + 1) & (H - 1);
         };
         for (int t = 0; t < turns; ++t) {
@@ -427,6 +433,7 @@ __device__ __forceinline__ void skinny_wide_tile(h8 *smem, const _Float16 *__res
             __builtin_amdgcn_s_waitcnt(vmcnt_at_most(COPIES * (MB < H ? MB : H)));
             __builtin_amdgcn_sched_barrier(0);
             const char *const meta = metas + (t % META_TURNS) * (META_SLOTS * 16);
+            const int row = lane_here() & 15; // whose weights the lane unpacks
             h8 a[S][4];
             h4 scales[S]; // of the rows 4c..4c+3, whose sums the lane holds
             uint32_t C[S][BITS];
@@ -437,7 +444,7 @@ __device__ __forceinline__ void skinny_wide_tile(h8 *smem, const _Float16 *__res
                 skinny_chunk<BITS, S>(w, sb0 % SUB, u, C[u]);
                 if constexpr (ROOM)
                     scales[u] = *reinterpret_cast<const h4 *>(meta + 64 * u + 8 * c);
-                const _Float16 z = *reinterpret_cast<const _Float16 *>(meta + 64 * u + 32 + 2 * r); // of the row r, whose weights the lane unpacks
+                const _Float16 z = *reinterpret_cast<const _Float16 *>(meta + 64 * u + 32 + 2 * row);
                 z2[u] = h2{z, z};
                 frac |= z != __builtin_truncf16(z);
             }
@@ -464,8 +471,7 @@ __device__ __forceinline__ void skinny_wide_tile(h8 *smem, const _Float16 *__res
                 if constexpr (ROOM && j + 1 < MB)
                     read(xf[(j + 1) & 1]); // on their way during the products below
                 if constexpr (!ROOM) {
-                    int off = 8 * c;
-                    asm volatile("" : "+v"(off)); // read again: kept over the blocks they would spill
+                    const int off = 8 * (lane_here() >> 4); // read again: kept over the blocks they would spill
 #pragma unroll
                     for (int u = 0; u < S; ++u)
                         scales[u] = *reinterpret_cast<const h4 *>(meta + 64 * u + off);

@@ -317,3 +317,21 @@ def test_extension_module_leaves_what_it_does_not_take():
                  lambda: fq.fq_token_nll(x, x, out=x), lambda: fq.fq_qlinear_mixed(x, [w], out=x), lambda: fq.fq_head_nll(x, x, x, out=x, workspace=x)):
         with pytest.raises(TypeError, match="device tensor"):
             call()
+
+
+def test_no_kernel_uses_scratch_memory():
+    """Registers that do not fit are kept in memory, and a kernel whose loops wait for their copies by count waits for all of them at
+    every reload.  Read from the metadata that the compiler leaves in the library beside each kernel."""
+    msgpack = pytest.importorskip("msgpack")
+    import struct
+
+    with open(os.path.join(os.path.dirname(fq.__file__), "libfq.so"), "rb") as f:
+        raw = f.read()
+    kernels, at = [], raw.find(b"AMDGPU\0")
+    while at >= 0:
+        name, size, kind = struct.unpack("<III", raw[at - 12:at])
+        if (name, kind) == (7, 32):
+            kernels += msgpack.unpackb(raw[at + 8:at + 8 + size])["amdhsa.kernels"]
+        at = raw.find(b"AMDGPU\0", at + 7)
+    assert len([k for k in kernels if "skinny_kernel" in k[".name"]]) == 15
+    assert [k[".name"] for k in kernels if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]] == []
