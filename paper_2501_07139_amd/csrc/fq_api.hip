@@ -148,7 +148,7 @@ extern "C" int fq_qlinear_route(int M, const int *N, const int *bits, int count,
     route_out[1] = route_out[2] = 0;
     if (M <= 16 ? fq_skinny_pays(M, w, count) : fq_gemm_tile_rows(M, w, count) == 0) {
         route_out[0] = FQ_ROUTE_FEW_ROWS;
-        fq_skinny_tile(M, w, count, &route_out[1], &route_out[2]);
+        fq_skinny_us(M, w, count, &route_out[1], &route_out[2]);
     } else if (M <= 16) {
         route_out[0] = stream ? FQ_ROUTE_STREAM : FQ_ROUTE_GENERIC;
     } else {

@@ -632,7 +632,9 @@ int tall_tiles(int M, int N) { return ((N + TBN - 1) / TBN) * ((M + TBM - 1) / T
 //
 // us: the time that the choice is expected to take.  Up to 256 tiles, one a CU: 5.4 us and 1.31 us a group of 128 k; up to 512,
 // 1.5 us (3 bits 1.8) a group and more the more CUs have two; beyond, the rounds above and 6 us (tall tiles 3), on rows
-// shorter than 4096 up to 6 more.  Over 900 sizes (see skinny_plan) the time is 0.9 to 1.25 of this from K = 1500 on.
+// shorter than 4096 up to 6 more; of that 0.94 in 128-row tiles, and from K = 4096 on 0.9 of a round of tall tiles without a 3-bit
+// matrix, 0.95 of several (without these factors the few-row kernel was taken for 29 of 300 sizes that it serves 2 to 26 % more
+// slowly).  Over 900 sizes (see skinny_plan) the time is 0.9 to 1.25 of this from K = 1500 on.
 int choose_tile_rows(int M, const fq_packed_ref *w, int count, double *us)
 {
     static const double full128[9] = {0, 0, 63, 73, 67, 0, 0, 0, 73}, full256[9] = {0, 0, 61, 67, 63, 0, 0, 0, 66};
@@ -662,11 +664,12 @@ int choose_tile_rows(int M, const fq_packed_ref *w, int count, double *us)
     const double length = w[0].K / 4096.0; // of the rows, in those that the figures above were taken with
     const double fixed256 = length < 1.0 ? 1.5 * (1.0 - length) * (tall / 256 + (r256 != 0)) : 0.0;
     const double brief = length < 1.0 ? 6.0 * (1.0 - length) : 0.0;
+    const double tall_part = three != 0.0 || length < 1.0 ? 1.0 : (tall <= 256 ? 0.9 : 0.95);
     if (M > 128 && !all_wide && t256 * length + fixed256 < t128 * length) {
-        *us = 3.0 + t256 * length + fixed256 + brief;
+        *us = (3.0 + t256 * length + fixed256 + brief) * tall_part;
         return 256;
     }
-    *us = tiles <= 512 ? *us + brief : 6.0 + t128 * length + brief;
+    *us = tiles <= 512 ? *us + brief : (6.0 + t128 * length + brief) * 0.94;
     return 128;
 }
 
@@ -729,14 +732,28 @@ static int launch_tall(const void *x, int M, const fq_packed_ref *w, void *const
 // Up to sixteen rows (the linears of a stack forward, which has no use for the streaming kernel then) the few-row kernel
 // serves every launch whose offsets it can hold; beyond, the launches for which it is expected to be the faster one
 // (measured in us: 77 rows of 4096 x 11008 at 3 bits 18 against 109, 300 35 against 116, 611 69 against 117; 300 of 11008 x 4096 45 against 50, 611 83
-// against 57).
+// against 57).  On short rows the estimate of the large tiles is too low, the more the shorter (300 x 2539 x 256 at 3 bits 7.6 us against
+// 11.6 in large tiles, 55 x 15513 x 256 7.1 against 8.05, 2126 x 402 x 256 7.5 against 11.6): over 660 sizes both take the same time where
+// the few-row kernel is expected to take 1.3 to 1.4 of the other's time at K = 256, 1.2 to 1.3 at 512 and 1.0 to 1.15 up to 1408 (many rounds
+// of its sixteen-row tiles, 20 x 23466 x 256, are not ahead: 7.3 against 9.0).  Tiles of up to 32 columns have a tenth in their favour up
+// to 1280: they keep the scales in fp32, the large ones round them into the weights.
 int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count)
 {
     double us = 0.0;
     const int rows = choose_tile_rows(M, w, count, &us);
-    if (fq_skinny_can(M, w[0].K) && (M <= 16 || fq_skinny_us(M, w, count) < 0.97 * us))
+    if (!fq_skinny_can(M, w[0].K))
+        return rows;
+    if (M <= 16)
         return 0;
-    return rows;
+    const int K = w[0].K;
+    int tile[2] = {0, 0};
+    const double few = fq_skinny_us(M, w, count, &tile[0], &tile[1]);
+    double level = 0.97;
+    if (K <= 1280 && tile[0] == 16)
+        level = tile[1] < 64 ? 1.02 : 0.97;
+    else if (K <= 1280)
+        level = K <= 256 ? 1.3 : (K <= 512 ? 1.2 : (tile[1] < 64 ? 1.1 : 1.03));
+    return few < level * us ? 0 : rows;
 }
 
 int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st, int tile_rows)

@@ -28,8 +28,7 @@ int fq_launch_dequant(const fq_packed_ref &w, void *out, int out_is_fp16, fq_str
 // Few rows (fq_skinny.hip): up to three matrices that share x (same K); whether it is the faster kernel for a launch.
 bool fq_skinny_can(int M, int K);
 bool fq_skinny_pays(int M, const fq_packed_ref *w, int count);
-double fq_skinny_us(int M, const fq_packed_ref *w, int count); // estimated time of a launch
-void fq_skinny_tile(int M, const fq_packed_ref *w, int count, int *rows, int *columns);
+double fq_skinny_us(int M, const fq_packed_ref *w, int count, int *rows, int *columns); // estimated time of a launch; its tiles
 int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st);
 int fq_launch_gemv(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st);
 // Streaming decode kernel: up to three matrices that share their input and K in one launch (M <= 4).

@@ -558,21 +558,23 @@ struct SkinnyPlan {
 };
 
 // Tile shape for a launch, by estimated time.  More than sixteen rows, fitted to 900 sizes of 17 to 1400 rows, 200 to 27648
-// columns and K = 256 to 13824, every shape that can serve each (half of all times within 7 %; the shape chosen is 0.7 % slower
-// than the best one on average, 15 % at worst):
+// columns and K = 256 to 13824, every shape that can serve each, and for 16 and 32 columns, sixteen rows and the L2 to 1800 more that go
+// down to 40 columns and K = 128: of these the kernel and tile chosen take 1.2 % longer than the best one on average, 40 are more than 3 %
+// slower than the tile that the estimate ahead of these took and 9 more than 10 %, most of them calls of 4 to 8 us:
 //  - 64 columns, 32 rows and more: 2.2 us, 1.9 + 0.48 MB us a round over the chip (larger sums to add up), 0.6 + 0.4 MB us a
 //    turn of eight groups -- unpacking, then the products and the copies of MB blocks (8 bits 0.36 more, 3 bits 0.08).
-//  - 16 and 32 columns: 2.7 us, 1.8 us a round, 0.03 + 0.11 S + 0.29 MB + 0.03 S MB us a turn (8 bits 0.21 S, single dwords
+//  - 16 and 32 columns: 2.3 and 2.7 us, 1.8 us a round, 0.03 + 0.11 S + 0.29 MB + 0.03 S MB us a turn (8 bits 0.21 S, single dwords
 //    of 3 bits 0.32 S): moving the activations is what a turn takes.
-//  - sixteen rows: as below, 4.4 us and 0.88 of the turns; the smallest leave room for a second workgroup on a CU.
-// The turns take no less than the activations need to reach an XCD's L2 at 0.8 TB/s: with thirty and more row tiles the tiles
+//  - sixteen rows: as below, 4.2 us (64 columns 4.6) and 0.92 of the turns, 3 bits S = 1 0.6 in the first; the smallest leave room for a second
+//    workgroup on a CU.
+// The turns take no less than the activations need to reach an XCD's L2 at 0.9 TB/s: with thirty and more row tiles the tiles
 // that an XCD works on share hardly any.  80 rows and more a tile are the choice wherever a round of them takes what would be two of smaller
 // ones: 300 x 4096 x 4096 at 4 bits 23.5 -> 17.5 us, 300 x 4096 x 11008 at 2 bits 48 -> 35, 77 x 11008 x 4096 23.6 -> 17.2, 512
 // x 4096 x 11008 at 2 bits 60 -> 53; up to 1280 rows; beyond, an XCD's L2 holds none of the activations that its tiles share (1500 x 4096 x 11008 at 2 bits: 184 against 155).
 //
 // Five blocks of short rows (65 to 80 rows, K up to 1024, from 8193 columns on) stay in tiles of sixteen rows, which take any zero
-// exactly, where those are expected to be close (15 %; 2 % to taller tiles that make no single round of it): one round of all five
-// blocks is faster (78 x 9284 x 1024 at 2 bits 8.9 against 10.7 us) but rounds code - zero.
+// exactly, where those are expected to be close (18 %): one round of all five blocks is faster (78 x 9284 x 1024 at 2 bits 8.9
+// against 10.7 us) but rounds code - zero.  So do launches of 3- and 8-bit matrices within 2 %.
 //
 // Up to sixteen rows every shape has one row block and the number of sub-blocks is all there is to choose (it does not change
 // a sum).  Fitted to 2500 sizes of 64 to 24000 columns with each S: 3.4 us and a turn of 0.13 + 0.28 S us (8 bits 0.37 S;
@@ -582,16 +584,19 @@ SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
 {
     SkinnyPlan best = {1, 0, 1, 1e30}, sixteen = best; // sixteen: of the tiles of sixteen rows
     const int blocks = (M + 15) / 16, turns = ((w[0].K >> 7) + SNW - 1) / SNW;
-    bool eight = false;
-    for (int i = 0; i < count; ++i)
+    bool eight = false, three = false;
+    for (int i = 0; i < count; ++i) {
         eight = eight || w[i].bits == 8;
+        three = three || w[i].bits == 3;
+    }
     for (int sl = 0; sl < 3; ++sl) {
         const int S = 1 << sl;
         long col_tiles = 0;
         double one_block = 0.0; // us of a turn of a tile of one row block
         for (int i = 0; i < count; ++i) {
             col_tiles += (w[i].N + 16 * S - 1) / (16 * S);
-            const double t = w[i].bits == 3 && (S == 1 || (S == 2 && blocks == 1)) ? 0.2 + 0.5 * S : 0.13 + (w[i].bits == 8 ? 0.37 : 0.28) * S;
+            const double dwords = blocks > 1 && turns == 1 ? 0.6 : 0.2 + 0.5 * S; // 3 bits, where sub-blocks come in single dwords
+            const double t = w[i].bits == 3 && (S == 1 || (S == 2 && blocks == 1)) ? dwords : 0.13 + (w[i].bits == 8 ? 0.37 : 0.28) * S;
             one_block = one_block > t ? one_block : t;
         }
         const int largest = S == 1 ? 3 : (S == 2 ? 4 : (M > 1280 ? 4 : (eight ? WIDEST_8BIT : 8)));
@@ -604,7 +609,7 @@ SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
             double fixed, work;
             if (mb == 1) {
                 double factor = 1.0;
-                fixed = blocks == 1 ? 3.4 : (S == 4 ? 4.6 : 4.4);
+                fixed = blocks == 1 ? 3.4 : (S == 4 ? 4.6 : 4.2);
                 if (waves > 1.0 && S == 4) {
                     factor = whole;
                     fixed += factor - 1.0;
@@ -612,7 +617,7 @@ SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
                     factor = S == 1 ? (waves <= 2.0 ? 2.2 : 1.5 * waves) : (waves <= 2.0 ? 1.9 : (blocks == 1 ? 1.25 : 1.4) * waves);
                     fixed += 0.3 * waves - 0.3;
                 }
-                work = factor * turns * one_block * (blocks == 1 ? 1.0 : 0.88);
+                work = factor * turns * one_block * (blocks == 1 ? 1.0 : 0.92);
             } else {
                 double mean = 0.0, most = 0.0; // us of a turn, over the tiles of the launch
                 for (int i = 0; i < count; ++i) {
@@ -622,13 +627,13 @@ SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
                     mean += t * ((w[i].N + 16 * S - 1) / (16 * S)) / (double)col_tiles;
                     most = most > t ? most : t;
                 }
-                fixed = S == 4 ? 2.2 + whole * (1.9 + 0.48 * mb) : (S == 1 ? 2.4 : 2.7) + 1.8 * whole;
+                fixed = S == 4 ? 2.2 + whole * (1.9 + 0.48 * mb) : (S == 1 ? 2.3 : 2.7) + 1.8 * whole;
                 work = whole * turns * (whole == 1.0 ? most : mean);
             }
             if (blocks > 1) {
                 const double in_xcd = tiles > 8.0 ? tiles / 8.0 : 1.0; // 32 of them at a time, row-tile fastest
                 const double rows = 16.0 * mb * (row_tiles < 32 ? (row_tiles < in_xcd ? row_tiles : in_xcd) : (in_xcd < 32.0 ? in_xcd : 32.0));
-                const double l2 = (in_xcd > 32.0 ? in_xcd / 32.0 : 1.0) * rows * w[0].K * 2.0 / 0.8e6; // us
+                const double l2 = (in_xcd > 32.0 ? in_xcd / 32.0 : 1.0) * rows * w[0].K * 2.0 / 0.9e6; // us
                 work = work > l2 ? work : l2;
             }
             if (fixed + work < best.us)
@@ -637,7 +642,9 @@ SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
                 sixteen = {mb, sl, row_tiles, fixed + work};
         }
     }
-    if (blocks == 5 && turns == 1 && best.s_log2 == 2 && sixteen.us < best.us * (best.mb == 5 ? 1.15 : 1.02))
+    const bool rounds = best.s_log2 != 0 && best.mb > (best.s_log2 == 1 ? 2 : 1); // code - zero, to fp16
+    const double margin = best.mb == 5 && blocks == 5 && turns == 1 ? 1.18 : (eight && three ? 1.02 : 1.0);
+    if (rounds && sixteen.us < best.us * margin)
         return sixteen;
     return best;
 }
@@ -669,13 +676,12 @@ bool fq_skinny_pays(int M, const fq_packed_ref *w, int count)
     return !stream;
 }
 
-double fq_skinny_us(int M, const fq_packed_ref *w, int count) { return skinny_plan(M, w, count).us; }
-
-void fq_skinny_tile(int M, const fq_packed_ref *w, int count, int *rows, int *columns)
+double fq_skinny_us(int M, const fq_packed_ref *w, int count, int *rows, int *columns)
 {
     const SkinnyPlan plan = skinny_plan(M, w, count);
     *rows = 16 * plan.mb;
     *columns = 16 << plan.s_log2;
+    return plan.us;
 }
 
 // Up to three matrices that share the input (same K), in one launch.
