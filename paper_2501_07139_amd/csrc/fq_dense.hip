@@ -32,6 +32,9 @@ struct LossParts {
     const int32_t *labels; // [M]
     float2 *pairs;         // [M][ceil(N / 64)]: (maximum, sum of exp(logit - maximum)) of 64 columns
     float *label_logit;    // [M]: the label's logit, written only where the label is in range
+    // Kernel arguments beyond the preloaded ones would be fetched where they are first used, when the products are done: with the first
+    // copies on their way instead, the loss of up to sixteen rows takes 4 to 5 % less (2 x 7284 x 1024 9.7 -> 9.3 us).
+    __device__ __forceinline__ void fetch() const { asm volatile("" ::"s"(labels), "s"(pairs), "s"(label_logit)); }
 };
 
 template <bool FUSED>
@@ -250,6 +253,8 @@ __device__ __forceinline__ void dense_rows_tile(h8 *smem, const _Float16 *__rest
 #pragma unroll
     for (int kt = 0; kt < D - 1; ++kt)
         copy_stage(kt, kt);
+    if constexpr (FUSED)
+        loss.fetch();
     for (int kt = 0, slot = 0; kt < KT; ++kt, slot = slot == D - 1 ? 0 : slot + 1) {
         // at least COPIES * (D - 2) copies are younger than this stage's
         __builtin_amdgcn_sched_barrier(0);
@@ -445,6 +450,8 @@ __device__ __forceinline__ void dense_split_tile(h8 *smem, const _Float16 *__res
 #pragma unroll
         for (int h = 0; h < H; ++h)
             copy();
+        if constexpr (FUSED)
+            loss.fetch();
         int rd[4]; // slot of operand (row r, k-step s) in a stage
 #pragma unroll
         for (int s = 0; s < 4; ++s)
@@ -495,12 +502,16 @@ __device__ __forceinline__ void dense_split_tile(h8 *smem, const _Float16 *__res
     // The partial sums take the rings' memory, JP row blocks at a time: every wavefront's copies have to land first.
     __builtin_amdgcn_s_waitcnt(FQ_WAIT_VMCNT0);
     constexpr int JP = MB * S <= 16 ? MB : 16 / S, PASSES = (MB + JP - 1) / JP, BLOCKS = JP * S;
-    const int waves = min(SPLIT_NW, G);
     f4 *red = reinterpret_cast<f4 *>(smem);
     auto total = [&](int b) { // of block b of the pass: lane holds m = lane%16 and n = 4*(lane/16) + v
-        f4 sum = red[b * 64 + lane];
-        for (int v = 1; v < waves; ++v)
-            sum += red[(v * BLOCKS + b) * 64 + lane];
+        f4 part[SPLIT_NW]; // of all wavefronts, zeros of those without a group: read at once, one after another took the loss of one row block 0.7 us
+#pragma unroll
+        for (int v = 0; v < SPLIT_NW; ++v)
+            part[v] = red[(v * BLOCKS + b) * 64 + lane];
+        f4 sum = part[0];
+#pragma unroll
+        for (int v = 1; v < SPLIT_NW; ++v)
+            sum += part[v];
         return sum;
     };
     static_for<PASSES>([&](auto pass_tag) {
