@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from typing import Optional, Sequence
 
 import numpy as np
@@ -102,11 +103,16 @@ _lib = _load()
 
 
 def _load_bind():
-    """The extension module that the small calls go through (csrc/fq_bind.cpp), bound to the library just loaded."""
+    """The extension module that the small calls go through (csrc/fq_bind.cpp), bound to the library just loaded; None where
+    it is not there for this interpreter and torch, and those calls go through ctypes like the others."""
     try:
         from . import _bind
+        if _bind.torch_version != torch.__version__:
+            raise ImportError(f"it was built with torch {_bind.torch_version}")
     except ImportError as e:
-        raise ImportError(f"{_PKG}/_bind is not built ({e}); run `python paper_2501_07139_amd/build.py`") from e
+        warnings.warn(f"{_PKG}/_bind is not built for this Python and torch ({e}): small calls take 1.7 us longer; "
+                      "`python paper_2501_07139_amd/build.py` builds it", RuntimeWarning, stacklevel=2)
+        return None
     names = ("fq_qlinear_tile", "fq_qlinear_mixed", "fq_dense_f16", "fq_head_nll", "fq_token_nll", "fq_logit_l2")
     _bind.bind(*(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in names))
     return _bind
@@ -245,7 +251,7 @@ def fq_dequant(w: PackedMatrix, fp16: bool = False, stream=None):
 
 
 def fq_qlinear(x, w: PackedMatrix, out=None, stream=None, group: int = GROUP, tile_rows: int = 0):
-    if out is not None:
+    if _bind is not None and out is not None:
         rc = _bind.qlinear(x, w, out, stream, group, tile_rows)
         if rc is not None:
             _check(rc)
@@ -283,7 +289,7 @@ class _Segment(ctypes.Structure):
 
 def fq_qlinear_mixed(x, segments, out=None, stream=None, group: int = GROUP):
     """One matrix stored as runs of output rows, each a PackedMatrix of its own bit-width over the same K."""
-    if out is not None:
+    if _bind is not None and out is not None:
         rc = _bind.mixed(x, segments, out, stream, group)
         if rc is not None:
             _check(rc)
@@ -423,7 +429,7 @@ def fq_dense_route(M: int, N: int, K: int, loss: bool = False):
 
 def fq_dense_f16(x, W, out=None, stream=None, tile_rows: int = 0):
     """tile_rows = 128 or 256 pins one of the two kernels (fq_dense_f16_tile); 0 lets the library choose."""
-    if out is not None and not tile_rows:
+    if _bind is not None and out is not None and not tile_rows:
         rc = _bind.dense_f16(x, W, out, stream)
         if rc is not None:
             _check(rc)
@@ -444,7 +450,7 @@ def fq_dense_f16(x, W, out=None, stream=None, tile_rows: int = 0):
 
 
 def fq_logit_l2(a, b, out=None, stream=None):
-    if out is not None:
+    if _bind is not None and out is not None:
         rc = _bind.logit_l2(a, b, out, stream)
         if rc is not None:
             _check(rc)
@@ -465,7 +471,7 @@ def fq_head_nll_workspace_bytes(M: int, V: int) -> int:
 
 
 def fq_head_nll(x, W, labels, out=None, workspace=None, stream=None):
-    if out is not None and workspace is not None:
+    if _bind is not None and out is not None and workspace is not None:
         rc = _bind.head_nll(x, W, labels, out, workspace, stream)
         if rc is not None:
             _check(rc)
@@ -487,7 +493,7 @@ def fq_head_nll(x, W, labels, out=None, workspace=None, stream=None):
 
 
 def fq_token_nll(logits, labels, out=None, stream=None):
-    if out is not None:
+    if _bind is not None and out is not None:
         rc = _bind.token_nll(logits, labels, out, stream)
         if rc is not None:
             _check(rc)

@@ -262,5 +262,10 @@ PyMODINIT_FUNC PyInit__bind()
     s_n = PyUnicode_InternFromString("N");
     s_k = PyUnicode_InternFromString("K");
     s_bits = PyUnicode_InternFromString("bits");
-    return PyModule_Create(&module);
+    PyObject *m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", FQ_TORCH_VERSION) != 0) { // tensors are read by this version's layout
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
 }

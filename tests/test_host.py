@@ -354,3 +354,35 @@ def test_no_kernel_uses_scratch_memory():
         at = raw.find(b"AMDGPU\0", at + 7)
     assert len([k for k in kernels if "skinny_kernel" in k[".name"]]) == 15
     assert [k[".name"] for k in kernels if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]] == []
+
+
+@pytest.mark.parametrize("lost", ["missing", "other torch"])
+def test_package_works_without_the_extension_module(lost):
+    """On a host whose Python or torch the extension module was not built for, the package imports and its calls go through ctypes."""
+    import subprocess
+    import sys
+
+    code = """
+import sys, warnings, torch
+if sys.argv[1] == "missing":
+    sys.modules["paper_2501_07139_amd._bind"] = None
+else:
+    torch.__version__ = "0.0"
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    import paper_2501_07139_amd as fq
+assert fq._bind is None and any("_bind" in str(w.message) for w in seen)
+assert fq.fq_qlinear_route(77, 4096, 3, 11008)[0] == "few_rows"
+x, w = torch.zeros(2, 128, dtype=torch.float16), fq.PackedMatrix(*[torch.zeros(64)] * 3, 64, 128, 4)
+for call in (lambda: fq.fq_qlinear(x, w, out=x), lambda: fq.fq_dense_f16(x, x, out=x), lambda: fq.fq_logit_l2(x, x, out=x),
+             lambda: fq.fq_token_nll(x, x, out=x), lambda: fq.fq_qlinear_mixed(x, [w], out=x), lambda: fq.fq_head_nll(x, x, x, out=x, workspace=x)):
+    try:
+        call()
+    except TypeError as e:
+        assert "device tensor" in str(e)
+    else:
+        raise AssertionError("accepted a host tensor")
+"""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code, lost], cwd=root, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
