@@ -41,6 +41,16 @@ __device__ __forceinline__ const T *kernel_argument(int at)
     return reinterpret_cast<const T *>((const char *)__builtin_amdgcn_kernarg_segment_ptr() + at);
 }
 
+// Where the last argument of a kernel stands: arguments follow one another, each at the next multiple of its alignment.  Every constant that
+// is handed to kernel_argument is held against it where its kernels are declared.
+template <class... A>
+constexpr int last_argument_at(void (*)(A...))
+{
+    int at = 0, end = 0;
+    ((at = (end + (int)alignof(A) - 1) / (int)alignof(A) * (int)alignof(A), end = at + (int)sizeof(A)), ...);
+    return at;
+}
+
 __device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
 __device__ __forceinline__ uint32_t as_u32(h2 h) { return __builtin_bit_cast(uint32_t, h); }
 

@@ -608,6 +608,8 @@ __global__ __launch_bounds__(512, 1) void qgemm_tall_kernel(const _Float16 *__re
     }
 }
 
+static_assert(last_argument_at(qgemm_multi_kernel) == GEMM_JOBS_AT && last_argument_at(qgemm_tall_kernel) == GEMM_JOBS_AT);
+
 // Weight-tile width.  Wide tiles (each wavefront 128 x 64) halve the LDS reads and activation copies per
 // MFMA but need at least two workgroups per CU to keep both wavefront slots of every SIMD filled.
 int wide_tiles_pay(int M, int N)

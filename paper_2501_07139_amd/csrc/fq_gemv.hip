@@ -708,6 +708,7 @@ __global__ __launch_bounds__(64 * GNW, 4) void gemv_stream_kernel(const _Float16
 }
 
 typedef void (*GemvKernel)(const _Float16 *, const _Float16 *, const _Float16 *, _Float16 *, int, int, int, int, GemvJobs);
+static_assert(last_argument_at(GemvKernel{}) == GEMV_JOBS_AT);
 
 // One kernel per input mode, for a single activation row and for several (mode 6, the decode step's, has one only).
 constexpr int GEMV_VARIANTS = 14, GEMV_MAX_PER_CU = 4;

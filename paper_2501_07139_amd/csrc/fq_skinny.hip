@@ -549,6 +549,7 @@ __global__ __launch_bounds__(64 * SNW, (MB == 1 && S <= 2) ? 4 : 2) void skinny_
 }
 
 typedef void (*SkinnyKernel)(const _Float16 *, int, int, int, int, int, int, SkinnyJobs);
+static_assert(last_argument_at(SkinnyKernel{}) == SKINNY_JOBS_AT);
 
 constexpr int SKINNY_CUS = 256;
 
