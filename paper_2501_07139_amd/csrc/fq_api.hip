@@ -146,16 +146,15 @@ extern "C" int fq_qlinear_route(int M, const int *N, const int *bits, int count,
         stream = stream && fq_gemv_can_stream(M, K, bits[i], 0);
     }
     route_out[1] = route_out[2] = 0;
-    if (M <= 16 ? fq_skinny_pays(M, w, count) : fq_gemm_tile_rows(M, w, count) == 0) {
-        route_out[0] = FQ_ROUTE_FEW_ROWS;
-        fq_skinny_us(M, w, count, &route_out[1], &route_out[2]);
-    } else if (M <= 16) {
+    if (M <= 16 && !fq_skinny_pays(M, w, count)) {
         route_out[0] = stream ? FQ_ROUTE_STREAM : FQ_ROUTE_GENERIC;
-    } else {
-        route_out[1] = fq_gemm_tile_rows(M, w, count);
-        route_out[2] = 128;
-        route_out[0] = route_out[1] == 256 ? FQ_ROUTE_TILES_256 : FQ_ROUTE_TILES_128;
+        return FQ_OK;
     }
+    fq_skinny_plan few;
+    const int rows = fq_gemm_tile_rows(M, w, count, &few);
+    route_out[0] = rows == 0 ? FQ_ROUTE_FEW_ROWS : (rows == 256 ? FQ_ROUTE_TILES_256 : FQ_ROUTE_TILES_128);
+    route_out[1] = rows == 0 ? 16 * few.mb : rows;
+    route_out[2] = rows == 0 ? 16 << few.s_log2 : 128;
     return FQ_OK;
 }
 
@@ -201,7 +200,7 @@ extern "C" int fq_qlinear_mixed(const void *x, int M, const fq_segment *segments
         if (M > 16)
             e = fq_launch_gemm_multi(x, M, &w[i], &outs[i], n, st);
         else if (fq_skinny_pays(M, &w[i], n))
-            e = fq_launch_skinny(x, M, &w[i], &outs[i], n, st);
+            e = fq_launch_skinny(x, M, &w[i], &outs[i], n, fq_plan_skinny(M, &w[i], n), st);
         else if (stream_all)
             e = fq_launch_gemv_multi(fq_gemv_input{x, nullptr, nullptr, nullptr, 0}, M, &w[i], &outs[i], n, st);
         else
@@ -241,12 +240,8 @@ extern "C" int fq_dense_f16_tile(const void *x, int M, const void *W, int N, int
         return fq_fail(FQ_ERR_SHAPE, "fq_dense_f16: M=%d N=%d K=%d: x and W must each stay below 4 GiB", M, N, K);
     if (tile_rows != 0 && tile_rows != 128 && tile_rows != 256)
         return fq_fail(FQ_ERR_SHAPE, "fq_dense_f16_tile: tile_rows=%d not in {0, 128, 256}", tile_rows);
-    if (tile_rows == 0 && fq_dense_few_pays(M, N, K))
-        return check_hip(fq_launch_dense_few(x, M, W, N, K, out, static_cast<fq_stream>(stream)), "fq_dense_f16 launch");
-    if (tile_rows != 128) // what the few-row tiles leave is at least half a large tile a CU
-        return check_hip(fq_launch_dense_tiled(x, M, W, N, K, out, static_cast<fq_stream>(stream)),
-                         "fq_dense_f16 launch");
-    return check_hip(fq_launch_dense(x, M, W, N, K, out, static_cast<fq_stream>(stream)), "fq_dense_f16 launch");
+    auto *launch = tile_rows == 0 ? fq_launch_dense_planned : (tile_rows == 256 ? fq_launch_dense_tiled : fq_launch_dense);
+    return check_hip(launch(x, M, W, N, K, out, static_cast<fq_stream>(stream)), "fq_dense_f16 launch");
 }
 
 extern "C" int fq_dense_route(int M, int N, int K, int loss, int *route_out)

@@ -718,11 +718,11 @@ void fq_dense_plan(int M, int N, int K, bool fused, int *kind, int *rows, int *c
     *columns = plan.columns;
 }
 
-bool fq_dense_few_pays(int M, int N, int K) { return dense_plan(M, N, K, false).kind != DENSE_LARGE; }
-
-int fq_launch_dense_few(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st)
+int fq_launch_dense_planned(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st)
 {
-    return launch_few(dense_plan(M, N, K, false), false, x, M, W, N, K, out, LossParts{}, st);
+    const DensePlan plan = dense_plan(M, N, K, false);
+    return plan.kind == DENSE_LARGE ? fq_launch_dense_tiled(x, M, W, N, K, out, st)
+                                    : launch_few(plan, false, x, M, W, N, K, out, LossParts{}, st);
 }
 
 // x and W are addressed through 32-bit byte offsets (checked by the caller); K is a multiple of 128.

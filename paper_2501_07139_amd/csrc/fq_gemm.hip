@@ -636,7 +636,7 @@ int tall_tiles(int M, int N) { return ((N + TBN - 1) / TBN) * ((M + TBM - 1) / T
 // 1.5 us (3 bits 1.8) a group and more the more CUs have two; beyond, the rounds above and 6 us (tall tiles 3), on rows
 // shorter than 4096 up to 6 more; of that 0.94 in 128-row tiles, and from K = 4096 on 0.9 of a round of tall tiles without a 3-bit
 // matrix, 0.95 of several (without these factors the few-row kernel was taken for 29 of 300 sizes that it serves 2 to 26 % more
-// slowly).  Over 900 sizes (see skinny_plan) the time is 0.9 to 1.25 of this from K = 1500 on.
+// slowly).  Over 900 sizes (see fq_plan_skinny) the time is 0.9 to 1.25 of this from K = 1500 on.
 int choose_tile_rows(int M, const fq_packed_ref *w, int count, double *us)
 {
     static const double full128[9] = {0, 0, 63, 73, 67, 0, 0, 0, 73}, full256[9] = {0, 0, 61, 67, 63, 0, 0, 0, 66};
@@ -739,23 +739,23 @@ static int launch_tall(const void *x, int M, const fq_packed_ref *w, void *const
 // the few-row kernel is expected to take 1.3 to 1.4 of the other's time at K = 256, 1.2 to 1.3 at 512 and 1.0 to 1.15 up to 1408 (many rounds
 // of its sixteen-row tiles, 20 x 23466 x 256, are not ahead: 7.3 against 9.0).  Tiles of up to 32 columns have a tenth in their favour up
 // to 1280: they keep the scales in fp32, the large ones round them into the weights.
-int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count)
+int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count, fq_skinny_plan *few)
 {
     double us = 0.0;
     const int rows = choose_tile_rows(M, w, count, &us);
     if (!fq_skinny_can(M, w[0].K))
         return rows;
+    *few = fq_plan_skinny(M, w, count);
     if (M <= 16)
         return 0;
     const int K = w[0].K;
-    int tile[2] = {0, 0};
-    const double few = fq_skinny_us(M, w, count, &tile[0], &tile[1]);
+    const bool narrow = few->s_log2 < 2;
     double level = 0.97;
-    if (K <= 1280 && tile[0] == 16)
-        level = tile[1] < 64 ? 1.02 : 0.97;
+    if (K <= 1280 && few->mb == 1)
+        level = narrow ? 1.02 : 0.97;
     else if (K <= 1280)
-        level = K <= 256 ? 1.3 : (K <= 512 ? 1.2 : (tile[1] < 64 ? 1.1 : 1.03));
-    return few < level * us ? 0 : rows;
+        level = K <= 256 ? 1.3 : (K <= 512 ? 1.2 : (narrow ? 1.1 : 1.03));
+    return few->us < level * us ? 0 : rows;
 }
 
 int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st, int tile_rows)
@@ -763,10 +763,11 @@ int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_s
     const size_t Np = ((size_t)w.N + 63) / 64 * 64;
     if (!fits_32bit(M, w.K, 2) || Np / 8 * w.K * w.bits >= ((size_t)1 << 32))
         return (int)hipErrorInvalidValue;
+    fq_skinny_plan few;
     if (tile_rows == 0)
-        tile_rows = fq_gemm_tile_rows(M, &w, 1);
+        tile_rows = fq_gemm_tile_rows(M, &w, 1, &few);
     if (tile_rows == 0)
-        return fq_launch_skinny(x, M, &w, &out, 1, st);
+        return fq_launch_skinny(x, M, &w, &out, 1, few, st);
     if (tile_rows == 256)
         return launch_tall(x, M, &w, &out, 1, st);
     if (w.ld && w.ld != w.N) // a column range of a wider output: the multi-matrix kernel carries the row pitch
@@ -790,10 +791,11 @@ int fq_launch_gemm_multi(const void *x, int M, const fq_packed_ref *w, void *con
         if (w[i].K != w[0].K || !fits_32bit(M, w[i].K, 2) || Np / 8 * w[i].K * w[i].bits >= ((size_t)1 << 32))
             return (int)hipErrorInvalidValue;
     }
+    fq_skinny_plan few;
     if (tile_rows == 0)
-        tile_rows = fq_gemm_tile_rows(M, w, count);
+        tile_rows = fq_gemm_tile_rows(M, w, count, &few);
     if (tile_rows == 0)
-        return fq_launch_skinny(x, M, w, outs, count, st);
+        return fq_launch_skinny(x, M, w, outs, count, few, st);
     if (tile_rows == 256)
         return launch_tall(x, M, w, outs, count, st);
     auto qnb = [&](int i) { return (w[i].bits == 2 || w[i].bits == 4) && wide_tiles_pay(M, w[i].N) ? 4 : 2; };

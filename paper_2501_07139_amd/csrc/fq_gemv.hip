@@ -942,7 +942,7 @@ int fq_launch_gemv_multi(const fq_gemv_input &src, int M, const fq_packed_ref *w
 int fq_launch_gemv(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st)
 {
     if (fq_skinny_pays(M, &w, 1))
-        return fq_launch_skinny(x, M, &w, &out, 1, st);
+        return fq_launch_skinny(x, M, &w, &out, 1, fq_plan_skinny(M, &w, 1), st);
     if (fq_gemv_can_stream(M, w.K, w.bits, 0)) {
         const fq_gemv_input src = {x, nullptr, nullptr, nullptr, 0};
         return fq_launch_gemv_multi(src, M, &w, &out, 1, st);

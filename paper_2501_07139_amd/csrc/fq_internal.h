@@ -28,8 +28,12 @@ int fq_launch_dequant(const fq_packed_ref &w, void *out, int out_is_fp16, fq_str
 // Few rows (fq_skinny.hip): up to three matrices that share x (same K); whether it is the faster kernel for a launch.
 bool fq_skinny_can(int M, int K);
 bool fq_skinny_pays(int M, const fq_packed_ref *w, int count);
-double fq_skinny_us(int M, const fq_packed_ref *w, int count, int *rows, int *columns); // estimated time of a launch; its tiles
-int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st);
+struct fq_skinny_plan {
+    int mb, s_log2, row_tiles; // tiles of 16 * mb rows by 16 << s_log2 columns; row tiles of the launch
+    double us;                 // estimated time
+};
+fq_skinny_plan fq_plan_skinny(int M, const fq_packed_ref *w, int count);
+int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, const fq_skinny_plan &plan, fq_stream st);
 int fq_launch_gemv(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st);
 // Streaming decode kernel: up to three matrices that share their input and K in one launch (M <= 4).
 // The input is x = f(a, b, c), fp16 [M,K] each, with the block's row-wise glue folded in:
@@ -64,18 +68,17 @@ int fq_decode_set_mode(int mode);    // 0: per-phase launches (default), 1: pers
 unsigned long long fq_decode_launches(); // persistent launches queued by this process so far
 int fq_decode_available(int H, int F); // pages per ring if the persistent kernel would run, else 0
 void fq_decode_partition_of(unsigned bits4, int ph, int N, int wg, int grid, int *out6);
-// M > 16.  Height of the large tiles of a launch (128 or 256), 0: the few-row kernel.
-int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count);
+// Height of the large tiles of a launch (128 or 256); 0: the few-row kernel, with this plan.
+int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count, fq_skinny_plan *few);
 // tile_rows: 0 lets the library choose, 128 or 256 pins one of the large-tile kernels.
 int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st, int tile_rows = 0);
 // Up to three matrices with the same input (same K) in one launch; M > 16, or any M for the few-row kernel.
 int fq_launch_gemm_multi(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st,
                          int tile_rows = 0);
-// Dense fp16 product: tiles of 16 to 128 rows that stream W or share K, and whether they are the library's choice; 256 x 256 tiles,
-// both operands through LDS, for what they leave; 128-row tiles, only where a caller asks for that height.
+// Dense fp16 product: as planned, in tiles of 16 to 128 rows that stream W or share K or in 256 x 256 tiles, both operands through
+// LDS; 128-row tiles, only where a caller asks for that height.
 void fq_dense_plan(int M, int N, int K, bool fused, int *kind, int *rows, int *columns); // kind: see FQ_DENSE_*
-bool fq_dense_few_pays(int M, int N, int K);
-int fq_launch_dense_few(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
+int fq_launch_dense_planned(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
 int fq_launch_dense(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
 int fq_launch_dense_tiled(const void *x, int M, const void *W, int N, int K, void *out, fq_stream st);
 // Head GEMM with the token loss in its epilogue; workspace of fq_head_nll_scratch_bytes(M, V) bytes.

@@ -517,7 +517,7 @@ __device__ __forceinline__ void skinny_any(h8 *smem, const _Float16 *__restrict_
         skinny_tile<BITS, MB, S>(smem, x, M, K, job, tile, row_tiles);
 }
 
-// 8-bit chunks and more than five row blocks are more registers than there are; skinny_plan does not put them together.
+// 8-bit chunks and more than five row blocks are more registers than there are; fq_plan_skinny does not put them together.
 constexpr int WIDEST_8BIT = 5;
 
 // The scalars come first: the build has them preloaded into registers at wavefront start, so that which tile, of which matrix, is known
@@ -553,10 +553,7 @@ static_assert(last_argument_at(SkinnyKernel{}) == SKINNY_JOBS_AT);
 
 constexpr int SKINNY_CUS = 256;
 
-struct SkinnyPlan {
-    int mb, s_log2, row_tiles;
-    double us;
-};
+} // namespace
 
 // Tile shape for a launch, by estimated time.  More than sixteen rows, fitted to 900 sizes of 17 to 1400 rows, 200 to 27648
 // columns and K = 256 to 13824, every shape that can serve each, and for 16 and 32 columns, sixteen rows and the L2 to 1800 more that go
@@ -581,9 +578,9 @@ struct SkinnyPlan {
 // a sum).  Fitted to 2500 sizes of 64 to 24000 columns with each S: 3.4 us and a turn of 0.13 + 0.28 S us (8 bits 0.37 S;
 // 3 bits S = 1 0.7, S = 2 1.2) while every CU has one tile; a second one on some CUs costs nearly a second turn, and from two a
 // CU on the time grows with the tiles.  64 columns a tile just beyond one round (20739 x 1664, 4 bits) 11.3 us, 32 columns 9.8.
-SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
+fq_skinny_plan fq_plan_skinny(int M, const fq_packed_ref *w, int count)
 {
-    SkinnyPlan best = {1, 0, 1, 1e30}, sixteen = best; // sixteen: of the tiles of sixteen rows
+    fq_skinny_plan best = {1, 0, 1, 1e30}, sixteen = best; // sixteen: of the tiles of sixteen rows
     const int blocks = (M + 15) / 16, turns = ((w[0].K >> 7) + SNW - 1) / SNW;
     bool eight = false, three = false;
     for (int i = 0; i < count; ++i) {
@@ -650,8 +647,6 @@ SkinnyPlan skinny_plan(int M, const fq_packed_ref *w, int count)
     return best;
 }
 
-} // namespace
-
 // Whether the kernel's 32-bit byte offsets reach all of a launch's activations and of a tile's weights.
 bool fq_skinny_can(int M, int K) { return K <= (1 << 22) && (size_t)M * K * 2 < ((size_t)1 << 32); }
 
@@ -677,16 +672,8 @@ bool fq_skinny_pays(int M, const fq_packed_ref *w, int count)
     return !stream;
 }
 
-double fq_skinny_us(int M, const fq_packed_ref *w, int count, int *rows, int *columns)
-{
-    const SkinnyPlan plan = skinny_plan(M, w, count);
-    *rows = 16 * plan.mb;
-    *columns = 16 << plan.s_log2;
-    return plan.us;
-}
-
-// Up to three matrices that share the input (same K), in one launch.
-int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st)
+// Up to three matrices that share the input (same K), in one launch; plan: fq_plan_skinny's for it.
+int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, const fq_skinny_plan &plan, fq_stream st)
 {
     static const SkinnyKernel table[8][3] = {
         {skinny_kernel<1, 1>, skinny_kernel<1, 2>, skinny_kernel<1, 4>},
@@ -698,7 +685,6 @@ int fq_launch_skinny(const void *x, int M, const fq_packed_ref *w, void *const *
         {nullptr, nullptr, skinny_kernel<7, 4>},
         {nullptr, nullptr, skinny_kernel<8, 4>},
     };
-    const SkinnyPlan plan = skinny_plan(M, w, count);
     SkinnyJobs jobs = {};
     int first[4] = {0, INT_MAX, INT_MAX, INT_MAX}, total = 0;
     for (int i = 0; i < count; ++i) {
