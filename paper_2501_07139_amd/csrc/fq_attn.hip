@@ -620,9 +620,12 @@ static void launch_prefill(PrefillArgs a, fq_stream st)
 }
 
 // Query rows per workgroup.  A CU holds two workgroups, and a workgroup's time is its key tiles, one after another, each mostly
-// latency and the reads of its operands from LDS.  128 rows read the least LDS per product and serve the largest grids; while
-// smaller tiles are still resident together, more of them at a time are worth the repeated reads: 64 rows up to three
-// workgroups a CU, and 32 rows, every key tile halved between two wavefronts, up to two and a half.  Measured with the preparing kernel (us,
+// latency and the reads of its operands from LDS.  128 rows read the least LDS per product and serve the largest grids; on
+// smaller ones more tiles at a time are worth the repeated reads.  The lines are where the measured times cross, over 500 sizes of 1 to 64
+// heads and 64 to 4096 positions: 32 rows, every key tile halved between two wavefronts, take 0.90 to 0.97 of the time of 64 up to 640
+// workgroups of them (513 to 640: 0.96, up to 256 positions 1.0), 1.03 at 641 to 704 and 1.13 from 769 on; 64 rows 0.7 to 0.9 of that of
+// 128 up to 768 workgroups, 0.97 to 1.0 up to 900 and 1.04 beyond.  This choice takes 0.3 % longer than the best tile of each size, and no
+// other pair of lines less than 0.2 %.  Some of them, measured with the preparing kernel (us,
 // 128 / 64 / 32 rows): 8 heads, 611 positions 24.9 / 18.4 / 16.6, 2048 63 / 45 / 39, 4096 113 / 79 / 97; 32 heads, 128 positions
 // 12.6 / 10.7 / 10.7, 300 18.9 / 15.7 / 16.1, 611 31 / 25.5 / 24.8, 800 35 / 28.6 / 31.8, 1200 50 / 38.6 / 49, 1500 59 / 53.7 / 66, 2048
 // 76 / 81 / 102.  (64 rows as two wavefronts of 32 rows by two halves read half the LDS of 64 rows and are slower: 611 positions

@@ -393,8 +393,9 @@ int launch_rows(bool fused, int mb, const void *x, int M, const void *W, int N, 
 // sixteen rows of either operand over one group are a stage (4 KiB) of a ring in LDS that is the wavefront's own, filled by
 // direct copies: the S stages of the weights, then the MB stages of the activations, one after the other, so there is no barrier in
 // the loop and a wavefront waits, by count, for its oldest stage only.  Partial sums meet in LDS, in a fixed order.
-// Bound by the way from L2 into LDS, which both operands of every tile take (26 to 33 TB/s over the chip, measured by itself):
-// 100 x 4000 x 4096 is 252 tiles of 64 x 32, 198 MB and 14.0 us (2.5 times as fast as tiles of 128 x 128).
+// Bound by latency, of the first stages and of the sums at the end, more than by the way from L2 into LDS that both operands of every tile
+// take (26 to 33 TB/s over the chip by itself): 100 x 4000 x 4096 is 250 tiles of 64 x 32, 197 MB in 13.6 us with the launch, 14 TB/s (2.5
+// times as fast as tiles of 128 x 128).
 constexpr int SPLIT_NW = 8, SPLIT_H = 4, SPLIT_STAGE = 256, SPLIT_COPIES = 4; // wavefronts; stages, 16-byte slots of one, copies that fill one
 
 template <int MB, int S, bool FUSED>

@@ -568,7 +568,9 @@ constexpr int SKINNY_CUS = 256;
 // The turns take no less than the activations need to reach an XCD's L2 at 0.9 TB/s: with thirty and more row tiles the tiles
 // that an XCD works on share hardly any.  80 rows and more a tile are the choice wherever a round of them takes what would be two of smaller
 // ones: 300 x 4096 x 4096 at 4 bits 23.5 -> 17.5 us, 300 x 4096 x 11008 at 2 bits 48 -> 35, 77 x 11008 x 4096 23.6 -> 17.2, 512
-// x 4096 x 11008 at 2 bits 60 -> 53; up to 1280 rows; beyond, an XCD's L2 holds none of the activations that its tiles share (1500 x 4096 x 11008 at 2 bits: 184 against 155).
+// x 4096 x 11008 at 2 bits 60 -> 53; up to 1280 rows, where the sizes end that their times were fitted to: beyond, they are up to a half longer
+// (1500 x 4096 x 11008 at 2 bits 184 us, against 155 in the large tiles).  Of 400 sizes of 700 to 4000 rows 9 would be more than 10 % slower
+// without that line, and all together 3 % faster: it is a matter for a fit of its own.
 //
 // Five blocks of short rows (65 to 80 rows, K up to 1024, from 8193 columns on) stay in tiles of sixteen rows, which take any zero
 // exactly, where those are expected to be close (18 %): one round of all five blocks is faster (78 x 9284 x 1024 at 2 bits 8.9
