@@ -15,6 +15,7 @@
 #include "fq.h"
 
 #include <climits>
+#include <memory>
 
 namespace {
 
@@ -156,12 +157,14 @@ PyObject *mixed(PyObject *, PyObject *const *a, Py_ssize_t n) // x, segments (li
         const at::Tensor *x = half_matrix(a[0], &M, &K), *out = device_tensor(a[2], at::kHalf);
         if (!x || !out || !(PyList_CheckExact(a[1]) || PyTuple_CheckExact(a[1])) || !stream_of(a[3], &stream) || !int_of(a[4], &group))
             return false;
-        const Py_ssize_t count = PySequence_Fast_GET_SIZE(a[1]);
+        // its items, held: reading an attribute may run Python code, which may change the list
+        const std::unique_ptr<PyObject, void (*)(PyObject *)> items(PySequence_Tuple(a[1]), [](PyObject *o) { Py_DECREF(o); });
+        const Py_ssize_t count = items ? PyTuple_GET_SIZE(items.get()) : 0;
         if (count < 1 || count > FQ_MAX_SEGMENTS)
             return false;
         for (Py_ssize_t i = 0; i < count; ++i) {
             int wk;
-            if (!matrix_of(PySequence_Fast_GET_ITEM(a[1], i), &seg[i], &wk) || wk != K)
+            if (!matrix_of(PyTuple_GET_ITEM(items.get(), i), &seg[i], &wk) || wk != K)
                 return false;
         }
         const void *px = x->data_ptr();

@@ -1261,6 +1261,27 @@ def test_qlinear_on_seeded_random_shapes(fq, torch, case):
         assert qerr(host16(out.half(M, N)), want) <= TOL, tile_rows
 
 
+def test_qlinear_mixed_holds_its_segments(fq, torch):
+    """A segment whose attributes are computed may change the list that it came in: the call goes on with the ones it was given."""
+    x = dev(torch, fq_synth.activations(95, 5, 256))
+    made = [fq.PackedMatrix.from_host(*oracle.quantize_rtn(fq_synth.weights(96 + n, n, 256), 4), 4) for n in (70, 64, 96)]
+    want = fq.fq_qlinear_mixed(x, made)
+
+    class Leaves:
+        def __init__(self, w, segments):
+            self.w, self.segments = w, segments
+
+        def __getattr__(self, name):
+            self.segments.clear()
+            return getattr(self.w, name)
+
+    segments = []
+    segments += [Leaves(w, segments) for w in made]
+    out = torch.zeros_like(want)
+    assert fq.fq_qlinear_mixed(x, segments, out=out) is out and segments == []
+    assert torch.equal(out, want)
+
+
 def test_calls_with_an_output_agree_with_those_that_allocate(fq, torch):
     """With every buffer given a call goes through the extension module: the same results bit for bit, on the current stream, on one
     given by object or by handle, and the same refusals."""
