@@ -634,9 +634,9 @@ int tall_tiles(int M, int N) { return ((N + TBN - 1) / TBN) * ((M + TBM - 1) / T
 //
 // us: the time that the choice is expected to take.  Up to 256 tiles, one a CU: 5.4 us and 1.31 us a group of 128 k; up to 512,
 // 1.5 us (3 bits 1.8) a group and more the more CUs have two; beyond, the rounds above and 6 us (tall tiles 3), on rows
-// shorter than 4096 up to 6 more; of that 0.94 in 128-row tiles, and from K = 4096 on 0.9 of a round of tall tiles without a 3-bit
-// matrix, 0.95 of several (without these factors the few-row kernel was taken for 29 of 300 sizes that it serves 2 to 26 % more
-// slowly).  Over 900 sizes (see fq_plan_skinny) the time is 0.9 to 1.25 of this from K = 1500 on.
+// shorter than 4096 up to 6 more.  Of that 0.92 in 128-row tiles (with a 3-bit matrix 0.9), up to 512 of them from K = 4096 on, and there too
+// 0.9 of a round of tall tiles without a 3-bit matrix, 0.95 of several: without these factors the few-row kernel was taken for 29 of
+// 300 sizes that it serves 2 to 26 % more slowly, with them for 10, up to 8 %.
 int choose_tile_rows(int M, const fq_packed_ref *w, int count, double *us)
 {
     static const double full128[9] = {0, 0, 63, 73, 67, 0, 0, 0, 73}, full256[9] = {0, 0, 61, 67, 63, 0, 0, 0, 66};
@@ -671,7 +671,8 @@ int choose_tile_rows(int M, const fq_packed_ref *w, int count, double *us)
         *us = (3.0 + t256 * length + fixed256 + brief) * tall_part;
         return 256;
     }
-    *us = tiles <= 512 ? *us + brief : (6.0 + t128 * length + brief) * 0.94;
+    const double long_part = three != 0.0 ? 0.9 : 0.92;
+    *us = tiles <= 512 ? (*us + brief) * (length < 1.0 ? 1.0 : long_part) : (6.0 + t128 * length + brief) * long_part;
     return 128;
 }
 

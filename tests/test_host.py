@@ -268,6 +268,8 @@ def test_short_rows_of_five_blocks_keep_their_zeros_exact():
 def test_tall_tiles_leave_short_rows_to_the_others():
     """A round of 256-row tiles has a fixed part that the 128-row ones lack: measured 11.9 against 9.0 us at the first of
     these, 13.0 / 10.0, 15.8 / 13.9, 13.4 / 11.9 (and 110 / 64 for two rounds, the second one almost empty); and sizes at which the tall ones are faster."""
+    for M, N, bits, K in ((638, 17743, 3, 12544), (1152, 7079, 3, 8832)):  # and many rounds, to the 128-row ones: 328 against 341, 164 / 184 in few-row tiles
+        assert route(M, N, bits, K) == "tiles_128"
     for M, N, bits, K in ((229, 20424, 4, 128), (1842, 3280, 3, 128), (1932, 3144, 4, 384), (675, 5636, 8, 256), (640, 11008, 4, 4096)):
         assert route(M, N, bits, K) == "tiles_128"
     for M, N, bits, K in ((2048, 11008, 2, 4096), (2048, 4096, 8, 11008), (2048, 11008, 3, 1024)):
