@@ -152,7 +152,8 @@ int fq_dequant(const void *packed, const void *scales, const void *zeros,
  * rows per workgroup, and 256 rows per workgroup of eight wavefronts with the
  * k-steps of every group split over two wavefront sets (each unpacked weight
  * feeds twice as many matrix instructions); the library takes whichever needs less
- * time for its rounds of tiles over the chip (as measured on MI355X).
+ * time for its rounds of tiles over the chip (as measured on MI355X).  The rows of a
+ * launch of the latter are cut into tiles of equal height, 128 to 256, by the same measure.
  * fq_qlinear_tile is the same call with the choice
  * made by the caller: tile_rows = 128 or 256 pins a kernel (any M > 16; for tests
  * and tuning; ignored for M <= 16), 0 leaves it to the library; anything else is
@@ -165,7 +166,7 @@ int fq_qlinear_tile(const void *x, int M, const void *packed, const void *scales
 /*
  * The kernel that fq_qlinear takes, or a launch of up to three matrices that share x (host only; for tests and tools).
  * N, bits: host, count entries.  route_out (host, 3 ints): one of FQ_ROUTE_*, then rows and columns of its tiles
- * (0, 0 for the first two).
+ * (0, 0 for the first two; FQ_ROUTE_TILES_256: 256, the most they have, and FQ_ROUTE_TILES_128: 128, in either kernel).
  */
 enum { FQ_ROUTE_STREAM, FQ_ROUTE_GENERIC, FQ_ROUTE_FEW_ROWS, FQ_ROUTE_TILES_128, FQ_ROUTE_TILES_256 };
 int fq_qlinear_route(int M, const int *N, const int *bits, int count, int K, int *route_out);

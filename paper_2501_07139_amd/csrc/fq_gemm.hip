@@ -369,7 +369,7 @@ __global__ __launch_bounds__(256, 2) void qgemm_multi_kernel(const _Float16 *__r
 }
 
 // ------------------------------------------------------------ tall tiles
-// 256 activation rows x 128 weight rows per workgroup of eight wavefronts, one workgroup per CU, for products
+// Up to 256 activation rows x 128 weight rows per workgroup of eight wavefronts, one workgroup per CU, for products
 // with many rows.  In the 128-row kernels every unpacked weight operand feeds 8 MFMAs and the unpacking is the
 // largest share of what a wavefront issues beside its MFMAs; here a wavefront owns 256 x 32 outputs (128
 // accumulator registers), so an operand feeds 16.  A 4096-column product at 2048 rows has only 256 such tiles,
@@ -415,75 +415,31 @@ __device__ __forceinline__ void load_whalf(WChunk<BITS> &w, const GemmBuffers &b
     w.zero = buf_load_u16(buf.zeros, mlo, meta_off);
 }
 
-// One 256 x 128 output tile.  Xs0, Xs1: the two activation tiles (256 rows x 128 k each, laid out like the
-// narrow tiles'); after the loop the same memory carries the second K half's partial sums to the first.
-template <int BITS>
-__device__ __forceinline__ void qgemm_tall_tile(h8 *Xs0, h8 *Xs1, const _Float16 *__restrict__ x, int M,
-                                                const uint32_t *__restrict__ packed,
-                                                const _Float16 *__restrict__ scales,
-                                                const _Float16 *__restrict__ zeros, int N, int K,
-                                                _Float16 *__restrict__ out, int ld, int tile)
-{
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int kh = wave >> 2, nq = wave & 3; // half of every group's k-steps, quarter of the tile's weight rows
-    // tiles are numbered in bands of two activation row-tiles (row-tile fastest): the 32 tiles an XCD holds at a
-    // time share 512 activation rows (4 MiB at k = 4096, the size of its L2) and 16 weight tiles
-    const int NT = (N + TBN - 1) / TBN, MT = (M + TBM - 1) / TBM;
-    const int band = tile / (2 * NT), rest = tile - band * 2 * NT, height = min(2, MT - 2 * band);
-    const int m0 = (2 * band + rest % height) * TBM, n0 = (rest / height) * TBN;
-    const int G = K >> 7;
-    const int Np16 = ((N + 63) / 64 * 64) >> 4;
-    const int rb0 = (n0 >> 4) + nq * TNB;
-
+// What a tall tile's body works on.
+struct TallTile {
     GemmBuffers buf;
-    buf.x = make_rsrc(x, (uint32_t)M * (uint32_t)K * 2u);
-    const uint32_t Np = (uint32_t)(N + 63) / 64u * 64u;
-    buf.packed = make_rsrc(packed, Np / 8u * (uint32_t)K * (uint32_t)BITS);
-    buf.scales = make_rsrc(scales, Np * (uint32_t)G * 2u);
-    buf.zeros = make_rsrc(zeros, Np * (uint32_t)G * 2u);
+    _Float16 *out;
+    uint32_t xoff0, xstep; // byte offset of the lane's part of copy 0, and from one copy to the next (32 rows)
+    int rb0, Np16, G, K;   // first sixteen-row weight block of the wavefront, those that there are, groups
+    int m0, m_end, N, ld;
+};
 
-    // Activation copies, global memory straight into LDS: copy i of a wavefront fills the 64 slots from
-    // 64*wave + 512*i, i.e. rows 4*wave + 32*i + lane/16; slot (row, pos) holds chunk pos ^ (row & 15).  The
-    // row is part of the lane offset, which the descriptor's range check covers (the scalar offset, which
-    // carries the group's bytes within the row, is not checked): rows past M read as zero and are never stored.
-    const int xrow = 4 * wave + (lane >> 4), xch = (lane & 15) ^ (xrow & 15);
-    const uint32_t xoff0 = ((uint32_t)(m0 + xrow) * (uint32_t)K + (uint32_t)xch * 8u) * 2u;
-    const uint32_t xstep = 64u * (uint32_t)K; // 32 rows
-
-    f4 acc[TNB][TMB];
+// The main loop and the store of a tile of H sixteen-row blocks.  Xs0, Xs1: the two activation tiles (256 rows x 128 k each, laid out like
+// the narrow tiles'); after the loop the same memory carries the second K half's partial sums to the first.
+template <int BITS, int H, bool INTZ, int KH>
+__device__ __forceinline__ void qgemm_tall_body(h8 *Xs0, h8 *Xs1, const TallTile &t)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nq = wave & 3;
+    const int G = t.G, brow = lane & 15;
+    f4 acc[TNB][H];
 #pragma unroll
     for (int i = 0; i < TNB; ++i)
 #pragma unroll
-        for (int j = 0; j < TMB; ++j)
+        for (int j = 0; j < H; ++j)
             acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.x, &Xs0[64 * wave + 512 * i], 16, xoff0 + xstep * i, 0, 0, 0);
-
-    // integer zeros: one addition takes bias and zero away (see qgemm_tile)
-    bool intz;
-    {
-        const uint32_t first = (uint32_t)(n0 >> 4) * (uint32_t)G * 16u, count = (TBN / 16) * (uint32_t)G * 16u;
-        int frac = 0;
-        for (uint32_t i = (uint32_t)tid * 8u; i < count; i += 512u * 8u) { // past the array: zeros
-            const h8 z = __builtin_bit_cast(h8, buf_load_b128(buf.zeros, (first + i) * 2u, 0));
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                frac |= z[e] != __builtin_truncf16(z[e]);
-        }
-        __builtin_amdgcn_s_waitcnt(FQ_WAIT_VMCNT0); // the first activation tile has landed ...
-        intz = !__syncthreads_or(frac);             // ... in every wavefront
-    }
-
     UnpackConsts<BITS> uc;
     uc.init();
-    const int brow = lane & 15;
-
-    auto main_loop = [&](auto intz_tag, auto kh_tag) {
-        constexpr bool INTZ = decltype(intz_tag)::value;
-        constexpr int KH = decltype(kh_tag)::value;
+    {
         WChunk<BITS> wc[TNB], wd[TNB];
         h8 a0[TNB][2], a1[TNB][2];
         auto unpack_all = [&](WChunk<BITS> (&w)[TNB], h8 (&a)[TNB][2]) {
@@ -494,34 +450,34 @@ __device__ __forceinline__ void qgemm_tall_tile(h8 *Xs0, h8 *Xs1, const _Float16
         auto load_all = [&](WChunk<BITS> (&w)[TNB], int g) {
 #pragma unroll
             for (int i = 0; i < TNB; ++i)
-                load_whalf<BITS, KH>(w[i], buf, rb0 + i, Np16, G, min(g, G - 1), lane);
+                load_whalf<BITS, KH>(w[i], t.buf, t.rb0 + i, t.Np16, G, min(g, G - 1), lane);
         };
         // Xc: this group's activations, Xn: the buffer the next group's are copied into.  Past the last group
         // both prefetches repeat it (nobody reads them): no branch in the iteration.
         auto body = [&](h8 *Xc, h8 *Xn, int g, h8 (&ac)[TNB][2], h8 (&an)[TNB][2], WChunk<BITS> (&wn)[TNB],
                         WChunk<BITS> (&wl)[TNB]) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(buf.x, &Xn[64 * wave + 512 * i], 16, xoff0 + xstep * i,
+            for (int i = 0; i < (H + 1) / 2; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(t.buf.x, &Xn[64 * wave + 512 * i], 16, t.xoff0 + t.xstep * i,
                                                          (uint32_t)min(g + 1, G - 1) * 256u, 0, 0);
             __builtin_amdgcn_sched_barrier(0); // the copies go out first: they have the whole iteration to land
             load_all(wl, g + 2);
             unpack_all(wn, an); // ahead of the MFMAs in program order: the scheduler fills their shadows with it
-            constexpr int JB = BITS == 3 ? 4 : 8; // operand reads per batch (3 bits: the fewest registers to spare)
+            constexpr int JB = BITS == 3 ? 4 : (H < 16 ? (H + 1) / 2 : 8); // operand reads per batch (3 bits: the fewest registers to spare)
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
 #pragma unroll
-                for (int jh = 0; jh < TMB; jh += JB) {
+                for (int jh = 0; jh < H; jh += JB) {
                     h8 b[JB];
 #pragma unroll
-                    for (int j = 0; j < JB; ++j) {
+                    for (int j = 0; j < JB && jh + j < H; ++j) {
                         const int ch = 4 * (2 * KH + s) + (lane >> 4);
                         b[j] = Xc[((jh + j) * 16 + brow) * 16 + (ch ^ brow)];
                     }
 #pragma unroll
                     for (int i = 0; i < TNB; ++i)
 #pragma unroll
-                        for (int j = 0; j < JB; ++j)
+                        for (int j = 0; j < JB && jh + j < H; ++j)
                             acc[i][jh + j] = mfma16x16x32(ac[i][s], b[j], acc[i][jh + j]);
                 }
             }
@@ -539,44 +495,34 @@ __device__ __forceinline__ void qgemm_tall_tile(h8 *Xs0, h8 *Xs1, const _Float16
         }
         if (g < G)
             body(Xs0, Xs1, g, a0, a1, wc, wd);
-    };
-    if (kh == 0) {
-        if (intz)
-            main_loop(std::true_type{}, std::integral_constant<int, 0>{});
-        else
-            main_loop(std::false_type{}, std::integral_constant<int, 0>{});
-    } else {
-        if (intz)
-            main_loop(std::true_type{}, std::integral_constant<int, 1>{});
-        else
-            main_loop(std::false_type{}, std::integral_constant<int, 1>{});
     }
 
     // The second K half hands its sums over (every iteration ended with a wait for all loads and a barrier, so
     // both arrays are free): block (i, j) of column quarter nq at float4 (nq*16 + j)*64 + lane of array i.
     f4 *red0 = reinterpret_cast<f4 *>(Xs0), *red1 = reinterpret_cast<f4 *>(Xs1);
-    if (kh == 1) {
+    if (KH == 1) {
 #pragma unroll
-        for (int j = 0; j < TMB; ++j) {
+        for (int j = 0; j < H; ++j) {
             red0[((nq * 16 + j) << 6) + lane] = acc[0][j];
             red1[((nq * 16 + j) << 6) + lane] = acc[1][j];
         }
     }
     __syncthreads();
-    if (kh == 1)
+    if (KH == 1)
         return;
     // store: lane holds m = lane%16 and n = 4*(lane/16) + v of each 16x16 block (see qgemm_tile)
-    const bool vec_ok = (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(out) & 7) == 0;
+    const int ld = t.ld, N = t.N;
+    const bool vec_ok = (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(t.out) & 7) == 0;
 #pragma unroll
-    for (int j = 0; j < TMB; ++j) {
-        const int m = m0 + j * 16 + (lane & 15);
+    for (int j = 0; j < H; ++j) {
+        const int m = t.m0 + j * 16 + (lane & 15);
 #pragma unroll
         for (int i = 0; i < TNB; ++i) {
             const f4 r = acc[i][j] + (i ? red1 : red0)[((nq * 16 + j) << 6) + lane];
-            const int n = (rb0 + i) * 16 + 4 * (lane >> 4);
-            if (m >= M)
+            const int n = (t.rb0 + i) * 16 + 4 * (lane >> 4);
+            if (m >= t.m_end)
                 continue;
-            _Float16 *o = out + (size_t)m * ld + n;
+            _Float16 *o = t.out + (size_t)m * ld + n;
             if (n + 3 < N && vec_ok) {
                 h4 v = {(_Float16)r[0], (_Float16)r[1], (_Float16)r[2], (_Float16)r[3]};
                 *reinterpret_cast<h4 *>(o) = v;
@@ -590,9 +536,104 @@ __device__ __forceinline__ void qgemm_tall_tile(h8 *Xs0, h8 *Xs1, const _Float16
     }
 }
 
+template <int BITS, int H, bool INTZ>
+__device__ __forceinline__ void qgemm_tall_halves(h8 *Xs0, h8 *Xs1, const TallTile &t, int kh)
+{
+    if (kh == 0)
+        qgemm_tall_body<BITS, H, INTZ, 0>(Xs0, Xs1, t);
+    else
+        qgemm_tall_body<BITS, H, INTZ, 1>(Xs0, Xs1, t);
+}
+
+// One output tile of up to 256 x 128.
+template <int BITS>
+__device__ __forceinline__ void qgemm_tall_tile(h8 *Xs0, h8 *Xs1, const _Float16 *__restrict__ x, int M,
+                                                const uint32_t *__restrict__ packed,
+                                                const _Float16 *__restrict__ scales,
+                                                const _Float16 *__restrict__ zeros, int N, int K,
+                                                _Float16 *__restrict__ out, int ld, int tile, int MT)
+{
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kh = wave >> 2, nq = wave & 3; // half of every group's k-steps, quarter of the tile's weight rows
+    // The rows are cut into MT tiles of as equal a height as blocks of sixteen allow.  Tiles are numbered in bands of two row-tiles (row-tile
+    // fastest): the 32 tiles an XCD holds at a
+    // time share up to 512 activation rows (4 MiB at k = 4096, the size of its L2) and 16 weight tiles
+    const int NT = (N + TBN - 1) / TBN, row_blocks = (M + 15) / 16;
+    const int band = tile / (2 * NT), rest = tile - band * 2 * NT, height = min(2, MT - 2 * band);
+    const int row_tile = 2 * band + rest % height, n0 = (rest / height) * TBN;
+    const int block0 = row_tile * row_blocks / MT, blocks = (row_tile + 1) * row_blocks / MT - block0; // up to TMB
+    TallTile t;
+    t.m0 = 16 * block0;
+    t.m_end = min(M, t.m0 + 16 * blocks);
+    t.G = K >> 7;
+    t.Np16 = ((N + 63) / 64 * 64) >> 4;
+    t.rb0 = (n0 >> 4) + nq * TNB;
+    t.N = N;
+    t.K = K;
+    t.ld = ld;
+    t.out = out;
+    const int G = t.G;
+
+    t.buf.x = make_rsrc(x, (uint32_t)t.m_end * (uint32_t)K * 2u);
+    const uint32_t Np = (uint32_t)(N + 63) / 64u * 64u;
+    t.buf.packed = make_rsrc(packed, Np / 8u * (uint32_t)K * (uint32_t)BITS);
+    t.buf.scales = make_rsrc(scales, Np * (uint32_t)G * 2u);
+    t.buf.zeros = make_rsrc(zeros, Np * (uint32_t)G * 2u);
+
+    // Activation copies, global memory straight into LDS: copy i of a wavefront fills the 64 slots from
+    // 64*wave + 512*i, i.e. rows 4*wave + 32*i + lane/16; slot (row, pos) holds chunk pos ^ (row & 15).  The
+    // row is part of the lane offset, which the descriptor's range check covers (the scalar offset, which
+    // carries the group's bytes within the row, is not checked): rows past the tile's read as zero and are never stored.
+    const int xrow = 4 * wave + (lane >> 4), xch = (lane & 15) ^ (xrow & 15);
+    t.xoff0 = ((uint32_t)(t.m0 + xrow) * (uint32_t)K + (uint32_t)xch * 8u) * 2u;
+    t.xstep = 64u * (uint32_t)K; // 32 rows
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(t.buf.x, &Xs0[64 * wave + 512 * i], 16, t.xoff0 + t.xstep * i, 0, 0, 0);
+
+    // integer zeros: one addition takes bias and zero away (see qgemm_tile)
+    bool intz;
+    {
+        const uint32_t first = (uint32_t)(n0 >> 4) * (uint32_t)G * 16u, count = (TBN / 16) * (uint32_t)G * 16u;
+        int frac = 0;
+        for (uint32_t i = (uint32_t)tid * 8u; i < count; i += 512u * 8u) { // past the array: zeros
+            const h8 z = __builtin_bit_cast(h8, buf_load_b128(t.buf.zeros, (first + i) * 2u, 0));
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                frac |= z[e] != __builtin_truncf16(z[e]);
+        }
+        __builtin_amdgcn_s_waitcnt(FQ_WAIT_VMCNT0); // the first activation tile has landed ...
+        intz = !__syncthreads_or(frac);             // ... in every wavefront
+    }
+
+    auto of_height = [&](auto height) {
+        constexpr int H = decltype(height)::value;
+        if (intz)
+            qgemm_tall_halves<BITS, H, true>(Xs0, Xs1, t, kh);
+        else
+            qgemm_tall_halves<BITS, H, false>(Xs0, Xs1, t, kh);
+    };
+    // the least height that holds the tile's blocks (see tall_height)
+    if (blocks > 15)
+        of_height(std::integral_constant<int, 16>{});
+    else if (blocks > 14)
+        of_height(std::integral_constant<int, 15>{});
+    else if (blocks > 13)
+        of_height(std::integral_constant<int, 14>{});
+    else if (blocks > 12)
+        of_height(std::integral_constant<int, 13>{});
+    else if (blocks > 10)
+        of_height(std::integral_constant<int, 12>{});
+    else if (blocks > 8)
+        of_height(std::integral_constant<int, 10>{});
+    else
+        of_height(std::integral_constant<int, 8>{});
+}
+
 // Eight wavefronts of 256 registers each: one workgroup per CU, two wavefronts per SIMD.
 __global__ __launch_bounds__(512, 1) void qgemm_tall_kernel(const _Float16 *__restrict__ x, int M, int K, int total, int first1, int first2,
-                                                            GemmJobs)
+                                                            int row_tiles, GemmJobs)
 {
     __shared__ h8 Xs0[TBM * 16];
     __shared__ h8 Xs1[TBM * 16];
@@ -601,10 +642,10 @@ __global__ __launch_bounds__(512, 1) void qgemm_tall_kernel(const _Float16 *__re
         return;
     const GemmJob job = gemm_job(tile, first1, first2);
     switch (job.bits) {
-    case 2: qgemm_tall_tile<2>(Xs0, Xs1, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile); break;
-    case 3: qgemm_tall_tile<3>(Xs0, Xs1, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile); break;
-    case 4: qgemm_tall_tile<4>(Xs0, Xs1, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile); break;
-    default: qgemm_tall_tile<8>(Xs0, Xs1, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile); break;
+    case 2: qgemm_tall_tile<2>(Xs0, Xs1, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile, row_tiles); break;
+    case 3: qgemm_tall_tile<3>(Xs0, Xs1, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile, row_tiles); break;
+    case 4: qgemm_tall_tile<4>(Xs0, Xs1, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile, row_tiles); break;
+    default: qgemm_tall_tile<8>(Xs0, Xs1, x, M, job.packed, job.scales, job.zeros, job.N, K, job.out, job.ld, tile, row_tiles); break;
     }
 }
 
@@ -618,62 +659,101 @@ int wide_tiles_pay(int M, int N)
     return tiles >= 2 * 256;
 }
 
-int tall_tiles(int M, int N) { return ((N + TBN - 1) / TBN) * ((M + TBM - 1) / TBM); }
+constexpr int CUS = 256;
 
-// Tile height for a launch of `count` matrices.  Both kernels run in rounds over the 256 CUs, two 128-row tiles or
-// one tall tile a CU, and a round that is not full costs most of a full one.  Measured over 32 groups, 512 to 2048
-// rows, 4096 to 22016 columns (us at 2 / 3 / 4 / 8 bits): a full round of 128-row tiles 63 / 73 / 67 / 73, its last one 47 when
-// at most one tile a CU is left and 4 under a full one otherwise; a full round of tall tiles 61 / 67 / 63 / 66, a last
-// one 50 to 60.  So 640 rows of 11008 columns (430 tiles or 258) take 64 against 110 us, 2048 rows (1376 or 688) 204
-// against 184.  All of it follows the number of groups, but on shorter rows a round of tall tiles keeps up to 1.5 us more (the
-// two halves of its K meet through LDS): without them such rows went to tall tiles that took up to a third longer (229
-// rows of 20424 x 128 11.9 against 9.0 us, 1932 of 3144 x 384 15.8 against 13.9).  Of 960 sizes 12 are more than 2 % slower
-// than in tall tiles wherever there are 256 of them, the rule without rounds (56 were), and on average they are 8 %
-// faster.  From 4096 rows on, the 128 x 256 tiles of 2- and 4-bit matrices run several full rounds and are level or
-// 2-6 % ahead of the tall ones, so launches made of such matrices only stay with them.
+// Row blocks that a tile of `blocks` is worked on as: the heights there are bodies for.
+int tall_height(int blocks) { return blocks > 12 ? blocks : (blocks > 10 ? 12 : (blocks > 8 ? 10 : 8)); }
+
+// Row tiles that a launch of tall tiles cuts M into, by estimated time (fitted to 29000 launches; from K = 2560 on 5 % off, shorter ones
+// up to 20).  Rounds over the CUs, a tile each; a last round that is
+// not full takes nearly as long as a full one.  A round takes, of every group of 128 k, a part that does not depend on the height (a tile's weights
+// are unpacked whatever it is) and one that does.  Tiles of TBM rows are the fewest; more and lower ones are better where they fill the
+// rounds better, and a launch's tiles are only as high as they have to be: at full height, rows that do not divide by TBM cost a last tile
+// of a few rows as much as a whole one.  Measured, us, full height -> as chosen: 1200 x 4096 x
+// 11008 at 4 bits 136 -> 107 (eight of 160), 1500 x 11008 x 4096 at 2 bits 158 -> 135 (eight of 192), 800 x 22016 x 4096 at 4 bits 168 -> 137 (four of 208), 1890
+// x 1420 x 6400 at 2 bits 74 -> 50 (fifteen of 128).  Exactly as many tiles as whole rounds hold, by one more in some of the columns, gave 3 % more at
+// one size in sixteen: a chip that is
+// full clocks lower, and 2048 x 11008 x 4096 takes 166 us in 2.7 rounds of full height as in three of 240 rows.
+int plan_tall(int M, const fq_packed_ref *w, int count, double *us)
+{
+    static const double whole[9] = {0, 0, 0.390, 0.812, 0.362, 0, 0, 0, 0.418}, block[9] = {0, 0, 0.063, 0.049, 0.067, 0, 0, 0, 0.066};
+    int columns = 0;
+    double fixed = 0.0, each = 0.0;
+    for (int i = 0; i < count; ++i) {
+        const int n = (w[i].N + TBN - 1) / TBN;
+        columns += n;
+        fixed += n * whole[w[i].bits];
+        each += n * block[w[i].bits];
+    }
+    const int blocks = (M + 15) / 16, least = (blocks + TMB - 1) / TMB, G = w[0].K >> 7;
+    int best = least;
+    *us = 1e30;
+    for (int k = least; k <= least + 16; ++k) {
+        const int high = (blocks + k - 1) / k, H = tall_height(high);
+        if (k > least && high < 7)
+            break;
+        const long tiles = (long)k * columns, whole_rounds = tiles / CUS;
+        const double rest = (double)(tiles % CUS) / CUS;
+        const double rounds = (double)whole_rounds + (rest == 0.0 ? 0.0 : (whole_rounds == 0 ? 0.83 + 0.16 * rest : 0.89 + 0.10 * rest));
+        const double t = 2.5 + (double)(whole_rounds + (rest != 0.0)) * (0.92 + 0.658 * H) + G * rounds * (fixed + each * H) / columns;
+        if (t < *us) {
+            *us = t;
+            best = k;
+        }
+    }
+    return best;
+}
+
+// Tile height for a launch of `count` matrices that the few-row kernel does not serve: 128 rows or plan_tall's, by estimated times.  From
+// K = 2048 on both estimates hold for themselves: over 2830 sizes of 130 to 4096 rows and 300 to 27648 columns the choice takes 0.4 % longer than
+// the better one on average, 2 % in one of twenty (3-bit matrices over long rows, where both are closest, with a wider margin).  The one of the 128-row tiles: rounds over the 256 CUs, two tiles a CU; measured over 32
+// groups, 512 to 2048 rows, 4096 to 22016 columns (us at 2 / 3 / 4 / 8 bits) a full round 63 / 73 / 67 / 73, its last one 47 when
+// at most one tile a CU is left and 4 under a full one otherwise.  Up to 256 tiles, one a CU: 5.4 us and 1.31 us a group of 128 k; up to 512,
+// 1.5 us (3 bits 1.8) a group and more the more CUs have two; beyond, the rounds above and 6 us, on rows shorter than 4096 up to 6 more.
+// Of that 0.92 (with a 3-bit matrix 0.9), up to 512 tiles from K = 4096 on.  Shorter rows, where what a round takes beside its groups
+// counts, go by tall tiles of the full height: a round of them keeps up to 1.5 us more (the two halves of its K meet through LDS): 229 rows of
+// 20424 x 128 11.9 against 9.0 us, 1932 of 3144 x 384 15.8 against 13.9.
 //
-// us: the time that the choice is expected to take.  Up to 256 tiles, one a CU: 5.4 us and 1.31 us a group of 128 k; up to 512,
-// 1.5 us (3 bits 1.8) a group and more the more CUs have two; beyond, the rounds above and 6 us (tall tiles 3), on rows
-// shorter than 4096 up to 6 more.  Of that 0.92 in 128-row tiles (with a 3-bit matrix 0.9), up to 512 of them from K = 4096 on, and there too
-// 0.9 of a round of tall tiles without a 3-bit matrix, 0.95 of several: without these factors the few-row kernel was taken for 29 of
-// 300 sizes that it serves 2 to 26 % more slowly, with them for 10, up to 8 %.
+// us: what the few-row kernel's estimate is held against.  It is the one for tall tiles of the full height (or 128-row tiles): the lower ones
+// are up to a fifth faster than the few-row kernel at some sizes it serves (400 x 22016 x 4096 at 4 bits 87 us against 107), but they
+// round a scale into every weight, which that kernel applies to sums in fp32.  A full round of them 61 / 67 / 63 / 66, a last one 50
+// to 60, 1.5 us more on short rows (the two halves of their K meet through LDS), and the factors below: without them the few-row
+// kernel was taken for 29 of 300 sizes that it serves 2 to 26 % more slowly, with them for 10, up to 8 %.
 int choose_tile_rows(int M, const fq_packed_ref *w, int count, double *us)
 {
     static const double full128[9] = {0, 0, 63, 73, 67, 0, 0, 0, 73}, full256[9] = {0, 0, 61, 67, 63, 0, 0, 0, 66};
     long tiles = 0, tall = 0;
-    double f128 = 0.0, f256 = 0.0;
+    double f128 = 0.0, f256 = 0.0, three = 0.0;
     bool all_wide = M >= 4096;
     for (int i = 0; i < count; ++i) {
         const int t = ((w[i].N + 127) / 128) * ((M + 127) / 128);
         tiles += t;
-        tall += tall_tiles(M, w[i].N);
+        tall += ((w[i].N + TBN - 1) / TBN) * ((M + TBM - 1) / TBM);
         f128 += t * full128[w[i].bits];
         f256 += t * full256[w[i].bits];
+        three = w[i].bits == 3 ? 0.3 : three;
         all_wide = all_wide && (w[i].bits == 2 || w[i].bits == 4) && wide_tiles_pay(M, w[i].N);
     }
     const int G = w[0].K >> 7;
-    double three = 0.0;
-    for (int i = 0; i < count; ++i)
-        three = w[i].bits == 3 ? 0.3 : three;
-    *us = 5.4 + G * (tiles <= 256 ? 1.31 : 1.5 + three + 0.7 * (tiles - 256) / 256.0);
-    if (tiles <= 256)
-        return 128;
+    const double length = w[0].K / 4096.0; // of the rows, in those that the figures above were taken with
+    const double brief = length < 1.0 ? 6.0 * (1.0 - length) : 0.0, long_part = three != 0.0 ? 0.9 : 0.92;
     f128 /= tiles;
     f256 /= tiles;
     const long r128 = tiles % 512, r256 = tall % 256;
     const double t128 = (tiles / 512) * f128 + (r128 == 0 ? 0.0 : (r128 <= 256 ? 47.0 : f128 - 4.0));
     const double t256 = (tall / 256) * f256 + (r256 == 0 ? 0.0 : 50.0 + 10.0 * r256 / 256);
-    const double length = w[0].K / 4096.0; // of the rows, in those that the figures above were taken with
+    const double low = 5.4 + G * (tiles <= 256 ? 1.31 : 1.5 + three + 0.7 * (tiles - 256) / 256.0);
+    const double us128 = tiles <= 256 ? low : (tiles <= 512 ? (low + brief) * (length < 1.0 ? 1.0 : long_part) : (6.0 + t128 * length + brief) * long_part);
     const double fixed256 = length < 1.0 ? 1.5 * (1.0 - length) * (tall / 256 + (r256 != 0)) : 0.0;
-    const double brief = length < 1.0 ? 6.0 * (1.0 - length) : 0.0;
-    const double tall_part = three != 0.0 || length < 1.0 ? 1.0 : (tall <= 256 ? 0.9 : 0.95);
-    if (M > 128 && !all_wide && t256 * length + fixed256 < t128 * length) {
-        *us = (3.0 + t256 * length + fixed256 + brief) * tall_part;
-        return 256;
-    }
-    const double long_part = three != 0.0 ? 0.9 : 0.92;
-    *us = tiles <= 512 ? (*us + brief) * (length < 1.0 ? 1.0 : long_part) : (6.0 + t128 * length + brief) * long_part;
-    return 128;
+    *us = us128;
+    const bool full_height = M > 128 && tiles > 256 && !all_wide && t256 * length + fixed256 < t128 * length;
+    if (full_height)
+        *us = (3.0 + t256 * length + fixed256 + brief) * (three != 0.0 || length < 1.0 ? 1.0 : (tall <= 256 ? 0.9 : 0.95));
+    if (w[0].K < 2048)
+        return full_height ? 256 : 128;
+    double us256;
+    plan_tall(M, w, count, &us256);
+    return M > 128 && us256 < (three != 0.0 && w[0].K > 8192 ? 0.92 : 0.97) * us128 ? 256 : 128;
 }
 
 template <int BITS, int QNB>
@@ -724,11 +804,21 @@ struct GemmLaunch {
 
 } // namespace
 
+// Rows of the tiles of a launch that fq_gemm_tile_rows gives to the tall kernel.
+int fq_gemm_tall_rows(int M, const fq_packed_ref *w, int count)
+{
+    double us;
+    const int row_tiles = plan_tall(M, w, count, &us);
+    return 16 * tall_height(((M + 15) / 16 + row_tiles - 1) / row_tiles);
+}
+
 static int launch_tall(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st)
 {
-    const GemmLaunch l(w, outs, count, [&](int i) { return tall_tiles(M, w[i].N); }, [](int) { return 0; });
+    double us;
+    const int row_tiles = plan_tall(M, w, count, &us);
+    const GemmLaunch l(w, outs, count, [&](int i) { return row_tiles * ((w[i].N + TBN - 1) / TBN); }, [](int) { return 0; });
     hipLaunchKernelGGL(qgemm_tall_kernel, dim3(8 * ((l.total + 7) / 8)), dim3(512), 0, st,
-                       static_cast<const _Float16 *>(x), M, w[0].K, l.total, l.first[1], l.first[2], l.jobs);
+                       static_cast<const _Float16 *>(x), M, w[0].K, l.total, l.first[1], l.first[2], row_tiles, l.jobs);
     return (int)hipGetLastError();
 }
 

@@ -70,6 +70,7 @@ int fq_decode_available(int H, int F); // pages per ring if the persistent kerne
 void fq_decode_partition_of(unsigned bits4, int ph, int N, int wg, int grid, int *out6);
 // Height of the large tiles of a launch (128 or 256); 0: the few-row kernel, with this plan.
 int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count, fq_skinny_plan *few);
+int fq_gemm_tall_rows(int M, const fq_packed_ref *w, int count); // of the tiles of a launch of height 256, which are as high as they need be
 // tile_rows: 0 lets the library choose, 128 or 256 pins one of the large-tile kernels.
 int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st, int tile_rows = 0);
 // Up to three matrices with the same input (same K) in one launch; M > 16, or any M for the few-row kernel.

@@ -152,6 +152,28 @@ def test_qlinear_tall_tiles_against_oracle(fq, torch, bits, case):
     assert qerr(y, y128.astype(np.float64)) <= 1e-3
 
 
+# rows whose tall tiles are 8, 9, 10, 11, 12 to 16 blocks of sixteen high, whole blocks and ragged ones, in one row tile and in several
+TALL_HEIGHTS = [121, 144, 150, 161, 177, 192, 208, 209, 225, 240, 241, 300, 403, 611, 1200]
+
+
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("M", TALL_HEIGHTS)
+def test_qlinear_tall_tiles_of_every_height(fq, torch, bits, M):
+    """Integer and fractional zeros (their loops differ); the last column of tiles is ragged."""
+    N, K = 130, 384
+    codes = fq_synth.codes(121, N, K, bits)
+    s = np.random.default_rng(122).uniform(0.01, 0.02, (N, K // 128)).astype(np.float16)
+    X = fq_synth.activations(123, M, K)
+    for fraction in (0.0, 0.25):
+        z = (fq_synth.codes(124, N, K // 128, bits).astype(np.float32) + fraction).astype(np.float16)
+        r = oracle.qlinear(X, oracle.dequant(codes, s, z))
+        out = Guarded(torch, M * N * 2)
+        fq.fq_qlinear(dev(torch, X), fq.PackedMatrix.from_host(codes, s, z, bits), out=out.half(M, N), tile_rows=256)
+        torch.cuda.synchronize()
+        assert out.intact()
+        assert qerr(host16(out.half(M, N)), r) <= TOL
+
+
 @pytest.mark.parametrize("bits", BITS)
 @pytest.mark.parametrize("case", [(1, 5000, 128), (2, 5000, 1152), (1, 5120, 640), (3, 4100, 384), (1, 200, 8320)],
                          ids=lambda c: "M%d_N%d_K%d" % c)
