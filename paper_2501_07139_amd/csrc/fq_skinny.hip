@@ -106,9 +106,9 @@ __device__ __forceinline__ h4 row16_bcast(u2v v)
     return __builtin_bit_cast(h4, all);
 }
 
-// Partial sums of RED blocks of 16 x 16 at a time go through LDS.
+// Partial sums of so many blocks of 16 x 16 at a time go through LDS: two for each of the eight wavefronts to add up.
 template <int MB, int S>
-struct SkinnyRed { static constexpr int N = MB * S <= 16 ? MB * S : (MB * S % 16 == 0 ? 16 : (MB * S % 14 == 0 ? 14 : (MB * S % 12 == 0 ? 12 : 10))); };
+struct SkinnyRed { static constexpr int N = MB * S < 16 ? MB * S : 16; };
 
 // The sums of the wavefronts, in a fixed order, and the store.
 template <int MB, int S>
@@ -124,19 +124,30 @@ __device__ __forceinline__ void skinny_store(h8 *smem, const f4 (&acc)[S][MB], i
     const int waves = min(SNW, G);
     constexpr int RED = SkinnyRed<MB, S>::N;
     f4 *red = reinterpret_cast<f4 *>(smem);
-    static_assert(MB * S % RED == 0);
-    static_for<MB * S / RED>([&](auto pass_tag) {
-        constexpr int first = decltype(pass_tag)::value * RED; // block b = u * MB + j
+    static_for<(MB * S + RED - 1) / RED>([&](auto pass_tag) {
+        constexpr int first = decltype(pass_tag)::value * RED, N = MB * S - first < RED ? MB * S - first : RED; // block b = u * MB + j
         __syncthreads();
-        static_for<RED>([&](auto b_tag) {
+        static_for<N>([&](auto b_tag) {
             constexpr int b = decltype(b_tag)::value, u = (first + b) / MB, j = (first + b) % MB;
             red[(wave * RED + b) * 64 + lane] = acc[u][j];
         });
         __syncthreads();
-        for (int b = wave; b < RED; b += SNW) {
-            f4 sum = red[b * 64 + lane];
-            for (int v = 1; v < waves; ++v)
-                sum += red[(v * RED + b) * 64 + lane];
+        for (int b = wave; b < N; b += SNW) {
+            f4 sum;
+            if (waves == SNW) { // all of them at once: read one behind the other they took eight times an LDS access
+                f4 of[SNW];
+#pragma unroll
+                for (int v = 0; v < SNW; ++v)
+                    of[v] = red[(v * RED + b) * 64 + lane];
+                sum = of[0];
+#pragma unroll
+                for (int v = 1; v < SNW; ++v)
+                    sum += of[v];
+            } else {
+                sum = red[b * 64 + lane];
+                for (int v = 1; v < waves; ++v)
+                    sum += red[(v * RED + b) * 64 + lane];
+            }
             const int m = m0 + 16 * ((first + b) % MB) + r, n = 16 * (sb0 + (first + b) / MB) + 4 * c;
             if (m >= M)
                 continue;
