@@ -376,21 +376,28 @@ __device__ __forceinline__ void skinny_wide_tile(h8 *smem, const _Float16 *__res
         // chunk pos ^ row of the row's sixteen, so that the operand reads below touch every bank once.  The row is
         // part of the lane offset, which the descriptor's range check covers: rows past M read as zero and are not stored.
         h8 *const ring = smem + wave * (H * STAGE);
-        const fq_rsrc xr = make_rsrc(x, (uint32_t)M * (uint32_t)K * 2u);
-        // of copy 0; copy i's is 4 i rows further, and 64 i (bits that K * 2, a multiple of 256, leaves clear) exchanged in it
-        uint32_t xoff = ((uint32_t)(m0 + c) * (uint32_t)K + 8u * (uint32_t)(r ^ c)) * 2u;
+        // From the first row of a block: copy i's is 4 i rows further, and 64 i (bits that K * 2, a multiple of 256, leaves clear)
+        // exchanged in it.
+        uint32_t xoff[TIGHT ? 1 : COPIES];
+#pragma unroll
+        for (int i = 0; i < (TIGHT ? 1 : COPIES); ++i)
+            xoff[i] = ((uint32_t)(4 * i + c) * (uint32_t)K + 8u * (uint32_t)(r ^ c ^ (4 * i))) * 2u;
         const int turns = (G - wave + SNW - 1) / SNW; // groups of this wavefront
         int nt = 0, nj = 0, ns = 0;                   // group, row block and slot of the next copy
         auto copy = [&]() { // past the end: the last group's rows again, into a stage that is not read any more
             const uint32_t off = (uint32_t)(wave + SNW * min(nt, turns - 1)) * 256u;
-            uint32_t down = (uint32_t)nj * (32u * (uint32_t)K);
-            asm volatile("" : "+s"(down)); // added here: the sums of all row blocks would be kept in registers
+            // the descriptor starts at the block's first row and ends with the last row of all: scalar work, where block and row in
+            // the lane offset were two vector instructions a copy, a tenth of a turn's (300 x 4096 x 11008 at 3 bits 39.7 -> 38.5 us, at 4096 x
+            // 4096 17.5 -> 17.1; up to a tenth of what bounds it is all there was to gain: matrix and vector instructions share the issue port)
+            const int row = m0 + 16 * nj;
+            const fq_rsrc xr = make_rsrc(x + (size_t)row * K, row < M ? (uint32_t)(M - row) * (uint32_t)K * 2u : 0u);
             if constexpr (TIGHT)
-                asm volatile("" : "+v"(xoff));
+                asm volatile("" : "+v"(xoff[0]));
             h8 *dst = ring + ns * STAGE;
 #pragma unroll
             for (int i = 0; i < COPIES; ++i)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, dst + 64 * i, 16, (xoff ^ (64u * i)) + (down + 8u * i * (uint32_t)K), off, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, dst + 64 * i, 16, TIGHT ? (xoff[0] ^ (64u * i)) + 8u * i * (uint32_t)K : xoff[TIGHT ? 0 : i],
+                                                         off, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             ns = (ns + 1) & (H - 1);
             if (++nj == MB) {
@@ -576,6 +583,7 @@ constexpr int SKINNY_CUS = 256;
 //    of 3 bits 0.32 S): moving the activations is what a turn takes.
 //  - sixteen rows: as below, 4.2 us (64 columns 4.6) and 0.92 of the turns, 3 bits S = 1 0.6 in the first; the smallest leave room for a second
 //    workgroup on a CU.
+// (Taken when the partial sums of a block were still read one after another: a round is 0.2 to 0.5 us less now, in every shape.)
 // The turns take no less than the activations need to reach an XCD's L2 at 0.9 TB/s: with thirty and more row tiles the tiles
 // that an XCD works on share hardly any.  80 rows and more a tile are the choice wherever a round of them takes what would be two of smaller
 // ones: 300 x 4096 x 4096 at 4 bits 23.5 -> 17.5 us, 300 x 4096 x 11008 at 2 bits 48 -> 35, 77 x 11008 x 4096 23.6 -> 17.2, 512
