@@ -713,6 +713,7 @@ int plan_tall(int M, const fq_packed_ref *w, int count, double *us)
 // Of that 0.92 (with a 3-bit matrix 0.9), up to 512 tiles from K = 4096 on.  Shorter rows, where what a round takes beside its groups
 // counts, go by tall tiles of the full height: a round of them keeps up to 1.5 us more (the two halves of its K meet through LDS): 229 rows of
 // 20424 x 128 11.9 against 9.0 us, 1932 of 3144 x 384 15.8 against 13.9.
+// So do launches of 2- and 4-bit matrices only from 4096 rows on, whose 128 x 256 tiles run several full rounds and are level or 2-6 % ahead.
 //
 // us: what the few-row kernel's estimate is held against.  It is the one for tall tiles of the full height (or 128-row tiles): the lower ones
 // are up to a fifth faster than the few-row kernel at some sizes it serves (400 x 22016 x 4096 at 4 bits 87 us against 107), but they
@@ -749,7 +750,7 @@ int choose_tile_rows(int M, const fq_packed_ref *w, int count, double *us)
     const bool full_height = M > 128 && tiles > 256 && !all_wide && t256 * length + fixed256 < t128 * length;
     if (full_height)
         *us = (3.0 + t256 * length + fixed256 + brief) * (three != 0.0 || length < 1.0 ? 1.0 : (tall <= 256 ? 0.9 : 0.95));
-    if (w[0].K < 2048)
+    if (w[0].K < 2048 || all_wide)
         return full_height ? 256 : 128;
     double us256;
     plan_tall(M, w, count, &us256);
