@@ -170,6 +170,13 @@ int fq_qlinear_tile(const void *x, int M, const void *packed, const void *scales
  */
 enum { FQ_ROUTE_STREAM, FQ_ROUTE_GENERIC, FQ_ROUTE_FEW_ROWS, FQ_ROUTE_TILES_128, FQ_ROUTE_TILES_256 };
 int fq_qlinear_route(int M, const int *N, const int *bits, int count, int K, int *route_out);
+/*
+ * How a launch of the 256-row kernel cuts its rows (host only; for tests and tools): what fq_qlinear_tile pins with 256, and
+ * fq_qlinear takes where fq_qlinear_route says FQ_ROUTE_TILES_256.  out4 (host, 4 ints): row tiles of the launch, then of tile
+ * row_tile the first row, its rows, and those that it is worked on as (128, 160, 192, 208, 224, 240 or 256).  FQ_ERR_SHAPE for a tile
+ * that there is not, with out4[0] written.
+ */
+int fq_qlinear_tall_tile(int M, const int *N, const int *bits, int count, int K, int row_tile, int *out4);
 
 /*
  * Mixed precision WITHIN a matrix (Section "Large Language Model Quantization":

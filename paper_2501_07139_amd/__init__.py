@@ -61,6 +61,7 @@ def _load() -> ctypes.CDLL:
         "fq_qlinear": (ci, [vp, ci, vp, vp, vp, ci, ci, ci, ci, vp, vp]),
         "fq_qlinear_tile": (ci, [vp, ci, vp, vp, vp, ci, ci, ci, ci, vp, ci, vp]),
         "fq_qlinear_route": (ci, [ci, vp, vp, ci, ci, vp]),
+        "fq_qlinear_tall_tile": (ci, [ci, vp, vp, ci, ci, ci, vp]),
         "fq_dense_route": (ci, [ci, ci, ci, ci, vp]),
         "fq_stream_read": (ci, [vp, ctypes.c_size_t, vp, vp]),
         "fq_qlinear_mixed": (ci, [vp, ci, vp, ci, ci, ci, vp, vp]),
@@ -126,7 +127,7 @@ EXPORTS = ("fq_last_error", "fq_version", "fq_quantize_rtn", "fq_packed_bytes", 
            "fq_attn_prefill_workspace_bytes", "fq_prefill_workspace_bytes", "fq_attn_prefill", "fq_prefill_forward",
            "fq_init", "fq_dense_f16_tile", "fq_rope_table", "fq_stack_forward_noalloc", "fq_set_decode_mode",
            "fq_decode_give_up_ticks", "fq_async_error", "fq_clear_async_error", "fq_decode_partition", "fq_decode_persistent",
-           "fq_decode_persistent_launches", "fq_qlinear_route", "fq_dense_route")
+           "fq_decode_persistent_launches", "fq_qlinear_route", "fq_qlinear_tall_tile", "fq_dense_route")
 
 
 # The calls below that small ones are made of go through _bind where nothing is to be allocated; it answers None to whatever it does
@@ -277,6 +278,14 @@ def fq_qlinear_route(M: int, N, bits, K: int):
     out = np.zeros(3, dtype=np.int32)
     _check(_lib.fq_qlinear_route(M, _hp(N), _hp(bits), len(N), K, _hp(out)))
     return ROUTES[out[0]], int(out[1]), int(out[2])
+
+
+def fq_qlinear_tall_tile(M: int, N, bits, K: int, row_tile: int = 0):
+    """(row tiles, first row, rows, rows worked on) of a row tile of the 256-row kernel, for the matrices of ``fq_qlinear_route``."""
+    N, bits = (_np(np.atleast_1d(np.asarray(v, dtype=np.int32)), np.int32) for v in (N, bits))
+    out = np.zeros(4, dtype=np.int32)
+    _check(_lib.fq_qlinear_tall_tile(M, _hp(N), _hp(bits), len(N), K, row_tile, _hp(out)))
+    return tuple(int(v) for v in out)
 
 
 MAX_SEGMENTS = 8

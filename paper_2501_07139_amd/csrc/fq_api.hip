@@ -131,20 +131,33 @@ extern "C" int fq_qlinear_tile(const void *x, int M, const void *packed, const v
     return qlinear_checked(x, M, w, out, static_cast<fq_stream>(stream), tile_rows);
 }
 
+namespace {
+
+// The matrices of a launch as fq_qlinear_route and fq_qlinear_tall_tile are given them.
+int route_matrices(const char *fn, int M, const int *N, const int *bits, int count, int K, fq_packed_ref *w)
+{
+    if (M <= 0 || count < 1 || count > 3 || K <= 0 || K % 128 != 0)
+        return fq_fail(FQ_ERR_SHAPE, "%s: M=%d count=%d K=%d", fn, M, count, K);
+    for (int i = 0; i < count; ++i) {
+        if (N[i] <= 0 || fq_bits_index(bits[i]) < 0)
+            return fq_fail(N[i] <= 0 ? FQ_ERR_SHAPE : FQ_ERR_BITS, "%s: N=%d bits=%d", fn, N[i], bits[i]);
+        w[i] = fq_packed_ref{nullptr, nullptr, nullptr, N[i], K, bits[i]};
+    }
+    return FQ_OK;
+}
+
+} // namespace
+
 extern "C" int fq_qlinear_route(int M, const int *N, const int *bits, int count, int K, int *route_out)
 {
     if (!N || !bits || !route_out)
         return fq_fail(FQ_ERR_NULL, "fq_qlinear_route: NULL argument");
-    if (M <= 0 || count < 1 || count > 3 || K <= 0 || K % 128 != 0)
-        return fq_fail(FQ_ERR_SHAPE, "fq_qlinear_route: M=%d count=%d K=%d", M, count, K);
     fq_packed_ref w[3];
+    if (int rc = route_matrices("fq_qlinear_route", M, N, bits, count, K, w))
+        return rc;
     bool stream = true;
-    for (int i = 0; i < count; ++i) {
-        if (N[i] <= 0 || fq_bits_index(bits[i]) < 0)
-            return fq_fail(N[i] <= 0 ? FQ_ERR_SHAPE : FQ_ERR_BITS, "fq_qlinear_route: N=%d bits=%d", N[i], bits[i]);
-        w[i] = fq_packed_ref{nullptr, nullptr, nullptr, N[i], K, bits[i]};
+    for (int i = 0; i < count; ++i)
         stream = stream && fq_gemv_can_stream(M, K, bits[i], 0);
-    }
     route_out[1] = route_out[2] = 0;
     if (M <= 16 && !fq_skinny_pays(M, w, count)) {
         route_out[0] = stream ? FQ_ROUTE_STREAM : FQ_ROUTE_GENERIC;
@@ -157,6 +170,21 @@ extern "C" int fq_qlinear_route(int M, const int *N, const int *bits, int count,
     route_out[0] = rows == 0 ? FQ_ROUTE_FEW_ROWS : (rows == 256 ? FQ_ROUTE_TILES_256 : FQ_ROUTE_TILES_128);
     route_out[1] = rows == 0 ? 16 * few.mb : rows;
     route_out[2] = rows == 0 ? 16 << few.s_log2 : 128;
+    return FQ_OK;
+}
+
+extern "C" int fq_qlinear_tall_tile(int M, const int *N, const int *bits, int count, int K, int row_tile, int *out4)
+{
+    if (!N || !bits || !out4)
+        return fq_fail(FQ_ERR_NULL, "fq_qlinear_tall_tile: NULL argument");
+    fq_packed_ref w[3];
+    if (int rc = route_matrices("fq_qlinear_tall_tile", M, N, bits, count, K, w))
+        return rc;
+    if (!below_4gib(M, K, 2))
+        return fq_fail(FQ_ERR_SHAPE, "fq_qlinear_tall_tile: M=%d K=%d: activations must stay below 4 GiB", M, K);
+    out4[0] = fq_gemm_tall_tile(M, w, count, row_tile, &out4[1], &out4[2], &out4[3]);
+    if (row_tile < 0 || row_tile >= out4[0])
+        return fq_fail(FQ_ERR_SHAPE, "fq_qlinear_tall_tile: row_tile=%d of %d", row_tile, out4[0]);
     return FQ_OK;
 }
 

@@ -27,6 +27,7 @@
 #include "fq_device.h"
 #include "fq_internal.h"
 
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 #include <utility>
@@ -415,6 +416,17 @@ __device__ __forceinline__ void load_whalf(WChunk<BITS> &w, const GemmBuffers &b
     w.zero = buf_load_u16(buf.zeros, mlo, meta_off);
 }
 
+// Sixteen-row blocks of activation row tile `row_tile` of MT: as even a cut of row_blocks as blocks allow, the first tiles one block higher.
+// Quotient and remainder: row_tile * row_blocks passes 2^31 from 2.97 million rows, which are taken up to K = 640.
+struct TallCut {
+    int block0, blocks;
+};
+__host__ __device__ constexpr TallCut tall_cut(int row_blocks, int MT, int row_tile)
+{
+    const int each = row_blocks / MT, rest = row_blocks % MT;
+    return {row_tile * each + (row_tile < rest ? row_tile : rest), each + (row_tile < rest)};
+}
+
 // What a tall tile's body works on.
 struct TallTile {
     GemmBuffers buf;
@@ -556,15 +568,15 @@ __device__ __forceinline__ void qgemm_tall_tile(h8 *Xs0, h8 *Xs1, const _Float16
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kh = wave >> 2, nq = wave & 3; // half of every group's k-steps, quarter of the tile's weight rows
-    // The rows are cut into MT tiles of as equal a height as blocks of sixteen allow.  Tiles are numbered in bands of two row-tiles (row-tile
-    // fastest): the 32 tiles an XCD holds at a
+    // Tiles are numbered in bands of two row-tiles (row-tile fastest): the 32 tiles an XCD holds at a
     // time share up to 512 activation rows (4 MiB at k = 4096, the size of its L2) and 16 weight tiles
-    const int NT = (N + TBN - 1) / TBN, row_blocks = (M + 15) / 16;
+    const int NT = (N + TBN - 1) / TBN;
     const int band = tile / (2 * NT), rest = tile - band * 2 * NT, height = min(2, MT - 2 * band);
     const int row_tile = 2 * band + rest % height, n0 = (rest / height) * TBN;
-    const int block0 = row_tile * row_blocks / MT, blocks = (row_tile + 1) * row_blocks / MT - block0; // up to TMB
+    const TallCut cut = tall_cut((M + 15) / 16, MT, row_tile); // up to TMB blocks
+    const int blocks = cut.blocks;
     TallTile t;
-    t.m0 = 16 * block0;
+    t.m0 = 16 * cut.block0;
     t.m_end = min(M, t.m0 + 16 * blocks);
     t.G = K >> 7;
     t.Np16 = ((N + 63) / 64 * 64) >> 4;
@@ -811,6 +823,19 @@ int fq_gemm_tall_rows(int M, const fq_packed_ref *w, int count)
     double us;
     const int row_tiles = plan_tall(M, w, count, &us);
     return 16 * tall_height(((M + 15) / 16 + row_tiles - 1) / row_tiles);
+}
+
+int fq_gemm_tall_tile(int M, const fq_packed_ref *w, int count, int row_tile, int *first, int *rows, int *worked)
+{
+    double us;
+    const int row_tiles = plan_tall(M, w, count, &us);
+    if (row_tile >= 0 && row_tile < row_tiles) {
+        const TallCut cut = tall_cut((M + 15) / 16, row_tiles, row_tile);
+        *first = 16 * cut.block0;
+        *rows = std::min(M - *first, 16 * cut.blocks);
+        *worked = 16 * tall_height(cut.blocks);
+    }
+    return row_tiles;
 }
 
 static int launch_tall(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st)

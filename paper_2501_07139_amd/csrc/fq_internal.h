@@ -71,6 +71,8 @@ void fq_decode_partition_of(unsigned bits4, int ph, int N, int wg, int grid, int
 // Height of the large tiles of a launch (128 or 256); 0: the few-row kernel, with this plan.
 int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count, fq_skinny_plan *few);
 int fq_gemm_tall_rows(int M, const fq_packed_ref *w, int count); // of the tiles of a launch of height 256, which are as high as they need be
+// Row tiles of a launch of height 256; of tile row_tile, if there is one: its first row, its rows, and those that it is worked on as.
+int fq_gemm_tall_tile(int M, const fq_packed_ref *w, int count, int row_tile, int *first, int *rows, int *worked);
 // tile_rows: 0 lets the library choose, 128 or 256 pins one of the large-tile kernels.
 int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st, int tile_rows = 0);
 // Up to three matrices with the same input (same K) in one launch; M > 16, or any M for the few-row kernel.

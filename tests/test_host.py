@@ -294,6 +294,29 @@ def test_route_takes_every_size_that_the_linear_takes():
         fq.fq_qlinear_route(1, 64, 5, 128)
 
 
+def test_tall_tiles_cover_every_row_once():
+    """The kernel's own cut of the rows, up to the most whose activations stay below 4 GiB: tiles of one to sixteen blocks that follow one another
+    from the first row to the last."""
+    N, bits = np.array([64, 2000, 11008], dtype=np.int32), np.array([2, 8, 4], dtype=np.int32)
+    out = np.zeros(4, dtype=np.int32)
+    p = [a.ctypes.data_as(ctypes.c_void_p) for a in (N, bits, out)]
+    cut = lambda M, count, K, tile: fq._lib.fq_qlinear_tall_tile(M, p[0], p[1], count, K, tile, p[2])
+    for M, K in ((17, 128), (256, 128), (257, 384), (2048, 4096), (5003, 1024), (2965900, 640), (3355443, 640), ((1 << 24) - 1, 128)):
+        assert cut(M, 1, K, 0) == 0
+        row = 0
+        for tile in range(out[0]):
+            assert cut(M, 1, K, tile) == 0
+            _, first, rows, worked = out.tolist()
+            assert first == row and 1 <= rows <= worked and worked in (128, 160, 192, 208, 224, 240, 256), (M, K, tile, out)
+            row += rows
+        assert row == M and cut(M, 1, K, out[0]) == -2
+    for M in (300, 611, 1536, 4000):  # as many tiles for the matrices of a launch together
+        assert cut(M, 3, 4096, 0) == 0 and sum(fq.fq_qlinear_tall_tile(M, N, bits, 4096, t)[2] for t in range(out[0])) == M
+    assert fq._lib.fq_qlinear_tall_tile(300, p[0], None, 1, 128, 0, p[2]) == -1
+    for M, count, K, tile in ((0, 1, 128, 0), (300, 0, 128, 0), (300, 4, 128, 0), (300, 1, 100, 0), (300, 1, 128, -1), (1 << 24, 1, 128, 0)):
+        assert cut(M, count, K, tile) == -2
+
+
 @pytest.mark.parametrize("bits", BITS)
 def test_parity_cases_reach_every_tile_of_the_few_row_kernel(bits):
     """The tile shapes that the rule chooses over 20000 sizes against those of the GPU tests' lists of cases, and their number: up
