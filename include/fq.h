@@ -166,7 +166,7 @@ int fq_qlinear_tile(const void *x, int M, const void *packed, const void *scales
 /*
  * The kernel that fq_qlinear takes, or a launch of up to three matrices that share x (host only; for tests and tools).
  * N, bits: host, count entries.  route_out (host, 3 ints): one of FQ_ROUTE_*, then rows and columns of its tiles
- * (0, 0 for the first two; FQ_ROUTE_TILES_256: 256, the most they have, and FQ_ROUTE_TILES_128: 128, in either kernel).
+ * (0, 0 for the first two; FQ_ROUTE_TILES_256, the kernel of up to 256 rows: 128 to 256, what the highest tiles of the launch are worked on as).
  */
 enum { FQ_ROUTE_STREAM, FQ_ROUTE_GENERIC, FQ_ROUTE_FEW_ROWS, FQ_ROUTE_TILES_128, FQ_ROUTE_TILES_256 };
 int fq_qlinear_route(int M, const int *N, const int *bits, int count, int K, int *route_out);

@@ -164,11 +164,9 @@ extern "C" int fq_qlinear_route(int M, const int *N, const int *bits, int count,
         return FQ_OK;
     }
     fq_skinny_plan few;
-    int rows = fq_gemm_tile_rows(M, w, count, &few);
-    if (rows == 256 && fq_gemm_tall_rows(M, w, count) <= 128)
-        rows = 128;
+    const int rows = fq_gemm_tile_rows(M, w, count, &few);
     route_out[0] = rows == 0 ? FQ_ROUTE_FEW_ROWS : (rows == 256 ? FQ_ROUTE_TILES_256 : FQ_ROUTE_TILES_128);
-    route_out[1] = rows == 0 ? 16 * few.mb : rows;
+    route_out[1] = rows == 0 ? 16 * few.mb : (rows == 256 ? fq_gemm_tall_rows(M, w, count) : rows);
     route_out[2] = rows == 0 ? 16 << few.s_log2 : 128;
     return FQ_OK;
 }

@@ -817,12 +817,12 @@ struct GemmLaunch {
 
 } // namespace
 
-// Rows of the tiles of a launch that fq_gemm_tile_rows gives to the tall kernel.
+// Rows that the highest tiles of a launch of the tall kernel (its first) are worked on as.
 int fq_gemm_tall_rows(int M, const fq_packed_ref *w, int count)
 {
-    double us;
-    const int row_tiles = plan_tall(M, w, count, &us);
-    return 16 * tall_height(((M + 15) / 16 + row_tiles - 1) / row_tiles);
+    int first, rows, worked = 0;
+    fq_gemm_tall_tile(M, w, count, 0, &first, &rows, &worked);
+    return worked;
 }
 
 int fq_gemm_tall_tile(int M, const fq_packed_ref *w, int count, int row_tile, int *first, int *rows, int *worked)

@@ -70,7 +70,7 @@ int fq_decode_available(int H, int F); // pages per ring if the persistent kerne
 void fq_decode_partition_of(unsigned bits4, int ph, int N, int wg, int grid, int *out6);
 // Height of the large tiles of a launch (128 or 256); 0: the few-row kernel, with this plan.
 int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count, fq_skinny_plan *few);
-int fq_gemm_tall_rows(int M, const fq_packed_ref *w, int count); // of the tiles of a launch of height 256, which are as high as they need be
+int fq_gemm_tall_rows(int M, const fq_packed_ref *w, int count); // what the highest tiles of a launch of height 256 are worked on as
 // Row tiles of a launch of height 256; of tile row_tile, if there is one: its first row, its rows, and those that it is worked on as.
 int fq_gemm_tall_tile(int M, const fq_packed_ref *w, int count, int row_tile, int *first, int *rows, int *worked);
 // tile_rows: 0 lets the library choose, 128 or 256 pins one of the large-tile kernels.

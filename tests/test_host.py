@@ -222,10 +222,10 @@ def route(M, N, bits, K):
 @pytest.mark.parametrize("bits", BITS)
 def test_few_row_kernel_leaves_the_sizes_that_others_run_faster(bits):
     """Sizes at which the few-row kernel was measured slower than the kernel of the general path: many rows whose
-    activations no L2 holds (2048 x 1024 x 2816: 37 against 30 us), three and four rows of wide matrices (four of
+    activations no L2 holds (2048 x 1024 x 2816: 37 against 30 us in 128-row tiles, 24 to 29 in tall tiles of 128 rows), three and four rows of wide matrices (four of
     19741 x 1792: 11.0 against 9.2); and neighbours at which it is the faster one."""
     for M, N, K in ((2048, 1024, 2816), (1890, 1420, 6400), (2480, 1066, 15616)):
-        assert route(M, N, bits, K) == "tiles_128"
+        assert fq.fq_qlinear_route(M, N, bits, K) == ("tiles_256", 128, 128)
     for M, N, K in ((1024, 1024, 2816), (512, 4096, 4096), (77, 4096, 11008), (300, 70, 256)):
         assert route(M, N, bits, K) == "few_rows"
     for M, N, K in ((3, 21160, 8192), (4, 19741, 1792), (4, 18581, 1024), (3, 4096, 4096), (2, 4096, 4096), (1, 11008, 4096)):
@@ -292,6 +292,17 @@ def test_route_takes_every_size_that_the_linear_takes():
         assert fq._lib.fq_qlinear_route(M, p[0], p[1], count, K, p[2]) == -2
     with pytest.raises(fq.FqError):
         fq.fq_qlinear_route(1, 64, 5, 128)
+
+
+def test_route_names_the_kernel_and_the_height_of_its_tiles():
+    """The 256-row kernel is named as itself however low its tiles are, with the height of the highest."""
+    heights = set()
+    for M, N, bits, K in ((1890, 1420, 2, 6400), (800, 22016, 4, 4096), (2048, 11008, 2, 4096), (1500, 11008, 2, 4096), (1536, [4096, 4096, 4096], [4, 3, 2], 4096)):
+        name, rows, columns = fq.fq_qlinear_route(M, N, bits, K)
+        assert (name, columns) == ("tiles_256", 128) and rows == fq.fq_qlinear_tall_tile(M, N, bits, K)[3]
+        heights.add(rows)
+    assert len(heights) > 3 and min(heights) == 128 and max(heights) == 256
+    assert fq.fq_qlinear_route(640, 11008, 4, 4096) == ("tiles_128", 128, 128)
 
 
 def test_tall_tiles_cover_every_row_once():
