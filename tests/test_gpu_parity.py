@@ -129,8 +129,8 @@ def test_qlinear_against_oracle(fq, torch, bits, case):
     assert np.max(np.abs(y.astype(np.float64) - r)) / np.max(np.abs(r)) <= TOL
 
 
-# 256-row tiles (two halves of K per workgroup): one group, odd and even group counts, ragged rows and columns,
-# rows that leave the last tile almost empty
+# The 256-row kernel (two halves of K per workgroup) in tiles of 8 blocks of sixteen rows, what matrices of so few columns are cut into: one group,
+# odd and even group counts, ragged rows and columns
 TALL_CASES = [(256, 128, 128), (300, 200, 384), (520, 384, 1024), (17, 70, 256), (512, 1030, 640), (700, 264, 2816)]
 
 
@@ -152,15 +152,19 @@ def test_qlinear_tall_tiles_against_oracle(fq, torch, bits, case):
     assert qerr(y, y128.astype(np.float64)) <= 1e-3
 
 
-# rows whose tall tiles are 8, 9, 10, 11, 12 to 16 blocks of sixteen high, whole blocks and ragged ones, in one row tile and in several
-TALL_HEIGHTS = [121, 144, 150, 161, 177, 192, 208, 209, 225, 240, 241, 300, 403, 611, 1200]
+# Few columns: their tiles fill one round however low, so the rows are cut into tiles of 8, 10 or 12 blocks of sixteen; whole blocks and ragged ones,
+# in one row tile and in several
+TALL_LOW = {121: (1, 128), 144: (1, 160), 150: (1, 160), 161: (1, 192), 177: (1, 192), 192: (1, 192), 208: (2, 128), 209: (2, 128), 225: (2, 128),
+            240: (2, 128), 241: (2, 128), 300: (3, 128), 403: (4, 128), 611: (5, 128), 1200: (10, 128)}
 
 
 @pytest.mark.parametrize("bits", BITS)
-@pytest.mark.parametrize("M", TALL_HEIGHTS)
-def test_qlinear_tall_tiles_of_every_height(fq, torch, bits, M):
+@pytest.mark.parametrize("M", TALL_LOW)
+def test_qlinear_low_tall_tiles(fq, torch, bits, M):
     """Integer and fractional zeros (their loops differ); the last column of tiles is ragged."""
     N, K = 130, 384
+    tiles, _, _, worked = fq.fq_qlinear_tall_tile(M, N, bits, K)
+    assert (tiles, worked) == TALL_LOW[M]
     codes = fq_synth.codes(121, N, K, bits)
     s = np.random.default_rng(122).uniform(0.01, 0.02, (N, K // 128)).astype(np.float16)
     X = fq_synth.activations(123, M, K)
@@ -172,6 +176,48 @@ def test_qlinear_tall_tiles_of_every_height(fq, torch, bits, M):
         torch.cuda.synchronize()
         assert out.intact()
         assert qerr(host16(out.half(M, N)), r) <= TOL
+
+
+# 256 columns of tiles: a row tile is a round of its own, so the tiles are as few and high as can be.  Every height, in one row tile and in
+# several, that differ by a block too; whole blocks and ragged ones
+TALL_WIDE = {119: (128,), 135: (160,), 151: (160,), 167: (192,), 183: (192,), 199: (208,), 208: (208,), 215: (224,), 231: (240,), 247: (256,), 256: (256,),
+             281: (160, 160), 345: (192, 192), 397: (208, 192), 409: (208, 208), 429: (224, 208), 441: (224, 224), 461: (240, 224), 473: (240, 240),
+             493: (256, 240), 505: (256, 256), 749: (256, 256, 240)}
+
+
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("K", [128, 384, 640])
+@pytest.mark.parametrize("fraction", [0.0, 0.25])
+def test_qlinear_tall_tiles_of_every_height(fq, torch, bits, K, fraction):
+    """The first and last columns and sampled ones against the oracle, all of them against the 128-row kernel; one group and odd numbers of
+    them, integer and fractional zeros, a last column of tiles that is ragged, guard bytes.
+
+    The oracle takes the weights as the kernel has them, rounded to fp16 once (code - zero, of at most ten bits here, is exact): what is left is the
+    result's own rounding, 2^-11 = 4.9e-4, and fp32 sums of 640 products, below 640 * 2^-24 = 4e-5 of sum |x w|, in practice 1e-6 of the rms."""
+    N = 32707
+    assert {h for heights in TALL_WIDE.values() for h in heights} == {128, 160, 192, 208, 224, 240, 256}
+    rng = np.random.default_rng(125)
+    codes = fq_synth.codes(126, N, K, bits)
+    s = rng.uniform(0.01, 0.02, (N, K // 128)).astype(np.float16)
+    z = (fq_synth.codes(127, N, K // 128, bits).astype(np.float32) + fraction).astype(np.float16)
+    w = fq.PackedMatrix.from_host(codes, s, z, bits)
+    cols = np.unique(np.concatenate([rng.integers(0, N, size=64), np.arange(128), np.arange(N - 80, N)]))
+    sampled = oracle.dequant(codes[cols], s[cols], z[cols])
+    X = fq_synth.activations(128, max(TALL_WIDE), K)
+    r = oracle.qlinear(X, oracle.round_f16(sampled.astype(np.float64)).astype(np.float32))
+    Xd, index = dev(torch, X), torch.from_numpy(cols).cuda()
+    for M, heights in TALL_WIDE.items():
+        tiles = [fq.fq_qlinear_tall_tile(M, N, bits, K, t) for t in range(len(heights))]
+        assert tuple(t[3] for t in tiles) == heights and tiles[0][0] == len(heights), M
+        out = Guarded(torch, M * N * 2)
+        fq.fq_qlinear(Xd[:M], w, out=out.half(M, N), tile_rows=256)
+        torch.cuda.synchronize()
+        assert out.intact(), M
+        assert qerr(host16(out.half(M, N)[:, index]), r[:M]) <= 5.2e-4, M
+        # the 128-row kernel on the same inputs: same products, fp32 sums in another order
+        y, y128 = out.half(M, N).float(), fq.fq_qlinear(Xd[:M], w, tile_rows=128).float()
+        rms = y128.square().mean(1, keepdim=True).sqrt()
+        assert float(((y - y128).abs() / torch.maximum(y128.abs(), rms)).max()) <= 1e-3, M
 
 
 @pytest.mark.parametrize("bits", BITS)
