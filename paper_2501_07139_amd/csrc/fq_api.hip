@@ -163,11 +163,10 @@ extern "C" int fq_qlinear_route(int M, const int *N, const int *bits, int count,
         route_out[0] = stream ? FQ_ROUTE_STREAM : FQ_ROUTE_GENERIC;
         return FQ_OK;
     }
-    fq_skinny_plan few;
-    const int rows = fq_gemm_tile_rows(M, w, count, &few);
-    route_out[0] = rows == 0 ? FQ_ROUTE_FEW_ROWS : (rows == 256 ? FQ_ROUTE_TILES_256 : FQ_ROUTE_TILES_128);
-    route_out[1] = rows == 0 ? 16 * few.mb : (rows == 256 ? fq_gemm_tall_rows(M, w, count) : rows);
-    route_out[2] = rows == 0 ? 16 << few.s_log2 : 128;
+    const fq_gemm_plan plan = fq_plan_gemm(M, w, count);
+    route_out[0] = plan.tile_rows == 0 ? FQ_ROUTE_FEW_ROWS : (plan.tile_rows == 256 ? FQ_ROUTE_TILES_256 : FQ_ROUTE_TILES_128);
+    route_out[1] = plan.tile_rows == 0 ? 16 * plan.few.mb : plan.height;
+    route_out[2] = plan.tile_rows == 0 ? 16 << plan.few.s_log2 : 128;
     return FQ_OK;
 }
 

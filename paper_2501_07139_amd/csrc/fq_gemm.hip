@@ -716,7 +716,8 @@ int plan_tall(int M, const fq_packed_ref *w, int count, double *us)
     return best;
 }
 
-// Tile height for a launch of `count` matrices that the few-row kernel does not serve: 128 rows or plan_tall's, by estimated times.  From
+// Estimated times of the large tiles for a launch of `count` matrices, of which one that the few-row kernel does not serve takes 128 rows or
+// plan_tall's (see tall_row_tiles).  From
 // K = 2048 on both estimates hold for themselves: over 2830 sizes of 130 to 4096 rows and 300 to 27648 columns the choice takes 0.4 % longer than
 // the better one on average, 2 % in one of twenty (3-bit matrices over long rows, where both are closest, with a wider margin).  The one of the 128-row tiles: rounds over the 256 CUs, two tiles a CU; measured over 32
 // groups, 512 to 2048 rows, 4096 to 22016 columns (us at 2 / 3 / 4 / 8 bits) a full round 63 / 73 / 67 / 73, its last one 47 when
@@ -732,7 +733,11 @@ int plan_tall(int M, const fq_packed_ref *w, int count, double *us)
 // round a scale into every weight, which that kernel applies to sums in fp32.  A full round of them 61 / 67 / 63 / 66, a last one 50
 // to 60, 1.5 us more on short rows (the two halves of their K meet through LDS), and the factors below: without them the few-row
 // kernel was taken for 29 of 300 sizes that it serves 2 to 26 % more slowly, with them for 10, up to 8 %.
-int choose_tile_rows(int M, const fq_packed_ref *w, int count, double *us)
+struct LargeTiles {
+    double us, us128;
+    bool full_height, all_wide;
+};
+LargeTiles large_tiles(int M, const fq_packed_ref *w, int count)
 {
     static const double full128[9] = {0, 0, 63, 73, 67, 0, 0, 0, 73}, full256[9] = {0, 0, 61, 67, 63, 0, 0, 0, 66};
     long tiles = 0, tall = 0;
@@ -758,15 +763,27 @@ int choose_tile_rows(int M, const fq_packed_ref *w, int count, double *us)
     const double low = 5.4 + G * (tiles <= 256 ? 1.31 : 1.5 + three + 0.7 * (tiles - 256) / 256.0);
     const double us128 = tiles <= 256 ? low : (tiles <= 512 ? (low + brief) * (length < 1.0 ? 1.0 : long_part) : (6.0 + t128 * length + brief) * long_part);
     const double fixed256 = length < 1.0 ? 1.5 * (1.0 - length) * (tall / 256 + (r256 != 0)) : 0.0;
-    *us = us128;
     const bool full_height = M > 128 && tiles > 256 && !all_wide && t256 * length + fixed256 < t128 * length;
+    double us = us128;
     if (full_height)
-        *us = (3.0 + t256 * length + fixed256 + brief) * (three != 0.0 || length < 1.0 ? 1.0 : (tall <= 256 ? 0.9 : 0.95));
-    if (w[0].K < 2048 || all_wide)
-        return full_height ? 256 : 128;
+        us = (3.0 + t256 * length + fixed256 + brief) * (three != 0.0 || length < 1.0 ? 1.0 : (tall <= 256 ? 0.9 : 0.95));
+    return {us, us128, full_height, all_wide};
+}
+
+// Row tiles of the tall kernel, or 0: the 128-row kernel.
+int tall_row_tiles(int M, const fq_packed_ref *w, int count, const LargeTiles &large)
+{
+    const bool by_full_height = w[0].K < 2048 || large.all_wide;
+    if (M <= 128 || (by_full_height && !large.full_height))
+        return 0;
     double us256;
-    plan_tall(M, w, count, &us256);
-    return M > 128 && us256 < (three != 0.0 && w[0].K > 8192 ? 0.92 : 0.97) * us128 ? 256 : 128;
+    const int row_tiles = plan_tall(M, w, count, &us256);
+    if (by_full_height)
+        return row_tiles;
+    bool three = false;
+    for (int i = 0; i < count; ++i)
+        three = three || w[i].bits == 3;
+    return us256 < (three && w[0].K > 8192 ? 0.92 : 0.97) * large.us128 ? row_tiles : 0;
 }
 
 template <int BITS, int QNB>
@@ -817,13 +834,8 @@ struct GemmLaunch {
 
 } // namespace
 
-// Rows that the highest tiles of a launch of the tall kernel (its first) are worked on as.
-int fq_gemm_tall_rows(int M, const fq_packed_ref *w, int count)
-{
-    int first, rows, worked = 0;
-    fq_gemm_tall_tile(M, w, count, 0, &first, &rows, &worked);
-    return worked;
-}
+// What the highest tiles of a launch of the tall kernel are worked on as.
+static int highest_rows(int M, int row_tiles) { return 16 * tall_height(((M + 15) / 16 + row_tiles - 1) / row_tiles); }
 
 int fq_gemm_tall_tile(int M, const fq_packed_ref *w, int count, int row_tile, int *first, int *rows, int *worked)
 {
@@ -838,10 +850,12 @@ int fq_gemm_tall_tile(int M, const fq_packed_ref *w, int count, int row_tile, in
     return row_tiles;
 }
 
-static int launch_tall(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st)
+// row_tiles: as planned; 0 where the caller pins the kernel.
+static int launch_tall(const void *x, int M, const fq_packed_ref *w, void *const *outs, int count, fq_stream st, int row_tiles)
 {
     double us;
-    const int row_tiles = plan_tall(M, w, count, &us);
+    if (row_tiles == 0)
+        row_tiles = plan_tall(M, w, count, &us);
     const GemmLaunch l(w, outs, count, [&](int i) { return row_tiles * ((w[i].N + TBN - 1) / TBN); }, [](int) { return 0; });
     hipLaunchKernelGGL(qgemm_tall_kernel, dim3(8 * ((l.total + 7) / 8)), dim3(512), 0, st,
                        static_cast<const _Float16 *>(x), M, w[0].K, l.total, l.first[1], l.first[2], row_tiles, l.jobs);
@@ -856,23 +870,28 @@ static int launch_tall(const void *x, int M, const fq_packed_ref *w, void *const
 // the few-row kernel is expected to take 1.3 to 1.4 of the other's time at K = 256, 1.2 to 1.3 at 512 and 1.0 to 1.15 up to 1408 (many rounds
 // of its sixteen-row tiles, 20 x 23466 x 256, are not ahead: 7.3 against 9.0).  Tiles of up to 32 columns have a tenth in their favour up
 // to 1280: they keep the scales in fp32, the large ones round them into the weights.
-int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count, fq_skinny_plan *few)
+fq_gemm_plan fq_plan_gemm(int M, const fq_packed_ref *w, int count)
 {
-    double us = 0.0;
-    const int rows = choose_tile_rows(M, w, count, &us);
-    if (!fq_skinny_can(M, w[0].K))
-        return rows;
-    *few = fq_plan_skinny(M, w, count);
-    if (M <= 16)
-        return 0;
-    const int K = w[0].K;
-    const bool narrow = few->s_log2 < 2;
-    double level = 0.97;
-    if (K <= 1280 && few->mb == 1)
-        level = narrow ? 1.02 : 0.97;
-    else if (K <= 1280)
-        level = K <= 256 ? 1.3 : (K <= 512 ? 1.2 : (narrow ? 1.1 : 1.03));
-    return few->us < level * us ? 0 : rows;
+    const LargeTiles large = large_tiles(M, w, count);
+    fq_gemm_plan plan = {};
+    if (fq_skinny_can(M, w[0].K)) {
+        plan.few = fq_plan_skinny(M, w, count);
+        if (M <= 16)
+            return plan;
+        const int K = w[0].K;
+        const bool narrow = plan.few.s_log2 < 2;
+        double level = 0.97;
+        if (K <= 1280 && plan.few.mb == 1)
+            level = narrow ? 1.02 : 0.97;
+        else if (K <= 1280)
+            level = K <= 256 ? 1.3 : (K <= 512 ? 1.2 : (narrow ? 1.1 : 1.03));
+        if (plan.few.us < level * large.us)
+            return plan;
+    }
+    plan.row_tiles = tall_row_tiles(M, w, count, large);
+    plan.tile_rows = plan.row_tiles ? 256 : 128;
+    plan.height = plan.row_tiles ? highest_rows(M, plan.row_tiles) : 128;
+    return plan;
 }
 
 int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_stream st, int tile_rows)
@@ -880,13 +899,15 @@ int fq_launch_gemm(const void *x, int M, const fq_packed_ref &w, void *out, fq_s
     const size_t Np = ((size_t)w.N + 63) / 64 * 64;
     if (!fits_32bit(M, w.K, 2) || Np / 8 * w.K * w.bits >= ((size_t)1 << 32))
         return (int)hipErrorInvalidValue;
-    fq_skinny_plan few;
+    fq_gemm_plan plan = {};
+    if (tile_rows == 0) {
+        plan = fq_plan_gemm(M, &w, 1);
+        tile_rows = plan.tile_rows;
+    }
     if (tile_rows == 0)
-        tile_rows = fq_gemm_tile_rows(M, &w, 1, &few);
-    if (tile_rows == 0)
-        return fq_launch_skinny(x, M, &w, &out, 1, few, st);
+        return fq_launch_skinny(x, M, &w, &out, 1, plan.few, st);
     if (tile_rows == 256)
-        return launch_tall(x, M, &w, &out, 1, st);
+        return launch_tall(x, M, &w, &out, 1, st, plan.row_tiles);
     if (w.ld && w.ld != w.N) // a column range of a wider output: the multi-matrix kernel carries the row pitch
         return fq_launch_gemm_multi(x, M, &w, &out, 1, st, 128);
     switch (w.bits) {
@@ -908,13 +929,15 @@ int fq_launch_gemm_multi(const void *x, int M, const fq_packed_ref *w, void *con
         if (w[i].K != w[0].K || !fits_32bit(M, w[i].K, 2) || Np / 8 * w[i].K * w[i].bits >= ((size_t)1 << 32))
             return (int)hipErrorInvalidValue;
     }
-    fq_skinny_plan few;
+    fq_gemm_plan plan = {};
+    if (tile_rows == 0) {
+        plan = fq_plan_gemm(M, w, count);
+        tile_rows = plan.tile_rows;
+    }
     if (tile_rows == 0)
-        tile_rows = fq_gemm_tile_rows(M, w, count, &few);
-    if (tile_rows == 0)
-        return fq_launch_skinny(x, M, w, outs, count, few, st);
+        return fq_launch_skinny(x, M, w, outs, count, plan.few, st);
     if (tile_rows == 256)
-        return launch_tall(x, M, w, outs, count, st);
+        return launch_tall(x, M, w, outs, count, st, plan.row_tiles);
     auto qnb = [&](int i) { return (w[i].bits == 2 || w[i].bits == 4) && wide_tiles_pay(M, w[i].N) ? 4 : 2; };
     const GemmLaunch l(w, outs, count, [&](int i) { return ((w[i].N + 64 * qnb(i) - 1) / (64 * qnb(i))) * ((M + QBM - 1) / QBM); }, qnb);
     hipLaunchKernelGGL(qgemm_multi_kernel, dim3(8 * ((l.total + 7) / 8)), dim3(256), 0, st,

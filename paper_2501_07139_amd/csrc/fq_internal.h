@@ -68,9 +68,14 @@ int fq_decode_set_mode(int mode);    // 0: per-phase launches (default), 1: pers
 unsigned long long fq_decode_launches(); // persistent launches queued by this process so far
 int fq_decode_available(int H, int F); // pages per ring if the persistent kernel would run, else 0
 void fq_decode_partition_of(unsigned bits4, int ph, int N, int wg, int grid, int *out6);
-// Height of the large tiles of a launch (128 or 256); 0: the few-row kernel, with this plan.
-int fq_gemm_tile_rows(int M, const fq_packed_ref *w, int count, fq_skinny_plan *few);
-int fq_gemm_tall_rows(int M, const fq_packed_ref *w, int count); // what the highest tiles of a launch of height 256 are worked on as
+// Planned once a call: the kernel of a launch of more than sixteen rows.
+struct fq_gemm_plan {
+    int tile_rows;      // 128 or 256: the large-tile kernel; 0: the few-row kernel
+    fq_skinny_plan few; // of the few-row kernel
+    int row_tiles;      // of height 256: what the rows are cut into
+    int height;         // of the large tiles: rows that the highest are worked on as
+};
+fq_gemm_plan fq_plan_gemm(int M, const fq_packed_ref *w, int count);
 // Row tiles of a launch of height 256; of tile row_tile, if there is one: its first row, its rows, and those that it is worked on as.
 int fq_gemm_tall_tile(int M, const fq_packed_ref *w, int count, int row_tile, int *first, int *rows, int *worked);
 // tile_rows: 0 lets the library choose, 128 or 256 pins one of the large-tile kernels.

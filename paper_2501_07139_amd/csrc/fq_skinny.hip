@@ -671,7 +671,7 @@ fq_skinny_plan fq_plan_skinny(int M, const fq_packed_ref *w, int count)
 // Whether the kernel's 32-bit byte offsets reach all of a launch's activations and of a tile's weights.
 bool fq_skinny_can(int M, int K) { return K <= (1 << 22) && (size_t)M * K * 2 < ((size_t)1 << 32); }
 
-// Whether a launch of up to sixteen rows goes to the skinny kernel (more rows: see fq_gemm_tile_rows): from four rows on,
+// Whether a launch of up to sixteen rows goes to the skinny kernel (more rows: see fq_plan_gemm): from four rows on,
 // three of long rows, where the
 // streaming kernel stages one row after another (4096 x 4096, 4 bits: 7.5 against 5.8 us at 4 rows, 17 against 6.0 at 16; at
 // one row 4.2 against 6.1; 4096 x 11008 at 3 rows 11.3 against 10), and where that kernel has no room for the rows.  Four
