@@ -734,7 +734,8 @@ int plan_tall(int M, const fq_packed_ref *w, int count, double *us)
 // to 60, 1.5 us more on short rows (the two halves of their K meet through LDS), and the factors below: without them the few-row
 // kernel was taken for 29 of 300 sizes that it serves 2 to 26 % more slowly, with them for 10, up to 8 %.
 struct LargeTiles {
-    double us, us128;
+    double us;
+    long tiles; // of 128 rows
     bool full_height, all_wide;
 };
 LargeTiles large_tiles(int M, const fq_packed_ref *w, int count)
@@ -767,10 +768,42 @@ LargeTiles large_tiles(int M, const fq_packed_ref *w, int count)
     double us = us128;
     if (full_height)
         us = (3.0 + t256 * length + fixed256 + brief) * (three != 0.0 || length < 1.0 ? 1.0 : (tall <= 256 ? 0.9 : 0.95));
-    return {us, us128, full_height, all_wide};
+    return {us, tiles, full_height, all_wide};
 }
 
-// Row tiles of the tall kernel, or 0: the 128-row kernel.
+// Estimated time of 128-row tiles that plan_tall's is held against, fitted to 2500 launches of 130 to 4096 rows from K = 2048 on (6.4 % off; the
+// one in large_tiles, which the few-row kernel is held against, 7.8, up to 20 too high where 257 to 512 tiles nearly fill the chip and as much too
+// low where they hardly start a second one a CU).  Rounds of 512 tiles, two a CU; a group of a full one takes 1.62 / 1.84 / 1.74 / 1.86 us at 2 / 3 / 4 / 8
+// bits, of one that is not full the parts below.  A launch of 128 x 256 tiles and others takes a fifth longer: each XCD has as many tiles as the next
+// (2174 rows of two 11008 x 4096 at 8 and 2 bits 478 us, 365 in tall tiles).
+double us_128(int M, const fq_packed_ref *w, int count)
+{
+    static const double group[9] = {0, 0, 1.62, 1.84, 1.74, 0, 0, 0, 1.86};
+    long tiles = 0;
+    double each = 0.0;
+    int wide = 0;
+    for (int i = 0; i < count; ++i) {
+        wide += (w[i].bits == 2 || w[i].bits == 4) && wide_tiles_pay(M, w[i].N);
+        const long t = (long)((w[i].N + 127) / 128) * ((M + 127) / 128);
+        tiles += t;
+        each += t * group[w[i].bits];
+    }
+    const long whole = tiles / (2 * CUS), rest = tiles % (2 * CUS);
+    const double x = (double)rest / CUS;
+    double part = 0.0;
+    if (rest != 0 && whole == 0)
+        part = x <= 1.0 ? 0.71 : 0.65 + 0.20 * x;
+    else if (rest != 0)
+        part = x <= 1.0 ? 0.60 + 0.09 * x : 0.64 + 0.25 * x;
+    const double us = 3.1 + 5.5 * (whole + (rest != 0)) + (w[0].K >> 7) * (each / tiles) * (whole + part);
+    return wide != 0 && wide != count ? 1.2 * us : us;
+}
+
+// Row tiles of the tall kernel, or 0: the 128-row kernel.  From K = 2048 on by the two estimates above, except that calls of up to two 128-row tiles
+// a CU that go to the tall kernel by tiles of the full height stay there, and with a margin for all that this choice gives to either kernel.  Over
+// 1500 sizes the calls take 9 % less on average than by full heights, 5 of them 5 to 6 % more (13, up to 16 %, by the estimate of large_tiles: 229 x 22016 x
+// 4096 at 8 bits 51.7 us in tall tiles and 58.6 in the others, 552 x 12288 x 11008 at 2 bits 183 and 150); over 1500 launches of two or three
+// matrices 7 % less, 6 over 5 % more (28, up to 30 %: 1213 rows of two 13824 x 4096 at 4 and 3 bits 298 and 363).
 int tall_row_tiles(int M, const fq_packed_ref *w, int count, const LargeTiles &large)
 {
     const bool by_full_height = w[0].K < 2048 || large.all_wide;
@@ -778,12 +811,9 @@ int tall_row_tiles(int M, const fq_packed_ref *w, int count, const LargeTiles &l
         return 0;
     double us256;
     const int row_tiles = plan_tall(M, w, count, &us256);
-    if (by_full_height)
+    if (by_full_height || (large.full_height && large.tiles <= 2 * CUS))
         return row_tiles;
-    bool three = false;
-    for (int i = 0; i < count; ++i)
-        three = three || w[i].bits == 3;
-    return us256 < (three && w[0].K > 8192 ? 0.92 : 0.97) * large.us128 ? row_tiles : 0;
+    return us256 < (large.full_height ? 1.03 : 0.98) * us_128(M, w, count) ? row_tiles : 0;
 }
 
 template <int BITS, int QNB>
