@@ -132,25 +132,10 @@ __device__ __forceinline__ void skinny_store(h8 *smem, const f4 (&acc)[S][MB], i
             red[(wave * RED + b) * 64 + lane] = acc[u][j];
         });
         __syncthreads();
-        for (int b = wave; b < N; b += SNW) {
-            f4 sum;
-            if (waves == SNW) { // all of them at once: read one behind the other they took eight times an LDS access
-                f4 of[SNW];
-#pragma unroll
-                for (int v = 0; v < SNW; ++v)
-                    of[v] = red[(v * RED + b) * 64 + lane];
-                sum = of[0];
-#pragma unroll
-                for (int v = 1; v < SNW; ++v)
-                    sum += of[v];
-            } else {
-                sum = red[b * 64 + lane];
-                for (int v = 1; v < waves; ++v)
-                    sum += red[(v * RED + b) * 64 + lane];
-            }
+        auto store = [&](int b, f4 sum) {
             const int m = m0 + 16 * ((first + b) % MB) + r, n = 16 * (sb0 + (first + b) / MB) + 4 * c;
             if (m >= M)
-                continue;
+                return;
             _Float16 *o = job.out + (size_t)m * job.ld + n;
             if (n + 3 < job.N && vec_ok) {
                 *reinterpret_cast<h4 *>(o) = h4{(_Float16)sum[0], (_Float16)sum[1], (_Float16)sum[2], (_Float16)sum[3]};
@@ -160,6 +145,31 @@ __device__ __forceinline__ void skinny_store(h8 *smem, const f4 (&acc)[S][MB], i
                     if (n + v < job.N)
                         o[v] = (_Float16)sum[v];
             }
+        };
+        auto at_once = [&](int b) { // read one behind the other they took eight times an LDS access
+            f4 of[SNW];
+#pragma unroll
+            for (int v = 0; v < SNW; ++v)
+                of[v] = red[(v * RED + b) * 64 + lane];
+            f4 sum = of[0];
+#pragma unroll
+            for (int v = 1; v < SNW; ++v)
+                sum += of[v];
+            return sum;
+        };
+        auto in_turn = [&](int b) {
+            f4 sum = red[b * 64 + lane];
+            for (int v = 1; v < waves; ++v)
+                sum += red[(v * RED + b) * 64 + lane];
+            return sum;
+        };
+        // two loops: with the choice inside of one, rows of up to 896 took 1 % longer
+        if (waves == SNW) {
+            for (int b = wave; b < N; b += SNW)
+                store(b, at_once(b));
+        } else {
+            for (int b = wave; b < N; b += SNW)
+                store(b, in_turn(b));
         }
     });
 }

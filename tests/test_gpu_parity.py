@@ -246,7 +246,9 @@ def test_qlinear_decode_units_against_oracle(fq, torch, bits, case):
 SKINNY_CASES = [(4, 512, 128), (16, 70, 1152), (9, 11008, 384), (17, 4096, 1152), (17, 8200, 1152), (33, 4096, 1152),
                 (48, 11008, 384), (60, 4096, 2176), (64, 11008, 1152), (77, 4096, 1152), (100, 201, 256),
                 (128, 4096, 1152), (200, 4096, 1152), (250, 1030, 1280), (5, 4150, 384), (1036, 98, 128), (620, 230, 896),
-                (1045, 193, 128)]
+                (1045, 193, 128),
+                # one block a tile, where wavefronts have no group: one of them, most, none
+                (20, 70, 896), (21, 68, 256), (33, 40, 1024)]
 
 
 @pytest.mark.parametrize("bits", BITS)
