@@ -774,11 +774,11 @@ LargeTiles large_tiles(int M, const fq_packed_ref *w, int count)
 // Estimated time of 128-row tiles that plan_tall's is held against, fitted to 2500 launches of 130 to 4096 rows from K = 2048 on (6.4 % off; the
 // one in large_tiles, which the few-row kernel is held against, 7.8, up to 20 too high where 257 to 512 tiles nearly fill the chip and as much too
 // low where they hardly start a second one a CU).  Rounds of 512 tiles, two a CU; a group of a full one takes 1.62 / 1.84 / 1.74 / 1.86 us at 2 / 3 / 4 / 8
-// bits, of one that is not full the parts below.  A launch of 128 x 256 tiles and others takes a fifth longer: each XCD has as many tiles as the next
+// bits (at 3 the 1.77 below: plan_tall's is as much too low there; 5473 x 374 x 2816 37.1 us and 39.4 in tall tiles), of one that is not full the parts below.  A launch of 128 x 256 tiles and others takes a fifth longer: each XCD has as many tiles as the next
 // (2174 rows of two 11008 x 4096 at 8 and 2 bits 478 us, 365 in tall tiles).
 double us_128(int M, const fq_packed_ref *w, int count)
 {
-    static const double group[9] = {0, 0, 1.62, 1.84, 1.74, 0, 0, 0, 1.86};
+    static const double group[9] = {0, 0, 1.62, 1.77, 1.74, 0, 0, 0, 1.86};
     long tiles = 0;
     double each = 0.0;
     int wide = 0;
@@ -801,9 +801,9 @@ double us_128(int M, const fq_packed_ref *w, int count)
 
 // Row tiles of the tall kernel, or 0: the 128-row kernel.  From K = 2048 on by the two estimates above, except that calls of up to two 128-row tiles
 // a CU that go to the tall kernel by tiles of the full height stay there, and with a margin for all that this choice gives to either kernel.  Over
-// 1500 sizes the calls take 9 % less on average than by full heights, 5 of them 5 to 6 % more (13, up to 16 %, by the estimate of large_tiles: 229 x 22016 x
-// 4096 at 8 bits 51.7 us in tall tiles and 58.6 in the others, 552 x 12288 x 11008 at 2 bits 183 and 150); over 1500 launches of two or three
-// matrices 7 % less, 6 over 5 % more (28, up to 30 %: 1213 rows of two 13824 x 4096 at 4 and 3 bits 298 and 363).
+// 2000 sizes of 130 to 16000 rows the calls take 9 % less on average than by full heights, 4 of them 5 to 9 % more (9, up to 22 %, by the estimate of
+// large_tiles: 252 x 22016 x 4096 at 8 bits 51.4 us in tall tiles and 59.6 in the others, 578 x 12288 x 11008 at 2 bits 183 and 150); over 1500 launches
+// of two or three matrices 7 % less, one over 5 % more (27, up to 46 %: 1223 rows of two 13824 x 4096 at 4 and 3 bits 295 and 373).
 int tall_row_tiles(int M, const fq_packed_ref *w, int count, const LargeTiles &large)
 {
     const bool by_full_height = w[0].K < 2048 || large.all_wide;

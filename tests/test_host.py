@@ -296,11 +296,12 @@ def test_route_takes_every_size_that_the_linear_takes():
 
 def test_large_tiles_by_their_measured_times():
     """Calls from K = 2048 on that an earlier estimate of the 128-row tiles had given to the slower kernel.  us in tall tiles and in the others:
-    51.7 / 58.6, 64.4 / 74.9, 36.3 / 41.3, 65.5 / 74.0, 365 / 478, 298 / 367; then 183 / 150, 169 / 152, 148 / 133, 79.0 / 60.5, 155 / 122."""
+    51.7 / 58.6, 64.4 / 74.9, 36.3 / 41.3, 65.5 / 74.0, 365 / 478, 298 / 367; then 183 / 150, 169 / 152, 148 / 133, 39.4 / 37.1,
+    79.0 / 60.5, 155 / 122."""
     for M, N, bits, K in ((229, 22016, 8, 4096), (250, 22016, 8, 5120), (234, 17177, 2, 2304), (499, 11008, 8, 5120), (2174, [11008, 11008], [8, 2], 4096),
                           (1223, [13824, 13824], [4, 3], 4096)):
         assert route(M, N, bits, K) == "tiles_256"
-    for M, N, bits, K in ((552, 12288, 2, 11008), (1811, 4164, 4, 10112), (1032, 7134, 2, 8960), (314, [15852, 850], [2, 3], 3968),
+    for M, N, bits, K in ((552, 12288, 2, 11008), (1811, 4164, 4, 10112), (1032, 7134, 2, 8960), (5473, 374, 3, 2816), (314, [15852, 850], [2, 3], 3968),
                           (538, [231, 1204, 10772], [4, 3, 2], 7424)):
         assert route(M, N, bits, K) == "tiles_128"
 
