@@ -153,7 +153,8 @@ int fq_dequant(const void *packed, const void *scales, const void *zeros,
  * k-steps of every group split over two wavefront sets (each unpacked weight
  * feeds twice as many matrix instructions); the library takes whichever needs less
  * time for its rounds of tiles over the chip (as measured on MI355X).  The rows of a
- * launch of the latter are cut into tiles of equal height, 128 to 256, by the same measure.
+ * launch of the latter are cut into tiles as even as blocks of sixteen rows allow, of up to
+ * 256 rows and worked on as 128 to 256, by the same measure.
  * fq_qlinear_tile is the same call with the choice
  * made by the caller: tile_rows = 128 or 256 pins a kernel (any M > 16; for tests
  * and tuning; ignored for M <= 16), 0 leaves it to the library; anything else is

@@ -673,19 +673,19 @@ int wide_tiles_pay(int M, int N)
 
 constexpr int CUS = 256;
 
-// Row blocks that a tile of `blocks` is worked on as: the heights there are bodies for.
+// Row blocks that a tile of `blocks` is worked on as: the heights there are bodies for.  13 blocks take 4 % less than 14 (1 to 7 over four widths, K =
+// 1024 to 11008, one and two rounds), 14 take 6 % less than 15 and 15 take 3 % less than 16; 9 and 11 would gain 1 to 3 on the next.
 int tall_height(int blocks) { return blocks > 12 ? blocks : (blocks > 10 ? 12 : (blocks > 8 ? 10 : 8)); }
 
 // Row tiles that a launch of tall tiles cuts M into, by estimated time (fitted to 29000 launches; from K = 2560 on 5 % off, shorter ones
-// up to 20).  Rounds over the CUs, a tile each; a last round that is
-// not full takes nearly as long as a full one.  A round takes, of every group of 128 k, a part that does not depend on the height (a tile's weights
-// are unpacked whatever it is) and one that does.  Tiles of TBM rows are the fewest; more and lower ones are better where they fill the
-// rounds better, and a launch's tiles are only as high as they have to be: at full height, rows that do not divide by TBM cost a last tile
-// of a few rows as much as a whole one.  Measured, us, full height -> as chosen: 1200 x 4096 x
-// 11008 at 4 bits 136 -> 107 (eight of 160), 1500 x 11008 x 4096 at 2 bits 158 -> 135 (eight of 192), 800 x 22016 x 4096 at 4 bits 168 -> 137 (four of 208), 1890
-// x 1420 x 6400 at 2 bits 74 -> 50 (fifteen of 128).  Exactly as many tiles as whole rounds hold, by one more in some of the columns, gave 3 % more at
-// one size in sixteen: a chip that is
-// full clocks lower, and 2048 x 11008 x 4096 takes 166 us in 2.7 rounds of full height as in three of 240 rows.
+// up to 20).  Rounds over the CUs, a tile each; a last round that is not full takes nearly as long as a full one.  A round takes, of every group
+// of 128 k, a part that does not depend on the height (a tile's weights are unpacked whatever it is) and one that does.  Tiles of TBM rows are the
+// fewest; more and lower ones are better where they fill the rounds better, and a launch's tiles are only as high as they have to be: at full
+// height, rows that do not divide by TBM cost a last tile of a few rows as much as a whole one.  Measured, us, full height -> as chosen: 1500 x 11008 x 4096
+// at 2 bits 158 -> 135 (eight of 192), 800 x 22016 x 4096 at 4 bits 168 -> 137 (four of 208); a call that was the 128-row kernel's, 1890 x 1420 x 6400 at 2
+// bits, 70 -> 52 (fifteen of 128).  On rows shorter than 2048, whose kernel is chosen by full heights, the cut takes 8 % less than those over 300 sizes and
+// nowhere over 2 % more.  Exactly as many tiles as whole rounds hold, by one more in some of the columns, gave 3 % more at one size in sixteen: a chip
+// that is full clocks lower, and 2048 x 11008 x 4096 takes 166 us in 2.7 rounds of full height as in three of 240 rows.
 int plan_tall(int M, const fq_packed_ref *w, int count, double *us)
 {
     static const double whole[9] = {0, 0, 0.390, 0.812, 0.362, 0, 0, 0, 0.418}, block[9] = {0, 0, 0.063, 0.049, 0.067, 0, 0, 0, 0.066};
@@ -716,23 +716,21 @@ int plan_tall(int M, const fq_packed_ref *w, int count, double *us)
     return best;
 }
 
-// Estimated times of the large tiles for a launch of `count` matrices, of which one that the few-row kernel does not serve takes 128 rows or
-// plan_tall's (see tall_row_tiles).  From
-// K = 2048 on both estimates hold for themselves: over 2830 sizes of 130 to 4096 rows and 300 to 27648 columns the choice takes 0.4 % longer than
-// the better one on average, 2 % in one of twenty (3-bit matrices over long rows, where both are closest, with a wider margin).  The one of the 128-row tiles: rounds over the 256 CUs, two tiles a CU; measured over 32
-// groups, 512 to 2048 rows, 4096 to 22016 columns (us at 2 / 3 / 4 / 8 bits) a full round 63 / 73 / 67 / 73, its last one 47 when
-// at most one tile a CU is left and 4 under a full one otherwise.  Up to 256 tiles, one a CU: 5.4 us and 1.31 us a group of 128 k; up to 512,
-// 1.5 us (3 bits 1.8) a group and more the more CUs have two; beyond, the rounds above and 6 us, on rows shorter than 4096 up to 6 more.
-// Of that 0.92 (with a 3-bit matrix 0.9), up to 512 tiles from K = 4096 on.  Shorter rows, where what a round takes beside its groups
-// counts, go by tall tiles of the full height: a round of them keeps up to 1.5 us more (the two halves of its K meet through LDS): 229 rows of
-// 20424 x 128 11.9 against 9.0 us, 1932 of 3144 x 384 15.8 against 13.9.
-// So do launches of 2- and 4-bit matrices only from 4096 rows on, whose 128 x 256 tiles run several full rounds and are level or 2-6 % ahead.
+// What the few-row kernel's estimate is held against (us), and what gives a call to the tall kernel by tiles of the full height (full_height).  The
+// times: rounds over the 256 CUs, two 128-row tiles a CU or one tall one; measured over 32 groups, 512 to 2048 rows, 4096 to 22016 columns (us at 2 / 3 / 4 / 8
+// bits) a full round of 128-row tiles 63 / 73 / 67 / 73, its last one 47 when at most one tile a CU is left and 4 under a full one otherwise; of tall ones
+// 61 / 67 / 63 / 66, a last one 50 to 60.  Up to 256 128-row tiles, one a CU: 5.4 us and 1.31 us a group of 128 k; up to 512, 1.5 us (3 bits 1.8) a group and
+// more the more CUs have two; beyond, the rounds above and 6 us, on rows shorter than 4096 up to 6 more.  Of that 0.92 (with a 3-bit matrix 0.9), up to
+// 512 tiles from K = 4096 on, and the factors of the tall tiles below: without them the few-row kernel was taken for 29 of 300 sizes that it
+// serves 2 to 26 % more slowly, with them for 10, up to 8 %.
 //
-// us: what the few-row kernel's estimate is held against.  It is the one for tall tiles of the full height (or 128-row tiles): the lower ones
-// are up to a fifth faster than the few-row kernel at some sizes it serves (400 x 22016 x 4096 at 4 bits 87 us against 107), but they
-// round a scale into every weight, which that kernel applies to sums in fp32.  A full round of them 61 / 67 / 63 / 66, a last one 50
-// to 60, 1.5 us more on short rows (the two halves of their K meet through LDS), and the factors below: without them the few-row
-// kernel was taken for 29 of 300 sizes that it serves 2 to 26 % more slowly, with them for 10, up to 8 %.
+// Rows shorter than 2048, where what a round takes beside its groups counts, go by full_height alone: a round of tall tiles keeps up to 1.5 us more (the
+// two halves of its K meet through LDS): 229 rows of 20424 x 128 11.9 against 9.0 us, 1932 of 3144 x 384 15.8 against 13.9.  So do launches of 2- and
+// 4-bit matrices only from 4096 rows on, whose 128 x 256 tiles run several full rounds and are level or 2-6 % ahead.
+//
+// The lower tall tiles are not in `us`: they would take calls from the few-row kernel, which applies a scale to sums in fp32 where they round it into
+// every weight.  Over 1000 of its calls of 129 to 2200 rows from K = 2048 on, large tiles would take over 10 % less at 47 and over a quarter less at
+// two (1282 x 6491 x 11008 at 3 bits 255 us against 414, 1363 x 1857 x 13824 at 4 bits 104 against 139; 1200 x 4096 x 11008 at 4 bits 107 against 159).
 struct LargeTiles {
     double us;
     long tiles; // of 128 rows

@@ -396,9 +396,9 @@ __device__ __forceinline__ void skinny_wide_tile(h8 *smem, const _Float16 *__res
         int nt = 0, nj = 0, ns = 0;                   // group, row block and slot of the next copy
         auto copy = [&]() { // past the end: the last group's rows again, into a stage that is not read any more
             const uint32_t off = (uint32_t)(wave + SNW * min(nt, turns - 1)) * 256u;
-            // the descriptor starts at the block's first row and ends with the last row of all: scalar work, where block and row in
-            // the lane offset were two vector instructions a copy, a tenth of a turn's (300 x 4096 x 11008 at 3 bits 39.7 -> 38.5 us, at 4096 x
-            // 4096 17.5 -> 17.1; up to a tenth of what bounds it is all there was to gain: matrix and vector instructions share the issue port)
+            // The descriptor starts at the block's first row and ends with the last row of all: scalar work, where block and row in
+            // the lane offset were two vector instructions a copy, a tenth of a turn's (300 x 4096 x 11008 at 3 bits 40.0 -> 38.9 us, at 4096 x
+            // 4096 17.9 -> 17.7; over 52 sizes 0 to 4 % less, 1.7 on average).
             const int row = m0 + 16 * nj;
             const fq_rsrc xr = make_rsrc(x + (size_t)row * K, row < M ? (uint32_t)(M - row) * (uint32_t)K * 2u : 0u);
             if constexpr (TIGHT)
